@@ -110,7 +110,7 @@ struct LevelTables {
   ulonglong2* dn_inv = nullptr;  // [K]
   u64* dn_mat = nullptr;         // [K+1][nlimbs]
   ulonglong2* pinv = nullptr;    // [nlimbs]
-  // N = 2^16 fused path
+  // two-pass path
   ulonglong2* up_scale = nullptr;  // [nlimbs]  (Q_j/q_i)^-1 / N mod q_i
   ulonglong2* dn_scale = nullptr;  // [K]       2^64 (P/p_k)^-1 / N mod p_k
   u64* dn_mat_plain = nullptr;     // dn_mat without the Montgomery factor
@@ -122,14 +122,14 @@ struct LevelTables {
   ulonglong2* rs_one = nullptr;    // [1]          Shoup pair of 1 (the single source needs no pre-scaling)
   u64* rs_mat = nullptr;           // [nlimbs-1][5] row i = (1, 0, 0, 0, -q_last) mod q_i, Montgomery form
   ulonglong2* rs_qinv = nullptr;   // [nlimbs-1]   q_last^-1 mod q_i, Shoup pair
-  ulonglong2* rs_qinv16 = nullptr; // same for the N = 2^16 kernels: (c, c/q) doubles on double-precision moduli
+  ulonglong2* rs_qinv16 = nullptr; // same for the two-pass kernels: (c, c/q) doubles on double-precision moduli
 };
 
 }  // namespace
 
 enum ProfKind {
   PK_NTT_FWD = 0, PK_NTT_INV,
-  // N = 2^16 kernels: three consecutive kinds each, one per modulus class (the kernel's template argument)
+  // two-pass kernels: three consecutive kinds each, one per modulus class (the kernel's template argument)
   PK_FWD_ROWS, PK_FWD_BLOCKS = PK_FWD_ROWS + 3, PK_INV_BLOCKS = PK_FWD_BLOCKS + 3, PK_INV_ROWS = PK_INV_BLOCKS + 3,
   PK_FWD_FINAL = PK_INV_ROWS + 3,
   PK_AUTOMORPH = PK_FWD_FINAL + 3, PK_MODUP, PK_INNER, PK_INNER16, PK_INNER16_INT, PK_INNER_C, PK_INNER8, PK_INNER8_BIG, PK_BCONV_ROWS, PK_MODDOWN = PK_BCONV_ROWS + 3, PK_FINAL, PK_TENSOR, PK_PMACC, PK_PMACC_FP, PK_ADD,
@@ -151,7 +151,7 @@ struct ProfRec {
 };
 
 struct ckks_ctx {
-  // Tuning knobs (ckks_tune_set; meanings in the public header). 0: workgroup mapping of the N = 2^16 kernels (-1: per
+  // Tuning knobs (ckks_tune_set; meanings in the public header). 0: workgroup mapping of the two-pass kernels (-1: per
   // kernel); 1: integer bodies everywhere; 2: 1 = base conversions inside the row passes; 3: 2 = inner product fused
   // with the final assembly on double-precision main limbs, 1 = separate kernels; 4: 0 = fork part of a key switch onto
   // the second stream; 5: general base-conversion reduction; 6: integer PCMM inner sums; 7: cap on giant steps per pass.
@@ -167,7 +167,7 @@ struct ckks_ctx {
   ModInfo* d_mods = nullptr;
   ulonglong2* d_tw_fwd = nullptr;
   ulonglong2* d_tw_inv = nullptr;
-  double* d_twfp_fwd = nullptr;  // N = 2^16 only: the twiddles as doubles for moduli < 2^50
+  double* d_twfp_fwd = nullptr;  // N = 2^12 .. 2^16: the twiddles as doubles for moduli < 2^50
   double* d_twfp_inv = nullptr;
   hipStream_t side = nullptr;       // second stream for the fork/join inside a key switch (default priority)
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -322,7 +322,7 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
     u64 inv = h_inv(v, m);
     pinv[i] = ulonglong2{inv, h_shoup(inv, m)};
   }
-  // Constants of the fused N = 2^16 path. 16-byte slots hold a Shoup pair (integer-class modulus) or the doubles
+  // Constants of the two-pass path. 16-byte slots hold a Shoup pair (integer-class modulus) or the doubles
   // (c, c/q) (double-precision class). Integer-class accumulators carry a factor 2^-64 (Montgomery products), which
   // dn_scale and pinv2 undo; double-precision accumulators are plain.
   std::vector<ulonglong2> up_scale(nlimbs), dn_scale(K), pinv2(nlimbs);
@@ -456,13 +456,13 @@ LimbMap ext_map(const ckks_ctx* c, u32 nlimbs) {
 }
 
 // Enqueue a transform of npoly polynomials x slots [slot0, slot0+nslots): reads src, writes dst (src == dst for an
-// in-place transform; out of place is supported only on the N = 2^16 path). Rows are *_stride elements apart.
-// Modulus class on the N = 2^16 path (must match mod_class() on the device).
+// in-place transform; out of place is supported at N = 2^12 .. 2^16). Rows are *_stride elements apart.
+// Modulus class (must match mod_class() on the device).
 inline int host_class(const ckks_ctx* c, u64 m) {
   if (c->tune[1] == 0 && (m >> 50) == 0) return 0;
   return (m >> 52) == 0 ? 1 : 2;
 }
-// Workgroup-to-tile mapping of the N = 2^16 kernels (ntt16_map). Knob 0 >= 0 forces one mode everywhere; by default
+// Workgroup-to-tile mapping of the two-pass kernels (ntt16_map). Knob 0 >= 0 forces one mode everywhere; by default
 // the transform passes and the final assembly, which share nothing but twiddles across polynomials, take the
 // XCD-swizzled tile-major order (measured best for them), and the kernels that read the key take the
 // group-per-XCD order when the batch shares one key (its slices then stay in that XCD's L2) and the plain
@@ -471,27 +471,65 @@ inline u32 map_mode_pass(const ckks_ctx* c) { return c->tune[0] >= 0 ? (u32)c->t
 inline u32 map_mode_inner(const ckks_ctx* c, bool shared_key) {
   return c->tune[0] >= 0 ? (u32)c->tune[0] : shared_key ? 4u : 2u;
 }
-// Launch KERNEL<cls> once per modulus class present among `nslots` slots, with ARGS.slots listing that class's slots.
-#define LAUNCH_BY_CLASS(CTX, PKBASE, KERNEL, ARGS, NX, NSLOTS, CLASS_OF_SLOT, STREAM)                      \
-  for (int cls_ = 0; cls_ < 3; cls_++) {                                                                    \
-    u32 cnt_ = 0;                                                                                           \
-    for (u32 s_ = 0; s_ < (NSLOTS); s_++)                                                                   \
-      if ((CLASS_OF_SLOT(s_)) == cls_) (ARGS).slots[cnt_++] = (unsigned char)s_;                            \
-    if (!cnt_) continue;                                                                                    \
-    dim3 grid_((NX), 16, cnt_), block_(NTT16_THREADS);                                                      \
-    ProfScope ps_((CTX), (PKBASE) + cls_, (STREAM));                                                        \
-    if (cls_ == 0) hipLaunchKernelGGL((KERNEL<0>), grid_, block_, 0, (STREAM), (ARGS));                     \
-    else if (cls_ == 1) hipLaunchKernelGGL((KERNEL<1>), grid_, block_, 0, (STREAM), (ARGS));                \
-    else hipLaunchKernelGGL((KERNEL<2>), grid_, block_, 0, (STREAM), (ARGS));                               \
+// The two-pass transforms and the kernels fused with them serve N = 2^13 .. 2^16. Below 2^13 a row pass would have fewer
+// rows than one radix-16 round; 2^17 needs 512 rows, more than a 4096-element tile with whole 128-byte lines holds. What
+// they replaced on 2^13 .. 2^15 was the stage-by-stage ntt_pass_kernel with one kernel per step of a key switch (a
+// butterfly's operands through LDS every stage, integer arithmetic throughout): 37 transforms of 4 limbs in both
+// directions at 2^13 104 -> 52 us, 12 rotations at 2^14 (5 limbs) 287 -> 117 us, 8 products at 2^15 (13 limbs)
+// 833 -> 348 us.
+inline bool two_pass(const ckks_ctx* c) { return c->logN >= 13 && c->logN <= 16; }
+inline u32 pass_tiles(const ckks_ctx* c) { return c->N >> 12; }   // 4096-element tiles of a limb
+
+// One launch per modulus class present among `nslots` slots, a.slots listing that class's slots: launch(cls, grid).
+// class_of_slot(slot) < 0 leaves a slot out.
+template <class Args, class ClassOf, class Launch>
+void launch_by_class(const ckks_ctx* c, int kind_base, Args& a, u32 nx, u32 nslots, ClassOf class_of_slot, hipStream_t st,
+                     Launch launch) {
+  for (int cls = 0; cls < 3; cls++) {
+    u32 cnt = 0;
+    for (u32 s = 0; s < nslots; s++)
+      if (class_of_slot(s) == cls) a.slots[cnt++] = (unsigned char)s;
+    if (!cnt) continue;
+    ProfScope ps(c, kind_base + cls, st);
+    launch(cls, dim3(nx, pass_tiles(c), cnt));
   }
+}
+#define LAUNCH_CLASS_KERNEL(KERNEL, CLS, GRID, STREAM, ARGS)                                             \
+  do {                                                                                                   \
+    if ((CLS) == 0) hipLaunchKernelGGL((KERNEL<0>), GRID, dim3(NTT16_THREADS), 0, STREAM, ARGS);         \
+    else if ((CLS) == 1) hipLaunchKernelGGL((KERNEL<1>), GRID, dim3(NTT16_THREADS), 0, STREAM, ARGS);    \
+    else hipLaunchKernelGGL((KERNEL<2>), GRID, dim3(NTT16_THREADS), 0, STREAM, ARGS);                    \
+  } while (0)
+// the row passes are instantiated per number of rows, N / 256
+template <int LOGR>
+void launch_rows_of(bool inverse, int cls, dim3 grid, hipStream_t st, const Ntt16Args& a) {
+  const dim3 block(NTT16_THREADS);
+  if (inverse) {
+    if (cls == 0) hipLaunchKernelGGL((ntt16_inv_rows_kernel<0, LOGR>), grid, block, 0, st, a);
+    else if (cls == 1) hipLaunchKernelGGL((ntt16_inv_rows_kernel<1, LOGR>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((ntt16_inv_rows_kernel<2, LOGR>), grid, block, 0, st, a);
+  } else {
+    if (cls == 0) hipLaunchKernelGGL((ntt16_fwd_rows_kernel<0, LOGR>), grid, block, 0, st, a);
+    else if (cls == 1) hipLaunchKernelGGL((ntt16_fwd_rows_kernel<1, LOGR>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((ntt16_fwd_rows_kernel<2, LOGR>), grid, block, 0, st, a);
+  }
+}
+void launch_rows(u32 logN, bool inverse, int cls, dim3 grid, hipStream_t st, const Ntt16Args& a) {
+  switch (logN) {
+    case 13: launch_rows_of<5>(inverse, cls, grid, st, a); break;
+    case 14: launch_rows_of<6>(inverse, cls, grid, st, a); break;
+    case 15: launch_rows_of<7>(inverse, cls, grid, st, a); break;
+    default: launch_rows_of<8>(inverse, cls, grid, st, a); break;
+  }
+}
 
 struct NttOpts {
-  u32 galois = 0;                     // N = 2^16 inverse only: read src through the eval-domain Galois map
+  u32 galois = 0;                     // two-pass inverse only: read src through the eval-domain Galois map
   const u32* galois_pc = nullptr;     // same, one element per polynomial (host array, npoly <= KS_MULTI_MAX entries)
-  const ulonglong2* scale = nullptr;  // N = 2^16 inverse only: per-slot constants (from slot0) replacing N^-1
+  const ulonglong2* scale = nullptr;  // two-pass inverse only: per-slot constants (from slot0) replacing N^-1
   bool split_out = false;             // N = 2^16 inverse only: write the shifted, split form the fused base conversion reads
-  bool rows_only = false;             // N = 2^16 forward only: stop after the row pass (a fused kernel does the rest)
-  bool blocks_only = false;           // N = 2^16 forward only: only the block pass, in place on dst
+  bool rows_only = false;             // two-pass forward only: stop after the row pass (a fused kernel does the rest)
+  bool blocks_only = false;           // two-pass forward only: only the block pass, in place on dst
   bool raw_out = false;               // with blocks_only: leave reduced doubles on double-precision moduli
   int only_class = -1;                // >= 0: touch only the slots of this modulus class
   int exclude_class = -1;             // >= 0: leave the slots of this modulus class alone
@@ -501,8 +539,9 @@ int launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, u64 src_stride, 
                const NttOpts& opt = NttOpts()) {
   if (npoly == 0 || nslots == 0) return CKKS_OK;
   const int kind = inverse ? PK_NTT_INV : PK_NTT_FWD;
-  if (c->logN == 16) {
+  if (two_pass(c)) {
     Ntt16Args a;
+    a.logN = c->logN;
     a.src = src + (size_t)slot0 * c->N;
     a.dst = dst + (size_t)slot0 * c->N;
     a.tw = inverse ? c->d_tw_inv : c->d_tw_fwd;
@@ -533,16 +572,19 @@ int launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, u64 src_stride, 
       if (opt.exclude_class >= 0 && k == opt.exclude_class) return -1;
       return k;
     };
+    auto rows = [&](Ntt16Args& r, int kind_base) {
+      launch_by_class(c, kind_base, r, npoly, nslots, cls_of, st,
+                      [&](int cls, dim3 grid) { launch_rows(c->logN, inverse, cls, grid, st, r); });
+    };
     if (!inverse) {
-      if (!opt.blocks_only) {
-        LAUNCH_BY_CLASS(c, PK_FWD_ROWS, ntt16_fwd_rows_kernel, a, npoly, nslots, cls_of, st)
-      }
-      if (!opt.rows_only) {
-        LAUNCH_BY_CLASS(c, PK_FWD_BLOCKS, ntt16_fwd_blocks_kernel, b, npoly, nslots, cls_of, st)
-      }
+      if (!opt.blocks_only) rows(a, PK_FWD_ROWS);
+      if (!opt.rows_only)
+        launch_by_class(c, PK_FWD_BLOCKS, b, npoly, nslots, cls_of, st,
+                        [&](int cls, dim3 grid) { LAUNCH_CLASS_KERNEL(ntt16_fwd_blocks_kernel, cls, grid, st, b); });
     } else {
-      LAUNCH_BY_CLASS(c, PK_INV_BLOCKS, ntt16_inv_blocks_kernel, a, npoly, nslots, cls_of, st)
-      LAUNCH_BY_CLASS(c, PK_INV_ROWS, ntt16_inv_rows_kernel, b, npoly, nslots, cls_of, st)
+      launch_by_class(c, PK_INV_BLOCKS, a, npoly, nslots, cls_of, st,
+                      [&](int cls, dim3 grid) { LAUNCH_CLASS_KERNEL(ntt16_inv_blocks_kernel, cls, grid, st, a); });
+      rows(b, PK_INV_ROWS);
     }
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
@@ -696,15 +738,15 @@ void launch_moddown(const ckks_ctx* c, const ModDownArgs& a, u32 B2, bool narrow
 struct KsIo {
   const u64* d;          // polynomial to switch, eval domain; limb-vector (b, i) at d + b*d_stride + i*N
   u64 d_stride;
-  u32 d_galois;          // != 0: d is read through the eval-domain Galois map (HRot's sigma(c1)); N = 2^16 path only
+  u32 d_galois;          // != 0: d is read through the eval-domain Galois map (HRot's sigma(c1)); two-pass path only
   u64* out;              // [B][2][nlimbs][N]
-  u32 mode[2];           // per component: bit 0: + add2 (out itself when null); bit 1: + sigma_g(add_src) (N = 2^16 path only)
+  u32 mode[2];           // per component: bit 0: + add2 (out itself when null); bit 1: + sigma_g(add_src) (two-pass path only)
   const u64* add_src;    // [B][2][nlimbs][N]
   u32 add_galois;
-  // N = 2^16 path, B <= KS_MULTI_MAX: ciphertext b uses galois_pc[b] (for d and add_src) and the key evk_pc[b]
+  // two-pass path, B <= KS_MULTI_MAX: ciphertext b uses galois_pc[b] (for d and add_src) and the key evk_pc[b]
   const u32* galois_pc = nullptr;
   const u64* const* evk_pc = nullptr;
-  const u64* add2 = nullptr;   // [B][2][nlimbs][N] plain addend of mode bit 0 (N = 2^16 path); null = out, in place
+  const u64* add2 = nullptr;   // [B][2][nlimbs][N] plain addend of mode bit 0 (two-pass path); null = out, in place
   bool add2_three = false;     // add2 is [B][3][nlimbs][N]; its first two components are the addends
 };
 
@@ -739,13 +781,13 @@ int launch_bconv_rows(const ckks_ctx* c, BconvRowsArgs a, u32 npoly, bool narrow
   return CKKS_OK;
 }
 
-// ModDown's conversion and the first forward pass of its result on the N = 2^16 path: the special limbs of both
+// ModDown's conversion and the first forward pass of its result on the two-pass path: the special limbs of both
 // accumulators back to coefficient form (scaled by (P/p_k)^-1 / N), P -> Q_l, stages 0..7; tq receives the converted
 // limbs in row-pass form. Knob 2 = 1 does the conversion inside the row pass (ntt16_bconv_rows_kernel).
 int ks16_moddown_rows(ckks_ctx* c, const LevelTables* lt, u32 B, u32 nlimbs, u64* acc, u64* tq, hipStream_t st) {
   int rc;
   const u32 N = c->N, next = lt->next, K = c->np;
-  const bool fused = c->tune[2] == 1;
+  const bool fused = c->tune[2] == 1 && c->logN == 16;
   LimbMap pmap;
   for (u32 k = 0; k < CKKS_MAX_SLOTS; k++) pmap.id[k] = (unsigned char)(k < K ? c->nq + k : 0);
   NttOpts o3;
@@ -781,7 +823,7 @@ int ks16_moddown_rows(ckks_ctx* c, const LevelTables* lt, u32 B, u32 nlimbs, u64
   return launch_bconv_rows(c, a, B * 2, lt->narrow_dn, [&](u32 s) { return host_class(c, c->mod[s]); }, st);
 }
 
-// Last kernel of a key switch on the N = 2^16 path: block pass of tq fused with (acc - tq) / P and the addends.
+// Last kernel of a key switch on the two-pass path: block pass of tq fused with (acc - tq) / P and the addends.
 // exclude_class >= 0 leaves the limbs of that modulus class to another kernel.
 int ks16_assemble(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B, u32 nlimbs, const u64* acc, const u64* tq,
                   hipStream_t st, int exclude_class = -1) {
@@ -796,6 +838,7 @@ int ks16_assemble(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B, u32
   a.twfp = c->d_twfp_fwd;
   a.mods = c->d_mods;
   a.pinv = lt->pinv2;
+  a.logN = c->logN;
   a.nlimbs = nlimbs;
   a.next = lt->next;
   a.mode0 = io.mode[0];
@@ -810,12 +853,13 @@ int ks16_assemble(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B, u32
     const int k = host_class(c, c->mod[s]);
     return k == exclude_class ? -1 : k;
   };
-  LAUNCH_BY_CLASS(c, PK_FWD_FINAL, ntt16_fwd_blocks_final_kernel, a, B * 2, nlimbs, cls_of, st)
+  launch_by_class(c, PK_FWD_FINAL, a, B * 2, nlimbs, cls_of, st,
+                  [&](int cls, dim3 grid) { LAUNCH_CLASS_KERNEL(ntt16_fwd_blocks_final_kernel, cls, grid, st, a); });
   HIP_TRY(hipGetLastError());
   return CKKS_OK;
 }
 
-// Second half of a key switch on the N = 2^16 path: from the accumulators (all slots) to the assembled output.
+// Second half of a key switch on the two-pass path: from the accumulators (all slots) to the assembled output.
 // acc_in: accumulators held outside the workspace ([B][2][next][N]; their special-prime slots are overwritten).
 int ks16_finish(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B, u32 nlimbs, char* ws, hipStream_t st,
                 u64* acc_in = nullptr) {
@@ -827,7 +871,17 @@ int ks16_finish(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B, u32 n
   return ks16_assemble(c, lt, io, B, nlimbs, acc, tq, st);
 }
 
-// N = 2^16: transforms fused with their neighbours.
+void launch_inner_c(const ckks_ctx* c, u32 B, u32 nslots, const FwdInnerArgs& a, hipStream_t st) {
+  const dim3 grid(B * 2, pass_tiles(c), nslots), block(NTT16_THREADS);
+  switch (c->logN) {
+    case 13: hipLaunchKernelGGL(ntt16_fwd_blocks_inner_c_kernel<13>, grid, block, 0, st, a); break;
+    case 14: hipLaunchKernelGGL(ntt16_fwd_blocks_inner_c_kernel<14>, grid, block, 0, st, a); break;
+    case 15: hipLaunchKernelGGL(ntt16_fwd_blocks_inner_c_kernel<15>, grid, block, 0, st, a); break;
+    default: hipLaunchKernelGGL(ntt16_fwd_blocks_inner_c_kernel<16>, grid, block, 0, st, a); break;
+  }
+}
+
+// Two-pass path: transforms fused with their neighbours.
 //   1. INTT(d) with (Q_j/q_i)^-1 / N folded in, written in the split form
 //   2. ModUp conversion and row pass of every slot a digit does not own (two kernels; knob 2 = 1: one fused kernel)
 //   3. integer-class slots (the special primes): [block pass + evk inner product] (x 2^-64 from the Montgomery products)
@@ -861,7 +915,7 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
     any_int |= !fp;
     if (s_ >= nlimbs) special_fp |= fp;
   }
-  const bool fused_up = c->tune[2] == 1;
+  const bool fused_up = c->tune[2] == 1 && c->logN == 16;
   // 1.
   NttOpts o1;
   o1.galois = io.d_galois;
@@ -932,6 +986,7 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
   ia.tw = c->d_tw_fwd;
   ia.twfp = c->d_twfp_fwd;
   ia.mods = c->d_mods;
+  ia.logN = c->logN;
   ia.nlimbs = nlimbs;
   ia.nq = c->nq;
   ia.nm = c->nm;
@@ -951,7 +1006,7 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
     ia.c0 = io.add_src;
     ia.c0_poly_stride = 2 * (u64)nlimbs * N;
   }
-  // 3. integer-class slots, 8 values per lane (grid.y = 32 tiles of 8 blocks)
+  // 3. integer-class slots, 8 values per lane (grid.y = tiles of 8 blocks)
   for (int cls = 1; cls <= 2; cls++) {
     FwdInnerArgs a = ia;
     u32 cnt = 0;
@@ -959,8 +1014,8 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
       if (ext_class(s_) == cls) a.slots[cnt++] = (unsigned char)s_;
     if (!cnt) continue;
     ProfScope ps(c, PK_INNER8 + cls - 1, st);
-    if (cls == 1) hipLaunchKernelGGL(ntt16_fwd_blocks_inner8_kernel<1>, dim3(B, 32, cnt), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL(ntt16_fwd_blocks_inner8_kernel<2>, dim3(B, 32, cnt), dim3(256), 0, st, a);
+    if (cls == 1) hipLaunchKernelGGL(ntt16_fwd_blocks_inner8_kernel<1>, dim3(B, N / 2048, cnt), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(ntt16_fwd_blocks_inner8_kernel<2>, dim3(B, N / 2048, cnt), dim3(256), 0, st, a);
   }
   HIP_TRY(hipGetLastError());
   // double-precision slots whose accumulators are needed in memory: the special ones always (ModDown reads them),
@@ -973,7 +1028,7 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
     if (!cnt) return CKKS_OK;
     if (fused_fp) {
       ProfScope ps(c, PK_INNER_C, s);
-      hipLaunchKernelGGL(ntt16_fwd_blocks_inner_c_kernel, dim3(B * 2, 16, cnt), dim3(NTT16_THREADS), 0, s, a);
+      launch_inner_c(c, B, cnt, a, s);
     } else {
       // plain block pass of every converted double-precision slot (own limbs are skipped), then a streaming product
       NttOpts o;
@@ -983,7 +1038,7 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
       int r2 = launch_ntt(c, false, ext, (u64)next * N, ext, (u64)next * N, B * beta, 0, next, emap, beta, nlimbs, s, o);
       if (r2) return r2;
       ProfScope ps(c, PK_INNER16, s);
-      hipLaunchKernelGGL(inner16_fp_kernel, dim3(B, 128, cnt), dim3(256), 0, s, a);
+      hipLaunchKernelGGL(inner16_fp_kernel, dim3(B, N / 512, cnt), dim3(256), 0, s, a);
     }
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
@@ -1012,14 +1067,14 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
       a.fin_mode1 = io.mode[1];
       a.fin_galois = io.add_galois;
       ProfScope ps(c, PK_INNER_C, st);
-      hipLaunchKernelGGL(ntt16_fwd_blocks_inner_c_kernel, dim3(B * 2, 16, cnt), dim3(NTT16_THREADS), 0, st, a);
+      launch_inner_c(c, B, cnt, a, st);
       HIP_TRY(hipGetLastError());
     }
   }
   return ks16_assemble(c, lt, io, B, nlimbs, acc, tq, st, fused_fp ? 0 : -1);
 }
 
-// Shared front of the hoisted rotations at N = 2^16: inverse transform, ModUp and forward transform of c1 of ct_in
+// Shared front of the hoisted rotations: inverse transform, ModUp and forward transform of c1 of ct_in
 // ([B][2][nlimbs][N]) into the workspace, and the arguments of the streaming inner-product kernels that read them
 // (accumulators default to the workspace's own).
 static int hoist_front16(ckks_ctx* c, const LevelTables* lt, const u64* ct_in, u32 B, u32 nlimbs, char* ws, hipStream_t st,
@@ -1053,6 +1108,7 @@ static int hoist_front16(ckks_ctx* c, const LevelTables* lt, const u64* ct_in, u
   ia.tw = c->d_tw_fwd;
   ia.twfp = c->d_twfp_fwd;
   ia.mods = c->d_mods;
+  ia.logN = c->logN;
   ia.nlimbs = nlimbs;
   ia.nq = c->nq;
   ia.nm = c->nm;
@@ -1063,7 +1119,7 @@ static int hoist_front16(ckks_ctx* c, const LevelTables* lt, const u64* ct_in, u
   return CKKS_OK;
 }
 
-// Hoisted rotations, N = 2^16: out[r] = HRot_{g_r}(ct_in) for r < R. The Galois map commutes exactly with the
+// Hoisted rotations: out[r] = HRot_{g_r}(ct_in) for r < R. The Galois map commutes exactly with the
 // centred base conversion (it permutes coefficients up to sign, and the conversion is odd), so INTT, ModUp and the
 // forward transform of c1 are done once on the un-rotated polynomial; each rotation then reads the transformed
 // digits through its own index map in the streaming inner product and finishes as usual.
@@ -1107,7 +1163,7 @@ int hrot_hoisted16(ckks_ctx* c, u64* out_base, u64 out_stride, const u64* ct_in,
         if (!cnt) continue;
         ProfScope ps(c, fp ? PK_INNER16 : PK_INNER16_INT, st);
         const u32 cb = fp ? INNER16_ROT_CB_FP : INNER16_ROT_CB;
-        const dim3 grid((B + cb - 1) / cb, 256, cnt);
+        const dim3 grid((B + cb - 1) / cb, N / 256, cnt);
         if (fp && beta == 1) hipLaunchKernelGGL((inner16_rot_fp_kernel<1, true>), grid, dim3(256), 0, st, a, B);
         else if (fp && beta == 2) hipLaunchKernelGGL((inner16_rot_fp_kernel<2, true>), grid, dim3(256), 0, st, a, B);
         else if (fp && beta == 3) hipLaunchKernelGGL((inner16_rot_fp_kernel<3, true>), grid, dim3(256), 0, st, a, B);
@@ -1152,8 +1208,8 @@ int hrot_hoisted16(ckks_ctx* c, u64* out_base, u64 out_stride, const u64* ct_in,
         if ((host_class(c, c->mod[emap.id[s_]]) == 0) == (fp == 1)) a.slots[cnt++] = (unsigned char)s_;
       if (!cnt) continue;
       ProfScope ps(c, fp ? PK_INNER16 : PK_INNER16_INT, st);
-      if (fp) hipLaunchKernelGGL(inner16_fp_kernel, dim3(B, 128, cnt), dim3(256), 0, st, a);
-      else hipLaunchKernelGGL(inner16_int_kernel, dim3(B, 128, cnt), dim3(256), 0, st, a);
+      if (fp) hipLaunchKernelGGL(inner16_fp_kernel, dim3(B, N / 512, cnt), dim3(256), 0, st, a);
+      else hipLaunchKernelGGL(inner16_int_kernel, dim3(B, N / 512, cnt), dim3(256), 0, st, a);
     }
     HIP_TRY(hipGetLastError());
     if (acc_base) continue;
@@ -1168,9 +1224,9 @@ int keyswitch_impl(ckks_ctx* c, const KsIo& io, u32 B, u32 nlimbs, const u64* ev
   const LevelTables* lt;
   int rc = get_level(c, nlimbs, &lt);
   if (rc) return rc;
-  if (c->logN == 16) return keyswitch_fused16(c, lt, io, B, nlimbs, evk, ws, st);
+  if (two_pass(c)) return keyswitch_fused16(c, lt, io, B, nlimbs, evk, ws, st);
   if (io.d_galois || io.mode[0] >= 2 || io.mode[1] >= 2 || io.add2)
-    return fail(CKKS_EINVAL, "internal: gather modes and separate addends need the N = 2^16 path");
+    return fail(CKKS_EINVAL, "internal: gather modes and separate addends need the two-pass path");
   const u64* d = io.d;
   u64* out = io.out;
   const u32 add_mask = (io.mode[0] ? 1u : 0u) | (io.mode[1] ? 2u : 0u);
@@ -1305,7 +1361,7 @@ int ckks_ctx_create(ckks_ctx** out, uint32_t logN, const uint64_t* q, uint32_t n
   std::vector<ModInfo> mods(c->nm);
   std::vector<ulonglong2> fwd((size_t)c->nm * N), inv((size_t)c->nm * N);
   std::vector<double> fwdfp, invfp;
-  if (logN == 16 || logN == 12) {
+  if (logN >= 12 && logN <= 16) {   // the rings with double-precision bodies
     fwdfp.assign((size_t)c->nm * N, 0.0);
     invfp.assign((size_t)c->nm * N, 0.0);
   }
@@ -1342,7 +1398,7 @@ int ckks_ctx_create(ckks_ctx** out, uint32_t logN, const uint64_t* q, uint32_t n
       u32 e = h_brev(k, logN);
       u64 wi = e == 0 ? 1 : m - pw[N - e];
       inv[(size_t)i * N + k] = ulonglong2{wi, h_shoup(wi, m)};
-      if ((logN == 16 || logN == 12) && (m >> 50) == 0) {
+      if (!fwdfp.empty() && (m >> 50) == 0) {
         fwdfp[(size_t)i * N + k] = (double)w;
         invfp[(size_t)i * N + k] = (double)wi;
       }
@@ -1550,7 +1606,7 @@ int ckks_hrot(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint32_t B, 
               const uint64_t* evk, void* ws, size_t ws_bytes, void* stream) {
   return hrot_impl(c, ct_out, ct_in, B, nlimbs, g, evk, ws, ws_bytes, stream, nullptr);
 }
-// ct_add != null: ct_out = ct_add + HRot(ct_in); ct_add == ct_out accumulates in place (N = 2^16 path only).
+// ct_add != null: ct_out = ct_add + HRot(ct_in); ct_add == ct_out accumulates in place (two-pass path only).
 static int hrot_impl(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint32_t B, uint32_t nlimbs, uint32_t g,
                      const uint64_t* evk, void* ws, size_t ws_bytes, void* stream, const uint64_t* ct_add) {
   int rc = check_common(c, B, nlimbs);
@@ -1565,7 +1621,7 @@ static int hrot_impl(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint3
   DeviceGuard guard(c->device);
   if (!guard.ok) return fail(CKKS_EHIP, "cannot select the context's device");
   hipStream_t st = (hipStream_t)stream;
-  if (c->logN == 16) {
+  if (two_pass(c)) {
     // the permutation is applied where the ciphertext is read: by the first inverse pass and the fused inner product
     // (sigma(c1)) and by the final assembly (sigma(c0)), which also adds ct_add
     KsIo io{(const u64*)ct_in + polyN, 2 * polyN, g, (u64*)ct_out, {ct_add ? 3u : 2u, ct_add ? 1u : 0u},
@@ -1573,7 +1629,7 @@ static int hrot_impl(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint3
     io.add2 = (const u64*)ct_add;
     return keyswitch_impl(c, io, B, nlimbs, (const u64*)evk, (char*)ws, st);
   }
-  if (ct_add && ct_add == ct_out) return fail(CKKS_EINVAL, "internal: accumulating in place needs the N = 2^16 path");
+  if (ct_add && ct_add == ct_out) return fail(CKKS_EINVAL, "internal: accumulating in place needs the two-pass path");
   const size_t ks = ks_layout(c, B, nlimbs).total;
   u64* d = (u64*)((char*)ws + ks);
   const LimbMap qmap = identity_map(nlimbs);
@@ -1629,7 +1685,7 @@ int ckks_hrot_multi(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint32
   if ((rc = check_ws(c, CKKS_OP_HROT, B, nlimbs, 0, ws, ws_bytes))) return rc;
   const size_t polyN = (size_t)nlimbs * c->N, ct_bytes = (size_t)B * 2 * polyN * 8;
   if (overlap(ct_out, ct_bytes, ct_in, ct_bytes)) return fail(CKKS_EINVAL, "ct_out overlaps ct_in");
-  if (c->logN != 16) {
+  if (!two_pass(c)) {
     // other ring sizes: one rotation at a time through the general path
     for (u32 b = 0; b < B; b++)
       if ((rc = hrot_impl(c, ct_out + b * 2 * polyN, ct_in + b * 2 * polyN, 1, nlimbs, galois_elts[b], evks[b], ws, ws_bytes,
@@ -1712,7 +1768,7 @@ int ckks_relin(ckks_ctx* c, uint64_t* ct_out, const uint64_t* d_in, uint32_t B, 
   hipStream_t st = (hipStream_t)stream;
   const u64* d = (const u64*)d_in;
   KsIo io{d + 2 * polyN, 3 * (u64)polyN, 0, (u64*)ct_out, {1, 1}, nullptr, 0};
-  if (c->logN == 16) {
+  if (two_pass(c)) {
     // the last kernel of the key switch reads d0 and d1 in place
     io.add2 = d;
     io.add2_three = true;
@@ -1764,7 +1820,7 @@ int ckks_hrot_hoisted(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint
   if (overlap(ct_out, (size_t)R * ct_elems * 8, ct_in, ct_elems * 8)) return fail(CKKS_EINVAL, "ct_out overlaps ct_in");
   DeviceGuard guard(c->device);
   if (!guard.ok) return fail(CKKS_EHIP, "cannot select the context's device");
-  if (c->logN == 16) {
+  if (two_pass(c)) {
     // workspace beyond the required size holds accumulators of rotations that then share a pass over the digits
     const size_t need = ckks_workspace_bytes(c, CKKS_OP_HROT, B, nlimbs, 0);
     const size_t one = (size_t)B * 2 * (nlimbs + c->np) * c->N * 8;
@@ -1822,8 +1878,8 @@ int ckks_hrot_sum(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint32_t
         if ((host_class(c, c->mod[emap.id[s_]]) == 0) == (fp == 1)) a.slots[cnt++] = (unsigned char)s_;
       if (!cnt) continue;
       ProfScope ps(c, fp ? PK_INNER16 : PK_INNER16_INT, st);
-      if (fp) hipLaunchKernelGGL(inner16_sum_fp_kernel, dim3(B, 128, cnt), dim3(256), 0, st, a);
-      else hipLaunchKernelGGL(inner16_sum_int_kernel, dim3(B, 128, cnt), dim3(256), 0, st, a);
+      if (fp) hipLaunchKernelGGL(inner16_sum_fp_kernel, dim3(B, N / 512, cnt), dim3(256), 0, st, a);
+      else hipLaunchKernelGGL(inner16_sum_int_kernel, dim3(B, N / 512, cnt), dim3(256), 0, st, a);
     }
     HIP_TRY(hipGetLastError());
   }
@@ -1898,7 +1954,7 @@ static int pcmm_impl(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint3
   } else if (hoisted && n1 > 1) {
     std::vector<u32> gs(n1 - 1);
     for (u32 b = 1; b < n1; b++) gs[b - 1] = galois((u64)b * stride);
-    if (c->logN == 16) {
+    if (two_pass(c)) {
       // the region of the inner sums is free until the baby steps are done: it holds the accumulators of as many
       // rotations as fit, which then share one pass over the hoisted digits
       const size_t one = (size_t)B * 2 * (nlimbs + c->np) * N * 8;
@@ -2014,7 +2070,7 @@ static int pcmm_impl(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint3
       }
       if (g == 0) continue;
       const u64* src = inner + (size_t)k * ct_elems;
-      if (c->logN == 16) {
+      if (two_pass(c)) {
         rc = hrot_impl(c, ct_out, (const uint64_t*)src, B, nlimbs, galois((u64)g * n1 * stride), evk_giant[g - 1], hws,
                        hws_bytes, stream, /*ct_add=*/ct_out);
         if (rc) return rc;
@@ -2068,7 +2124,7 @@ int ckks_rescale(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint32_t 
   }
   // 3. back to the evaluation domain, subtract, divide by q_last
   const LimbMap qmap = identity_map(nl1);
-  if (c->logN == 16) {
+  if (two_pass(c)) {
     NttOpts o;
     o.rows_only = true;
     if ((rc = launch_ntt(c, false, tq, (u64)nl1 * N, tq, (u64)nl1 * N, B * 2, 0, nl1, qmap, 0, 0, st, o))) return rc;
@@ -2082,13 +2138,15 @@ int ckks_rescale(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint32_t 
     a.twfp = c->d_twfp_fwd;
     a.mods = c->d_mods;
     a.pinv = lt->rs_qinv16;
+    a.logN = c->logN;
     a.nlimbs = nl1;
     a.next = nlimbs;
     a.mode0 = a.mode1 = 0;
     a.galois = 0;
     a.map_mode = map_mode_pass(c);
     auto cls_of = [&](u32 s) { return host_class(c, c->mod[s]); };
-    LAUNCH_BY_CLASS(c, PK_FWD_FINAL, ntt16_fwd_blocks_final_kernel, a, B * 2, nl1, cls_of, st)
+    launch_by_class(c, PK_FWD_FINAL, a, B * 2, nl1, cls_of, st,
+                    [&](int cls, dim3 grid) { LAUNCH_CLASS_KERNEL(ntt16_fwd_blocks_final_kernel, cls, grid, st, a); });
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
   }

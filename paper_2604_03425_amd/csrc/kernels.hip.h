@@ -89,13 +89,6 @@ __global__ void __launch_bounds__(NTT_THREADS) ntt_pass_kernel(NttArgs a) {
 
 // ---------------------------------------------------------------------------------------------
 // Galois automorphism.
-// Evaluation domain (bit-reversed order): out[k] = in[k'], 2*brev(k')+1 = (2*brev(k)+1)*g mod 2N.
-__device__ __forceinline__ u32 galois_src_index(u32 k, u32 g, u32 logN) {
-  u32 e = 2 * (__brev(k) >> (32 - logN)) + 1;
-  u32 t = (e * g) & ((2u << logN) - 1);
-  return __brev(t >> 1) >> (32 - logN);
-}
-
 struct AutoArgs {
   u64* out;
   const u64* in;

@@ -178,6 +178,13 @@ __device__ __forceinline__ u64 redc(Acc128 v, u64 m, u64 minv) {
   return v.hi + mul_hi64(u, m) + (v.lo != 0 ? 1ull : 0ull);
 }
 
+// Eval-domain Galois map: out[k] = in[k'], 2*brev(k')+1 = (2*brev(k)+1)*g mod 2N. It maps every aligned 16-element
+// segment onto an aligned 16-element segment, so 16 adjacent lanes still read one 128-byte line. Computed on values
+// scaled by 2^(31 - logN), where the reduction modulo 2N is the 32-bit wrap-around.
+__device__ __forceinline__ u32 galois_src_index(u32 k, u32 g, u32 logN) {
+  return __brev(__brev(k) * g + (g << (31 - logN))) & ((1u << logN) - 1);
+}
+
 // Workgroup index remapped so that consecutive logical indices run on the same XCD (the dispatcher deals
 // workgroups to the 8 XCDs round-robin in linear order). Returns the logical linear index for this workgroup.
 __device__ __forceinline__ u32 xcd_swizzled_linear_id() {

@@ -1,8 +1,10 @@
-// Two-pass negacyclic NTT for N = 2^16 on gfx950: each pass does 8 butterfly stages on a 4096-element
-// tile held as 16 registers per lane (256 lanes), as two in-register radix-16 rounds with one LDS
-// transpose between them. Pass "row" works on 256 rows x 16 adjacent columns of the 256x256 view of a
-// limb (stride-256 butterflies, stages 0..7); pass "blk" works on 16 contiguous 256-element blocks
-// (stages 8..15). Global loads and stores always have 16 adjacent lanes on 128 contiguous bytes.
+// Two-pass negacyclic NTT for N = 2^13 .. 2^16 on gfx950. A limb is viewed as R = N / 256 rows of 256 elements; each pass
+// works on 4096-element tiles held as 16 registers per lane (256 lanes), as in-register radix-16 rounds with one LDS
+// transpose between them. Pass "row" does the first log2 R stages (stride-256 butterflies) on all R rows x 4096 / R
+// adjacent columns; pass "blk" does the last 8 stages on 16 contiguous 256-element blocks. Global loads and stores
+// always have 16 adjacent lanes on 128 contiguous bytes. The block bodies take R at run time (block h of R takes its
+// stage-s twiddles from R << s onward, so R only shifts an index); the row bodies are instantiated per LOGR = log2 R,
+// which fixes how many of the second round's stages exist: a lane then holds 16 / (R / 16) columns of that round.
 //
 // Lazy ranges. Every twiddle product is the approximate shoup_lazy4 (below 4q), and the lazy constant the bodies
 // pass around is 4q. SMALL primes (q < 2^52): forward butterflies never correct, values grow by 4q per
@@ -101,6 +103,40 @@ __device__ __forceinline__ void radix16_inv_staged(u64 (&x)[16], u64 q, u64 c0, 
     after(s);
   }
 }
+// The first LG stages only, on the 16 >> LG groups of 2^LG adjacent registers (the second round of a row pass over R =
+// 2^(4 + LG) rows): all groups share the twiddles.
+template <bool BIG, int LG, class TW>
+__device__ __forceinline__ void radix_groups_fwd(u64 (&x)[16], u64 q, u64 q2, TW tw) {
+#pragma unroll
+  for (int s = 0; s < LG; s++) {
+    const int half = (1 << LG) >> (s + 1);
+#pragma unroll
+    for (int g = 0; g < (1 << s); g++) {
+      ulonglong2 w = tw(s, g);
+#pragma unroll
+      for (int k = 0; k < 16; k += 1 << LG)
+#pragma unroll
+        for (int p = 0; p < half; p++) bf_fwd<BIG>(x[k + g * 2 * half + p], x[k + g * 2 * half + p + half], w, q, q2);
+    }
+  }
+}
+template <bool BIG, int LG, class TW>
+__device__ __forceinline__ void radix_groups_inv(u64 (&x)[16], u64 q, u64 c0, TW tw) {
+  u64 c = c0;
+#pragma unroll
+  for (int s = LG - 1; s >= 0; s--) {
+    const int half = (1 << LG) >> (s + 1);
+#pragma unroll
+    for (int g = 0; g < (1 << s); g++) {
+      ulonglong2 w = tw(s, g);
+#pragma unroll
+      for (int k = 0; k < 16; k += 1 << LG)
+#pragma unroll
+        for (int p = 0; p < half; p++) bf_inv<BIG>(x[k + g * 2 * half + p], x[k + g * 2 * half + p + half], w, q, c);
+    }
+    if (!BIG) c <<= 1;
+  }
+}
 // Slot of the twiddle pair of stage s, group g in a round's table of 15.
 #define NTT16_TW_INDEX(s, g) ((1 << (s)) - 1 + (g))
 // The 2^s twiddle pairs of stage s, from `src`, into their slots of a round's table. Written out per stage so that
@@ -120,21 +156,37 @@ __device__ __forceinline__ void ntt16_load_stage(ulonglong2 (&t)[15], const ulon
 
 __device__ __forceinline__ u64 barrett_lazy(u64 v, u64 mu, u64 q) { return v - mul_hi64(v, mu) * q; }  // [0,2q)
 
-// ---- pass bodies. `base` points at one limb-vector of 65536 words, `tw` at that modulus' table. ----
+// ---- pass bodies. `base` points at one limb-vector of N words, `tw` at that modulus' table. ----
 
-// Forward, stages 0..7. In: canonical (or < 2q). Out: SMALL < 33q (+in), BIG < 8q.
-// `x` holds, for lane (r0 = t>>4, col = t&15), the rows i*16 + r0 (i = 0..15) of column col0 + col.
-template <bool BIG>
+// Lane layouts of a row pass over R = 2^LOGR rows (NC = 4096 / R columns per tile, J = R / 16). First round: lane
+// (r0 = t / NC, col = t % NC) holds rows i*J + r0 (i = 0..15) of column col0 + col. Second round: lane (i0 = t >> 4,
+// c = t & 15) holds rows i0*J + j (j < J) of the columns col0 + c + 16*k (k < 16 / J) in register k*J + j.
+template <int LOGR>
+struct RowTile {
+  static constexpr int LG = LOGR - 4, J = 1 << LG, NC = 4096 >> LOGR;
+  // offset of register i of a lane inside the limb, first round / second round
+  static __device__ __forceinline__ u32 first(u32 i, u32 t, u32 tile) { return ((i << LG) + t / NC) * 256 + tile * NC + t % NC; }
+  static __device__ __forceinline__ u32 second(u32 r, u32 t, u32 tile) {
+    return (((t >> 4) << LG) + (r & (J - 1))) * 256 + tile * NC + (t & 15) + 16 * (r >> LG);
+  }
+  // the same inside the LDS tile [R][NC]; the first round's layout is i * 256 + t
+  static __device__ __forceinline__ u32 lds_second(u32 r, u32 t) {
+    return (((t >> 4) << LG) + (r & (J - 1))) * NC + (t & 15) + 16 * (r >> LG);
+  }
+};
+
+// Forward, stages 0..LOGR-1. In: canonical (or < 2q). Out: SMALL < 33q (+in), BIG < 8q. `x` holds the first round's layout.
+template <bool BIG, int LOGR>
 __device__ __forceinline__ void ntt16_fwd_rows_loaded(u64 (&x)[16], u64* __restrict__ dst, const ulonglong2* __restrict__ tw,
                                                       u64 q, u32 tile, u64* sm) {
-  const u32 t = threadIdx.x, col = t & 15, r0 = t >> 4, col0 = tile * 16;
+  typedef RowTile<LOGR> T;
+  const u32 t = threadIdx.x, i0 = t >> 4;
   const u64 q2 = lazy_const<BIG>(q);
-  const u32 i0 = r0;
   // the second round's twiddles (one set per 16-lane group) are requested here, next to the data loads, and arrive
   // during the first round, whose own twiddles are wave-uniform scalar loads
   ulonglong2 twb[15];
 #pragma unroll
-  for (int s = 0; s < 4; s++)
+  for (int s = 0; s < T::LG; s++)
 #pragma unroll
     for (int g = 0; g < (1 << s); g++) twb[NTT16_TW_INDEX(s, g)] = tw[(16 << s) + (i0 << s) + g];
   __builtin_amdgcn_sched_barrier(0);
@@ -143,26 +195,25 @@ __device__ __forceinline__ void ntt16_fwd_rows_loaded(u64 (&x)[16], u64* __restr
   for (int i = 0; i < 16; i++) sm[i * 256 + t] = x[i];
   lds_barrier();
 #pragma unroll
-  for (int j = 0; j < 16; j++) x[j] = sm[(i0 * 16 + j) * 16 + col];
-  radix16_fwd<BIG>(x, q, q2, [&](int s, int g) { return twb[NTT16_TW_INDEX(s, g)]; });
+  for (int r = 0; r < 16; r++) x[r] = sm[T::lds_second(r, t)];
+  radix_groups_fwd<BIG, T::LG>(x, q, q2, [&](int s, int g) { return twb[NTT16_TW_INDEX(s, g)]; });
 #pragma unroll
-  for (int j = 0; j < 16; j++) dst[(size_t)(i0 * 16 + j) * 256 + col0 + col] = x[j];
+  for (int r = 0; r < 16; r++) dst[T::second(r, t, tile)] = x[r];
 }
-template <bool BIG>
+template <bool BIG, int LOGR>
 __device__ __forceinline__ void ntt16_fwd_rows(const u64* __restrict__ src, u64* __restrict__ dst, const ulonglong2* __restrict__ tw,
                                                u64 q, u32 tile, u64* sm) {
-  const u32 t = threadIdx.x, col = t & 15, r0 = t >> 4, col0 = tile * 16;
   u64 x[16];
 #pragma unroll
-  for (int i = 0; i < 16; i++) x[i] = src[(size_t)(i * 16 + r0) * 256 + col0 + col];
-  ntt16_fwd_rows_loaded<BIG>(x, dst, tw, q, tile, sm);
+  for (int i = 0; i < 16; i++) x[i] = src[RowTile<LOGR>::first(i, threadIdx.x, tile)];
+  ntt16_fwd_rows_loaded<BIG, LOGR>(x, dst, tw, q, tile, sm);
 }
 
-// Forward, stages 8..15, then canonical (CANON) or < 2q. `x` is left holding, for lane (hb = t>>4, j0 = t&15), the 16 values at
+// Forward, the last 8 stages of a limb of R blocks, then canonical (CANON) or < 2q. `x` is left holding, for lane (hb = t>>4, j0 = t&15), the 16 values at
 // block h = tile*16 + hb, positions i*16 + j0 (i = 0..15), ready for a coalesced store or a fused epilogue.
 template <bool BIG, bool CANON = true>
 __device__ __forceinline__ void ntt16_fwd_blocks_loaded(u64 (&x)[16], const ulonglong2* __restrict__ tw, u64 q, u64 mu,
-                                                        u32 tile, u64* sm) {
+                                                        u32 tile, u32 R, u64* sm) {
   const u32 t = threadIdx.x, j0 = t & 15, hb = t >> 4, h = tile * 16 + hb;
   const u64 q2 = lazy_const<BIG>(q);
   const u32 i0 = j0;
@@ -172,13 +223,13 @@ __device__ __forceinline__ void ntt16_fwd_blocks_loaded(u64 (&x)[16], const ulon
 #pragma unroll
   for (int s = 0; s < 4; s++)
 #pragma unroll
-    for (int g = 0; g < (1 << s); g++) twa[NTT16_TW_INDEX(s, g)] = tw[(256 << s) + (h << s) + g];
+    for (int g = 0; g < (1 << s); g++) twa[NTT16_TW_INDEX(s, g)] = tw[(R << s) + (h << s) + g];
   __builtin_amdgcn_sched_barrier(0);
   radix16_fwd_staged<BIG>(
       x, q, q2, [&](int s, int g) { return twa[NTT16_TW_INDEX(s, g)]; },
       [&](int s) {
         __builtin_amdgcn_sched_barrier(0);
-        ntt16_load_stage(twb, tw + (4096 << s) + (h << (4 + s)) + (i0 << s), s);
+        ntt16_load_stage(twb, tw + (R << (4 + s)) + (h << (4 + s)) + (i0 << s), s);
         __builtin_amdgcn_sched_barrier(0);
       });
 #pragma unroll
@@ -204,16 +255,15 @@ __device__ __forceinline__ void ntt16_fwd_blocks_loaded(u64 (&x)[16], const ulon
 
 template <bool BIG, bool CANON = true>
 __device__ __forceinline__ void ntt16_fwd_blocks(u64 (&x)[16], const u64* __restrict__ src, const ulonglong2* __restrict__ tw,
-                                                 u64 q, u64 mu, u32 tile, u64* sm) {
+                                                 u64 q, u64 mu, u32 tile, u32 R, u64* sm) {
   const u32 t = threadIdx.x, j0 = t & 15, h = tile * 16 + (t >> 4);
   const u64* blk = src + (size_t)h * 256;
 #pragma unroll
   for (int i = 0; i < 16; i++) x[i] = blk[i * 16 + j0];
-  ntt16_fwd_blocks_loaded<BIG, CANON>(x, tw, q, mu, tile, sm);
+  ntt16_fwd_blocks_loaded<BIG, CANON>(x, tw, q, mu, tile, R, sm);
 }
 
-// Forward, stages 8..15 of one 256-element block by 32 adjacent lanes with 8 values each (the layout of
-// ntt256_fwd_blocks_fp8: radix-8, exchange, radix-8, exchange, radix-4; LDS rows of pitch 35 words per 32 elements,
+// Forward, the last 8 stages of one 256-element block h of R by 32 adjacent lanes with 8 values each (radix-8, exchange, radix-8, exchange, radix-4; LDS rows of pitch 35 words per 32 elements,
 // all exchanges inside the half-wave). In: x[i] = element i*32 + l, lazy (BIG: < 8q). Out: x[c] = element
 // (l >> 2)*32 + (l & 3)*8 + c, below 2q. `between` runs after the first exchange has been written.
 #define NTT8_PITCH_I 35
@@ -247,7 +297,7 @@ __device__ __forceinline__ void radix8_fwd_staged(u64 (&x)[8], u64 q, u64 q2, TW
 }
 template <bool BIG, class BETWEEN>
 __device__ __forceinline__ void ntt256_fwd_blocks_int8(u64 (&x)[8], const ulonglong2* __restrict__ tw, u64 q, u64 mu, u32 h,
-                                                       u32 l, u64* smb, BETWEEN between) {
+                                                       u32 R, u32 l, u64* smb, BETWEEN between) {
   const u32 a = l >> 2, b = l & 3;
   const u64 q2 = lazy_const<BIG>(q);
   // The first two rounds' twiddles are requested before `between` runs: the first round's here, the second round's
@@ -258,13 +308,13 @@ __device__ __forceinline__ void ntt256_fwd_blocks_int8(u64 (&x)[8], const ulongl
 #pragma unroll
   for (int s = 0; s < 3; s++)
 #pragma unroll
-    for (int g = 0; g < (1 << s); g++) t1[(1 << s) - 1 + g] = tw[(256 << s) + (h << s) + g];
+    for (int g = 0; g < (1 << s); g++) t1[(1 << s) - 1 + g] = tw[(R << s) + (h << s) + g];
   __builtin_amdgcn_sched_barrier(0);
   radix8_fwd_staged<BIG>(
       x, q, q2, [&](int s, int g) { return t1[(1 << s) - 1 + g]; },
       [&](int s) {
         __builtin_amdgcn_sched_barrier(0);
-        const ulonglong2* ts = tw + (2048 << s) + (h << (3 + s)) + (a << s);
+        const ulonglong2* ts = tw + (R << (3 + s)) + (h << (3 + s)) + (a << s);
         if (s == 0) {
           t2[0] = ts[0];
         } else if (s == 1) {
@@ -284,9 +334,9 @@ __device__ __forceinline__ void ntt256_fwd_blocks_int8(u64 (&x)[8], const ulongl
   radix8_fwd<BIG>(x, q, q2, [&](int s, int g) { return t2[(1 << s) - 1 + g]; });
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int u = 0; u < 2; u++) t3[u] = tw[16384 + (h << 6) + (a << 3) + (b << 1) + u];
+  for (int u = 0; u < 2; u++) t3[u] = tw[(R << 6) + (h << 6) + (a << 3) + (b << 1) + u];
 #pragma unroll
-  for (int k = 0; k < 4; k++) t3[2 + k] = tw[32768 + (h << 7) + (a << 4) + (b << 2) + k];
+  for (int k = 0; k < 4; k++) t3[2 + k] = tw[(R << 7) + (h << 7) + (a << 4) + (b << 2) + k];
   __builtin_amdgcn_sched_barrier(0);
   wave_lds_sync();
 #pragma unroll
@@ -305,11 +355,11 @@ __device__ __forceinline__ void ntt256_fwd_blocks_int8(u64 (&x)[8], const ulongl
   for (int c = 0; c < 8; c++) x[c] = BIG ? csub(csub(x[c], q2), 2 * q) : barrett_lazy(x[c], mu, q);
 }
 
-// Inverse, stages 15..8 on contiguous blocks. In: x holds, for lane (hb, j0), the values at positions i*16 + j0
+// Inverse, the first 8 stages, on contiguous blocks. In: x holds, for lane (hb, j0), the values at positions i*16 + j0
 // of block h (any value < 2q). Out: < 2q (BIG: < 4q), same lane layout, ready for a coalesced store.
 template <bool BIG>
 __device__ __forceinline__ void ntt16_inv_blocks(u64 (&x)[16], const ulonglong2* __restrict__ twi, u64 q, u64 mu, u32 tile,
-                                                 u64* sm) {
+                                                 u32 R, u64* sm) {
   const u32 t = threadIdx.x, j0 = t & 15, hb = t >> 4, h = tile * 16 + hb;
   const u64 q2 = lazy_const<BIG>(q);
   const u32 i0 = j0;
@@ -319,7 +369,7 @@ __device__ __forceinline__ void ntt16_inv_blocks(u64 (&x)[16], const ulonglong2*
 #pragma unroll
   for (int s = 0; s < 4; s++)
 #pragma unroll
-    for (int g = 0; g < (1 << s); g++) twa[NTT16_TW_INDEX(s, g)] = twi[(4096 << s) + (h << (4 + s)) + (i0 << s) + g];
+    for (int g = 0; g < (1 << s); g++) twa[NTT16_TW_INDEX(s, g)] = twi[(R << (4 + s)) + (h << (4 + s)) + (i0 << s) + g];
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int i = 0; i < 16; i++) sm[hb * 272 + i * 17 + j0] = x[i];
@@ -331,7 +381,7 @@ __device__ __forceinline__ void ntt16_inv_blocks(u64 (&x)[16], const ulonglong2*
       x, q, q2, [&](int s, int g) { return twa[NTT16_TW_INDEX(s, g)]; },
       [&](int s) {
         __builtin_amdgcn_sched_barrier(0);
-        ntt16_load_stage(twb, twi + (256 << s) + (h << s), s);
+        ntt16_load_stage(twb, twi + (R << s) + (h << s), s);
         __builtin_amdgcn_sched_barrier(0);
       });
   wave_lds_sync();
@@ -347,52 +397,53 @@ __device__ __forceinline__ void ntt16_inv_blocks(u64 (&x)[16], const ulonglong2*
   }
 }
 
-// Inverse, stages 7..0 on 256 rows x 16 columns, then multiplication by the constant (sc, scs) (N^-1, possibly
-// merged with another per-limb constant) and canonical output. In: < 2q (BIG: < 4q). x holds for lane (r0 = t>>4, col = t&15)
-// the rows i*16 + r0 of column col0 + col.
-template <bool BIG>
+// Inverse, stages LOGR-1..0 on R rows x NC columns, then multiplication by the constant (sc, scs) (N^-1, possibly
+// merged with another per-limb constant) and canonical output. In: < 2q (BIG: < 4q). x receives the first round's layout
+// of the row tile.
+template <bool BIG, int LOGR>
 __device__ __forceinline__ void ntt16_inv_rows(u64 (&x)[16], const u64* __restrict__ src, const ulonglong2* __restrict__ twi,
                                                u64 q, u64 sc, u64 scs, u32 tile, u64* sm) {
-  const u32 t = threadIdx.x, col = t & 15, i0 = t >> 4, col0 = tile * 16;
+  typedef RowTile<LOGR> T;
+  const u32 t = threadIdx.x, i0 = t >> 4;
   const u64 q2 = lazy_const<BIG>(q);
 #pragma unroll
-  for (int j = 0; j < 16; j++) x[j] = src[(size_t)(i0 * 16 + j) * 256 + col0 + col];
+  for (int r = 0; r < 16; r++) x[r] = src[T::second(r, t, tile)];
   // first round's twiddles (one set per group) travel with the data; the second round's are scalar loads
   ulonglong2 twa[15];
 #pragma unroll
-  for (int s = 0; s < 4; s++)
+  for (int s = 0; s < T::LG; s++)
 #pragma unroll
     for (int g = 0; g < (1 << s); g++) twa[NTT16_TW_INDEX(s, g)] = twi[(16 << s) + (i0 << s) + g];
   __builtin_amdgcn_sched_barrier(0);
-  radix16_inv<BIG>(x, q, q2, [&](int s, int g) { return twa[NTT16_TW_INDEX(s, g)]; });
+  radix_groups_inv<BIG, T::LG>(x, q, q2, [&](int s, int g) { return twa[NTT16_TW_INDEX(s, g)]; });
 #pragma unroll
-  for (int j = 0; j < 16; j++) sm[(i0 * 16 + j) * 16 + col] = x[j];
+  for (int r = 0; r < 16; r++) sm[T::lds_second(r, t)] = x[r];
   lds_barrier();
 #pragma unroll
   for (int i = 0; i < 16; i++) x[i] = sm[i * 256 + t];
-  radix16_inv<BIG>(x, q, BIG ? q2 : (q2 << 4), [&](int s, int g) { return twi[(1 << s) + g]; });
+  radix16_inv<BIG>(x, q, BIG ? q2 : (q2 << T::LG), [&](int s, int g) { return twi[(1 << s) + g]; });
 #pragma unroll
   for (int i = 0; i < 16; i++) x[i] = shoup(x[i], sc, scs, q);
-}
-
-// Eval-domain Galois map for N = 2^16: out[k] = in[k'], 2*brev(k')+1 = (2*brev(k)+1)*g mod 2N. It maps every aligned
-// 16-element segment onto an aligned 16-element segment, so 16 adjacent lanes still read one 128-byte line.
-__device__ __forceinline__ u32 galois_src_index16(u32 k, u32 g) {
-  u32 e = 2 * (__brev(k) >> 16) + 1;
-  u32 t = (e * g) & 0x1FFFFu;
-  return __brev(t >> 1) >> 16;
 }
 
 // Workgroup -> (poly, tile, slot). mode 0: dispatch order is polynomial-fastest; 1: same, made XCD-contiguous;
 // 2: tile-fastest; 3: tile-fastest, XCD-contiguous; 4: all polynomials of one (tile, slot) group run on one XCD
 // (they share that group's twiddles and key slices in its L2) while eight consecutive groups, one per XCD, are in
-// flight together, which keeps the XCDs evenly loaded. gridDim.y * gridDim.z must be a multiple of 8 for mode 4.
+// flight together, which keeps the XCDs evenly loaded (groups beyond the last multiple of 8 are dealt out in order).
 __device__ __forceinline__ void ntt16_map(u32 mode, u32& poly, u32& tile, u32& slot) {
   const u32 lin0 = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
   if (mode == 4) {
-    const u32 x = lin0 & 7, rest = lin0 >> 3;
-    poly = rest % gridDim.x;
-    const u32 group = x + 8 * (rest / gridDim.x);
+    const u32 whole = (gridDim.y * gridDim.z) & ~7u;
+    u32 group;
+    if (lin0 < whole * gridDim.x) {
+      const u32 x = lin0 & 7, rest = lin0 >> 3;
+      poly = rest % gridDim.x;
+      group = x + 8 * (rest / gridDim.x);
+    } else {
+      const u32 rest = lin0 - whole * gridDim.x;
+      poly = rest % gridDim.x;
+      group = whole + rest / gridDim.x;
+    }
     tile = group % gridDim.y;
     slot = group / gridDim.y;
     return;

@@ -1,4 +1,4 @@
-// Kernels of the N = 2^16 path: the four transform passes and the two fused last-pass kernels of key switching.
+// Kernels of the two-pass path (N = 2^13 .. 2^16): the four transform passes and the two fused last-pass kernels of key switching.
 // Each kernel picks, per modulus (uniform per workgroup), the double-precision bodies (q < 2^50), the integer
 // bodies without butterfly corrections (q < 2^52) or the Harvey bodies (q < 2^60). The class also fixes the
 // format of the data between the two passes of a transform (reduced doubles / lazy integers) and of the
@@ -7,7 +7,7 @@
 #include "ntt16.hip.h"
 #include "ntt16fp.hip.h"
 
-// ---- standalone passes: grid = (polynomials, 16 tiles, limb slots) ----
+// ---- standalone passes: grid = (polynomials, N / 4096 tiles, limb slots) ----
 // A batched rotation may give every ciphertext its own Galois element and key: the kernels then take both from
 // small per-ciphertext tables carried in the kernel arguments (at most this many ciphertexts per launch sequence).
 #define KS_MULTI_MAX 64
@@ -15,9 +15,10 @@
 struct Ntt16Args {
   const u64* src;
   u64* dst;
-  const ulonglong2* tw;     // integer table (forward or inverse), [nm][65536]
+  const ulonglong2* tw;     // integer table (forward or inverse), [nm][N]
   const double* twfp;       // double table, same indexing (rows of moduli >= 2^50 unused)
   const ModInfo* mods;
+  u32 logN;
   u64 src_poly_stride, dst_poly_stride;  // elements between polynomials
   u32 skip_beta, skip_alpha, skip_nq;    // digit p % skip_beta leaves its own limbs alone (ModUp'ed digits)
   u32 map_mode;                          // workgroup -> (poly, tile, slot) mapping, see ntt16_map
@@ -38,37 +39,40 @@ __device__ __forceinline__ bool ntt16_skip(const Ntt16Args& a, u32 poly, u32 slo
   u32 j = poly % a.skip_beta, lo = j * a.skip_alpha, hi = min(lo + a.skip_alpha, a.skip_nq);
   return slot >= lo && slot < hi;
 }
-#define NTT16_PROLOGUE                                                              \
-  __shared__ u64 sm[NTT16_LDS_BYTES / 8];                                           \
+#define NTT16_PROLOGUE(LOGN, LDS_WORDS)                                             \
+  __shared__ u64 sm[LDS_WORDS];                                                     \
   u32 poly, tile, zi;                                                               \
   ntt16_map(a.map_mode, poly, tile, zi);                                            \
   const u32 slot = a.slots[zi];                                                     \
   if (ntt16_skip(a, poly, slot)) return;                                            \
   const u32 id = a.id[slot];                                                        \
   const ModInfo mi = a.mods[id];                                                    \
-  const ulonglong2* tw = a.tw + (size_t)id * 65536;                                 \
-  const double* twfp = a.twfp + (size_t)id * 65536;                                 \
-  const u64* src = a.src + (size_t)poly * a.src_poly_stride + (size_t)slot * 65536; \
-  u64* dst = a.dst + (size_t)poly * a.dst_poly_stride + (size_t)slot * 65536;       \
+  const u32 logN = LOGN, R = 1u << (logN - 8);                                      \
+  const ulonglong2* tw = a.tw + ((size_t)id << logN);                               \
+  const double* twfp = a.twfp + ((size_t)id << logN);                               \
+  const u64* src = a.src + (size_t)poly * a.src_poly_stride + ((size_t)slot << logN); \
+  u64* dst = a.dst + (size_t)poly * a.dst_poly_stride + ((size_t)slot << logN);     \
+  (void)R;                                                                          \
   const int cls = CLS;
 
 // CLS: modulus class of every slot of the launch (0 double precision, 1 integer uncorrected, 2 Harvey); one
 // instantiation per class so that each gets its own register allocation.
-template <int CLS>
+// The row passes take a 32 KB tile: on double-precision moduli (under 96 registers) five workgroups share a compute unit.
+template <int CLS, int LOGR>
 __global__ void __launch_bounds__(NTT16_THREADS) ntt16_fwd_rows_kernel(Ntt16Args a) {
-  NTT16_PROLOGUE
-  if (cls == 0) ntt16_fwd_rows_fp(src, (double*)dst, twfp, mi.qd, mi.qinv, tile, (double*)sm);
-  else if (cls == 2) ntt16_fwd_rows<true>(src, dst, tw, mi.m, tile, sm);
-  else ntt16_fwd_rows<false>(src, dst, tw, mi.m, tile, sm);
+  NTT16_PROLOGUE(LOGR + 8, CLS == 0 ? 4096 : NTT16_LDS_BYTES / 8)
+  if (cls == 0) ntt16_fwd_rows_fp<LOGR>(src, (double*)dst, twfp, mi.qd, mi.qinv, tile, (double*)sm);
+  else if (cls == 2) ntt16_fwd_rows<true, LOGR>(src, dst, tw, mi.m, tile, sm);
+  else ntt16_fwd_rows<false, LOGR>(src, dst, tw, mi.m, tile, sm);
 }
 template <int CLS>
 __global__ void __launch_bounds__(NTT16_THREADS) ntt16_fwd_blocks_kernel(Ntt16Args a) {
-  NTT16_PROLOGUE
+  NTT16_PROLOGUE(a.logN, NTT16_LDS_BYTES / 8)
   const u32 t = threadIdx.x, j0 = t & 15, h = tile * 16 + (t >> 4);
   u64 x[16];
   if (cls == 0) {
     double xd[16];
-    ntt16_fwd_blocks_fp(xd, (const double*)src, twfp, mi.qd, mi.qinv, tile, (double*)sm);
+    ntt16_fwd_blocks_fp(xd, (const double*)src, twfp, mi.qd, mi.qinv, tile, R, (double*)sm);
     if (a.raw_out) {
 #pragma unroll
       for (int i = 0; i < 16; i++) x[i] = (u64)__double_as_longlong(xd[i]);
@@ -77,22 +81,22 @@ __global__ void __launch_bounds__(NTT16_THREADS) ntt16_fwd_blocks_kernel(Ntt16Ar
       for (int i = 0; i < 16; i++) x[i] = d2u_canon(xd[i], mi.qd);
     }
   } else if (cls == 2) {
-    ntt16_fwd_blocks<true>(x, src, tw, mi.m, mi.mu64, tile, sm);
+    ntt16_fwd_blocks<true>(x, src, tw, mi.m, mi.mu64, tile, R, sm);
   } else {
-    ntt16_fwd_blocks<false>(x, src, tw, mi.m, mi.mu64, tile, sm);
+    ntt16_fwd_blocks<false>(x, src, tw, mi.m, mi.mu64, tile, R, sm);
   }
 #pragma unroll
   for (int i = 0; i < 16; i++) dst[(size_t)h * 256 + i * 16 + j0] = x[i];
 }
 template <int CLS>
 __global__ void __launch_bounds__(NTT16_THREADS) ntt16_inv_blocks_kernel(Ntt16Args a) {
-  NTT16_PROLOGUE
+  NTT16_PROLOGUE(a.logN, NTT16_LDS_BYTES / 8)
   const u32 t = threadIdx.x, j0 = t & 15, h = tile * 16 + (t >> 4);
   u64 x[16];
   const u32 g = a.multi ? a.galois_pc[__builtin_amdgcn_readfirstlane(poly)] : a.galois;
   if (g) {
 #pragma unroll
-    for (int i = 0; i < 16; i++) x[i] = src[galois_src_index16(h * 256 + i * 16 + j0, g)];
+    for (int i = 0; i < 16; i++) x[i] = src[galois_src_index(h * 256 + i * 16 + j0, g, logN)];
   } else {
 #pragma unroll
     for (int i = 0; i < 16; i++) x[i] = src[(size_t)h * 256 + i * 16 + j0];
@@ -101,20 +105,20 @@ __global__ void __launch_bounds__(NTT16_THREADS) ntt16_inv_blocks_kernel(Ntt16Ar
     double xd[16];
 #pragma unroll
     for (int i = 0; i < 16; i++) xd[i] = u2d(x[i]);
-    ntt16_inv_blocks_fp(xd, twfp, mi.qd, mi.qinv, tile, (double*)sm);
+    ntt16_inv_blocks_fp(xd, twfp, mi.qd, mi.qinv, tile, R, (double*)sm);
 #pragma unroll
     for (int i = 0; i < 16; i++) x[i] = (u64)__double_as_longlong(xd[i]);
   } else if (cls == 2) {
-    ntt16_inv_blocks<true>(x, tw, mi.m, mi.mu64, tile, sm);
+    ntt16_inv_blocks<true>(x, tw, mi.m, mi.mu64, tile, R, sm);
   } else {
-    ntt16_inv_blocks<false>(x, tw, mi.m, mi.mu64, tile, sm);
+    ntt16_inv_blocks<false>(x, tw, mi.m, mi.mu64, tile, R, sm);
   }
 #pragma unroll
   for (int i = 0; i < 16; i++) dst[(size_t)h * 256 + i * 16 + j0] = x[i];
 }
-template <int CLS>
+template <int CLS, int LOGR>
 __global__ void __launch_bounds__(NTT16_THREADS) ntt16_inv_rows_kernel(Ntt16Args a) {
-  NTT16_PROLOGUE
+  NTT16_PROLOGUE(LOGR + 8, CLS == 0 ? 4096 : NTT16_LDS_BYTES / 8)
   u64 x[16];
   if (cls == 0) {
     double sc = mi.ninvd, scq = mi.ninvq;
@@ -123,7 +127,7 @@ __global__ void __launch_bounds__(NTT16_THREADS) ntt16_inv_rows_kernel(Ntt16Args
       sc = v.x;
       scq = v.y;
     }
-    ntt16_inv_rows_fp(x, (const double*)src, twfp, mi.qd, mi.qinv, sc, scq, tile, (double*)sm);
+    ntt16_inv_rows_fp<LOGR>(x, (const double*)src, twfp, mi.qd, mi.qinv, sc, scq, tile, (double*)sm);
   } else {
     u64 sc = mi.ninv, scs = mi.ninvs;
     if (a.scale) {
@@ -131,8 +135,8 @@ __global__ void __launch_bounds__(NTT16_THREADS) ntt16_inv_rows_kernel(Ntt16Args
       sc = v.x;
       scs = v.y;
     }
-    if (cls == 2) ntt16_inv_rows<true>(x, src, tw, mi.m, sc, scs, tile, sm);
-    else ntt16_inv_rows<false>(x, src, tw, mi.m, sc, scs, tile, sm);
+    if (cls == 2) ntt16_inv_rows<true, LOGR>(x, src, tw, mi.m, sc, scs, tile, sm);
+    else ntt16_inv_rows<false, LOGR>(x, src, tw, mi.m, sc, scs, tile, sm);
   }
   if (a.split_out) {   // wave-uniform
     const u64 hq = mi.m >> 1;
@@ -142,12 +146,11 @@ __global__ void __launch_bounds__(NTT16_THREADS) ntt16_inv_rows_kernel(Ntt16Args
       x[i] = (y & 0x3FFFFFFFull) | ((y >> 30) << 32);
     }
   }
-  const u32 t = threadIdx.x, col = t & 15, r0 = t >> 4, col0 = tile * 16;
 #pragma unroll
-  for (int i = 0; i < 16; i++) dst[(size_t)(i * 16 + r0) * 256 + col0 + col] = x[i];
+  for (int i = 0; i < 16; i++) dst[RowTile<LOGR>::first(i, threadIdx.x, tile)] = x[i];
 }
 
-// ---- fused: base conversion + first forward pass (ModUp and ModDown) ----
+// ---- fused: base conversion + first forward pass (ModUp and ModDown), N = 2^16 ----
 // The coefficient-domain sources arrive in the form the inverse row pass writes when Ntt16Args::split_out is set:
 // for a source modulus c with h = (c - 1) / 2, the word holds yt = (y + h) mod c, y = [x (C/c)^-1]_c, as two 30-bit
 // halves (bits 0..29 and bits 32..62). Since yt - h is the centred representative of y,
@@ -325,11 +328,11 @@ __global__ void __launch_bounds__(NTT16_THREADS) ntt16_bconv_rows_kernel(BconvRo
     double xd[16];
 #pragma unroll
     for (int i = 0; i < 16; i++) xd[i] = u2d(x[i]);
-    ntt16_fwd_rows_fp_loaded(xd, (double*)dst, a.twfp + (size_t)id * 65536, mi.qd, mi.qinv, tile, (double*)sm);
+    ntt16_fwd_rows_fp_loaded<8>(xd, (double*)dst, a.twfp + (size_t)id * 65536, mi.qd, mi.qinv, tile, (double*)sm);
   } else if (CLS == 2) {
-    ntt16_fwd_rows_loaded<true>(x, dst, a.tw + (size_t)id * 65536, mi.m, tile, sm);
+    ntt16_fwd_rows_loaded<true, 8>(x, dst, a.tw + (size_t)id * 65536, mi.m, tile, sm);
   } else {
-    ntt16_fwd_rows_loaded<false>(x, dst, a.tw + (size_t)id * 65536, mi.m, tile, sm);
+    ntt16_fwd_rows_loaded<false, 8>(x, dst, a.tw + (size_t)id * 65536, mi.m, tile, sm);
   }
 }
 
@@ -348,7 +351,7 @@ struct FwdInnerArgs {
   const ulonglong2* tw;
   const double* twfp; 
   const ModInfo* mods;
-  u32 nlimbs, nq, nm, alpha, beta, next, map_mode, galois;
+  u32 logN, nlimbs, nq, nm, alpha, beta, next, map_mode, galois;
   u32 ext_galois;            // streaming kernels only: != 0 reads ext through the Galois map too (hoisted digits:
                              // ext holds the transform of the un-rotated polynomial, shared by many rotations)
   unsigned char slots[128];  // grid.z index -> extended slot (one modulus class per launch)
@@ -406,10 +409,12 @@ typedef __attribute__((address_space(1))) const void* global_void_ptr;
 typedef const __attribute__((address_space(1))) u64* global_u64_ptr;
 typedef u64 global_u64x2 __attribute__((ext_vector_type(2)));
 #define INNER_C_EX_WORDS (16 * 272)
+template <int LOGN>   // compile-time ring: with a run-time shift the kernel spills
 __device__ __forceinline__ void fwd_inner_c_body_fp(const FwdInnerArgs& a, u32 bc, u32 tile, u32 t, u32 id, const ModInfo& mi,
                                                     u32* ex, double* img, double* twl) {
   const u32 b = bc >> 1, c = bc & 1;
-  const size_t N = 65536;
+  constexpr size_t N = (size_t)1 << LOGN;
+  constexpr u32 R = 1u << (LOGN - 8);
   const double q = mi.qd, qinv = mi.qinv;
   const double* tw = a.twfp + (size_t)id * N;
   const u64* evk = fwd_inner_evk(a, b) + ((size_t)c * a.nm + id) * N;
@@ -454,7 +459,7 @@ __device__ __forceinline__ void fwd_inner_c_body_fp(const FwdInnerArgs& a, u32 b
   u32 jn = jo == 0 ? 1u : 0u;   // next converted digit
   if (jn < beta) request(ext_limb(jn));
   else if (tq_limb) request(tq_limb);
-  const double twv = ntt16_twl_fetch(tw, tile);
+  const double twv = ntt16_twl_fetch(tw, tile, R);
   u32 cnt = 0;
   if (jo != 0xFFFFFFFFu) {
     const u32 pos = lane_pos();
@@ -464,7 +469,7 @@ __device__ __forceinline__ void fwd_inner_c_body_fp(const FwdInnerArgs& a, u32 b
     for (int i = 0; i < 16; i++) e[i] = k[i * 16];
     if (g) {
 #pragma unroll
-      for (int i = 0; i < 16; i++) x[i] = u2d(src[galois_src_index16(pos + i * 16, g)]);
+      for (int i = 0; i < 16; i++) x[i] = u2d(src[galois_src_index(pos + i * 16, g, LOGN)]);
     } else {
 #pragma unroll
       for (int i = 0; i < 16; i++) x[i] = u2d(src[pos + i * 16]);
@@ -483,7 +488,7 @@ __device__ __forceinline__ void fwd_inner_c_body_fp(const FwdInnerArgs& a, u32 b
     // loads, which wait for the prefetch in case it lands where they read)
     const global_u64_ptr k = (global_u64_ptr)(evk + (size_t)jn * 2 * a.nm * N + lane_pos());
     ntt16_fwd_blocks_fp_words(
-        x, tw, q, qinv, tile, ex, twl,
+        x, tw, q, qinv, tile, R, ex, twl,
         [&] {
           // always issued (the current tile again when nothing follows), so that the waits of the two rounds are
           // the same static counts on every path
@@ -509,14 +514,14 @@ __device__ __forceinline__ void fwd_inner_c_body_fp(const FwdInnerArgs& a, u32 b
     const u64* a2 = a.fin_add2 + (a2poly * a.nlimbs + t) * N;
     const u64* as = a.fin_add_src + ((size_t)bc * a.nlimbs + t) * N;
     take(x);
-    ntt16_fwd_blocks_fp_words(x, tw, q, qinv, tile, ex, twl, [] {}, [&] {
+    ntt16_fwd_blocks_fp_words(x, tw, q, qinv, tile, R, ex, twl, [] {}, [&] {
       const u32 pos = lane_pos();
       if (mode & 1) {
 #pragma unroll
         for (int i = 0; i < 16; i++) e[i] = a2[pos + i * 16];
       } else if (mode == 2) {
 #pragma unroll
-        for (int i = 0; i < 16; i++) e[i] = as[galois_src_index16(pos + i * 16, gf)];
+        for (int i = 0; i < 16; i++) e[i] = as[galois_src_index(pos + i * 16, gf, LOGN)];
       }
     });
     const double2 pv = ((const double2*)a.fin_pinv)[t];
@@ -527,7 +532,7 @@ __device__ __forceinline__ void fwd_inner_c_body_fp(const FwdInnerArgs& a, u32 b
       double r = fp_mulmod_const(fp_reduce(acc[i], qinv, q) - x[i], pv.x, pv.y, q);   // |r| <= 0.75 q
       if (mode) r += u2d(e[i]);
       if (mode == 3) {
-        r += u2d(as[galois_src_index16(pos + i * 16, gf)]);
+        r += u2d(as[galois_src_index(pos + i * 16, gf, LOGN)]);
         r = r >= q ? r - q : r;
       }
       o[i * 16] = d2u_canon(r, q);
@@ -544,12 +549,13 @@ __device__ __forceinline__ void fwd_inner_c_body_fp(const FwdInnerArgs& a, u32 b
       const double pm = u2d(mi.pmod);
       const u32 pos = lane_pos();
 #pragma unroll
-      for (int i = 0; i < 16; i++) acc[i] += fp_mulmod_var(u2d(src[galois_src_index16(pos + i * 16, g)]), pm, qinv, q);
+      for (int i = 0; i < 16; i++) acc[i] += fp_mulmod_var(u2d(src[galois_src_index(pos + i * 16, g, LOGN)]), pm, qinv, q);
     }
   }
 #pragma unroll
   for (int i = 0; i < 16; i++) o[i * 16] = d2u_canon(fp_reduce(acc[i], qinv, q), q);
 }
+template <int LOGN>
 __global__ void __launch_bounds__(NTT16_THREADS) __attribute__((amdgpu_waves_per_eu(3, 3)))
 ntt16_fwd_blocks_inner_c_kernel(FwdInnerArgs a) {
   // separate arrays, so that the compiler knows the transposes never touch the image a prefetch is landing in
@@ -561,11 +567,11 @@ ntt16_fwd_blocks_inner_c_kernel(FwdInnerArgs a) {
   const u32 t = a.slots[zi];
   const u32 id = t < a.nlimbs ? t : t - a.nlimbs + a.nq;
   const ModInfo mi = a.mods[id];
-  fwd_inner_c_body_fp(a, bc, tile, t, id, mi, ex, img, twl);
+  fwd_inner_c_body_fp<LOGN>(a, bc, tile, t, id, mi, ex, img, twl);
 }
 
 // Integer-class moduli (the special primes): both key components per workgroup, 8 values per lane: a workgroup takes
-// 8 of the 256-element blocks of a (ciphertext, slot) (grid.y = 32 tiles), each block transformed by 32 lanes
+// 8 of the 256-element blocks of a (ciphertext, slot) (grid.y = N / 2048 tiles), each block transformed by 32 lanes
 // (ntt256_fwd_blocks_int8), which keeps the kernel at 3 waves per SIMD. After the transform a lane holds 8 consecutive
 // coefficients, so key words and accumulators move as 16-byte accesses. Products go through a Montgomery reduction:
 // acc carries the factor 2^-64, which the later stages absorb into their constants.
@@ -580,14 +586,13 @@ ntt16_fwd_blocks_inner8_kernel(FwdInnerArgs a) {
   const u32 t = a.slots[zi];
   const u32 id = t < a.nlimbs ? t : t - a.nlimbs + a.nq;
   const ModInfo mi = a.mods[id];
-  const size_t N = 65536;
+  const size_t N = (size_t)1 << a.logN;
   const u64 q = mi.m, q2 = 2 * mi.m;
   const ulonglong2* tw = a.tw + (size_t)id * N;
   const u32 tid = threadIdx.x, l = tid & 31, hb = tid >> 5, h = tile * 8 + hb;
   u64* smb = sm + hb * NTT8_BLOCK_LDS_I;
   const u64* evk = fwd_inner_evk(a, b) + (size_t)id * N;
   const u32 g = __builtin_amdgcn_readfirstlane(fwd_inner_galois(a, b));
-  const u32 posA = h * 256 + l;
   const u32 posC = h * 256 + (l >> 2) * 32 + (l & 3) * 8;
   u64 acc0[8], acc1[8], x[8];
   ulonglong2 e0[4], e1[4];
@@ -654,7 +659,7 @@ ntt16_fwd_blocks_inner8_kernel(FwdInnerArgs a) {
     request_key(jo);
     if (g) {
 #pragma unroll
-      for (int c = 0; c < 8; c++) x[c] = src[galois_src_index16(posC + c, g)];
+      for (int c = 0; c < 8; c++) x[c] = src[galois_src_index(posC + c, g, a.logN)];
     } else {
 #pragma unroll
       for (int v = 0; v < 4; v++) {
@@ -671,7 +676,7 @@ ntt16_fwd_blocks_inner8_kernel(FwdInnerArgs a) {
     u32 jnext = jn + 1;
     if (jnext == jo) jnext++;
     const u32 jcur = jn;
-    ntt256_fwd_blocks_int8<BIG>(x, tw, q, mi.mu64, h, l, smb, [&] { request_key(jcur); });
+    ntt256_fwd_blocks_int8<BIG>(x, tw, q, mi.mu64, h, 1u << (a.logN - 8), l, smb, [&] { request_key(jcur); });
     __builtin_amdgcn_sched_barrier(0);
     // younger than every load the products wait for, so it stays in flight across them (the current tile again when
     // nothing follows: the same static wait counts on every path)
@@ -696,7 +701,7 @@ ntt16_fwd_blocks_inner8_kernel(FwdInnerArgs a) {
       const u64* src = a.c0 + (size_t)b * a.c0_poly_stride + (size_t)t * N;
 #pragma unroll
       for (int c = 0; c < 8; c++) {
-        const u64 v = src[galois_src_index16(posC + c, g)];
+        const u64 v = src[galois_src_index(posC + c, g, a.logN)];
         Acc128 p = {v * mi.pmod, mul_hi64(v, mi.pmod)};
         acc0[c] = csub(acc0[c] + redc(p, q, mi.minv), q2);
       }
@@ -724,7 +729,7 @@ struct FwdFinalArgs {
   const double* twfp; 
   const ModInfo* mods;
   const ulonglong2* pinv;  // [nlimbs]
-  u32 nlimbs, next, mode0, mode1, galois, map_mode;
+  u32 logN, nlimbs, next, mode0, mode1, galois, map_mode;
   unsigned char slots[128];  // grid.z index -> limb (one modulus class per launch)
   u32 multi = 0;             // != 0: ciphertext b = bc / 2 reads add_src through galois_pc[b]
   u32 galois_pc[KS_MULTI_MAX];
@@ -737,10 +742,11 @@ __device__ __forceinline__ size_t final_add2_poly(const FwdFinalArgs& a, u32 bc)
 template <bool BIG>
 __device__ __forceinline__ void fwd_final_body(const FwdFinalArgs& a, u32 bc, u32 tile, u32 i_limb, const ModInfo& mi, u64* sm) {
   const u32 tid = threadIdx.x, j0 = tid & 15, h = tile * 16 + (tid >> 4);
-  const size_t N = 65536;
+  const size_t N = (size_t)1 << a.logN;
   const u64 q = mi.m, q2 = 2 * mi.m;
   u64 x[16];
-  ntt16_fwd_blocks<BIG, false>(x, a.tq + ((size_t)bc * a.nlimbs + i_limb) * N, a.tw + (size_t)i_limb * N, q, mi.mu64, tile, sm);
+  ntt16_fwd_blocks<BIG, false>(x, a.tq + ((size_t)bc * a.nlimbs + i_limb) * N, a.tw + (size_t)i_limb * N, q, mi.mu64, tile,
+                               1u << (a.logN - 8), sm);
   const ulonglong2 pv = a.pinv[i_limb];
   const u64* ac = a.acc + ((size_t)bc * a.next + i_limb) * N + (size_t)h * 256 + j0;
   u64* o = a.out + ((size_t)bc * a.nlimbs + i_limb) * N + (size_t)h * 256 + j0;
@@ -752,14 +758,14 @@ __device__ __forceinline__ void fwd_final_body(const FwdFinalArgs& a, u32 bc, u3
   for (int i = 0; i < 16; i++) {
     u64 r = shoup(ac[i * 16] + q2 - x[i], pv.x, pv.y, q);
     if (mode & 1) r = addmod(r, a2[i * 16], q);
-    if (mode & 2) r = addmod(r, as[galois_src_index16(h * 256 + i * 16 + j0, g)], q);
+    if (mode & 2) r = addmod(r, as[galois_src_index(h * 256 + i * 16 + j0, g, a.logN)], q);
     o[i * 16] = r;
   }
 }
 __device__ __forceinline__ void fwd_final_body_fp(const FwdFinalArgs& a, u32 bc, u32 tile, u32 i_limb, const ModInfo& mi,
                                                   double* sm) {
   const u32 tid = threadIdx.x, j0 = tid & 15, h = tile * 16 + (tid >> 4);
-  const size_t N = 65536;
+  const size_t N = (size_t)1 << a.logN;
   const double q = mi.qd, qinv = mi.qinv;
   double x[16];
   const u64* ac = a.acc + ((size_t)bc * a.next + i_limb) * N + (size_t)h * 256 + j0;
@@ -777,17 +783,17 @@ __device__ __forceinline__ void fwd_final_body_fp(const FwdFinalArgs& a, u32 bc,
     for (int i = 0; i < 16; i++) ad[i] = a2[i * 16];
   } else if (mode == 2) {
 #pragma unroll
-    for (int i = 0; i < 16; i++) ad[i] = as[galois_src_index16(h * 256 + i * 16 + j0, g)];
+    for (int i = 0; i < 16; i++) ad[i] = as[galois_src_index(h * 256 + i * 16 + j0, g, a.logN)];
   }
   ntt16_fwd_blocks_fp(x, (const double*)(a.tq + ((size_t)bc * a.nlimbs + i_limb) * N), a.twfp + (size_t)i_limb * N, q, qinv,
-                      tile, sm);
+                      tile, 1u << (a.logN - 8), sm);
   const double2 pv = ((const double2*)a.pinv)[i_limb];
 #pragma unroll
   for (int i = 0; i < 16; i++) {
     double r = fp_mulmod_const(u2d(av[i]) - x[i], pv.x, pv.y, q);  // |r| <= 0.9 q
     if (mode) r += u2d(ad[i]);
     if (mode == 3) {   // two addends: the gathered one is fetched here; bring the sum back below 2q first
-      r += u2d(as[galois_src_index16(h * 256 + i * 16 + j0, g)]);
+      r += u2d(as[galois_src_index(h * 256 + i * 16 + j0, g, a.logN)]);
       r = r >= q ? r - q : r;
     }
     o[i * 16] = d2u_canon(r, q);
@@ -813,7 +819,7 @@ __global__ void __launch_bounds__(NTT16_THREADS) ntt16_fwd_blocks_final_kernel(F
 // (B, N/256, slots of the class), batch innermost so that consecutive workgroups share the key slice.
 __global__ void __launch_bounds__(256) inner16_fp_kernel(FwdInnerArgs a) {
   // two adjacent coefficients per lane (16-byte accesses); grid.y = N / 512
-  const size_t N = 65536;
+  const size_t N = (size_t)1 << a.logN;
   u32 b, blk, zi;
   ntt16_map(a.map_mode, b, blk, zi);
   const u32 t = a.slots[zi];
@@ -829,8 +835,8 @@ __global__ void __launch_bounds__(256) inner16_fp_kernel(FwdInnerArgs a) {
     if (fwd_inner_owns(a, t, j)) {
       const u64* src = a.d + (size_t)b * a.d_poly_stride + (size_t)t * N;
       if (g_own) {
-        x[0] = u2d(src[galois_src_index16(n, g_own)]);
-        x[1] = u2d(src[galois_src_index16(n + 1, g_own)]);
+        x[0] = u2d(src[galois_src_index(n, g_own, a.logN)]);
+        x[1] = u2d(src[galois_src_index(n + 1, g_own, a.logN)]);
       } else {
         const ulonglong2 v = *(const ulonglong2*)(src + n);
         x[0] = u2d(v.x);
@@ -839,8 +845,8 @@ __global__ void __launch_bounds__(256) inner16_fp_kernel(FwdInnerArgs a) {
     } else {
       const u64* e = a.ext + (((size_t)b * a.beta + j) * a.next + t) * N;
       if (a.ext_galois) {
-        x[0] = __longlong_as_double((long long)e[galois_src_index16(n, a.ext_galois)]);
-        x[1] = __longlong_as_double((long long)e[galois_src_index16(n + 1, a.ext_galois)]);
+        x[0] = __longlong_as_double((long long)e[galois_src_index(n, a.ext_galois, a.logN)]);
+        x[1] = __longlong_as_double((long long)e[galois_src_index(n + 1, a.ext_galois, a.logN)]);
       } else {
         const double2 v = *(const double2*)(e + n);
         x[0] = v.x;
@@ -865,8 +871,8 @@ __global__ void __launch_bounds__(256) inner16_fp_kernel(FwdInnerArgs a) {
   if (a.c0 && t < a.nlimbs) {   // at most three products are pending here, a fourth keeps the sum below 2^52
     const u64* src = a.c0 + (size_t)b * a.c0_poly_stride + (size_t)t * N;
     const double pm = u2d(mi.pmod);
-    s0[0] += fp_mulmod_var(u2d(src[galois_src_index16(n, g_own)]), pm, qinv, q);
-    s0[1] += fp_mulmod_var(u2d(src[galois_src_index16(n + 1, g_own)]), pm, qinv, q);
+    s0[0] += fp_mulmod_var(u2d(src[galois_src_index(n, g_own, a.logN)]), pm, qinv, q);
+    s0[1] += fp_mulmod_var(u2d(src[galois_src_index(n + 1, g_own, a.logN)]), pm, qinv, q);
   }
   u64* o0 = a.acc + (((size_t)b * 2 + 0) * a.next + t) * N + n;
   if (a.accumulate) {   // fold first (|.| <= q/2), then the old canonical values fit under the same bound
@@ -884,7 +890,7 @@ __global__ void __launch_bounds__(256) inner16_fp_kernel(FwdInnerArgs a) {
 // Same for integer-class moduli (hoisted rotations only): ext holds canonical residues in the evaluation domain;
 // products go through a Montgomery reduction, so acc carries the factor 2^-64 like the fused kernel's.
 __global__ void __launch_bounds__(256) inner16_int_kernel(FwdInnerArgs a) {
-  const size_t N = 65536;
+  const size_t N = (size_t)1 << a.logN;
   u32 b, blk, zi;
   ntt16_map(a.map_mode, b, blk, zi);
   const u32 t = a.slots[zi];
@@ -902,8 +908,8 @@ __global__ void __launch_bounds__(256) inner16_int_kernel(FwdInnerArgs a) {
     const u32 g = own ? g_own : a.ext_galois;
     u64 x[2];
     if (g) {
-      x[0] = src[galois_src_index16(n, g)];
-      x[1] = src[galois_src_index16(n + 1, g)];
+      x[0] = src[galois_src_index(n, g, a.logN)];
+      x[1] = src[galois_src_index(n + 1, g, a.logN)];
     } else {
       const ulonglong2 v = *(const ulonglong2*)(src + n);
       x[0] = v.x;
@@ -928,7 +934,7 @@ __global__ void __launch_bounds__(256) inner16_int_kernel(FwdInnerArgs a) {
     const u64* src = a.c0 + (size_t)b * a.c0_poly_stride + (size_t)t * N;
 #pragma unroll
     for (int e = 0; e < 2; e++) {
-      const u64 v = src[galois_src_index16(n + e, g_own)];
+      const u64 v = src[galois_src_index(n + e, g_own, a.logN)];
       Acc128 p0;
       p0.lo = v * mi.pmod;
       p0.hi = mul_hi64(v, mi.pmod);
@@ -963,7 +969,7 @@ __global__ void __launch_bounds__(256) inner16_int_kernel(FwdInnerArgs a) {
 template <int MAXB, bool EXACT>   // EXACT: beta == MAXB (no per-digit tests), else beta <= MAXB
 __global__ void __launch_bounds__(256) inner16_rot_fp_kernel(FwdInnerArgs a, u32 B) {
   constexpr int CB = INNER16_ROT_CB_FP;
-  const size_t N = 65536;
+  const size_t N = (size_t)1 << a.logN;
   u32 bg, blk, zi;
   ntt16_map(a.map_mode, bg, blk, zi);
   const u32 t = a.slots[zi];
@@ -994,7 +1000,7 @@ __global__ void __launch_bounds__(256) inner16_rot_fp_kernel(FwdInnerArgs a, u32
   }
   // the key words of rotation r + 1 are requested before the sums of rotation r are formed
   u64 kw[MAXB][2], kn[MAXB][2];
-  u32 m_next = galois_src_index16(n, a.galois_pc[0]);
+  u32 m_next = galois_src_index(n, a.galois_pc[0], a.logN);
   const size_t comp_stride = (size_t)a.nm * N, id_off = (size_t)id * N;
   auto load_keys = [&](u64 (&w)[MAXB][2], u32 r, u32 m) {
     const u64* kp = uniform_ptr(a.evk_pc[r]) + id_off + m;
@@ -1017,7 +1023,7 @@ __global__ void __launch_bounds__(256) inner16_rot_fp_kernel(FwdInnerArgs a, u32
       kw[j][1] = kn[j][1];
     }
     if (r + 1 < a.nrot) {
-      m_next = galois_src_index16(n, a.galois_pc[r + 1]);
+      m_next = galois_src_index(n, a.galois_pc[r + 1], a.logN);
       load_keys(kn, r + 1, m_next);
     }
     double s0[CB], s1[CB];
@@ -1061,7 +1067,7 @@ __global__ void __launch_bounds__(256) inner16_rot_fp_kernel(FwdInnerArgs a, u32
 template <int MAXB>
 __global__ void __launch_bounds__(256) inner16_rot_int_kernel(FwdInnerArgs a, u32 B) {
   constexpr int CB = INNER16_ROT_CB;
-  const size_t N = 65536;
+  const size_t N = (size_t)1 << a.logN;
   u32 bg, blk, zi;
   ntt16_map(a.map_mode, bg, blk, zi);
   const u32 t = a.slots[zi];
@@ -1092,7 +1098,7 @@ __global__ void __launch_bounds__(256) inner16_rot_int_kernel(FwdInnerArgs a, u3
     }
   }
   for (u32 r = 0; r < a.nrot; r++) {
-    const u32 m = galois_src_index16(n, a.galois_pc[r]);
+    const u32 m = galois_src_index(n, a.galois_pc[r], a.logN);
     const u64* evk = uniform_ptr(a.evk_pc[r]) + (size_t)id * N + m;
     // up to 8 products below 2^120 summed in 128 bits, one Montgomery reduction per output (result below 2q)
     Acc128 v0[CB], v1[CB];
@@ -1128,7 +1134,7 @@ __global__ void __launch_bounds__(256) inner16_rot_int_kernel(FwdInnerArgs a, u3
 // Galois element of rotation r, evk_pc[r] its key; d = c1 and c0 are the two components of the input ciphertext.
 // Same grid and mapping as inner16_fp_kernel.
 __global__ void __launch_bounds__(256) inner16_sum_fp_kernel(FwdInnerArgs a) {
-  const size_t N = 65536;
+  const size_t N = (size_t)1 << a.logN;
   u32 b, blk, zi;
   ntt16_map(a.map_mode, b, blk, zi);
   const u32 t = a.slots[zi];
@@ -1154,7 +1160,7 @@ __global__ void __launch_bounds__(256) inner16_sum_fp_kernel(FwdInnerArgs a) {
   for (u32 r = 0; r < a.nrot; r++) {
     const u32 g = a.galois_pc[r];
     const u64* evk = uniform_ptr(a.evk_pc[r]) + (size_t)id * N + n;
-    const u32 m[2] = {galois_src_index16(n, g), galois_src_index16(n + 1, g)};
+    const u32 m[2] = {galois_src_index(n, g, a.logN), galois_src_index(n + 1, g, a.logN)};
     // the running sums enter a rotation below 1.5 q in magnitude; three products (0.75 q each) are added between folds
     u32 pending = 0;
     for (u32 j = 0; j < a.beta; j++) {
@@ -1198,7 +1204,7 @@ __global__ void __launch_bounds__(256) inner16_sum_fp_kernel(FwdInnerArgs a) {
 
 // The same for integer-class moduli (every term with the factor 2^-64, as in inner16_int_kernel).
 __global__ void __launch_bounds__(256) inner16_sum_int_kernel(FwdInnerArgs a) {
-  const size_t N = 65536;
+  const size_t N = (size_t)1 << a.logN;
   u32 b, blk, zi;
   ntt16_map(a.map_mode, b, blk, zi);
   const u32 t = a.slots[zi];
@@ -1226,7 +1232,7 @@ __global__ void __launch_bounds__(256) inner16_sum_int_kernel(FwdInnerArgs a) {
   for (u32 r = 0; r < a.nrot; r++) {
     const u32 g = a.galois_pc[r];
     const u64* evk = uniform_ptr(a.evk_pc[r]) + (size_t)id * N + n;
-    const u32 m[2] = {galois_src_index16(n, g), galois_src_index16(n + 1, g)};
+    const u32 m[2] = {galois_src_index(n, g, a.logN), galois_src_index(n + 1, g, a.logN)};
     for (u32 j = 0; j < a.beta; j++) {
       const u64* src = fwd_inner_owns(a, t, j) ? c1 : a.ext + (((size_t)b * a.beta + j) * a.next + t) * N;
       const u64 x[2] = {src[m[0]], src[m[1]]};

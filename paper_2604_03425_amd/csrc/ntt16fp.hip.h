@@ -1,4 +1,4 @@
-// Double-precision variants of the N = 2^16 pass bodies of ntt16.hip.h, for primes q < 2^50.
+// Double-precision variants of the two-pass bodies of ntt16.hip.h, for primes q < 2^50.
 // On gfx950 the vector FP64 units run at full rate, and a modular multiply by a constant is 6 FP64
 // instructions (against ~23 integer instructions for the 64-bit Shoup form), exact because every value is an
 // integer below 2^53. Same tiles, lane layouts and LDS transposes as the integer bodies.
@@ -56,16 +56,68 @@ __device__ __forceinline__ void radix16_inv_fp(double (&x)[16], double q, double
   }
 }
 
-// Forward, stages 0..7. `x` holds integers of magnitude at most q (residues as doubles) in the row layout of
-// ntt16_fwd_rows_loaded; dst receives reduced doubles.
+// The first LG stages only, on 16 >> LG groups of 2^LG adjacent registers sharing the twiddles; reduced at the end
+// (forward) / after every two stages and at the end (inverse).
+template <int LG, class TW>
+__device__ __forceinline__ void radix_groups_fwd_fp(double (&x)[16], double q, double qinv, TW tw) {
+#pragma unroll
+  for (int s = 0; s < LG; s++) {
+    const int half = (1 << LG) >> (s + 1);
+#pragma unroll
+    for (int g = 0; g < (1 << s); g++) {
+      const double w = tw(s, g);
+#pragma unroll
+      for (int k = 0; k < 16; k += 1 << LG)
+#pragma unroll
+        for (int p = 0; p < half; p++) {
+          double& X = x[k + g * 2 * half + p];
+          double& Y = x[k + g * 2 * half + p + half];
+          const double T = fp_mulmod_var(Y, w, qinv, q);
+          Y = X - T;
+          X = X + T;
+        }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 16; i++) x[i] = fp_reduce(x[i], qinv, q);
+}
+template <int LG, class TW>
+__device__ __forceinline__ void radix_groups_inv_fp(double (&x)[16], double q, double qinv, TW tw) {
+#pragma unroll
+  for (int s = LG - 1; s >= 0; s--) {
+    const int half = (1 << LG) >> (s + 1);
+#pragma unroll
+    for (int g = 0; g < (1 << s); g++) {
+      const double w = tw(s, g);
+#pragma unroll
+      for (int k = 0; k < 16; k += 1 << LG)
+#pragma unroll
+        for (int p = 0; p < half; p++) {
+          double& X = x[k + g * 2 * half + p];
+          double& Y = x[k + g * 2 * half + p + half];
+          const double D = X - Y;
+          X = X + Y;
+          Y = fp_mulmod_var(D, w, qinv, q);
+        }
+    }
+    if (((LG - s) & 1) == 0 || s == 0) {
+#pragma unroll
+      for (int i = 0; i < 16; i++) x[i] = fp_reduce(x[i], qinv, q);
+    }
+  }
+}
+
+// Forward, stages 0..LOGR-1. `x` holds integers of magnitude at most q (residues as doubles) in the first round's layout
+// of the row tile (RowTile); dst receives reduced doubles.
+template <int LOGR>
 __device__ __forceinline__ void ntt16_fwd_rows_fp_loaded(double (&x)[16], double* __restrict__ dst,
                                                          const double* __restrict__ tw, double q, double qinv, u32 tile,
                                                          double* sm) {
-  const u32 t = threadIdx.x, col = t & 15, r0 = t >> 4, col0 = tile * 16;
-  const u32 i0 = r0;
+  typedef RowTile<LOGR> T;
+  const u32 t = threadIdx.x, i0 = t >> 4;
   double twb[15];  // second-round twiddles, requested before the first round
 #pragma unroll
-  for (int s = 0; s < 4; s++)
+  for (int s = 0; s < T::LG; s++)
 #pragma unroll
     for (int g = 0; g < (1 << s); g++) twb[(1 << s) - 1 + g] = tw[(16 << s) + (i0 << s) + g];
   radix16_fwd_fp(x, q, qinv, [&](int s, int g) { return tw[(1 << s) + g]; });
@@ -73,28 +125,28 @@ __device__ __forceinline__ void ntt16_fwd_rows_fp_loaded(double (&x)[16], double
   for (int i = 0; i < 16; i++) sm[i * 256 + t] = x[i];
   lds_barrier();
 #pragma unroll
-  for (int j = 0; j < 16; j++) x[j] = sm[(i0 * 16 + j) * 16 + col];
-  radix16_fwd_fp(x, q, qinv, [&](int s, int g) { return twb[(1 << s) - 1 + g]; });
+  for (int r = 0; r < 16; r++) x[r] = sm[T::lds_second(r, t)];
+  radix_groups_fwd_fp<T::LG>(x, q, qinv, [&](int s, int g) { return twb[(1 << s) - 1 + g]; });
 #pragma unroll
-  for (int j = 0; j < 16; j++) dst[(size_t)(i0 * 16 + j) * 256 + col0 + col] = x[j];
+  for (int r = 0; r < 16; r++) dst[T::second(r, t, tile)] = x[r];
 }
 // The same from canonical residues (uint64) in memory.
+template <int LOGR>
 __device__ __forceinline__ void ntt16_fwd_rows_fp(const u64* __restrict__ src, double* __restrict__ dst,
                                                   const double* __restrict__ tw, double q, double qinv, u32 tile, double* sm) {
-  const u32 t = threadIdx.x, col = t & 15, r0 = t >> 4, col0 = tile * 16;
   double x[16];
 #pragma unroll
-  for (int i = 0; i < 16; i++) x[i] = u2d(src[(size_t)(i * 16 + r0) * 256 + col0 + col]);
-  ntt16_fwd_rows_fp_loaded(x, dst, tw, q, qinv, tile, sm);
+  for (int i = 0; i < 16; i++) x[i] = u2d(src[RowTile<LOGR>::first(i, threadIdx.x, tile)]);
+  ntt16_fwd_rows_fp_loaded<LOGR>(x, dst, tw, q, qinv, tile, sm);
 }
 
-// Forward, stages 8..15 on reduced doubles. Leaves x (|x| <= q/2) in the i-layout of ntt16_fwd_blocks.
+// Forward, the last 8 stages of a limb of R blocks, on reduced doubles. Leaves x (|x| <= q/2) in the i-layout of ntt16_fwd_blocks.
 // `x` must already hold the tile in the i-layout (lane (hb, j0) holds positions i*16 + j0 of block h).
 // `between` runs after the first round (its twiddles are dead by then), e.g. to request data the caller needs
 // after the transform.
 template <class BETWEEN>
 __device__ __forceinline__ void ntt16_fwd_blocks_fp_loaded(double (&x)[16], const double* __restrict__ tw, double q,
-                                                           double qinv, u32 tile, double* sm, BETWEEN between) {
+                                                           double qinv, u32 tile, u32 R, double* sm, BETWEEN between) {
   const u32 t = threadIdx.x, j0 = t & 15, hb = t >> 4, h = tile * 16 + hb;
   const u32 i0 = j0;
   // the second round's 15 twiddles are requested up front so they arrive during the first round
@@ -102,8 +154,8 @@ __device__ __forceinline__ void ntt16_fwd_blocks_fp_loaded(double (&x)[16], cons
 #pragma unroll
   for (int s = 0; s < 4; s++)
 #pragma unroll
-    for (int g = 0; g < (1 << s); g++) twb[(1 << s) - 1 + g] = tw[(4096 << s) + (h << (4 + s)) + (i0 << s) + g];
-  radix16_fwd_fp(x, q, qinv, [&](int s, int g) { return tw[(256 << s) + (h << s) + g]; });
+    for (int g = 0; g < (1 << s); g++) twb[(1 << s) - 1 + g] = tw[(R << (4 + s)) + (h << (4 + s)) + (i0 << s) + g];
+  radix16_fwd_fp(x, q, qinv, [&](int s, int g) { return tw[(R << s) + (h << s) + g]; });
 #pragma unroll
   for (int i = 0; i < 16; i++) sm[hb * 272 + i * 17 + j0] = x[i];
   between();
@@ -119,8 +171,8 @@ __device__ __forceinline__ void ntt16_fwd_blocks_fp_loaded(double (&x)[16], cons
   for (int i = 0; i < 16; i++) x[i] = sm[hb * 272 + i * 17 + j0];
 }
 __device__ __forceinline__ void ntt16_fwd_blocks_fp_loaded(double (&x)[16], const double* __restrict__ tw, double q,
-                                                           double qinv, u32 tile, double* sm) {
-  ntt16_fwd_blocks_fp_loaded(x, tw, q, qinv, tile, sm, [] {});
+                                                           double qinv, u32 tile, u32 R, double* sm) {
+  ntt16_fwd_blocks_fp_loaded(x, tw, q, qinv, tile, R, sm, [] {});
 }
 
 // The same block pass with its 16 x 16 transposes done in two halves, low words then high words, through a tile of
@@ -154,11 +206,11 @@ __device__ __forceinline__ void fp_transpose16_words(double (&x)[16], u32* row_m
 #define NTT16_TWL_PITCH 18
 // Filling it is split in two so that a caller can put other work between the request and the use of the value:
 // wave w fills the rows of its own four groups, lane L < 60 moving twiddle L % 15 of group 4w + L / 15.
-__device__ __forceinline__ double ntt16_twl_fetch(const double* __restrict__ tw, u32 tile) {
+__device__ __forceinline__ double ntt16_twl_fetch(const double* __restrict__ tw, u32 tile, u32 R) {
   const u32 t = threadIdx.x, L = min(t & 63, 59u);
   const u32 hb = (t >> 6) * 4 + L / 15, k = L % 15, h = tile * 16 + hb;
   const u32 s = k >= 7 ? 3 : k >= 3 ? 2 : k >= 1 ? 1 : 0, g = k + 1 - (1u << s);
-  return tw[(256 << s) + (h << s) + g];
+  return tw[(R << s) + (h << s) + g];
 }
 __device__ __forceinline__ void ntt16_twl_store(double v, double* twl) {
   const u32 t = threadIdx.x, L = t & 63;
@@ -166,7 +218,7 @@ __device__ __forceinline__ void ntt16_twl_store(double v, double* twl) {
 }
 template <class LOADED, class BETWEEN>
 __device__ __forceinline__ void ntt16_fwd_blocks_fp_words(double (&x)[16], const double* __restrict__ tw, double q,
-                                                          double qinv, u32 tile, u32* ex, const double* twl, LOADED loaded,
+                                                          double qinv, u32 tile, u32 R, u32* ex, const double* twl, LOADED loaded,
                                                           BETWEEN between) {
   const u32 t = threadIdx.x, j0 = t & 15, hb = t >> 4, h = tile * 16 + hb;
   const u32 i0 = j0;
@@ -175,7 +227,7 @@ __device__ __forceinline__ void ntt16_fwd_blocks_fp_words(double (&x)[16], const
 #pragma unroll
   for (int s = 0; s < 4; s++)
 #pragma unroll
-    for (int g = 0; g < (1 << s); g++) twb[(1 << s) - 1 + g] = tw[(4096 << s) + (h << (4 + s)) + (i0 << s) + g];
+    for (int g = 0; g < (1 << s); g++) twb[(1 << s) - 1 + g] = tw[(R << (4 + s)) + (h << (4 + s)) + (i0 << s) + g];
 #pragma unroll
   for (int k = 0; k < 15; k++) twa[k] = twl[hb * NTT16_TWL_PITCH + k];
   asm volatile("" ::: "memory");
@@ -191,9 +243,9 @@ __device__ __forceinline__ void ntt16_fwd_blocks_fp_words(double (&x)[16], const
   fp_transpose16_words(x, grp, 1, i0 * 17, 17, j0);
 }
 
-// Inverse, stages 15..8. In: x = canonical residues as doubles, i-layout. Out: reduced doubles, i-layout.
+// Inverse, the first 8 stages. In: x = canonical residues as doubles, i-layout. Out: reduced doubles, i-layout.
 __device__ __forceinline__ void ntt16_inv_blocks_fp(double (&x)[16], const double* __restrict__ twi, double q, double qinv,
-                                                    u32 tile, double* sm) {
+                                                    u32 tile, u32 R, double* sm) {
   const u32 t = threadIdx.x, j0 = t & 15, hb = t >> 4, h = tile * 16 + hb;
   const u32 i0 = j0;
   double twa[15], twb[15];  // both rounds' twiddles, requested before the first transpose
@@ -201,8 +253,8 @@ __device__ __forceinline__ void ntt16_inv_blocks_fp(double (&x)[16], const doubl
   for (int s = 0; s < 4; s++)
 #pragma unroll
     for (int g = 0; g < (1 << s); g++) {
-      twa[(1 << s) - 1 + g] = twi[(4096 << s) + (h << (4 + s)) + (i0 << s) + g];
-      twb[(1 << s) - 1 + g] = twi[(256 << s) + (h << s) + g];
+      twa[(1 << s) - 1 + g] = twi[(R << (4 + s)) + (h << (4 + s)) + (i0 << s) + g];
+      twb[(1 << s) - 1 + g] = twi[(R << s) + (h << s) + g];
     }
 #pragma unroll
   for (int i = 0; i < 16; i++) sm[hb * 272 + i * 17 + j0] = x[i];
@@ -219,16 +271,19 @@ __device__ __forceinline__ void ntt16_inv_blocks_fp(double (&x)[16], const doubl
   radix16_inv_fp(x, q, qinv, [&](int s, int g) { return twb[(1 << s) - 1 + g]; });
 }
 
-// Inverse, stages 7..0, then multiplication by (sc, sc/q); x receives canonical residues (uint64), row layout.
+// Inverse, stages LOGR-1..0, then multiplication by (sc, sc/q); out receives canonical residues (uint64) in the first
+// round's layout of the row tile.
+template <int LOGR>
 __device__ __forceinline__ void ntt16_inv_rows_fp(u64 (&out)[16], const double* __restrict__ src, const double* __restrict__ twi,
                                                   double q, double qinv, double sc, double scq, u32 tile, double* sm) {
-  const u32 t = threadIdx.x, col = t & 15, i0 = t >> 4, col0 = tile * 16;
+  typedef RowTile<LOGR> T;
+  const u32 t = threadIdx.x, i0 = t >> 4;
   double x[16];
 #pragma unroll
-  for (int j = 0; j < 16; j++) x[j] = src[(size_t)(i0 * 16 + j) * 256 + col0 + col];
-  radix16_inv_fp(x, q, qinv, [&](int s, int g) { return twi[(16 << s) + (i0 << s) + g]; });
+  for (int r = 0; r < 16; r++) x[r] = src[T::second(r, t, tile)];
+  radix_groups_inv_fp<T::LG>(x, q, qinv, [&](int s, int g) { return twi[(16 << s) + (i0 << s) + g]; });
 #pragma unroll
-  for (int j = 0; j < 16; j++) sm[(i0 * 16 + j) * 16 + col] = x[j];
+  for (int r = 0; r < 16; r++) sm[T::lds_second(r, t)] = x[r];
   lds_barrier();
 #pragma unroll
   for (int i = 0; i < 16; i++) x[i] = sm[i * 256 + t];
@@ -238,91 +293,10 @@ __device__ __forceinline__ void ntt16_inv_rows_fp(u64 (&out)[16], const double* 
 }
 
 __device__ __forceinline__ void ntt16_fwd_blocks_fp(double (&x)[16], const double* __restrict__ src,
-                                                    const double* __restrict__ tw, double q, double qinv, u32 tile, double* sm) {
+                                                    const double* __restrict__ tw, double q, double qinv, u32 tile, u32 R, double* sm) {
   const u32 t = threadIdx.x, j0 = t & 15, h = tile * 16 + (t >> 4);
   const double* blk = src + (size_t)h * 256;
 #pragma unroll
   for (int i = 0; i < 16; i++) x[i] = blk[i * 16 + j0];
-  ntt16_fwd_blocks_fp_loaded(x, tw, q, qinv, tile, sm);
-}
-
-// ---- block pass with 8 values per lane (used where a kernel needs the registers for something else) ----
-// One 256-element block is transformed by 32 adjacent lanes: radix-8 on stages 8..10, exchange, radix-8 on stages
-// 11..13, exchange, radix-4 on stages 14..15; the exchanges go through the block's own LDS rows (pitch 35 doubles per
-// 32 elements: near conflict-free for all three access patterns) and stay inside the half-wave, so no workgroup
-// barrier. In: x[i] = element i*32 + l of block h (l = lane & 31), |x| <= q/2. Out: x[c] = element
-// (l >> 2)*32 + (l & 3)*8 + c, i.e. 8 consecutive elements per lane, |x| <= q/2. Ranges: reduced after the first
-// round; the following five stages take |x| <= 0.5 q to at most 7.7 q < 2^53 / q.
-#define NTT8_PITCH 35
-#define NTT8_BLOCK_LDS (8 * NTT8_PITCH)
-
-template <class TW>
-__device__ __forceinline__ void radix8_fwd_fp(double (&x)[8], double q, double qinv, TW tw) {
-#pragma unroll
-  for (int s = 0; s < 3; s++) {
-    const int half = 4 >> s;
-#pragma unroll
-    for (int g = 0; g < (1 << s); g++) {
-      const double w = tw(s, g);
-#pragma unroll
-      for (int p = 0; p < half; p++) {
-        double& X = x[g * 2 * half + p];
-        double& Y = x[g * 2 * half + p + half];
-        const double T = fp_mulmod_var(Y, w, qinv, q);
-        Y = X - T;
-        X = X + T;
-      }
-    }
-  }
-}
-
-template <class BETWEEN>
-__device__ __forceinline__ void ntt256_fwd_blocks_fp8(double (&x)[8], const double* __restrict__ tw, double q, double qinv,
-                                                      u32 h, u32 l, double* smb, BETWEEN between) {
-  const u32 a = l >> 2, b = l & 3;
-  // the twiddles of the second and third round are requested up front so they arrive during the first
-  double t2[7], t3[6];
-#pragma unroll
-  for (int s = 0; s < 3; s++)
-#pragma unroll
-    for (int g = 0; g < (1 << s); g++) t2[(1 << s) - 1 + g] = tw[(2048 << s) + (h << (3 + s)) + (a << s) + g];
-#pragma unroll
-  for (int u = 0; u < 2; u++) t3[u] = tw[16384 + (h << 6) + (a << 3) + (b << 1) + u];
-#pragma unroll
-  for (int k = 0; k < 4; k++) t3[2 + k] = tw[32768 + (h << 7) + (a << 4) + (b << 2) + k];
-  radix8_fwd_fp(x, q, qinv, [&](int s, int g) { return tw[(256 << s) + (h << s) + g]; });
-#pragma unroll
-  for (int i = 0; i < 8; i++) smb[i * NTT8_PITCH + l] = fp_reduce(x[i], qinv, q);
-  between();
-  wave_lds_sync();
-#pragma unroll
-  for (int r = 0; r < 8; r++) x[r] = smb[a * NTT8_PITCH + r * 4 + b];
-  radix8_fwd_fp(x, q, qinv, [&](int s, int g) { return t2[(1 << s) - 1 + g]; });
-  wave_lds_sync();
-#pragma unroll
-  for (int r = 0; r < 8; r++) smb[a * NTT8_PITCH + r * 4 + b] = x[r];
-  wave_lds_sync();
-#pragma unroll
-  for (int c = 0; c < 8; c++) x[c] = smb[a * NTT8_PITCH + b * 8 + c];
-  // stage 14: pairs (c, c + 2) inside each half; stage 15: pairs (2k, 2k + 1)
-#pragma unroll
-  for (int u = 0; u < 2; u++)
-#pragma unroll
-    for (int p = 0; p < 2; p++) {
-      double& X = x[u * 4 + p];
-      double& Y = x[u * 4 + p + 2];
-      const double T = fp_mulmod_var(Y, t3[u], qinv, q);
-      Y = X - T;
-      X = X + T;
-    }
-#pragma unroll
-  for (int k = 0; k < 4; k++) {
-    double& X = x[2 * k];
-    double& Y = x[2 * k + 1];
-    const double T = fp_mulmod_var(Y, t3[2 + k], qinv, q);
-    Y = X - T;
-    X = X + T;
-  }
-#pragma unroll
-  for (int c = 0; c < 8; c++) x[c] = fp_reduce(x[c], qinv, q);
+  ntt16_fwd_blocks_fp_loaded(x, tw, q, qinv, tile, R, sm);
 }
