@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "kernels.hip.h"
+#include "ks12.hip.h"
 #include "ntt12.hip.h"
 #include "ntt16_kernels.hip.h"
 
@@ -133,7 +134,7 @@ enum ProfKind {
   PK_FWD_ROWS, PK_FWD_BLOCKS = PK_FWD_ROWS + 3, PK_INV_BLOCKS = PK_FWD_BLOCKS + 3, PK_INV_ROWS = PK_INV_BLOCKS + 3,
   PK_FWD_FINAL = PK_INV_ROWS + 3,
   PK_AUTOMORPH = PK_FWD_FINAL + 3, PK_MODUP, PK_INNER, PK_INNER16, PK_INNER16_INT, PK_INNER_C, PK_INNER8, PK_INNER8_BIG, PK_BCONV_ROWS, PK_MODDOWN = PK_BCONV_ROWS + 3, PK_FINAL, PK_TENSOR, PK_PMACC, PK_PMACC_FP, PK_ADD,
-  PK_COPY, PK_COUNT
+  PK_KS12_FRONT, PK_KS12_DIGITS, PK_KS12_SPECIAL, PK_KS12_FINAL, PK_COPY, PK_COUNT
 };
 static const char* const kProfNames[PK_COUNT] = {
     "ntt_fwd_pass", "ntt_inv_pass",
@@ -144,7 +145,8 @@ static const char* const kProfNames[PK_COUNT] = {
     "ntt16_fwd_blocks_final_kernel<0>", "ntt16_fwd_blocks_final_kernel<1>", "ntt16_fwd_blocks_final_kernel<2>",
     "automorph_kernel", "modup_kernel", "inner_kernel", "inner16_fp_kernel", "inner16_int_kernel", "ntt16_fwd_blocks_inner_c_kernel", "ntt16_fwd_blocks_inner8_kernel<1>", "ntt16_fwd_blocks_inner8_kernel<2>",
     "ntt16_bconv_rows_kernel<0>", "ntt16_bconv_rows_kernel<1>", "ntt16_bconv_rows_kernel<2>", "moddown_kernel", "ks_final_kernel", "tensor_kernel",
-    "pmacc_int_kernel", "pmacc_fp_kernel", "addto_kernel", "copy"};
+    "pmacc_int_kernel", "pmacc_fp_kernel", "addto_kernel",
+    "ks12_front_kernel", "ks12_digits_kernel", "ks12_special_kernel", "ks12_final_kernel", "copy"};
 struct ProfRec {
   int kind;
   hipEvent_t start, stop;
@@ -478,6 +480,11 @@ inline u32 map_mode_inner(const ckks_ctx* c, bool shared_key) {
 // directions at 2^13 104 -> 52 us, 12 rotations at 2^14 (5 limbs) 287 -> 117 us, 8 products at 2^15 (13 limbs)
 // 833 -> 348 us.
 inline bool two_pass(const ckks_ctx* c) { return c->logN >= 13 && c->logN <= 16; }
+// Ring 2^12: a key switch in four kernels that hold a whole limb per workgroup (ks12.hip.h). 8 rotations with their own
+// keys (4 limbs, 2 digits), which took ten launches each: 322 -> 37 us; 8 rotations of one key (5 limbs, 3 digits) 60 -> 46 us.
+inline bool whole_limb(const ckks_ctx* c) { return c->logN == 12; }
+// Both kinds read what they switch through the Galois map and take separate addends and per-ciphertext keys.
+inline bool gathers(const ckks_ctx* c) { return two_pass(c) || whole_limb(c); }
 inline u32 pass_tiles(const ckks_ctx* c) { return c->N >> 12; }   // 4096-element tiles of a limb
 
 // One launch per modulus class present among `nslots` slots, a.slots listing that class's slots: launch(cls, grid).
@@ -748,6 +755,9 @@ struct KsIo {
   const u64* const* evk_pc = nullptr;
   const u64* add2 = nullptr;   // [B][2][nlimbs][N] plain addend of mode bit 0 (two-pass path); null = out, in place
   bool add2_three = false;     // add2 is [B][3][nlimbs][N]; its first two components are the addends
+  // ring 2^12: d is the product of the second components of two ciphertexts [B][2][nlimbs][N], whose other two product
+  // terms are the addends
+  const u64 *prod_a = nullptr, *prod_b = nullptr;
 };
 
 // Base conversion fused with the first forward pass (ntt16_bconv_rows_kernel): one launch per modulus class among
@@ -1219,14 +1229,86 @@ int hrot_hoisted16(ckks_ctx* c, u64* out_base, u64 out_stride, const u64* ct_in,
   return CKKS_OK;
 }
 
+// Ring 2^12: front, digits, special, final (ks12.hip.h).
+int keyswitch_whole12(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B, u32 nlimbs, const u64* evk, char* ws,
+                      hipStream_t st) {
+  if (io.galois_pc && B > KS_MULTI_MAX) return fail(CKKS_ESHAPE, "internal: per-ciphertext keys for too many ciphertexts");
+  const KsLayout L = ks_layout(c, B, nlimbs);
+  Ks12Args a;
+  a.d = io.d;
+  a.d_stride = io.d_stride;
+  a.pa = io.prod_a;
+  a.pb = io.prod_b;
+  a.dcoef = (u64*)(ws + L.dcoef);
+  a.ext = (u64*)(ws + L.ext);
+  a.acc = (u64*)(ws + L.acc);
+  a.out = io.out;
+  a.evk = evk;
+  a.add2 = io.add2 ? io.add2 : io.out;
+  a.add_src = io.add_src;
+  a.add2_three = io.add2 && io.add2_three ? 1u : 0u;
+  a.tw = c->d_tw_fwd;
+  a.twi = c->d_tw_inv;
+  a.twfp = c->d_twfp_fwd;
+  a.twifp = c->d_twfp_inv;
+  a.mods = c->d_mods;
+  a.up_scale = lt->up_scale;
+  a.dn_scale = lt->dn_scale;
+  a.pinv = lt->pinv2;
+  a.up_mat = lt->up_mat;
+  a.up_off = lt->up_off;
+  a.dn_mat = lt->dn_mat_plain;
+  a.dn_off = lt->dn_off;
+  a.up_pitch = lt->up_pitch;
+  a.dn_pitch = lt->dn_pitch;
+  a.nlimbs = nlimbs;
+  a.nq = c->nq;
+  a.nm = c->nm;
+  a.alpha = c->alpha;
+  a.beta = lt->beta;
+  a.next = lt->next;
+  a.fp_on = c->tune[1] == 0 ? 1u : 0u;
+  a.mode0 = io.mode[0];
+  a.mode1 = io.mode[1];
+  a.d_galois = io.d_galois;
+  a.add_galois = io.add_galois;
+  a.multi = io.galois_pc ? 1u : 0u;
+  if (io.galois_pc)
+    for (u32 i = 0; i < B; i++) a.galois_pc[i] = io.galois_pc[i], a.evk_pc[i] = io.evk_pc[i];
+  const dim3 block(WL_THREADS);
+  {
+    ProfScope ps(c, PK_KS12_FRONT, st);
+    hipLaunchKernelGGL(ks12_front_kernel, dim3(B, nlimbs), block, 0, st, a);
+  }
+  {
+    ProfScope ps(c, PK_KS12_DIGITS, st);
+    const dim3 grid(B * lt->beta, lt->next);
+    if (lt->narrow_up) hipLaunchKernelGGL(ks12_digits_kernel<true>, grid, block, 0, st, a);
+    else hipLaunchKernelGGL(ks12_digits_kernel<false>, grid, block, 0, st, a);
+  }
+  {
+    ProfScope ps(c, PK_KS12_SPECIAL, st);
+    hipLaunchKernelGGL(ks12_special_kernel, dim3(2 * B, c->np), block, 0, st, a);
+  }
+  {
+    ProfScope ps(c, PK_KS12_FINAL, st);
+    const dim3 grid(2 * B, nlimbs);
+    if (lt->narrow_dn) hipLaunchKernelGGL(ks12_final_kernel<true>, grid, block, 0, st, a);
+    else hipLaunchKernelGGL(ks12_final_kernel<false>, grid, block, 0, st, a);
+  }
+  HIP_TRY(hipGetLastError());
+  return CKKS_OK;
+}
+
 // Key switch of io.d with evk into io.out (see KsIo). Other ring degrees: one kernel per step.
 int keyswitch_impl(ckks_ctx* c, const KsIo& io, u32 B, u32 nlimbs, const u64* evk, char* ws, hipStream_t st) {
   const LevelTables* lt;
   int rc = get_level(c, nlimbs, &lt);
   if (rc) return rc;
   if (two_pass(c)) return keyswitch_fused16(c, lt, io, B, nlimbs, evk, ws, st);
+  if (whole_limb(c)) return keyswitch_whole12(c, lt, io, B, nlimbs, evk, ws, st);
   if (io.d_galois || io.mode[0] >= 2 || io.mode[1] >= 2 || io.add2)
-    return fail(CKKS_EINVAL, "internal: gather modes and separate addends need the two-pass path");
+    return fail(CKKS_EINVAL, "internal: gather modes and separate addends need the fused paths");
   const u64* d = io.d;
   u64* out = io.out;
   const u32 add_mask = (io.mode[0] ? 1u : 0u) | (io.mode[1] ? 2u : 0u);
@@ -1606,7 +1688,7 @@ int ckks_hrot(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint32_t B, 
               const uint64_t* evk, void* ws, size_t ws_bytes, void* stream) {
   return hrot_impl(c, ct_out, ct_in, B, nlimbs, g, evk, ws, ws_bytes, stream, nullptr);
 }
-// ct_add != null: ct_out = ct_add + HRot(ct_in); ct_add == ct_out accumulates in place (two-pass path only).
+// ct_add != null: ct_out = ct_add + HRot(ct_in); ct_add == ct_out accumulates in place (fused paths only).
 static int hrot_impl(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint32_t B, uint32_t nlimbs, uint32_t g,
                      const uint64_t* evk, void* ws, size_t ws_bytes, void* stream, const uint64_t* ct_add) {
   int rc = check_common(c, B, nlimbs);
@@ -1621,7 +1703,7 @@ static int hrot_impl(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint3
   DeviceGuard guard(c->device);
   if (!guard.ok) return fail(CKKS_EHIP, "cannot select the context's device");
   hipStream_t st = (hipStream_t)stream;
-  if (two_pass(c)) {
+  if (gathers(c)) {
     // the permutation is applied where the ciphertext is read: by the first inverse pass and the fused inner product
     // (sigma(c1)) and by the final assembly (sigma(c0)), which also adds ct_add
     KsIo io{(const u64*)ct_in + polyN, 2 * polyN, g, (u64*)ct_out, {ct_add ? 3u : 2u, ct_add ? 1u : 0u},
@@ -1629,7 +1711,7 @@ static int hrot_impl(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint3
     io.add2 = (const u64*)ct_add;
     return keyswitch_impl(c, io, B, nlimbs, (const u64*)evk, (char*)ws, st);
   }
-  if (ct_add && ct_add == ct_out) return fail(CKKS_EINVAL, "internal: accumulating in place needs the two-pass path");
+  if (ct_add && ct_add == ct_out) return fail(CKKS_EINVAL, "internal: accumulating in place needs the fused paths");
   const size_t ks = ks_layout(c, B, nlimbs).total;
   u64* d = (u64*)((char*)ws + ks);
   const LimbMap qmap = identity_map(nlimbs);
@@ -1685,7 +1767,7 @@ int ckks_hrot_multi(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint32
   if ((rc = check_ws(c, CKKS_OP_HROT, B, nlimbs, 0, ws, ws_bytes))) return rc;
   const size_t polyN = (size_t)nlimbs * c->N, ct_bytes = (size_t)B * 2 * polyN * 8;
   if (overlap(ct_out, ct_bytes, ct_in, ct_bytes)) return fail(CKKS_EINVAL, "ct_out overlaps ct_in");
-  if (!two_pass(c)) {
+  if (!gathers(c)) {
     // other ring sizes: one rotation at a time through the general path
     for (u32 b = 0; b < B; b++)
       if ((rc = hrot_impl(c, ct_out + b * 2 * polyN, ct_in + b * 2 * polyN, 1, nlimbs, galois_elts[b], evks[b], ws, ws_bytes,
@@ -1720,6 +1802,12 @@ int ckks_hmult_relin(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_a, const 
   DeviceGuard guard(c->device);
   if (!guard.ok) return fail(CKKS_EHIP, "cannot select the context's device");
   hipStream_t st = (hipStream_t)stream;
+  if (whole_limb(c)) {
+    KsIo io{nullptr, 0, 0, (u64*)ct_out, {0, 0}, nullptr, 0};
+    io.prod_a = (const u64*)ct_a;
+    io.prod_b = (const u64*)ct_b;
+    return keyswitch_impl(c, io, B, nlimbs, (const u64*)evk, (char*)ws, st);
+  }
   const size_t ks = ks_layout(c, B, nlimbs).total;
   u64* d2 = (u64*)((char*)ws + ks);
   TensorArgs a{(const u64*)ct_a, (const u64*)ct_b, (u64*)ct_out, d2, c->d_mods, c->logN, nlimbs};
@@ -1768,7 +1856,7 @@ int ckks_relin(ckks_ctx* c, uint64_t* ct_out, const uint64_t* d_in, uint32_t B, 
   hipStream_t st = (hipStream_t)stream;
   const u64* d = (const u64*)d_in;
   KsIo io{d + 2 * polyN, 3 * (u64)polyN, 0, (u64*)ct_out, {1, 1}, nullptr, 0};
-  if (two_pass(c)) {
+  if (gathers(c)) {
     // the last kernel of the key switch reads d0 and d1 in place
     io.add2 = d;
     io.add2_three = true;
@@ -2070,7 +2158,7 @@ static int pcmm_impl(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint3
       }
       if (g == 0) continue;
       const u64* src = inner + (size_t)k * ct_elems;
-      if (two_pass(c)) {
+      if (gathers(c)) {
         rc = hrot_impl(c, ct_out, (const uint64_t*)src, B, nlimbs, galois((u64)g * n1 * stride), evk_giant[g - 1], hws,
                        hws_bytes, stream, /*ct_add=*/ct_out);
         if (rc) return rc;

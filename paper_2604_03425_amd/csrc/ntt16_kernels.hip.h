@@ -189,18 +189,17 @@ __device__ __forceinline__ const u64* uniform_ptr(const u64* p) {
   return (const u64*)(((u64)hi << 32) | lo);
 }
 #define BCONV_M30 0x3FFFFFFFu
-// Converted values for 8 of the lane's 16 tile positions (those at voff[0..7], offsets inside a limb). Two word
-// buffers alternate, so the loads of source k + 1 are in flight while source k is multiplied in.
-template <bool NARROW>
-struct BconvAcc8 {
-  Dot30N n[8];
-  Dot30 g[8];
-  u64 r[8];
+// Running conversions at V positions of a lane, from source words in split form.
+template <int V, bool NARROW>
+struct BconvAcc {
+  Dot30N n[V];
+  Dot30 g[V];
+  u64 r[V];
   u32 pending;
   __device__ __forceinline__ void init(u64 offc) {
     pending = 0;
 #pragma unroll
-    for (int i = 0; i < 8; i++) {
+    for (int i = 0; i < V; i++) {
       r[i] = 0;
       if (NARROW) {
         n[i].a = (u32)offc & BCONV_M30;
@@ -215,7 +214,7 @@ struct BconvAcc8 {
   }
   __device__ __forceinline__ void fold(u64 m, u64 minv) {
 #pragma unroll
-    for (int i = 0; i < 8; i++) {
+    for (int i = 0; i < V; i++) {
       if (NARROW) {
         r[i] += dot30n_redc90(n[i], m, minv);   // each part < m + 2^34
         dot30n_init(n[i]);
@@ -226,17 +225,18 @@ struct BconvAcc8 {
     }
     pending = 0;
   }
-  __device__ __forceinline__ void mac(const u64 (&w)[8], u64 c, bool more, u64 m, u64 minv) {
+  __device__ __forceinline__ void mac(const u64 (&w)[V], u64 c, bool more, u64 m, u64 minv) {
     const u32 c0 = (u32)c & BCONV_M30, c1 = (u32)(c >> 30);
 #pragma unroll
-    for (int i = 0; i < 8; i++) {
+    for (int i = 0; i < V; i++) {
       if (NARROW) dot30n_mac(n[i], (u32)w[i], (u32)(w[i] >> 32), c0, c1);
       else dot30_mac(g[i], (u32)w[i], (u32)(w[i] >> 32), c0, c1);
     }
     if (++pending == 15 && more) fold(m, minv);   // wave-uniform: chunks of 15 terms are reduced separately
   }
 };
-// boff: byte offsets of the 8 positions inside a limb. The source limbs of the digit are read through a buffer
+// Converted values for 8 of the lane's 16 tile positions; two word buffers alternate, so the loads of source k + 1 are in
+// flight while source k is multiplied in. boff: byte offsets of the 8 positions inside a limb. The source limbs of the digit are read through a buffer
 // resource (scalar base, bounds = the digit's len limbs; scalar offset = the limb, vector offset = the position), so
 // addressing costs no vector instructions. The loads are unconditional (a source index past the end is clamped and
 // meets the constant 0) and fenced against reordering: the younger buffer's loads stay in flight while the older
@@ -247,7 +247,7 @@ __device__ __forceinline__ void bconv_rows_eight(u64 (&r)[8], const u64* __restr
                                                  const u64* __restrict__ crow, u64 offc, const ModInfo& mi) {
   const u64 m = mi.m;
   u64 wa[8], wb[8];
-  BconvAcc8<NARROW> acc;
+  BconvAcc<8, NARROW> acc;
   acc.init(offc);
   const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)src, 0, (int)(len * 524288u), 0x00020000);
   auto load8 = [&](u64 (&w)[8], u32 k) {
