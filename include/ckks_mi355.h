@@ -310,8 +310,9 @@ int ckks_prof_copy(ckks_ctx* ctx, void* dst, const void* src, size_t bytes, void
 /* Tuning knobs for experiments (defaults in brackets):
  * knob 0 [-1] workgroup-to-tile mapping of the N = 2^16 kernels: 0..4 forces one mapping everywhere, -1 chooses per kernel;
  * knob 1 [0]  != 0 turns the double-precision bodies for primes < 2^50 off (integer bodies everywhere);
- * knob 2 [0]  1 = the base conversions of ModUp and ModDown run inside the following row pass (one kernel each)
- *             instead of a conversion kernel followed by a row pass; measured slower, kept for the measurement;
+ * knob 2 [0]  base conversions of ModUp and ModDown: 0 = with the row passes on both sides of them in one kernel, where a
+ *             conversion has at most 8 sources of one arithmetic kind (2 otherwise); 1 = inside the following row pass only;
+ *             2 = kernels of their own (1 and 2 measured slower, kept for the measurement);
  * knob 3 [2]  inner product on double-precision main limbs: 2 = block pass of the digits, product with one key
  *             component, block pass of the ModDown correction and final assembly in one kernel; 1 = plain block
  *             pass, streaming product and a separate assembly kernel;

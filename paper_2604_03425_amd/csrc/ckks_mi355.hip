@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "kernels.hip.h"
+#include "convert.hip.h"
 #include "ks12.hip.h"
 #include "ntt12.hip.h"
 #include "ntt16_kernels.hip.h"
@@ -116,6 +117,8 @@ struct LevelTables {
   ulonglong2* dn_scale = nullptr;  // [K]       2^64 (P/p_k)^-1 / N mod p_k
   u64* dn_mat_plain = nullptr;     // dn_mat without the Montgomery factor
   u64* up_off = nullptr;           // [beta][next] -sum_i ((q_i-1)/2) (Q_j/q_i) mod m_t, scaled like up_mat
+  double* up_matd = nullptr;       // [beta][next][up_pitch - 1] centred (Q_j/q_i) mod m_t on double-precision targets
+  double* dn_matd = nullptr;       // [nlimbs][dn_pitch - 1] centred (P/p_k) mod q_i on double-precision targets
   u64* dn_off = nullptr;           // [nlimbs]     -sum_k ((p_k-1)/2) (P/p_k) mod q_i, scaled like dn_mat_plain
   u32 up_pitch = 0, dn_pitch = 0;  // constants per target in up_mat / dn_mat_plain
   ulonglong2* pinv2 = nullptr;     // [nlimbs]  2^64 / P mod q_i
@@ -134,7 +137,7 @@ enum ProfKind {
   PK_FWD_ROWS, PK_FWD_BLOCKS = PK_FWD_ROWS + 3, PK_INV_BLOCKS = PK_FWD_BLOCKS + 3, PK_INV_ROWS = PK_INV_BLOCKS + 3,
   PK_FWD_FINAL = PK_INV_ROWS + 3,
   PK_AUTOMORPH = PK_FWD_FINAL + 3, PK_MODUP, PK_INNER, PK_INNER16, PK_INNER16_INT, PK_INNER_C, PK_INNER8, PK_INNER8_BIG, PK_BCONV_ROWS, PK_MODDOWN = PK_BCONV_ROWS + 3, PK_FINAL, PK_TENSOR, PK_PMACC, PK_PMACC_FP, PK_ADD,
-  PK_KS12_FRONT, PK_KS12_DIGITS, PK_KS12_SPECIAL, PK_KS12_FINAL, PK_COPY, PK_COUNT
+  PK_KS12_FRONT, PK_KS12_DIGITS, PK_KS12_SPECIAL, PK_KS12_FINAL, PK_CONV_ROWS, PK_COPY, PK_COUNT
 };
 static const char* const kProfNames[PK_COUNT] = {
     "ntt_fwd_pass", "ntt_inv_pass",
@@ -146,7 +149,7 @@ static const char* const kProfNames[PK_COUNT] = {
     "automorph_kernel", "modup_kernel", "inner_kernel", "inner16_fp_kernel", "inner16_int_kernel", "ntt16_fwd_blocks_inner_c_kernel", "ntt16_fwd_blocks_inner8_kernel<1>", "ntt16_fwd_blocks_inner8_kernel<2>",
     "ntt16_bconv_rows_kernel<0>", "ntt16_bconv_rows_kernel<1>", "ntt16_bconv_rows_kernel<2>", "moddown_kernel", "ks_final_kernel", "tensor_kernel",
     "pmacc_int_kernel", "pmacc_fp_kernel", "addto_kernel",
-    "ks12_front_kernel", "ks12_digits_kernel", "ks12_special_kernel", "ks12_final_kernel", "copy"};
+    "ks12_front_kernel", "ks12_digits_kernel", "ks12_special_kernel", "ks12_final_kernel", "conv_rows_kernel", "copy"};
 struct ProfRec {
   int kind;
   hipEvent_t start, stop;
@@ -270,6 +273,7 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
   auto mont_rs = [&](u64 v, u64 m) { return t.narrow_rs ? h_mont90(v, m) : h_mont(v, m); };
   std::vector<ulonglong2> up_inv((size_t)t.beta * alpha, ulonglong2{0, 0});
   std::vector<u64> up_mat((size_t)t.beta * next * (R + 1), 0), up_off((size_t)t.beta * next, 0);
+  std::vector<double> up_matd((size_t)t.beta * next * R, 0.0);
   t.up_pitch = R + 1;
   t.dn_pitch = RK + 1;
   for (u32 j = 0; j < t.beta; j++) {
@@ -285,6 +289,7 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
         for (u32 k = lo; k < hi; k++)
           if (k != i) v = h_mul(v, c->mod[k] % m, m);
         up_mat[((size_t)j * next + s) * (R + 1) + (i - lo)] = mont_up(v, m);
+        if (is_fp(m)) up_matd[((size_t)j * next + s) * R + (i - lo)] = v > m / 2 ? -(double)(m - v) : (double)v;
       }
     }
     for (u32 s = 0; s < next; s++) {
@@ -304,6 +309,7 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
   }
   std::vector<ulonglong2> dn_inv(K), pinv(nlimbs);
   std::vector<u64> dn_mat((size_t)nlimbs * (RK + 1), 0);
+  std::vector<double> dn_matd((size_t)nlimbs * RK, 0.0);
   for (u32 k = 0; k < K; k++) {
     u64 pk = c->mod[c->nq + k], h = 1;
     for (u32 r = 0; r < K; r++)
@@ -315,6 +321,7 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
       for (u32 r = 0; r < K; r++)
         if (r != k) v = h_mul(v, c->mod[c->nq + r] % m, m);
       dn_mat[(size_t)i * (RK + 1) + k] = mont_dn(v, m);
+      if (is_fp(m)) dn_matd[(size_t)i * RK + k] = v > m / 2 ? -(double)(m - v) : (double)v;
     }
   }
   for (u32 i = 0; i < nlimbs; i++) {
@@ -395,7 +402,9 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
   t.dn_scale = arena.add(dn_scale);
   t.dn_mat_plain = arena.add(dn_mat_plain);
   t.up_off = arena.add(up_off);
+  t.up_matd = arena.add(up_matd);
   t.dn_off = arena.add(dn_off);
+  t.dn_matd = arena.add(dn_matd);
   t.pinv2 = arena.add(pinv2);
   t.up_inv = arena.add(up_inv);
   t.up_mat = arena.add(up_mat);
@@ -425,7 +434,7 @@ int build_levels(ckks_ctx* c) {
     LevelTables& t = lv[nl];
     rebase(t.up_inv); rebase(t.up_mat); rebase(t.dn_inv); rebase(t.dn_mat); rebase(t.pinv);
     rebase(t.up_scale); rebase(t.dn_scale); rebase(t.dn_mat_plain); rebase(t.pinv2);
-    rebase(t.up_off); rebase(t.dn_off);
+    rebase(t.up_off); rebase(t.up_matd); rebase(t.dn_matd); rebase(t.dn_off);
     rebase(t.rs_one); rebase(t.rs_mat); rebase(t.rs_qinv); rebase(t.rs_qinv16);
   }
   if (c->d_levels) {
@@ -536,7 +545,7 @@ struct NttOpts {
   const ulonglong2* scale = nullptr;  // two-pass inverse only: per-slot constants (from slot0) replacing N^-1
   bool split_out = false;             // N = 2^16 inverse only: write the shifted, split form the fused base conversion reads
   bool rows_only = false;             // two-pass forward only: stop after the row pass (a fused kernel does the rest)
-  bool blocks_only = false;           // two-pass forward only: only the block pass, in place on dst
+  bool blocks_only = false;           // two-pass only: only the block pass (forward: in place on dst)
   bool raw_out = false;               // with blocks_only: leave reduced doubles on double-precision moduli
   int only_class = -1;                // >= 0: touch only the slots of this modulus class
   int exclude_class = -1;             // >= 0: leave the slots of this modulus class alone
@@ -591,7 +600,7 @@ int launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, u64 src_stride, 
     } else {
       launch_by_class(c, PK_INV_BLOCKS, a, npoly, nslots, cls_of, st,
                       [&](int cls, dim3 grid) { LAUNCH_CLASS_KERNEL(ntt16_inv_blocks_kernel, cls, grid, st, a); });
-      rows(b, PK_INV_ROWS);
+      if (!opt.blocks_only) rows(b, PK_INV_ROWS);
     }
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
@@ -791,6 +800,92 @@ int launch_bconv_rows(const ckks_ctx* c, BconvRowsArgs a, u32 npoly, bool narrow
   return CKKS_OK;
 }
 
+// Whether the conversion of digits of `alpha` limbs with modulus ids [id0, id0 + n) runs inside the transform passes around it
+// (conv_rows_kernel): the kernel keeps up to 8 sources per position in registers, all of one arithmetic kind, and converts
+// double-precision sources to integer targets in the three-sum form only. Knob 2 = 0 (the default) allows it.
+bool conv_fits(const ckks_ctx* c, u32 id0, u32 n, u32 alpha, bool narrow) {
+  if (c->tune[2] != 0 || alpha > CONV_MAX_SRC) return false;
+  const bool fp = host_class(c, c->mod[id0]) == 0;
+  for (u32 i = 1; i < n; i++)
+    if ((host_class(c, c->mod[id0 + i]) == 0) != fp) return false;
+  return narrow || !fp;
+}
+template <int LOGR, int MAXLEN>
+void launch_conv_len(const ConvArgs& a, bool fp, bool narrow, dim3 grid, hipStream_t st) {
+  const dim3 block(CONV_THREADS);
+  if (fp) hipLaunchKernelGGL((conv_rows_kernel<LOGR, MAXLEN, true, true>), grid, block, 0, st, a);
+  else if (narrow) hipLaunchKernelGGL((conv_rows_kernel<LOGR, MAXLEN, false, true>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((conv_rows_kernel<LOGR, MAXLEN, false, false>), grid, block, 0, st, a);
+}
+template <int LOGR>
+void launch_conv_of(const ConvArgs& a, bool fp, bool narrow, dim3 grid, hipStream_t st) {
+  if (a.alpha <= 4) launch_conv_len<LOGR, 4>(a, fp, narrow, grid, st);
+  else if (a.alpha <= 6) launch_conv_len<LOGR, 6>(a, fp, narrow, grid, st);
+  else launch_conv_len<LOGR, 8>(a, fp, narrow, grid, st);
+}
+// a: everything but the tables of the ring, the target lists and nsplit; target_id(slot) = modulus id of a target slot.
+template <class TargetId>
+int launch_conv_rows(const ckks_ctx* c, ConvArgs a, u32 npoly, bool narrow, TargetId target_id, hipStream_t st) {
+  a.tw = c->d_tw_fwd;
+  a.twi = c->d_tw_inv;
+  a.twfp = c->d_twfp_fwd;
+  a.twifp = c->d_twfp_inv;
+  a.mods = c->d_mods;
+  a.nfp = a.nint = 0;
+  for (int fp = 1; fp >= 0; fp--)
+    for (u32 s = 0; s < a.ntarget; s++) {
+      const u32 id = target_id(s);
+      if ((host_class(c, c->mod[id]) == 0) != (fp == 1)) continue;
+      const u32 n = a.nfp + a.nint;
+      a.target[n] = s | id << 8;
+      if (fp) a.nfp++;
+      else a.nint++;
+    }
+  // Shares of the targets per (polynomial, tile): every share repeats the inverse pass of the sources, but a call on few
+  // ciphertexts has fewer workgroups than the chip holds (two per compute unit, of which a lone one runs at three quarters
+  // of their joint rate). Weights are instructions per limb of work, in hundreds.
+  const bool fp = host_class(c, c->mod[a.src_id0]) == 0;
+  const u32 tiles = c->N / CONV_TILE, wsrc = a.alpha * (fp ? 4 : 6), wfp = a.nfp * (fp ? 4 : 5), wint = a.nint * 8;
+  const u64 groups = (u64)npoly * tiles;
+  u64 best = ~0ull;
+  a.nsplit = 1;
+  for (u32 n = 1; n <= a.nfp + a.nint; n++) {
+    const u64 per_cu = (groups * n + 255) / 256, cost = (per_cu / 2 * 8 + per_cu % 2 * 6) * (wsrc + (wfp + wint + n - 1) / n);
+    if (cost < best) best = cost, a.nsplit = n;
+  }
+  if (groups * a.nsplit > 0x7FFFFFFFull) return fail(CKKS_ESHAPE, "batch too large for one launch");
+  const dim3 grid((u32)(groups * a.nsplit));
+  ProfScope ps(c, PK_CONV_ROWS, st);
+  switch (c->logN) {
+    case 13: launch_conv_of<5>(a, fp, narrow, grid, st); break;
+    case 14: launch_conv_of<6>(a, fp, narrow, grid, st); break;
+    case 15: launch_conv_of<7>(a, fp, narrow, grid, st); break;
+    default: launch_conv_of<8>(a, fp, narrow, grid, st); break;
+  }
+  HIP_TRY(hipGetLastError());
+  return CKKS_OK;
+}
+// ModUp on the two-pass path, from the inverse block pass of the polynomial (in dcoef) to ext after the row pass.
+int ks16_conv_up(const ckks_ctx* c, const LevelTables* lt, const u64* dcoef, u64* ext, u32 B, u32 nlimbs, hipStream_t st) {
+  ConvArgs a;
+  a.src = dcoef;
+  a.dst = ext;
+  a.src_poly_stride = (u64)nlimbs * c->N;
+  a.dst_poly_stride = (u64)lt->next * c->N;
+  a.src_slot0 = a.src_id0 = 0;
+  a.src_nlimbs = nlimbs;
+  a.alpha = c->alpha;
+  a.beta = lt->beta;
+  a.skip_own = 1;
+  a.ntarget = lt->next;
+  a.pitch = lt->up_pitch;
+  a.mat = lt->up_mat;
+  a.off = lt->up_off;
+  a.matd = lt->up_matd;
+  a.scale = lt->up_scale;
+  return launch_conv_rows(c, a, B * lt->beta, lt->narrow_up, [&](u32 s) { return s < nlimbs ? s : s - nlimbs + c->nq; }, st);
+}
+
 // ModDown's conversion and the first forward pass of its result on the two-pass path: the special limbs of both
 // accumulators back to coefficient form (scaled by (P/p_k)^-1 / N), P -> Q_l, stages 0..7; tq receives the converted
 // limbs in row-pass form. Knob 2 = 1 does the conversion inside the row pass (ntt16_bconv_rows_kernel).
@@ -798,12 +893,33 @@ int ks16_moddown_rows(ckks_ctx* c, const LevelTables* lt, u32 B, u32 nlimbs, u64
   int rc;
   const u32 N = c->N, next = lt->next, K = c->np;
   const bool fused = c->tune[2] == 1 && c->logN == 16;
+  const bool conv = conv_fits(c, c->nq, K, K, lt->narrow_dn);
   LimbMap pmap;
   for (u32 k = 0; k < CKKS_MAX_SLOTS; k++) pmap.id[k] = (unsigned char)(k < K ? c->nq + k : 0);
   NttOpts o3;
   o3.scale = lt->dn_scale;
   o3.split_out = fused;
+  o3.blocks_only = conv;
   if ((rc = launch_ntt(c, true, acc, (u64)next * N, acc, (u64)next * N, B * 2, nlimbs, K, pmap, 0, 0, st, o3))) return rc;
+  if (conv) {
+    ConvArgs a;
+    a.src = acc;
+    a.dst = tq;
+    a.src_poly_stride = (u64)next * N;
+    a.dst_poly_stride = (u64)nlimbs * N;
+    a.src_slot0 = nlimbs;
+    a.src_id0 = c->nq;
+    a.src_nlimbs = a.alpha = K;
+    a.beta = 1;
+    a.skip_own = 0;
+    a.ntarget = nlimbs;
+    a.pitch = lt->dn_pitch;
+    a.mat = lt->dn_mat_plain;
+    a.off = lt->dn_off;
+    a.matd = lt->dn_matd;
+    a.scale = lt->dn_scale;
+    return launch_conv_rows(c, a, B * 2, lt->narrow_dn, [](u32 s) { return s; }, st);
+  }
   if (!fused) {
     {
       ModDownArgs a{acc, tq, c->d_mods, lt->dn_inv, lt->dn_mat_plain, c->logN, nlimbs, c->nq, K, next, nlimbs, c->nq};
@@ -926,18 +1042,22 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
     if (s_ >= nlimbs) special_fp |= fp;
   }
   const bool fused_up = c->tune[2] == 1 && c->logN == 16;
+  const bool conv_up = conv_fits(c, 0, nlimbs, c->alpha, lt->narrow_up);
   // 1.
   NttOpts o1;
   o1.galois = io.d_galois;
   o1.galois_pc = io.galois_pc;
   o1.scale = lt->up_scale;
   o1.split_out = fused_up;
+  o1.blocks_only = conv_up;
   if ((rc = launch_ntt(c, true, io.d, io.d_stride, dcoef, (u64)nlimbs * N, B, 0, nlimbs, qmap, 0, 0, st, o1))) return rc;
   // 2. The double-precision part of the row pass (memory-bound) may run on the second stream beside the
   // integer-class chain of steps 2-4 (arithmetic-bound), which does not depend on it.
-  const bool fork = any_fp && any_int && !special_fp && !acc_add && c->tune[4] == 0;
+  const bool fork = any_fp && any_int && !special_fp && !acc_add && !conv_up && c->tune[4] == 0;
   hipStream_t sb = st;
-  if (!fused_up) {
+  if (conv_up) {
+    if ((rc = ks16_conv_up(c, lt, dcoef, ext, B, nlimbs, st))) return rc;
+  } else if (!fused_up) {
     ModUpArgs a{dcoef, ext, c->d_mods, lt->up_inv, lt->up_mat, c->logN, nlimbs, c->nq, c->alpha, beta, next};
     ProfScope ps(c, PK_MODUP, st);
     launch_modup<true>(c, a, beta, B, lt->narrow_up, st);
@@ -948,7 +1068,8 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
     HIP_TRY(hipEventRecord(c->ev_fork, st));
     HIP_TRY(hipStreamWaitEvent(sb, c->ev_fork, 0));
   }
-  if (!fused_up) {
+  if (conv_up) {
+  } else if (!fused_up) {
     NttOpts o2;
     o2.rows_only = true;
     if (any_fp) {
@@ -1098,16 +1219,18 @@ static int hoist_front16(ckks_ctx* c, const LevelTables* lt, const u64* ct_in, u
   u64* acc = (u64*)(ws + L.acc);
   const LimbMap qmap = identity_map(nlimbs), emap = ext_map(c, nlimbs);
   const u64* c1 = ct_in + polyN;
-  NttOpts o1;
+  NttOpts o1, of;
   o1.scale = lt->up_scale;
+  o1.blocks_only = of.blocks_only = conv_fits(c, 0, nlimbs, c->alpha, lt->narrow_up);
   if ((rc = launch_ntt(c, true, c1, 2 * polyN, dcoef, polyN, B, 0, nlimbs, qmap, 0, 0, st, o1))) return rc;
-  {
+  if (o1.blocks_only) {
+    if ((rc = ks16_conv_up(c, lt, dcoef, ext, B, nlimbs, st))) return rc;
+  } else {
     ModUpArgs a{dcoef, ext, c->d_mods, lt->up_inv, lt->up_mat, c->logN, nlimbs, c->nq, c->alpha, beta, next};
     ProfScope ps(c, PK_MODUP, st);
     launch_modup<true>(c, a, beta, B, lt->narrow_up, st);
     HIP_TRY(hipGetLastError());
   }
-  NttOpts of;
   of.raw_out = true;  // reduced doubles on double-precision moduli, canonical residues elsewhere
   if ((rc = launch_ntt(c, false, ext, (u64)next * N, ext, (u64)next * N, B * beta, 0, next, emap, beta, nlimbs, st, of)))
     return rc;

@@ -212,26 +212,26 @@ struct BconvAcc {
       }
     }
   }
+  __device__ __forceinline__ u64 folded(int i, u64 m, u64 minv) const {   // < m + 2^34 / < 2m
+    return NARROW ? dot30n_redc90(n[i], m, minv) : redc(dot30_value(g[i]), m, minv);
+  }
   __device__ __forceinline__ void fold(u64 m, u64 minv) {
 #pragma unroll
     for (int i = 0; i < V; i++) {
-      if (NARROW) {
-        r[i] += dot30n_redc90(n[i], m, minv);   // each part < m + 2^34
-        dot30n_init(n[i]);
-      } else {
-        r[i] += redc(dot30_value(g[i]), m, minv);   // each part < 2m
-        dot30_init(g[i]);
-      }
+      r[i] += folded(i, m, minv);
+      if (NARROW) dot30n_init(n[i]);
+      else dot30_init(g[i]);
     }
     pending = 0;
+  }
+  __device__ __forceinline__ void add(int i, u32 y0, u32 y1, u32 c0, u32 c1) {
+    if (NARROW) dot30n_mac(n[i], y0, y1, c0, c1);
+    else dot30_mac(g[i], y0, y1, c0, c1);
   }
   __device__ __forceinline__ void mac(const u64 (&w)[V], u64 c, bool more, u64 m, u64 minv) {
     const u32 c0 = (u32)c & BCONV_M30, c1 = (u32)(c >> 30);
 #pragma unroll
-    for (int i = 0; i < V; i++) {
-      if (NARROW) dot30n_mac(n[i], (u32)w[i], (u32)(w[i] >> 32), c0, c1);
-      else dot30_mac(g[i], (u32)w[i], (u32)(w[i] >> 32), c0, c1);
-    }
+    for (int i = 0; i < V; i++) add(i, (u32)w[i], (u32)(w[i] >> 32), c0, c1);
     if (++pending == 15 && more) fold(m, minv);   // wave-uniform: chunks of 15 terms are reduced separately
   }
 };
