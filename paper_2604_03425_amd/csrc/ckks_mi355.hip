@@ -1485,6 +1485,26 @@ int keyswitch_impl(ckks_ctx* c, const KsIo& io, u32 B, u32 nlimbs, const u64* ev
   return CKKS_OK;
 }
 
+// Hoisted sums are instantiated for up to 4 digits and for any number. Ciphertexts go four to a lane, a remainder of one or
+// two in lanes of its own (one of three as four).
+template <int CB>
+void launch_inner_sum_fp_of(u32 b0, u32 groups, u32 blocks, u32 slots, const FwdInnerArgs& a, u32 B, hipStream_t st) {
+  const dim3 grid(groups, blocks, slots), block(256);
+  switch (a.beta) {
+    case 1: hipLaunchKernelGGL((inner16_sum_fp_kernel<CB, 1>), grid, block, 0, st, a, B, b0); break;
+    case 2: hipLaunchKernelGGL((inner16_sum_fp_kernel<CB, 2>), grid, block, 0, st, a, B, b0); break;
+    case 3: hipLaunchKernelGGL((inner16_sum_fp_kernel<CB, 3>), grid, block, 0, st, a, B, b0); break;
+    case 4: hipLaunchKernelGGL((inner16_sum_fp_kernel<CB, 4>), grid, block, 0, st, a, B, b0); break;
+    default: hipLaunchKernelGGL((inner16_sum_fp_kernel<CB, 0>), grid, block, 0, st, a, B, b0); break;
+  }
+}
+void launch_inner_sum_fp(u32 B, u32 blocks, u32 slots, const FwdInnerArgs& a, hipStream_t st) {
+  const u32 rest = B % 4 == 3 ? 0 : B % 4, fours = (B - rest + 3) / 4;
+  if (fours) launch_inner_sum_fp_of<4>(0, fours, blocks, slots, a, B, st);
+  if (rest == 1) launch_inner_sum_fp_of<1>(B - 1, 1, blocks, slots, a, B, st);
+  if (rest == 2) launch_inner_sum_fp_of<2>(B - 2, 1, blocks, slots, a, B, st);
+}
+
 int check_common(const ckks_ctx* c, u32 B, u32 nlimbs) {
   if (!c) return fail(CKKS_EINVAL, "null context");
   if (nlimbs == 0 || nlimbs > c->nq) return fail(CKKS_ESHAPE, "nlimbs must be in [1, L+1]");
@@ -2089,8 +2109,9 @@ int ckks_hrot_sum(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint32_t
         if ((host_class(c, c->mod[emap.id[s_]]) == 0) == (fp == 1)) a.slots[cnt++] = (unsigned char)s_;
       if (!cnt) continue;
       ProfScope ps(c, fp ? PK_INNER16 : PK_INNER16_INT, st);
-      if (fp) hipLaunchKernelGGL(inner16_sum_fp_kernel, dim3(B, N / 512, cnt), dim3(256), 0, st, a);
-      else hipLaunchKernelGGL(inner16_sum_int_kernel, dim3(B, N / 512, cnt), dim3(256), 0, st, a);
+      if (fp) launch_inner_sum_fp(B, (u32)N / 256, cnt, a, st);
+      else hipLaunchKernelGGL(inner16_sum_int_kernel, dim3((B + INNER16_SUM_CB_INT - 1) / INNER16_SUM_CB_INT, N / 256, cnt),
+                              dim3(256), 0, st, a, B);
     }
     HIP_TRY(hipGetLastError());
   }

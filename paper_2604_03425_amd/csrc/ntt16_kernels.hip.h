@@ -188,6 +188,11 @@ __device__ __forceinline__ const u64* uniform_ptr(const u64* p) {
   const u32 lo = __builtin_amdgcn_readfirstlane((u32)v), hi = __builtin_amdgcn_readfirstlane((u32)(v >> 32));
   return (const u64*)(((u64)hi << 32) | lo);
 }
+// The word `offset` bytes behind a pointer that is the same in every lane: scalar base, 32-bit vector offset, and a global
+// (not flat) access also where the pointer was rebuilt from scalar halves.
+__device__ __forceinline__ u64 uniform_load(const u64* base, u32 offset) {
+  return *(const __attribute__((address_space(1))) u64*)((const __attribute__((address_space(1))) char*)base + offset);
+}
 #define BCONV_M30 0x3FFFFFFFu
 // Running conversions at V positions of a lane, from source words in split form.
 template <int V, bool NARROW>
@@ -1003,13 +1008,13 @@ __global__ void __launch_bounds__(256) inner16_rot_fp_kernel(FwdInnerArgs a, u32
   u32 m_next = galois_src_index(n, a.galois_pc[0], a.logN);
   const size_t comp_stride = (size_t)a.nm * N, id_off = (size_t)id * N;
   auto load_keys = [&](u64 (&w)[MAXB][2], u32 r, u32 m) {
-    const u64* kp = uniform_ptr(a.evk_pc[r]) + id_off + m;
+    const u64* kp = uniform_ptr(a.evk_pc[r]) + id_off;
 #pragma unroll
     for (int j = 0; j < MAXB; j++) {
       w[j][0] = w[j][1] = 0;
       if (EXACT || (u32)j < a.beta) {
-        w[j][0] = kp[0];
-        w[j][1] = kp[comp_stride];
+        w[j][0] = uniform_load(kp, m * 8);
+        w[j][1] = uniform_load(kp + comp_stride, m * 8);
       }
       kp += 2 * comp_stride;
     }
@@ -1129,128 +1134,220 @@ __global__ void __launch_bounds__(256) inner16_rot_int_kernel(FwdInnerArgs a, u3
 // ---- a ciphertext plus many of its rotations, summed before ModDown (hoisted rotate-and-sum) ----
 // acc[b][c][t][n] = P * ct[b][c][t][n] (main primes; or what acc holds, if accumulate)
 //                   + sum_r ( sum_j D_j[pi_r(n)] * evk_r[j][c][id(t)][n]  + [c = 0] P * c0[b][t][pi_r(n)] ),
-// output-stationary: a lane owns two adjacent positions, walks over the rotations with its sums in registers (digits,
-// c1 and c0 read through rotation r's index map, key words read in place) and stores once. galois_pc[r] is the
-// Galois element of rotation r, evk_pc[r] its key; d = c1 and c0 are the two components of the input ciphertext.
-// Same grid and mapping as inner16_fp_kernel.
-__global__ void __launch_bounds__(256) inner16_sum_fp_kernel(FwdInnerArgs a) {
+// output-stationary: a lane owns one position of up to CB ciphertexts, walks over the rotations with its sums in registers
+// (digits, c1 and c0 read through rotation r's index map, key words read in place, once for all its ciphertexts and one
+// rotation ahead) and stores once. galois_pc[r] is the Galois element of rotation r, evk_pc[r] its key; d = c1 and c0 are
+// the two components of the input ciphertext. grid = (groups of CB ciphertexts from b_first on, N / 256, slots of the class).
+// What bounds it: the latency of the gathers, each of which brings 5 words of a ciphertext per position. All loads of a
+// rotation are in flight together (with a branch on the own digit between them every one was waited for), and the key
+// words, two thirds of the reads with one ciphertext per lane, serve four. 8 ciphertexts of 20 limbs, 4 digits, 7
+// rotations: 541 -> 436 us.
+// Workgroup -> (ciphertext group, block of positions, slot): all blocks of one (group, slot) run on one XCD, in order, so that
+// a line of a digit is fetched into that L2 once and found there by the other rotations (every rotation reads every line,
+// at another position); groups beyond the last multiple of 8 are dealt out in order.
+__device__ __forceinline__ void inner16_sum_map(u32& bg, u32& blk, u32& zi) {
+  const u32 lin = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), whole = (gridDim.x * gridDim.z) & ~7u;
+  u32 unit;
+  if (lin < whole * gridDim.y) {
+    const u32 rest = lin >> 3;
+    blk = rest % gridDim.y;
+    unit = (lin & 7) + 8 * (rest / gridDim.y);
+  } else {
+    const u32 rest = lin - whole * gridDim.y;
+    blk = rest % gridDim.y;
+    unit = whole + rest / gridDim.y;
+  }
+  bg = unit % gridDim.x;
+  zi = unit / gridDim.x;
+}
+template <int CB, int BETA>   // BETA: the number of digits, 0 = any (no look-ahead)
+__global__ void __launch_bounds__(256) inner16_sum_fp_kernel(FwdInnerArgs a, u32 B, u32 b_first) {
   const size_t N = (size_t)1 << a.logN;
-  u32 b, blk, zi;
-  ntt16_map(a.map_mode, b, blk, zi);
+  u32 bg, blk, zi;
+  inner16_sum_map(bg, blk, zi);
   const u32 t = a.slots[zi];
   const u32 id = t < a.nlimbs ? t : t - a.nlimbs + a.nq;
   const ModInfo mi = a.mods[id];
   const double q = mi.qd, qinv = mi.qinv;
-  const u32 n = (blk * 256 + threadIdx.x) * 2;
+  const u32 n = blk * 256 + threadIdx.x;
   const bool main_prime = t < a.nlimbs;
-  const double pm = u2d(mi.pmod);
-  const u64* c0 = a.c0 + (size_t)b * a.c0_poly_stride + (size_t)t * N;
-  const u64* c1 = a.d + (size_t)b * a.d_poly_stride + (size_t)t * N;
-  u64* o0 = a.acc + (((size_t)b * 2 + 0) * a.next + t) * N + n;
-  u64* o1 = o0 + (size_t)a.next * N;
-  double s0[2] = {0.0, 0.0}, s1[2] = {0.0, 0.0};
-  if (a.accumulate) {
-    const ulonglong2 p0 = *(const ulonglong2*)o0, p1 = *(const ulonglong2*)o1;
-    s0[0] = u2d(p0.x), s0[1] = u2d(p0.y), s1[0] = u2d(p1.x), s1[1] = u2d(p1.y);
-  } else if (main_prime) {
-    const ulonglong2 v0 = *(const ulonglong2*)(c0 + n), v1 = *(const ulonglong2*)(c1 + n);
-    s0[0] = fp_mulmod_var(u2d(v0.x), pm, qinv, q), s0[1] = fp_mulmod_var(u2d(v0.y), pm, qinv, q);
-    s1[0] = fp_mulmod_var(u2d(v1.x), pm, qinv, q), s1[1] = fp_mulmod_var(u2d(v1.y), pm, qinv, q);
-  }
-  for (u32 r = 0; r < a.nrot; r++) {
-    const u32 g = a.galois_pc[r];
-    const u64* evk = uniform_ptr(a.evk_pc[r]) + (size_t)id * N + n;
-    const u32 m[2] = {galois_src_index(n, g, a.logN), galois_src_index(n + 1, g, a.logN)};
-    // the running sums enter a rotation below 1.5 q in magnitude; three products (0.75 q each) are added between folds
-    u32 pending = 0;
-    for (u32 j = 0; j < a.beta; j++) {
-      double x[2];
-      if (fwd_inner_owns(a, t, j)) {
-        x[0] = u2d(c1[m[0]]);
-        x[1] = u2d(c1[m[1]]);
-      } else {
-        const u64* e = a.ext + (((size_t)b * a.beta + j) * a.next + t) * N;
-        x[0] = __longlong_as_double((long long)e[m[0]]);
-        x[1] = __longlong_as_double((long long)e[m[1]]);
-      }
-      const ulonglong2 eb = *(const ulonglong2*)(evk + ((size_t)j * 2 + 0) * a.nm * N);
-      const ulonglong2 ea = *(const ulonglong2*)(evk + ((size_t)j * 2 + 1) * a.nm * N);
-      s0[0] += fp_mulmod_var(x[0], u2d(eb.x), qinv, q);
-      s0[1] += fp_mulmod_var(x[1], u2d(eb.y), qinv, q);
-      s1[0] += fp_mulmod_var(x[0], u2d(ea.x), qinv, q);
-      s1[1] += fp_mulmod_var(x[1], u2d(ea.y), qinv, q);
-      if (++pending == 3) {
-        pending = 0;
+  const u32 b0 = b_first + bg * CB;
+  size_t bb[CB];   // a surplus slot repeats the last ciphertext and stores nothing: no branches between the loads
 #pragma unroll
-        for (int e2 = 0; e2 < 2; e2++) {
-          s0[e2] = fp_reduce(s0[e2], qinv, q);
-          s1[e2] = fp_reduce(s1[e2], qinv, q);
+  for (int k = 0; k < CB; k++) bb[k] = min(b0 + k, B - 1);
+  const double pm = u2d(mi.pmod);
+  constexpr int NB = BETA ? BETA : 1;
+  const size_t comp = (size_t)a.nm * N, ext_ct = (size_t)a.beta * a.next * N;
+  // Everything about a digit that depends on whether it holds limb t itself is a uniform value, so that the loads of a
+  // rotation follow one another without a branch or a wait: where it starts, its stride between ciphertexts, and what turns
+  // its words into doubles (residues: u2d; doubles: or with 0, minus 0).
+  const u32 jo = main_prime ? t / a.alpha : 0xFFFFFFFFu, tc = main_prime ? t : 0;
+  auto digit = [&](u32 j) { return j == jo ? a.d + (size_t)t * N : a.ext + ((size_t)j * a.next + t) * N; };
+  auto stride = [&](u32 j) { return j == jo ? (size_t)a.d_poly_stride : ext_ct; };
+  const u64* c0 = a.c0 + (size_t)tc * N;   // (on special limbs the sums of c0 are formed and not used)
+  double s0[CB], s1[CB], sc[CB];   // sc: sum of the c0 words, multiplied by P once at the end
+#pragma unroll
+  for (int k = 0; k < CB; k++) {
+    s0[k] = s1[k] = sc[k] = 0.0;
+    const u64* o = a.acc + ((bb[k] * 2) * a.next + t) * N + n;
+    if (a.accumulate) {
+      s0[k] = u2d(o[0]), s1[k] = u2d(o[(size_t)a.next * N]);
+    } else if (main_prime) {
+      sc[k] = u2d(c0[bb[k] * a.c0_poly_stride + n]);
+      s1[k] = fp_mulmod_var(u2d(a.d[bb[k] * a.d_poly_stride + (size_t)t * N + n]), pm, qinv, q);
+    }
+  }
+  u64 kw[NB][2], kn[NB][2];
+  auto load_keys = [&](u32 r, u32 j0) {
+    const u64* kp = uniform_ptr(a.evk_pc[r]) + (size_t)id * N + (size_t)j0 * 2 * comp;
+#pragma unroll
+    for (int j = 0; j < NB; j++) {
+      kn[j][0] = uniform_load(kp, n * 8), kn[j][1] = uniform_load(kp + comp, n * 8);
+      kp += 2 * comp;
+    }
+  };
+  if (BETA && a.nrot) load_keys(0, 0);
+  for (u32 r = 0; r < a.nrot; r++) {
+    const u32 m = galois_src_index(n, a.galois_pc[r], a.logN);
+    u64 cr[CB];
+    for (u32 j0 = 0; j0 < (BETA ? 1 : a.beta); j0++) {   // one pass over all digits, or one digit a pass
+      if (!BETA) load_keys(r, j0);
+#pragma unroll
+      for (int j = 0; j < NB; j++) kw[j][0] = kn[j][0], kw[j][1] = kn[j][1];
+      u64 xr[NB][CB];
+#pragma unroll
+      for (int j = 0; j < NB; j++) {
+        const u64* e = digit(j0 + j);
+        const size_t st = stride(j0 + j);
+#pragma unroll
+        for (int k = 0; k < CB; k++) xr[j][k] = uniform_load(e + bb[k] * st, m * 8);
+      }
+      if (j0 == 0) {
+#pragma unroll
+        for (int k = 0; k < CB; k++) cr[k] = uniform_load(c0 + bb[k] * a.c0_poly_stride, m * 8);
+      }
+      if (BETA) load_keys(min(r + 1, a.nrot - 1), 0);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < NB; j++) {
+        const u64 bias = j0 + j == jo ? 0x4330000000000000ull : 0ull;
+        const double less = __longlong_as_double((long long)bias), eb = u2d(kw[j][0]), ea = u2d(kw[j][1]);
+#pragma unroll
+        for (int k = 0; k < CB; k++) {
+          const double x = __longlong_as_double((long long)(xr[j][k] | bias)) - less;
+          // a sum enters a round at most q in magnitude, and at most four products below 0.9 q follow
+          s0[k] += fp_mulmod_var(x, eb, qinv, q);
+          s1[k] += fp_mulmod_var(x, ea, qinv, q);
         }
       }
-    }
-    if (main_prime) {
-      s0[0] += fp_mulmod_var(u2d(c0[m[0]]), pm, qinv, q);
-      s0[1] += fp_mulmod_var(u2d(c0[m[1]]), pm, qinv, q);
+#pragma unroll
+      for (int k = 0; k < CB; k++) {
+        s0[k] = fp_reduce(s0[k], qinv, q);
+        s1[k] = fp_reduce(s1[k], qinv, q);
+      }
     }
 #pragma unroll
-    for (int e2 = 0; e2 < 2; e2++) {   // back to |.| <= q/2 before the next rotation
-      s0[e2] = fp_reduce(s0[e2], qinv, q);
-      s1[e2] = fp_reduce(s1[e2], qinv, q);
-    }
+    for (int k = 0; k < CB; k++) sc[k] = fp_reduce(sc[k] + u2d(cr[k]), qinv, q);
   }
-  *(ulonglong2*)o0 = ulonglong2{d2u_canon(fp_reduce(s0[0], qinv, q), q), d2u_canon(fp_reduce(s0[1], qinv, q), q)};
-  *(ulonglong2*)o1 = ulonglong2{d2u_canon(fp_reduce(s1[0], qinv, q), q), d2u_canon(fp_reduce(s1[1], qinv, q), q)};
+#pragma unroll
+  for (int k = 0; k < CB; k++) {
+    if (b0 + k >= B) break;
+    u64* o = a.acc + ((bb[k] * 2) * a.next + t) * N + n;
+    if (main_prime) s0[k] += fp_mulmod_var(sc[k], pm, qinv, q);
+    o[0] = d2u_canon(fp_reduce(s0[k], qinv, q), q);
+    o[(size_t)a.next * N] = d2u_canon(fp_reduce(s1[k], qinv, q), q);
+  }
 }
 
-// The same for integer-class moduli (every term with the factor 2^-64, as in inner16_int_kernel).
-__global__ void __launch_bounds__(256) inner16_sum_int_kernel(FwdInnerArgs a) {
+// The same for integer-class moduli (every term with the factor 2^-64, as in inner16_int_kernel). Products are summed as
+// 30-bit partial products, 15 between folds into a 128-bit sum, and reduced once at the end instead of one by one: 8
+// ciphertexts, 5 special limbs, 4 digits, 7 rotations 168 -> 138 us.
+#define INNER16_SUM_CB_INT 2
+__global__ void __launch_bounds__(256) inner16_sum_int_kernel(FwdInnerArgs a, u32 B) {
+  constexpr int CB = INNER16_SUM_CB_INT;
   const size_t N = (size_t)1 << a.logN;
-  u32 b, blk, zi;
-  ntt16_map(a.map_mode, b, blk, zi);
+  u32 bg, blk, zi;
+  inner16_sum_map(bg, blk, zi);
   const u32 t = a.slots[zi];
   const u32 id = t < a.nlimbs ? t : t - a.nlimbs + a.nq;
   const ModInfo mi = a.mods[id];
-  const u64 q = mi.m, q2 = 2 * mi.m;
-  const u32 n = (blk * 256 + threadIdx.x) * 2;
+  const u64 q = mi.m;
+  const u32 n = blk * 256 + threadIdx.x;
   const bool main_prime = t < a.nlimbs;
-  const u64* c0 = a.c0 + (size_t)b * a.c0_poly_stride + (size_t)t * N;
-  const u64* c1 = a.d + (size_t)b * a.d_poly_stride + (size_t)t * N;
-  u64* o0 = a.acc + (((size_t)b * 2 + 0) * a.next + t) * N + n;
-  u64* o1 = o0 + (size_t)a.next * N;
-  auto times_p = [&](u64 v) {   // v * P * 2^-64, below 2q
-    Acc128 p = {v * mi.pmod, mul_hi64(v, mi.pmod)};
-    return redc(p, q, mi.minv);
-  };
-  u64 s0[2] = {0, 0}, s1[2] = {0, 0};   // kept below 2q
-  if (a.accumulate) {
-    const ulonglong2 p0 = *(const ulonglong2*)o0, p1 = *(const ulonglong2*)o1;
-    s0[0] = p0.x, s0[1] = p0.y, s1[0] = p1.x, s1[1] = p1.y;
-  } else if (main_prime) {
-    const ulonglong2 v0 = *(const ulonglong2*)(c0 + n), v1 = *(const ulonglong2*)(c1 + n);
-    s0[0] = times_p(v0.x), s0[1] = times_p(v0.y), s1[0] = times_p(v1.x), s1[1] = times_p(v1.y);
-  }
-  for (u32 r = 0; r < a.nrot; r++) {
-    const u32 g = a.galois_pc[r];
-    const u64* evk = uniform_ptr(a.evk_pc[r]) + (size_t)id * N + n;
-    const u32 m[2] = {galois_src_index(n, g, a.logN), galois_src_index(n + 1, g, a.logN)};
-    for (u32 j = 0; j < a.beta; j++) {
-      const u64* src = fwd_inner_owns(a, t, j) ? c1 : a.ext + (((size_t)b * a.beta + j) * a.next + t) * N;
-      const u64 x[2] = {src[m[0]], src[m[1]]};
-      const ulonglong2 eb = *(const ulonglong2*)(evk + ((size_t)j * 2 + 0) * a.nm * N);
-      const ulonglong2 ea = *(const ulonglong2*)(evk + ((size_t)j * 2 + 1) * a.nm * N);
-      const u64 e0[2] = {eb.x, eb.y}, e1[2] = {ea.x, ea.y};
+  const u32 b0 = bg * CB, nb = min((u32)CB, B - b0);
+  const u64 *c0[CB], *c1[CB], *ext[CB];
+  Dot30 d0[CB], d1[CB];
+  Acc128 v0[CB], v1[CB];
+  u64 r0[CB], r1[CB];   // residues below 2q: what acc held, and full 128-bit sums reduced early
 #pragma unroll
-      for (int e = 0; e < 2; e++) {
-        Acc128 p0 = {x[e] * e0[e], mul_hi64(x[e], e0[e])}, p1 = {x[e] * e1[e], mul_hi64(x[e], e1[e])};
-        s0[e] = csub(s0[e] + redc(p0, q, mi.minv), q2);
-        s1[e] = csub(s1[e] + redc(p1, q, mi.minv), q2);
+  for (int k = 0; k < CB; k++) {
+    const u32 b = min(b0 + k, B - 1);   // a surplus slot repeats the last ciphertext and stores nothing
+    c0[k] = a.c0 + (size_t)b * a.c0_poly_stride + (size_t)t * N;
+    c1[k] = a.d + (size_t)b * a.d_poly_stride + (size_t)t * N;
+    ext[k] = a.ext + (((size_t)b * a.beta) * a.next + t) * N;
+    dot30_init(d0[k]);
+    dot30_init(d1[k]);
+    v0[k] = v1[k] = Acc128{0, 0};
+    r0[k] = r1[k] = 0;
+    if (a.accumulate) {
+      const u64* o = a.acc + (((size_t)b * 2) * a.next + t) * N + n;
+      r0[k] = o[0], r1[k] = o[(size_t)a.next * N];
+    }
+  }
+  u32 terms = 0, folds = 0;
+  auto fold = [&](bool last) {
+    terms = 0;
+    folds++;
+#pragma unroll
+    for (int k = 0; k < CB; k++) {
+      const Acc128 p0 = dot30_value(d0[k]), p1 = dot30_value(d1[k]);
+      v0[k].lo += p0.lo;
+      v0[k].hi += p0.hi + (v0[k].lo < p0.lo ? 1ull : 0ull);
+      v1[k].lo += p1.lo;
+      v1[k].hi += p1.hi + (v1[k].lo < p1.lo ? 1ull : 0ull);
+      dot30_init(d0[k]);
+      dot30_init(d1[k]);
+      if (last || folds % 7 == 0) {   // at most 105 products: the reduced sum is below 8q
+        const u64 x0 = csub(csub(redc(v0[k], q, mi.minv), 4 * q), 2 * q), x1 = csub(csub(redc(v1[k], q, mi.minv), 4 * q), 2 * q);
+        r0[k] = csub(r0[k] + x0, 2 * q);
+        r1[k] = csub(r1[k] + x1, 2 * q);
+        v0[k] = v1[k] = Acc128{0, 0};
       }
     }
+  };
+  auto mac = [&](Dot30& d, u64 x, u64 e) { dot30_mac(d, (u32)x & 0x3FFFFFFFu, (u32)(x >> 30), (u32)e & 0x3FFFFFFFu, (u32)(e >> 30)); };
+  if (!a.accumulate && main_prime) {
+#pragma unroll
+    for (int k = 0; k < CB; k++) mac(d0[k], c0[k][n], mi.pmod), mac(d1[k], c1[k][n], mi.pmod);
+    terms = 1;
+  }
+  for (u32 r = 0; r < a.nrot; r++) {
+    const u64* evk = uniform_ptr(a.evk_pc[r]) + (size_t)id * N;
+    const u32 m = galois_src_index(n, a.galois_pc[r], a.logN);
+    for (u32 j = 0; j < a.beta; j++) {
+      const u64 e0 = uniform_load(evk + ((size_t)j * 2 + 0) * a.nm * N, n * 8);
+      const u64 e1 = uniform_load(evk + ((size_t)j * 2 + 1) * a.nm * N, n * 8);
+      const bool own = fwd_inner_owns(a, t, j);
+#pragma unroll
+      for (int k = 0; k < CB; k++) {
+        const u64 x = uniform_load(own ? c1[k] : ext[k] + (size_t)j * a.next * N, m * 8);
+        mac(d0[k], x, e0);
+        mac(d1[k], x, e1);
+      }
+      if (++terms == 15) fold(false);
+    }
     if (main_prime) {
-      s0[0] = csub(s0[0] + times_p(c0[m[0]]), q2);
-      s0[1] = csub(s0[1] + times_p(c0[m[1]]), q2);
+#pragma unroll
+      for (int k = 0; k < CB; k++) mac(d0[k], uniform_load(c0[k], m * 8), mi.pmod);
+      if (++terms == 15) fold(false);
     }
   }
-  *(ulonglong2*)o0 = ulonglong2{csub(s0[0], q), csub(s0[1], q)};
-  *(ulonglong2*)o1 = ulonglong2{csub(s1[0], q), csub(s1[1], q)};
+  fold(true);
+#pragma unroll
+  for (int k = 0; k < CB; k++) {
+    if ((u32)k >= nb) continue;
+    u64* o = a.acc + (((size_t)(b0 + k) * 2) * a.next + t) * N + n;
+    o[0] = csub(r0[k], q);
+    o[(size_t)a.next * N] = csub(r1[k], q);
+  }
 }

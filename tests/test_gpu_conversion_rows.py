@@ -63,3 +63,30 @@ def test_double_precision_conversion_is_exact_at_its_bounds():
         assert Fraction(s) == r + Fraction(L) and abs(s) < 2.0 ** 53
         out = Fraction(s) - Fraction(round(s * qinv)) * q
         assert (out - total) % q == 0 and abs(out) <= Fraction(q, 2) + 1
+
+
+@gpu_only
+@pytest.mark.parametrize("shape,nl,B,R", [
+    ((16, 5, 50, 2, 60, 5), 5, 6, 3),      # five digits: the kernel for any number; ciphertexts in fours and two
+    ((16, 4, 50, 2, 60, 4), 4, 5, 9),      # four digits, fours and one
+    ((16, 3, 50, 1, 50, 3), 2, 3, 2),      # double-precision special primes; three ciphertexts as four
+    ((16, 4, 60, 2, 60, 4), 4, 3, 30),     # integer main primes: 150 products, sums reduced on the way
+])
+def test_hoisted_sums_of_several_ciphertexts(shape, nl, B, R):
+    import torch
+    import paper_2604_03425_amd as gpu
+    from ckks_inputs import galois_element, make_params, uniform_residues
+    from gpu_util import assert_same, to_dev, to_host
+    from oracle import ref
+    p = make_params(*shape)
+    rc, gc = ref.RefContext(p), gpu.Context(p)
+    ct = uniform_residues(1, p.q[:nl], (B, 2), p.N)
+    ct[0] = [[[m - 1] for m in p.q[:nl]]] * 2
+    keys = [uniform_residues(2 + r, p.moduli, (p.dnum, 2), p.N) for r in range(min(R, 3))]
+    keys[0][:] = [[[[m - 1] for m in p.moduli]]]
+    evks, gs = [keys[r % 3] for r in range(R)], [galois_element(5 * r + 1, p.logN) for r in range(R)]
+    d_keys = [to_dev(k) for k in keys]
+    out = torch.empty((B, 2, nl, p.N), dtype=torch.int64, device="cuda")
+    gpu.ckks_hrot_sum(gc, out, to_dev(ct), B, nl, gs, [d_keys[r % 3] for r in range(R)], gc.workspace(gpu.OP_HROT_SUM, B, nl))
+    assert_same(to_host(out), rc.hrot_sum(ct, gs, evks), "hrot_sum")
+    gc.close()
