@@ -541,6 +541,7 @@ void launch_rows(u32 logN, bool inverse, int cls, dim3 grid, hipStream_t st, con
 
 struct NttOpts {
   u32 galois = 0;                     // two-pass inverse only: read src through the eval-domain Galois map
+  const u64* src_b = nullptr;         // two-pass inverse only: transform the products of src and src_b (double precision)
   const u32* galois_pc = nullptr;     // same, one element per polynomial (host array, npoly <= KS_MULTI_MAX entries)
   const ulonglong2* scale = nullptr;  // two-pass inverse only: per-slot constants (from slot0) replacing N^-1
   bool split_out = false;             // N = 2^16 inverse only: write the shifted, split form the fused base conversion reads
@@ -559,6 +560,7 @@ int launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, u64 src_stride, 
     Ntt16Args a;
     a.logN = c->logN;
     a.src = src + (size_t)slot0 * c->N;
+    a.src_b = opt.src_b ? opt.src_b + (size_t)slot0 * c->N : nullptr;
     a.dst = dst + (size_t)slot0 * c->N;
     a.tw = inverse ? c->d_tw_inv : c->d_tw_fwd;
     a.twfp = inverse ? c->d_twfp_inv : c->d_twfp_fwd;
@@ -764,8 +766,8 @@ struct KsIo {
   const u64* const* evk_pc = nullptr;
   const u64* add2 = nullptr;   // [B][2][nlimbs][N] plain addend of mode bit 0 (two-pass path); null = out, in place
   bool add2_three = false;     // add2 is [B][3][nlimbs][N]; its first two components are the addends
-  // ring 2^12: d is the product of the second components of two ciphertexts [B][2][nlimbs][N], whose other two product
-  // terms are the addends
+  // ring 2^12, and two-pass rings where every main prime is double precision (mode {4, 4}): d is the product of the second
+  // components of two ciphertexts [B][2][nlimbs][N], whose other two product terms are the addends
   const u64 *prod_a = nullptr, *prod_b = nullptr;
 };
 
@@ -1050,7 +1052,11 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
   o1.scale = lt->up_scale;
   o1.split_out = fused_up;
   o1.blocks_only = conv_up;
-  if ((rc = launch_ntt(c, true, io.d, io.d_stride, dcoef, (u64)nlimbs * N, B, 0, nlimbs, qmap, 0, 0, st, o1))) return rc;
+  const u64 polyN = (u64)nlimbs * N;
+  if (io.prod_a) o1.src_b = io.prod_b + polyN;
+  if ((rc = launch_ntt(c, true, io.prod_a ? io.prod_a + polyN : io.d, io.prod_a ? 2 * polyN : io.d_stride, dcoef, polyN, B, 0,
+                       nlimbs, qmap, 0, 0, st, o1)))
+    return rc;
   // 2. The double-precision part of the row pass (memory-bound) may run on the second stream beside the
   // integer-class chain of steps 2-4 (arithmetic-bound), which does not depend on it.
   const bool fork = any_fp && any_int && !special_fp && !acc_add && !conv_up && c->tune[4] == 0;
@@ -1197,6 +1203,8 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
       a.fin_mode0 = io.mode[0];
       a.fin_mode1 = io.mode[1];
       a.fin_galois = io.add_galois;
+      a.prod_a = io.prod_a;
+      a.prod_b = io.prod_b;
       ProfScope ps(c, PK_INNER_C, st);
       launch_inner_c(c, B, cnt, a, st);
       HIP_TRY(hipGetLastError());
@@ -1947,6 +1955,18 @@ int ckks_hmult_relin(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_a, const 
   hipStream_t st = (hipStream_t)stream;
   if (whole_limb(c)) {
     KsIo io{nullptr, 0, 0, (u64*)ct_out, {0, 0}, nullptr, 0};
+    io.prod_a = (const u64*)ct_a;
+    io.prod_b = (const u64*)ct_b;
+    return keyswitch_impl(c, io, B, nlimbs, (const u64*)evk, (char*)ws, st);
+  }
+  // Two-pass rings, double-precision main primes: the products are formed where they are read (first inverse pass, own
+  // digits, assembly), which takes 6 passes over a limb vector where a product kernel of its own and the reads of its
+  // results took 11: 32 products of 24 limbs at 2^16 3328 -> 3099 us, 3 of 11 limbs 230 -> 216, 8 of 13 limbs at 2^15
+  // 308 -> 293. Integer-class primes keep it: their kernels are bound by instructions, and a product costs 40.
+  bool all_fp = two_pass(c) && c->tune[3] != 1;
+  for (u32 i = 0; i < nlimbs; i++) all_fp = all_fp && host_class(c, c->mod[i]) == 0;
+  if (all_fp) {
+    KsIo io{nullptr, 0, 0, (u64*)ct_out, {4, 4}, nullptr, 0};
     io.prod_a = (const u64*)ct_a;
     io.prod_b = (const u64*)ct_b;
     return keyswitch_impl(c, io, B, nlimbs, (const u64*)evk, (char*)ws, st);

@@ -25,6 +25,8 @@ struct Ntt16Args {
   u32 raw_out;                           // forward last pass, double-precision class only: != 0 leaves reduced doubles
   u32 split_out = 0;                     // inverse second pass only: != 0 writes (y + (q-1)/2) mod q as two 30-bit halves
                                          // (bits 0..29, 32..62), the source form of ntt16_bconv_rows_kernel
+  const u64* src_b = nullptr;            // inverse first pass, double-precision class only: != null transforms the products of
+                                         // src and src_b (same layout) instead of src
   u32 galois;                            // inverse first pass only: != 0 reads src through the eval-domain Galois map
   u32 multi = 0;                         // != 0: polynomial p is read through galois_pc[p] instead (p < KS_MULTI_MAX)
   u32 galois_pc[KS_MULTI_MAX];
@@ -105,6 +107,12 @@ __global__ void __launch_bounds__(NTT16_THREADS) ntt16_inv_blocks_kernel(Ntt16Ar
     double xd[16];
 #pragma unroll
     for (int i = 0; i < 16; i++) xd[i] = u2d(x[i]);
+    if (a.src_b) {
+      const u64* sb = a.src_b + (size_t)poly * a.src_poly_stride + ((size_t)slot << logN);
+#pragma unroll
+      for (int i = 0; i < 16; i++)
+        xd[i] = fp_mulmod_var(xd[i], u2d(sb[(size_t)h * 256 + i * 16 + j0]), mi.qinv, mi.qd);   // below 0.9 q in magnitude
+    }
     ntt16_inv_blocks_fp(xd, twfp, mi.qd, mi.qinv, tile, R, (double*)sm);
 #pragma unroll
     for (int i = 0; i < 16; i++) x[i] = (u64)__double_as_longlong(xd[i]);
@@ -381,6 +389,9 @@ struct FwdInnerArgs {
   const u64* fin_add_src = nullptr;
   const ulonglong2* fin_pinv = nullptr;
   u32 fin_mode0 = 0, fin_mode1 = 0, fin_galois = 0, fin_add2_three = 0;
+  // the same kernel: != null switches the product of the second components of two ciphertexts ([B][2][nlimbs][N] each; d is
+  // not read) and adds the other two terms of the product to the result (fin_mode0 == fin_mode1 == 4)
+  const u64 *prod_a = nullptr, *prod_b = nullptr;
 };
 // b is the same for the whole workgroup; saying so keeps the table look-ups on the scalar unit and their results
 // in scalar registers.
@@ -472,7 +483,11 @@ __device__ __forceinline__ void fwd_inner_c_body_fp(const FwdInnerArgs& a, u32 b
     const u64* src = a.d + (size_t)b * a.d_poly_stride + (size_t)t * N;
 #pragma unroll
     for (int i = 0; i < 16; i++) e[i] = k[i * 16];
-    if (g) {
+    if (a.prod_a) {
+      const size_t o = ((size_t)(b * 2 + 1) * a.nlimbs + t) * N + pos;
+#pragma unroll
+      for (int i = 0; i < 16; i++) x[i] = fp_mulmod_var(u2d(a.prod_a[o + i * 16]), u2d(a.prod_b[o + i * 16]), qinv, q);
+    } else if (g) {
 #pragma unroll
       for (int i = 0; i < 16; i++) x[i] = u2d(src[galois_src_index(pos + i * 16, g, LOGN)]);
     } else {
@@ -527,11 +542,30 @@ __device__ __forceinline__ void fwd_inner_c_body_fp(const FwdInnerArgs& a, u32 b
       } else if (mode == 2) {
 #pragma unroll
         for (int i = 0; i < 16; i++) e[i] = as[galois_src_index(pos + i * 16, gf, LOGN)];
+      } else if (mode == 4) {
+        const u64* a0 = a.prod_a + ((size_t)b * 2 * a.nlimbs + t) * N;
+#pragma unroll
+        for (int i = 0; i < 16; i++) e[i] = a0[pos + i * 16];
       }
     });
     const double2 pv = ((const double2*)a.fin_pinv)[t];
     u64* o = a.fin_out + ((size_t)bc * a.nlimbs + t) * N + lane_pos();
     const u32 pos = lane_pos();
+    if (mode == 4) {   // d0 = a0 b0, d1 = a0 b1 + a1 b0; e holds a0
+      const size_t c0 = ((size_t)b * 2 * a.nlimbs + t) * N + pos, c1 = c0 + (size_t)a.nlimbs * N;
+      const u64* f = a.prod_b + (c ? c1 : c0);
+#pragma unroll
+      for (int i = 0; i < 16; i++)
+        x[i] = fp_mulmod_const(fp_reduce(acc[i], qinv, q) - x[i], pv.x, pv.y, q) +
+               fp_mulmod_var(u2d(e[i]), u2d(f[i * 16]), qinv, q);
+      if (c) {
+#pragma unroll
+        for (int i = 0; i < 16; i++) x[i] += fp_mulmod_var(u2d(a.prod_a[c1 + i * 16]), u2d(a.prod_b[c0 + i * 16]), qinv, q);
+      }
+#pragma unroll
+      for (int i = 0; i < 16; i++) o[i * 16] = d2u_canon(fp_reduce(x[i], qinv, q), q);
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < 16; i++) {
       double r = fp_mulmod_const(fp_reduce(acc[i], qinv, q) - x[i], pv.x, pv.y, q);   // |r| <= 0.75 q
