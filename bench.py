@@ -59,7 +59,7 @@ def measured_traffic():
     return {k: int(v) for k, v in rec.get("hbm_bytes_per_launch", {}).items()}
 
 
-def keyswitch_model(p, B, nl, hrot, hmult, fp_inner=2, bconv_fused=False):
+def keyswitch_model(p, B, nl, hrot, hmult, fp_inner=2, bconv=0):
     """Algorithmic bytes and lane-ops per kernel kind for ONE key-switch call on a batch of B (N = 2^16 path:
     double-precision bodies on primes < 2^50, with their inner product as a separate streaming kernel)."""
     N, K, alpha = p.N, len(p.p), p.alpha
@@ -85,14 +85,26 @@ def keyswitch_model(p, B, nl, hrot, hmult, fp_inner=2, bconv_fused=False):
         if nbytes or nops:
             m["%s<%d>" % (name, cls) if cls is not None else name] = dict(bytes=nbytes, ops=nops)
     # class 0 = double-precision bodies; the 60-bit special primes are class 2 (Harvey integer bodies)
-    put("ntt16_inv_blocks_kernel", 0, inv_fp * 2 * limb, inv_fp * bf_pass_fp)
+    put("ntt16_inv_blocks_kernel", 0, (inv_fp * 2 + (B * own_fp if hmult and own_int == 0 and fp_inner != 1 else 0)) * limb,
+        inv_fp * bf_pass_fp)
     put("ntt16_inv_blocks_kernel", 2, inv_int * 2 * limb, inv_int * bf_pass)
-    put("ntt16_inv_rows_kernel", 0, inv_fp * 2 * limb, inv_fp * (bf_pass_fp + N * OPS_SHOUP_FP))
-    put("ntt16_inv_rows_kernel", 2, inv_int * 2 * limb, inv_int * (bf_pass + N * OPS_SHOUP))
+    inv_rows_ops = inv_fp * (bf_pass_fp + N * OPS_SHOUP_FP) + inv_int * (bf_pass + N * OPS_SHOUP)
+    if bconv:
+        put("ntt16_inv_rows_kernel", 0, inv_fp * 2 * limb, inv_fp * (bf_pass_fp + N * OPS_SHOUP_FP))
+        put("ntt16_inv_rows_kernel", 2, inv_int * 2 * limb, inv_int * (bf_pass + N * OPS_SHOUP))
     fp_main = [t for t in range(nl) if fp[t]]
     fp_t, int_t = [t for t in range(nxt) if fp[t]], [t for t in range(nxt) if not fp[t]]
     dn_fp, dn_int = 2 * own_fp, 2 * own_int     # ModDown targets per ciphertext
-    if not bconv_fused:
+    if bconv == 0:
+        # inverse row pass of the sources, conversion (4 FP64 instructions per term and 9 per output between
+        # double-precision limbs, else 4 multiply-adds per term and 27), row pass of the targets; sources read and targets
+        # written once
+        new_ops = sum(sum(len(dg) * OPS_DOT30 + (9 if fp[t] and all(fp[i] for i in dg) else OPS_REDUCE90)
+                          for t in range(nxt) if t not in dg) for dg in digits)
+        put("conv_rows_kernel", None, (B * (nl + new_limbs) + 2 * B * (K + nl)) * limb,
+            inv_rows_ops + B * N * (new_ops + 2 * nl * (K * OPS_DOT30 + OPS_REDUCE90)) +
+            B * ((new_fp + dn_fp) * bf_pass_fp + (new_int + dn_int) * bf_pass))
+    elif bconv == 2:
         # base conversion, as executed: 4 multiply-adds per term on 30-bit halves + a 27-instruction reduction per output
         put("modup_kernel", None, B * (nl + new_limbs) * limb,
             B * N * sum((nxt - len(dg)) * ((len(dg) + 1) * OPS_DOT30 + OPS_REDUCE90) for dg in digits))
@@ -110,6 +122,8 @@ def keyswitch_model(p, B, nl, hrot, hmult, fp_inner=2, bconv_fused=False):
             B * (N * (up_ops(fp_t) + dn_fp * dn_term) + (new_fp + dn_fp) * bf_pass_fp))
         put("ntt16_bconv_rows_kernel", 2, B * ((nl if new_int else 0) + new_int + (2 * K if dn_int else 0) + dn_int) * limb,
             B * (N * (up_ops(int_t) + dn_int * dn_term) + (new_int + dn_int) * bf_pass))
+    # double-precision main primes: the products of a multiplication are formed where they are read
+    fused_product = hmult and own_int == 0 and fp_inner != 1
     addend = 1 if hrot else 2 if hmult else 0
     if fp_inner != 1:
         # default on double-precision main limbs: block pass of the digits fused with one key component per workgroup
@@ -131,7 +145,7 @@ def keyswitch_model(p, B, nl, hrot, hmult, fp_inner=2, bconv_fused=False):
         B * (new_int * bf_pass + N * n_int * beta * 2 * mul_redc))
     put("ntt16_fwd_blocks_final_kernel", 2, B * own_int * (6 + addend) * limb,
         2 * B * own_int * (bf_pass + N * (OPS_SHOUP + 2 * OPS_ADD)))
-    if hmult:
+    if hmult and not fused_product:
         put("tensor_kernel", None, B * nl * 7 * limb, B * nl * N * 4 * mul_redc)
     return m
 
@@ -618,14 +632,14 @@ def main():
         ck.ckks_tune_set(ctx, 0, args.map_mode)
     if args.int_only:
         ck.ckks_tune_set(ctx, 1, 1)
-    fp_inner, bconv_fused = 2, False   # library defaults of knobs 3 and 2
+    fp_inner, bconv = 2, 0   # library defaults of knobs 3 and 2
     for kv in filter(None, args.tune.split(",")):
         k, v = kv.split("=")
         ck.ckks_tune_set(ctx, int(k), int(v))
         if int(k) == 3:
             fp_inner = int(v)
         if int(k) == 2:
-            bconv_fused = int(v) == 1
+            bconv = int(v)
     gen = torch.Generator(device=dev).manual_seed(0xC0FFEE)
 
     def uniform(prefix, moduli):
@@ -690,7 +704,7 @@ def main():
     # --- per-kind roofline figures from the event durations of the timed region ---
     model = {}
     for (b, hrot, hmult, calls) in ((Bg, True, False, G), (B // 2, False, True, 1)):
-        for kind, v in keyswitch_model(p, b, nl, hrot, hmult, fp_inner, bconv_fused).items():
+        for kind, v in keyswitch_model(p, b, nl, hrot, hmult, fp_inner, bconv).items():
             acc = model.setdefault(kind, dict(bytes=0.0, ops=0.0))
             acc["bytes"] += v["bytes"] * calls
             acc["ops"] += v["ops"] * calls

@@ -1010,8 +1010,9 @@ void launch_inner_c(const ckks_ctx* c, u32 B, u32 nslots, const FwdInnerArgs& a,
 }
 
 // Two-pass path: transforms fused with their neighbours.
-//   1. INTT(d) with (Q_j/q_i)^-1 / N folded in, written in the split form
-//   2. ModUp conversion and row pass of every slot a digit does not own (two kernels; knob 2 = 1: one fused kernel)
+//   1. INTT(d) with (Q_j/q_i)^-1 / N folded in
+//   2. ModUp conversion and row pass of every slot a digit does not own
+//      (1's row pass and 2 are one kernel where conv_fits; else kernels of their own, knob 2 = 1: one fused kernel for 2)
 //   3. integer-class slots (the special primes): [block pass + evk inner product] (x 2^-64 from the Montgomery products)
 //   4. INTT of the special limbs with 2^64 (P/p_k)^-1 / N folded in; ModDown conversion and row pass (as step 2)
 //   5. double-precision main limbs: [block pass of the digits + evk inner product + block pass of the ModDown
@@ -1074,8 +1075,7 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
     HIP_TRY(hipEventRecord(c->ev_fork, st));
     HIP_TRY(hipStreamWaitEvent(sb, c->ev_fork, 0));
   }
-  if (conv_up) {
-  } else if (!fused_up) {
+  if (!conv_up && !fused_up) {
     NttOpts o2;
     o2.rows_only = true;
     if (any_fp) {
@@ -1090,7 +1090,7 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
       if ((rc = launch_ntt(c, false, ext, (u64)next * N, ext, (u64)next * N, B * beta, 0, next, emap, beta, nlimbs, st, o)))
         return rc;
     }
-  } else {
+  } else if (fused_up) {
     BconvRowsArgs up;
     up.src = dcoef;
     up.dst = ext;
