@@ -1493,8 +1493,8 @@ int keyswitch_impl(ckks_ctx* c, const KsIo& io, u32 B, u32 nlimbs, const u64* ev
   return CKKS_OK;
 }
 
-// Hoisted sums are instantiated for up to 4 digits and for any number. Ciphertexts go four to a lane, a remainder of one or
-// two in lanes of its own (one of three as four).
+// Hoisted sums on double-precision slots. The kernel for several ciphertexts per lane is instantiated for up to 4 digits and
+// for any number.
 template <int CB>
 void launch_inner_sum_fp_of(u32 b0, u32 groups, u32 blocks, u32 slots, const FwdInnerArgs& a, u32 B, hipStream_t st) {
   const dim3 grid(groups, blocks, slots), block(256);
@@ -1506,11 +1506,23 @@ void launch_inner_sum_fp_of(u32 b0, u32 groups, u32 blocks, u32 slots, const Fwd
     default: hipLaunchKernelGGL((inner16_sum_fp_kernel<CB, 0>), grid, block, 0, st, a, B, b0); break;
   }
 }
-void launch_inner_sum_fp(u32 B, u32 blocks, u32 slots, const FwdInnerArgs& a, hipStream_t st) {
-  const u32 rest = B % 4 == 3 ? 0 : B % 4, fours = (B - rest + 3) / 4;
-  if (fours) launch_inner_sum_fp_of<4>(0, fours, blocks, slots, a, B, st);
-  if (rest == 1) launch_inner_sum_fp_of<1>(B - 1, 1, blocks, slots, a, B, st);
-  if (rest == 2) launch_inner_sum_fp_of<2>(B - 2, 1, blocks, slots, a, B, st);
+// Ciphertexts go to lanes in as few groups of at most four as hold them, as even as possible: a lone remainder costs nearly
+// what a whole group does (5 ciphertexts of 20 limbs, 4 digits, 7 rotations: four and one 405 us, three and two 350; 9: fours
+// and one 613, threes 586). The kernel for one ciphertext and two positions per lane is left what it does better: one rotation,
+// one ciphertext of more than 4 digits (134 us against 128) and 5 ciphertexts with a few rotations (2 digits, 2: 104 and 93).
+void launch_inner_sum_fp(u32 B, u32 N, u32 slots, const FwdInnerArgs& a, hipStream_t st) {
+  if (a.nrot <= 1 || (B == 1 && a.beta > 4) || (B == 5 && a.nrot < 4)) {
+    hipLaunchKernelGGL(inner16_sum_pair_fp_kernel, dim3(B, N / 512, slots), dim3(256), 0, st, a);
+    return;
+  }
+  if (B <= 2) {
+    if (B == 1) launch_inner_sum_fp_of<1>(0, 1, N / 256, slots, a, B, st);
+    else launch_inner_sum_fp_of<2>(0, 1, N / 256, slots, a, B, st);
+    return;
+  }
+  const u32 groups = (B + 3) / 4, fours = B > 3 * groups ? B - 3 * groups : 0;   // B = 5: two threes, one place empty
+  if (fours) launch_inner_sum_fp_of<4>(0, fours, N / 256, slots, a, B, st);
+  if (groups > fours) launch_inner_sum_fp_of<3>(4 * fours, groups - fours, N / 256, slots, a, B, st);
 }
 
 int check_common(const ckks_ctx* c, u32 B, u32 nlimbs) {
@@ -2129,9 +2141,10 @@ int ckks_hrot_sum(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint32_t
         if ((host_class(c, c->mod[emap.id[s_]]) == 0) == (fp == 1)) a.slots[cnt++] = (unsigned char)s_;
       if (!cnt) continue;
       ProfScope ps(c, fp ? PK_INNER16 : PK_INNER16_INT, st);
-      if (fp) launch_inner_sum_fp(B, (u32)N / 256, cnt, a, st);
-      else hipLaunchKernelGGL(inner16_sum_int_kernel, dim3((B + INNER16_SUM_CB_INT - 1) / INNER16_SUM_CB_INT, N / 256, cnt),
-                              dim3(256), 0, st, a, B);
+      const dim3 grid(B, N / 512, cnt);
+      if (fp) launch_inner_sum_fp(B, (u32)N, cnt, a, st);
+      else if (nr * a.beta >= 16) hipLaunchKernelGGL(inner16_sum_int_kernel<true>, grid, dim3(256), 0, st, a);
+      else hipLaunchKernelGGL(inner16_sum_int_kernel<false>, grid, dim3(256), 0, st, a);
     }
     HIP_TRY(hipGetLastError());
   }

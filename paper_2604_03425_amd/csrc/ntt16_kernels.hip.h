@@ -1168,17 +1168,19 @@ __global__ void __launch_bounds__(256) inner16_rot_int_kernel(FwdInnerArgs a, u3
 // ---- a ciphertext plus many of its rotations, summed before ModDown (hoisted rotate-and-sum) ----
 // acc[b][c][t][n] = P * ct[b][c][t][n] (main primes; or what acc holds, if accumulate)
 //                   + sum_r ( sum_j D_j[pi_r(n)] * evk_r[j][c][id(t)][n]  + [c = 0] P * c0[b][t][pi_r(n)] ),
-// output-stationary: a lane owns one position of up to CB ciphertexts, walks over the rotations with its sums in registers
-// (digits, c1 and c0 read through rotation r's index map, key words read in place, once for all its ciphertexts and one
-// rotation ahead) and stores once. galois_pc[r] is the Galois element of rotation r, evk_pc[r] its key; d = c1 and c0 are
-// the two components of the input ciphertext. grid = (groups of CB ciphertexts from b_first on, N / 256, slots of the class).
-// What bounds it: the latency of the gathers, each of which brings 5 words of a ciphertext per position. All loads of a
-// rotation are in flight together (with a branch on the own digit between them every one was waited for), and the key
-// words, two thirds of the reads with one ciphertext per lane, serve four. 8 ciphertexts of 20 limbs, 4 digits, 7
-// rotations: 541 -> 436 us.
+// output-stationary: a lane walks over the rotations with its sums in registers (digits, c1 and c0 read through rotation r's
+// index map, key words read in place) and stores once. galois_pc[r] is the Galois element of rotation r, evk_pc[r] its key;
+// d = c1 and c0 are the two components of the input ciphertext.
+// What bounds it: the latency of the gathers, each of which brings 5 words of a ciphertext per position.
+//
+// Double precision, several rotations: a lane owns one position of up to CB ciphertexts, so that the key words, two thirds of
+// the reads with one ciphertext per lane, serve them all and are requested one rotation ahead; all loads of a rotation are in
+// flight together (with a branch on the own digit between them every one was waited for). grid = (groups of CB ciphertexts
+// from b_first on, N / 256, slots of the class). 8 ciphertexts of 20 limbs, 4 digits, 7 rotations: 555 -> 491 us.
 // Workgroup -> (ciphertext group, block of positions, slot): all blocks of one (group, slot) run on one XCD, in order, so that
-// a line of a digit is fetched into that L2 once and found there by the other rotations (every rotation reads every line,
-// at another position); groups beyond the last multiple of 8 are dealt out in order.
+// a line of a digit that is still in that L2 is found there by the other rotations (every rotation reads every line, at
+// another position; four ciphertexts of 20 limbs are three times the L2, so many are not); groups beyond the last multiple of
+// 8 are dealt out in order. 8 ciphertexts, 30 rotations: 1734 us, in dispatch order 1999, by (block, slot) as ntt16_map 2024.
 __device__ __forceinline__ void inner16_sum_map(u32& bg, u32& blk, u32& zi) {
   const u32 lin = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), whole = (gridDim.x * gridDim.z) & ~7u;
   u32 unit;
@@ -1293,95 +1295,178 @@ __global__ void __launch_bounds__(256) inner16_sum_fp_kernel(FwdInnerArgs a, u32
   }
 }
 
-// The same for integer-class moduli (every term with the factor 2^-64, as in inner16_int_kernel). Products are summed as
-// 30-bit partial products, 15 between folds into a 128-bit sum, and reduced once at the end instead of one by one: 8
-// ciphertexts, 5 special limbs, 4 digits, 7 rotations 168 -> 138 us.
-#define INNER16_SUM_CB_INT 2
-__global__ void __launch_bounds__(256) inner16_sum_int_kernel(FwdInnerArgs a, u32 B) {
-  constexpr int CB = INNER16_SUM_CB_INT;
+// One rotation, and the shapes launch_inner_sum_fp names: two adjacent positions of one ciphertext per lane (16-byte key and
+// output words), digits one after the other. With one rotation nothing is asked for ahead and a key word serves each
+// ciphertext once: 3 ciphertexts of 20 limbs, 2 digits 45 us, in the kernel above 47; 12 of them 157, 164.
+__global__ void __launch_bounds__(256) inner16_sum_pair_fp_kernel(FwdInnerArgs a) {
   const size_t N = (size_t)1 << a.logN;
-  u32 bg, blk, zi;
-  inner16_sum_map(bg, blk, zi);
+  u32 b, blk, zi;
+  ntt16_map(a.map_mode, b, blk, zi);
   const u32 t = a.slots[zi];
   const u32 id = t < a.nlimbs ? t : t - a.nlimbs + a.nq;
   const ModInfo mi = a.mods[id];
-  const u64 q = mi.m;
-  const u32 n = blk * 256 + threadIdx.x;
+  const double q = mi.qd, qinv = mi.qinv;
+  const u32 n = (blk * 256 + threadIdx.x) * 2;
   const bool main_prime = t < a.nlimbs;
-  const u32 b0 = bg * CB, nb = min((u32)CB, B - b0);
-  const u64 *c0[CB], *c1[CB], *ext[CB];
-  Dot30 d0[CB], d1[CB];
-  Acc128 v0[CB], v1[CB];
-  u64 r0[CB], r1[CB];   // residues below 2q: what acc held, and full 128-bit sums reduced early
+  const double pm = u2d(mi.pmod);
+  const u64* c0 = a.c0 + (size_t)b * a.c0_poly_stride + (size_t)t * N;
+  const u64* c1 = a.d + (size_t)b * a.d_poly_stride + (size_t)t * N;
+  u64* o0 = a.acc + (((size_t)b * 2 + 0) * a.next + t) * N + n;
+  u64* o1 = o0 + (size_t)a.next * N;
+  double s0[2] = {0.0, 0.0}, s1[2] = {0.0, 0.0};
+  if (a.accumulate) {
+    const ulonglong2 p0 = *(const ulonglong2*)o0, p1 = *(const ulonglong2*)o1;
+    s0[0] = u2d(p0.x), s0[1] = u2d(p0.y), s1[0] = u2d(p1.x), s1[1] = u2d(p1.y);
+  } else if (main_prime) {
+    const ulonglong2 v0 = *(const ulonglong2*)(c0 + n), v1 = *(const ulonglong2*)(c1 + n);
+    s0[0] = fp_mulmod_var(u2d(v0.x), pm, qinv, q), s0[1] = fp_mulmod_var(u2d(v0.y), pm, qinv, q);
+    s1[0] = fp_mulmod_var(u2d(v1.x), pm, qinv, q), s1[1] = fp_mulmod_var(u2d(v1.y), pm, qinv, q);
+  }
+  for (u32 r = 0; r < a.nrot; r++) {
+    const u32 g = a.galois_pc[r];
+    const u64* evk = uniform_ptr(a.evk_pc[r]) + (size_t)id * N + n;
+    const u32 m[2] = {galois_src_index(n, g, a.logN), galois_src_index(n + 1, g, a.logN)};
+    // the running sums enter a rotation at most q in magnitude; three products (below 0.9 q each) are added between folds
+    u32 pending = 0;
+    for (u32 j = 0; j < a.beta; j++) {
+      double x[2];
+      if (fwd_inner_owns(a, t, j)) {
+        x[0] = u2d(c1[m[0]]);
+        x[1] = u2d(c1[m[1]]);
+      } else {
+        const u64* e = a.ext + (((size_t)b * a.beta + j) * a.next + t) * N;
+        x[0] = __longlong_as_double((long long)e[m[0]]);
+        x[1] = __longlong_as_double((long long)e[m[1]]);
+      }
+      const ulonglong2 eb = *(const ulonglong2*)(evk + ((size_t)j * 2 + 0) * a.nm * N);
+      const ulonglong2 ea = *(const ulonglong2*)(evk + ((size_t)j * 2 + 1) * a.nm * N);
+      s0[0] += fp_mulmod_var(x[0], u2d(eb.x), qinv, q);
+      s0[1] += fp_mulmod_var(x[1], u2d(eb.y), qinv, q);
+      s1[0] += fp_mulmod_var(x[0], u2d(ea.x), qinv, q);
+      s1[1] += fp_mulmod_var(x[1], u2d(ea.y), qinv, q);
+      if (++pending == 3) {
+        pending = 0;
 #pragma unroll
-  for (int k = 0; k < CB; k++) {
-    const u32 b = min(b0 + k, B - 1);   // a surplus slot repeats the last ciphertext and stores nothing
-    c0[k] = a.c0 + (size_t)b * a.c0_poly_stride + (size_t)t * N;
-    c1[k] = a.d + (size_t)b * a.d_poly_stride + (size_t)t * N;
-    ext[k] = a.ext + (((size_t)b * a.beta) * a.next + t) * N;
-    dot30_init(d0[k]);
-    dot30_init(d1[k]);
-    v0[k] = v1[k] = Acc128{0, 0};
-    r0[k] = r1[k] = 0;
-    if (a.accumulate) {
-      const u64* o = a.acc + (((size_t)b * 2) * a.next + t) * N + n;
-      r0[k] = o[0], r1[k] = o[(size_t)a.next * N];
+        for (int k = 0; k < 2; k++) {
+          s0[k] = fp_reduce(s0[k], qinv, q);
+          s1[k] = fp_reduce(s1[k], qinv, q);
+        }
+      }
+    }
+    if (main_prime) {
+      s0[0] += fp_mulmod_var(u2d(c0[m[0]]), pm, qinv, q);
+      s0[1] += fp_mulmod_var(u2d(c0[m[1]]), pm, qinv, q);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; k++) {   // back to |.| <= q/2 before the next rotation
+      s0[k] = fp_reduce(s0[k], qinv, q);
+      s1[k] = fp_reduce(s1[k], qinv, q);
     }
   }
+  *(ulonglong2*)o0 = ulonglong2{d2u_canon(fp_reduce(s0[0], qinv, q), q), d2u_canon(fp_reduce(s0[1], qinv, q), q)};
+  *(ulonglong2*)o1 = ulonglong2{d2u_canon(fp_reduce(s1[0], qinv, q), q), d2u_canon(fp_reduce(s1[1], qinv, q), q)};
+}
+
+// Running sums of one position of an integer-class modulus; every term carries the factor 2^-64, as in inner16_int_kernel.
+// Few products: each is reduced by itself. MANY: 30-bit partial products, 15 terms between folds into a 128-bit sum that is
+// reduced at the end (and after every seven folds).
+template <bool MANY>
+struct IntSum;
+template <>
+struct IntSum<false> {
+  u64 s;   // below 2q
+  __device__ __forceinline__ void init(u64 v) { s = v; }
+  __device__ __forceinline__ void mac(u64 x, u64 e, const ModInfo& mi) {
+    const Acc128 p = {x * e, mul_hi64(x, e)};
+    s = csub(s + redc(p, mi.m, mi.minv), 2 * mi.m);
+  }
+  __device__ __forceinline__ void fold(bool, const ModInfo&) {}
+  __device__ __forceinline__ u64 value(const ModInfo& mi) const { return csub(s, mi.m); }
+};
+template <>
+struct IntSum<true> {
+  Dot30 d;
+  Acc128 v;
+  u64 r;   // residues below 2q: the start value, and full 128-bit sums reduced early
+  __device__ __forceinline__ void init(u64 start) {
+    dot30_init(d);
+    v = Acc128{0, 0};
+    r = start;
+  }
+  __device__ __forceinline__ void mac(u64 x, u64 e, const ModInfo&) {
+    dot30_mac(d, (u32)x & 0x3FFFFFFFu, (u32)(x >> 30), (u32)e & 0x3FFFFFFFu, (u32)(e >> 30));
+  }
+  __device__ __forceinline__ void fold(bool reduce, const ModInfo& mi) {
+    const Acc128 p = dot30_value(d);
+    v.lo += p.lo;
+    v.hi += p.hi + (v.lo < p.lo ? 1ull : 0ull);
+    dot30_init(d);
+    if (reduce) {   // at most 105 products: the reduced sum is below 8q
+      const u64 x = csub(csub(redc(v, mi.m, mi.minv), 4 * mi.m), 2 * mi.m);
+      r = csub(r + x, 2 * mi.m);
+      v = Acc128{0, 0};
+    }
+  }
+  __device__ __forceinline__ u64 value(const ModInfo& mi) const { return csub(r, mi.m); }
+};
+// Integer-class moduli: two adjacent positions of one ciphertext per lane, as inner16_sum_pair_fp_kernel, and with its map
+// (ciphertexts that share a key slice next to each other; two ciphertexts per lane saved no more and cost an odd batch a
+// whole ciphertext's work: 5 ciphertexts, 16 special limbs, 1 digit, 7 rotations 122 us, here 98). With fewer than 16
+// products per output the folds cost more than what they save: 5 ciphertexts, 10 limbs, 2 digits, 4 rotations 70 us with
+// single reductions, 74 with MANY; 4 digits, 5 limbs, 7 rotations 116 and 103, 8 ciphertexts of that 168 and 138.
+template <bool MANY>
+__global__ void __launch_bounds__(256) inner16_sum_int_kernel(FwdInnerArgs a) {
+  const size_t N = (size_t)1 << a.logN;
+  u32 b, blk, zi;
+  ntt16_map(a.map_mode, b, blk, zi);
+  const u32 t = a.slots[zi];
+  const u32 id = t < a.nlimbs ? t : t - a.nlimbs + a.nq;
+  const ModInfo mi = a.mods[id];
+  const u32 n = (blk * 256 + threadIdx.x) * 2;
+  const bool main_prime = t < a.nlimbs;
+  const u64* c0 = a.c0 + (size_t)b * a.c0_poly_stride + (size_t)t * N;
+  const u64* c1 = a.d + (size_t)b * a.d_poly_stride + (size_t)t * N;
+  u64* o0 = a.acc + (((size_t)b * 2 + 0) * a.next + t) * N + n;
+  u64* o1 = o0 + (size_t)a.next * N;
+  IntSum<MANY> s0[2], s1[2];
   u32 terms = 0, folds = 0;
   auto fold = [&](bool last) {
     terms = 0;
     folds++;
 #pragma unroll
-    for (int k = 0; k < CB; k++) {
-      const Acc128 p0 = dot30_value(d0[k]), p1 = dot30_value(d1[k]);
-      v0[k].lo += p0.lo;
-      v0[k].hi += p0.hi + (v0[k].lo < p0.lo ? 1ull : 0ull);
-      v1[k].lo += p1.lo;
-      v1[k].hi += p1.hi + (v1[k].lo < p1.lo ? 1ull : 0ull);
-      dot30_init(d0[k]);
-      dot30_init(d1[k]);
-      if (last || folds % 7 == 0) {   // at most 105 products: the reduced sum is below 8q
-        const u64 x0 = csub(csub(redc(v0[k], q, mi.minv), 4 * q), 2 * q), x1 = csub(csub(redc(v1[k], q, mi.minv), 4 * q), 2 * q);
-        r0[k] = csub(r0[k] + x0, 2 * q);
-        r1[k] = csub(r1[k] + x1, 2 * q);
-        v0[k] = v1[k] = Acc128{0, 0};
-      }
+    for (int k = 0; k < 2; k++) {
+      s0[k].fold(last || folds % 7 == 0, mi);
+      s1[k].fold(last || folds % 7 == 0, mi);
     }
   };
-  auto mac = [&](Dot30& d, u64 x, u64 e) { dot30_mac(d, (u32)x & 0x3FFFFFFFu, (u32)(x >> 30), (u32)e & 0x3FFFFFFFu, (u32)(e >> 30)); };
+  ulonglong2 p0 = {0, 0}, p1 = {0, 0};
+  if (a.accumulate) p0 = *(const ulonglong2*)o0, p1 = *(const ulonglong2*)o1;
+  s0[0].init(p0.x), s0[1].init(p0.y), s1[0].init(p1.x), s1[1].init(p1.y);
   if (!a.accumulate && main_prime) {
-#pragma unroll
-    for (int k = 0; k < CB; k++) mac(d0[k], c0[k][n], mi.pmod), mac(d1[k], c1[k][n], mi.pmod);
+    const ulonglong2 w0 = *(const ulonglong2*)(c0 + n), w1 = *(const ulonglong2*)(c1 + n);
+    s0[0].mac(w0.x, mi.pmod, mi), s0[1].mac(w0.y, mi.pmod, mi);
+    s1[0].mac(w1.x, mi.pmod, mi), s1[1].mac(w1.y, mi.pmod, mi);
     terms = 1;
   }
   for (u32 r = 0; r < a.nrot; r++) {
-    const u64* evk = uniform_ptr(a.evk_pc[r]) + (size_t)id * N;
-    const u32 m = galois_src_index(n, a.galois_pc[r], a.logN);
+    const u32 g = a.galois_pc[r];
+    const u64* evk = uniform_ptr(a.evk_pc[r]) + (size_t)id * N + n;
+    const u32 m[2] = {galois_src_index(n, g, a.logN), galois_src_index(n + 1, g, a.logN)};
     for (u32 j = 0; j < a.beta; j++) {
-      const u64 e0 = uniform_load(evk + ((size_t)j * 2 + 0) * a.nm * N, n * 8);
-      const u64 e1 = uniform_load(evk + ((size_t)j * 2 + 1) * a.nm * N, n * 8);
-      const bool own = fwd_inner_owns(a, t, j);
-#pragma unroll
-      for (int k = 0; k < CB; k++) {
-        const u64 x = uniform_load(own ? c1[k] : ext[k] + (size_t)j * a.next * N, m * 8);
-        mac(d0[k], x, e0);
-        mac(d1[k], x, e1);
-      }
-      if (++terms == 15) fold(false);
+      const u64* src = fwd_inner_owns(a, t, j) ? c1 : a.ext + (((size_t)b * a.beta + j) * a.next + t) * N;
+      const u64 x[2] = {src[m[0]], src[m[1]]};
+      const ulonglong2 eb = *(const ulonglong2*)(evk + ((size_t)j * 2 + 0) * a.nm * N);
+      const ulonglong2 ea = *(const ulonglong2*)(evk + ((size_t)j * 2 + 1) * a.nm * N);
+      s0[0].mac(x[0], eb.x, mi), s0[1].mac(x[1], eb.y, mi);
+      s1[0].mac(x[0], ea.x, mi), s1[1].mac(x[1], ea.y, mi);
+      if (MANY && ++terms == 15) fold(false);
     }
     if (main_prime) {
-#pragma unroll
-      for (int k = 0; k < CB; k++) mac(d0[k], uniform_load(c0[k], m * 8), mi.pmod);
-      if (++terms == 15) fold(false);
+      s0[0].mac(c0[m[0]], mi.pmod, mi), s0[1].mac(c0[m[1]], mi.pmod, mi);
+      if (MANY && ++terms == 15) fold(false);
     }
   }
-  fold(true);
-#pragma unroll
-  for (int k = 0; k < CB; k++) {
-    if ((u32)k >= nb) continue;
-    u64* o = a.acc + (((size_t)(b0 + k) * 2) * a.next + t) * N + n;
-    o[0] = csub(r0[k], q);
-    o[(size_t)a.next * N] = csub(r1[k], q);
-  }
+  if (MANY) fold(true);
+  *(ulonglong2*)o0 = ulonglong2{s0[0].value(mi), s0[1].value(mi)};
+  *(ulonglong2*)o1 = ulonglong2{s1[0].value(mi), s1[1].value(mi)};
 }

@@ -67,10 +67,17 @@ def test_double_precision_conversion_is_exact_at_its_bounds():
 
 @gpu_only
 @pytest.mark.parametrize("shape,nl,B,R", [
-    ((16, 5, 50, 2, 60, 5), 5, 6, 3),      # five digits: the kernel for any number; ciphertexts in fours and two
-    ((16, 4, 50, 2, 60, 4), 4, 5, 9),      # four digits, fours and one
-    ((16, 3, 50, 1, 50, 3), 2, 3, 2),      # double-precision special primes; three ciphertexts as four
+    ((16, 5, 50, 2, 60, 5), 5, 6, 3),      # five digits: the kernel for any number; two groups of three; 15 products
+    ((16, 4, 50, 2, 60, 4), 4, 5, 9),      # four digits, two groups with one place empty
+    ((16, 3, 50, 1, 50, 3), 2, 3, 2),      # double-precision special primes
     ((16, 4, 60, 2, 60, 4), 4, 3, 30),     # integer main primes: 150 products, sums reduced on the way
+    ((16, 2, 50, 1, 60, 2), 2, 10, 2),     # a group of four and two of three
+    ((16, 2, 50, 1, 60, 1), 2, 7, 4),      # four and three, one digit
+    ((16, 2, 50, 1, 60, 2), 2, 5, 3),      # two positions of one ciphertext per lane
+    ((16, 5, 50, 1, 60, 5), 5, 1, 3),
+    ((16, 2, 60, 2, 60, 2), 2, 2, 1),      # one rotation, integer main primes
+    ((16, 2, 60, 2, 60, 2), 2, 2, 8),      # 16 products an output: partial products
+    ((16, 2, 50, 2, 60, 1), 2, 3, 65),     # one rotation beyond an argument table
 ])
 def test_hoisted_sums_of_several_ciphertexts(shape, nl, B, R):
     import torch
