@@ -491,9 +491,24 @@ inline u32 map_mode_inner(const ckks_ctx* c, bool shared_key) {
 inline bool two_pass(const ckks_ctx* c) { return c->logN >= 13 && c->logN <= 16; }
 // Ring 2^12: a key switch in four kernels that hold a whole limb per workgroup (ks12.hip.h). 8 rotations with their own
 // keys (4 limbs, 2 digits), which took ten launches each: 322 -> 37 us; 8 rotations of one key (5 limbs, 3 digits) 60 -> 46 us.
-inline bool whole_limb(const ckks_ctx* c) { return c->logN == 12; }
+// A target rereads all sources of its conversion there, so large batches of many limbs are left to one kernel per step, which
+// reads a source once: from 100 MB of converted digits on (what the caches no longer hold) where a workgroup rereads two limbs or
+// more on average. One key, us, this way | by steps: 16 + 4 limbs, 4 digits, batch 32 162 | 176, 64 350 | 333, 512 2971 | 2386;
+// products of it at 64 380 | 348; 16 + 8 60-bit limbs, 2 digits, batch 64 335 | 334, 128 740 | 629; 8 + 8 limbs, 1 digit, 128
+// 295 | 311, 512 1291 | 1117; 8 + 2 limbs, 4 digits (1.6 limbs reread) 512 1212 | 1215, products of it (2.1) 1327 | 1299; 5 + 2
+// limbs, 3 digits (1.3) 512 695 | 714. A key per ciphertext always goes this way: by steps it is one sequence per ciphertext.
+bool whole_limb(const ckks_ctx* c, u32 B, u32 nlimbs, bool product) {
+  if (c->logN != 12) return false;
+  const u32 beta = (nlimbs + c->alpha - 1) / c->alpha, next = nlimbs + c->np, workgroups = (beta + 2) * next;
+  u32 reread = 2 * nlimbs * c->np + (product ? 4 * nlimbs : 0);
+  for (u32 lo = 0; lo < nlimbs; lo += c->alpha) {
+    const u32 len = std::min(c->alpha, nlimbs - lo);
+    reread += len * (next - len);
+  }
+  return (u64)B * beta * next < 3072 || reread < 2 * workgroups;
+}
 // Both kinds read what they switch through the Galois map and take separate addends and per-ciphertext keys.
-inline bool gathers(const ckks_ctx* c) { return two_pass(c) || whole_limb(c); }
+bool gathers(const ckks_ctx* c, u32 B, u32 nlimbs) { return two_pass(c) || whole_limb(c, B, nlimbs, false); }
 inline u32 pass_tiles(const ckks_ctx* c) { return c->N >> 12; }   // 4096-element tiles of a limb
 
 // One launch per modulus class present among `nslots` slots, a.slots listing that class's slots: launch(cls, grid).
@@ -769,6 +784,7 @@ struct KsIo {
   // ring 2^12, and two-pass rings where every main prime is double precision (mode {4, 4}): d is the product of the second
   // components of two ciphertexts [B][2][nlimbs][N], whose other two product terms are the addends
   const u64 *prod_a = nullptr, *prod_b = nullptr;
+  bool steps = false;          // ring 2^12: one kernel per step (whole_limb said no)
 };
 
 // Base conversion fused with the first forward pass (ntt16_bconv_rows_kernel): one launch per modulus class among
@@ -1431,13 +1447,13 @@ int keyswitch_whole12(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
   return CKKS_OK;
 }
 
-// Key switch of io.d with evk into io.out (see KsIo). Other ring degrees: one kernel per step.
+// Key switch of io.d with evk into io.out (see KsIo). Other ring degrees, and io.steps: one kernel per step.
 int keyswitch_impl(ckks_ctx* c, const KsIo& io, u32 B, u32 nlimbs, const u64* evk, char* ws, hipStream_t st) {
   const LevelTables* lt;
   int rc = get_level(c, nlimbs, &lt);
   if (rc) return rc;
   if (two_pass(c)) return keyswitch_fused16(c, lt, io, B, nlimbs, evk, ws, st);
-  if (whole_limb(c)) return keyswitch_whole12(c, lt, io, B, nlimbs, evk, ws, st);
+  if (c->logN == 12 && !io.steps) return keyswitch_whole12(c, lt, io, B, nlimbs, evk, ws, st);
   if (io.d_galois || io.mode[0] >= 2 || io.mode[1] >= 2 || io.add2)
     return fail(CKKS_EINVAL, "internal: gather modes and separate addends need the fused paths");
   const u64* d = io.d;
@@ -1842,6 +1858,7 @@ int ckks_keyswitch(ckks_ctx* c, uint64_t* ks_out, const uint64_t* d, uint32_t B,
   DeviceGuard guard(c->device);
   if (!guard.ok) return fail(CKKS_EHIP, "cannot select the context's device");
   KsIo io{(const u64*)d, (u64)nlimbs * c->N, 0, (u64*)ks_out, {0, 0}, nullptr, 0};
+  io.steps = !whole_limb(c, B, nlimbs, false);
   return keyswitch_impl(c, io, B, nlimbs, (const u64*)evk, (char*)ws, (hipStream_t)stream);
 }
 
@@ -1866,7 +1883,7 @@ static int hrot_impl(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint3
   DeviceGuard guard(c->device);
   if (!guard.ok) return fail(CKKS_EHIP, "cannot select the context's device");
   hipStream_t st = (hipStream_t)stream;
-  if (gathers(c)) {
+  if (gathers(c, B, nlimbs)) {
     // the permutation is applied where the ciphertext is read: by the first inverse pass and the fused inner product
     // (sigma(c1)) and by the final assembly (sigma(c0)), which also adds ct_add
     KsIo io{(const u64*)ct_in + polyN, 2 * polyN, g, (u64*)ct_out, {ct_add ? 3u : 2u, ct_add ? 1u : 0u},
@@ -1883,6 +1900,7 @@ static int hrot_impl(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint3
     return rc;
   if ((rc = launch_automorph(c, d, polyN, (const u64*)ct_in + polyN, 2 * polyN, B, nlimbs, qmap, g, true, st))) return rc;
   KsIo io{d, polyN, 0, (u64*)ct_out, {1, 0}, nullptr, 0};
+  io.steps = true;
   if ((rc = keyswitch_impl(c, io, B, nlimbs, (const u64*)evk, (char*)ws, st))) return rc;
   if (ct_add) {
     AddArgs ad{(u64*)ct_out, (const u64*)ct_add, c->d_mods, c->logN, nlimbs};
@@ -1930,7 +1948,7 @@ int ckks_hrot_multi(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint32
   if ((rc = check_ws(c, CKKS_OP_HROT, B, nlimbs, 0, ws, ws_bytes))) return rc;
   const size_t polyN = (size_t)nlimbs * c->N, ct_bytes = (size_t)B * 2 * polyN * 8;
   if (overlap(ct_out, ct_bytes, ct_in, ct_bytes)) return fail(CKKS_EINVAL, "ct_out overlaps ct_in");
-  if (!gathers(c)) {
+  if (!two_pass(c) && c->logN != 12) {
     // other ring sizes: one rotation at a time through the general path
     for (u32 b = 0; b < B; b++)
       if ((rc = hrot_impl(c, ct_out + b * 2 * polyN, ct_in + b * 2 * polyN, 1, nlimbs, galois_elts[b], evks[b], ws, ws_bytes,
@@ -1965,7 +1983,7 @@ int ckks_hmult_relin(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_a, const 
   DeviceGuard guard(c->device);
   if (!guard.ok) return fail(CKKS_EHIP, "cannot select the context's device");
   hipStream_t st = (hipStream_t)stream;
-  if (whole_limb(c)) {
+  if (whole_limb(c, B, nlimbs, true)) {
     KsIo io{nullptr, 0, 0, (u64*)ct_out, {0, 0}, nullptr, 0};
     io.prod_a = (const u64*)ct_a;
     io.prod_b = (const u64*)ct_b;
@@ -1992,6 +2010,7 @@ int ckks_hmult_relin(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_a, const 
   }
   HIP_TRY(hipGetLastError());
   KsIo io{d2, (u64)nlimbs * c->N, 0, (u64*)ct_out, {1, 1}, nullptr, 0};
+  io.steps = true;
   return keyswitch_impl(c, io, B, nlimbs, (const u64*)evk, (char*)ws, st);
 }
 
@@ -2031,12 +2050,13 @@ int ckks_relin(ckks_ctx* c, uint64_t* ct_out, const uint64_t* d_in, uint32_t B, 
   hipStream_t st = (hipStream_t)stream;
   const u64* d = (const u64*)d_in;
   KsIo io{d + 2 * polyN, 3 * (u64)polyN, 0, (u64*)ct_out, {1, 1}, nullptr, 0};
-  if (gathers(c)) {
+  if (gathers(c, B, nlimbs)) {
     // the last kernel of the key switch reads d0 and d1 in place
     io.add2 = d;
     io.add2_three = true;
   } else {
     // general path: d0, d1 are copied into ct_out and the key switch adds to them in place
+    io.steps = true;
     const size_t pl2 = polyN / 2;
     ProfScope ps(c, PK_ADD, st);
     hipLaunchKernelGGL(first_two_components_kernel, dim3((unsigned)((2 * pl2 + 255) / 256), B), dim3(256), 0, st,
@@ -2335,7 +2355,7 @@ static int pcmm_impl(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint3
       }
       if (g == 0) continue;
       const u64* src = inner + (size_t)k * ct_elems;
-      if (gathers(c)) {
+      if (gathers(c, B, nlimbs)) {
         rc = hrot_impl(c, ct_out, (const uint64_t*)src, B, nlimbs, galois((u64)g * n1 * stride), evk_giant[g - 1], hws,
                        hws_bytes, stream, /*ct_add=*/ct_out);
         if (rc) return rc;
