@@ -863,11 +863,13 @@ int launch_conv_rows(const ckks_ctx* c, ConvArgs a, u32 npoly, bool narrow, Targ
   // ciphertexts has fewer workgroups than the chip holds (two per compute unit, of which a lone one runs at three quarters
   // of their joint rate). Weights are instructions per limb of work, in hundreds.
   const bool fp = host_class(c, c->mod[a.src_id0]) == 0;
-  const u32 tiles = c->N / CONV_TILE, wsrc = a.alpha * (fp ? 4 : 6), wfp = a.nfp * (fp ? 4 : 5), wint = a.nint * 8;
+  const u32 own = a.skip_own ? std::min(a.alpha, a.src_nlimbs) : 0;   // not converted, of the sources' kind
+  const u32 nfp = a.nfp - (fp ? own : 0), nint = a.nint - (fp ? 0 : own);
+  const u32 tiles = c->N / CONV_TILE, wsrc = a.alpha * (fp ? 4 : 6), wfp = nfp * (fp ? 4 : 5), wint = nint * 8;
   const u64 groups = (u64)npoly * tiles;
   u64 best = ~0ull;
   a.nsplit = 1;
-  for (u32 n = 1; n <= a.nfp + a.nint; n++) {
+  for (u32 n = 1; n <= nfp + nint; n++) {
     const u64 per_cu = (groups * n + 255) / 256, cost = (per_cu / 2 * 8 + per_cu % 2 * 6) * (wsrc + (wfp + wint + n - 1) / n);
     if (cost < best) best = cost, a.nsplit = n;
   }

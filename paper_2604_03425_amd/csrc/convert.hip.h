@@ -418,18 +418,24 @@ __global__ void __launch_bounds__(CONV_THREADS) __attribute__((amdgpu_waves_per_
     }
   });
   lds_barrier();   // the last inverse exchange has been read everywhere
-  // targets n, n + nsplit, .. of list [first, first + count): `body` does one
-  auto walk = [&](u32 first, u32 count, u32 n, auto chain, auto body) {
+  // targets n, n + nsplit, .. of list [first, first + count) less the digit's own limbs, which stand together in the list of
+  // their kind (lists are in the order of the slots): `body` does one
+  auto walk = [&](u32 first, u32 count, bool own_kind, u32 n, auto chain, auto body) {
+    const u32 skip = own_kind && a.skip_own ? len : 0;
+    count -= skip;
     if (n >= count) return;
-    const u32 last = first + count - 1;
+    auto at = [&](u32 i) {
+      i = min(i, count - 1);
+      return a.target[first + i + (i >= lo ? skip : 0)];
+    };
     ConvTarget<MAXLEN> cur, next;
-    cur.template fetch<decltype(chain)::value>(a, a.target[first + n], j);
-    u32 info = a.target[min(first + n + a.nsplit, last)];
+    cur.template fetch<decltype(chain)::value>(a, at(n), j);
+    u32 info = at(n + a.nsplit);
 #pragma nounroll
     for (; n < count; n += a.nsplit) {
       next.template fetch<decltype(chain)::value>(a, info, j);
-      info = a.target[min(first + n + 2 * a.nsplit, last)];
-      if (!(a.skip_own && cur.slot >= lo && cur.slot < lo + len)) body(cur);
+      info = at(n + 2 * a.nsplit);
+      body(cur);
       cur = next;
     }
   };
@@ -452,8 +458,8 @@ __global__ void __launch_bounds__(CONV_THREADS) __attribute__((amdgpu_waves_per_
 #pragma unroll
     for (int i = 0; i < 4; i++) d[i * 256] = x[i];
   };
-  if (SRC_FP) walk(0, a.nfp, share, std::true_type{}, fp_target);
-  else walk(0, a.nfp, share, std::false_type{}, fp_target);
+  if (SRC_FP) walk(0, a.nfp, true, share, std::true_type{}, fp_target);
+  else walk(0, a.nfp, false, share, std::false_type{}, fp_target);
   if (a.nint == 0) return;
   if (SRC_FP) {
     conv_each<MAXLEN>([&](auto kc) {
@@ -466,7 +472,7 @@ __global__ void __launch_bounds__(CONV_THREADS) __attribute__((amdgpu_waves_per_
     });
   }
   // the shares that got one double-precision target more are the last to get an integer one
-  walk(a.nfp, a.nint, a.nsplit - 1 - share, std::false_type{}, [&](const ConvTarget<MAXLEN>& tg) {
+  walk(a.nfp, a.nint, !SRC_FP, a.nsplit - 1 - share, std::false_type{}, [&](const ConvTarget<MAXLEN>& tg) {
     const ulonglong2* tw = a.tw + ((size_t)tg.id << LOGN);
     ConvTwiddles<ulonglong2> w;
     w.load(tw);
