@@ -828,22 +828,58 @@ bool conv_fits(const ckks_ctx* c, u32 id0, u32 n, u32 alpha, bool narrow) {
     if ((host_class(c, c->mod[id0 + i]) == 0) != fp) return false;
   return narrow || !fp;
 }
-template <int LOGR, int MAXLEN>
-void launch_conv_len(const ConvArgs& a, bool fp, bool narrow, dim3 grid, hipStream_t st) {
+// A fused conversion about to be launched. READY: the sources' inverse row pass runs in a kernel of its own before it.
+struct ConvJob {
+  ConvArgs a;
+  u32 npoly;
+  bool fp, narrow, ready;
+};
+template <int LOGR, int MAXLEN, bool READY>
+void launch_conv_len(const ConvJob& j, dim3 grid, hipStream_t st) {
   const dim3 block(CONV_THREADS);
-  if (fp) hipLaunchKernelGGL((conv_rows_kernel<LOGR, MAXLEN, true, true>), grid, block, 0, st, a);
-  else if (narrow) hipLaunchKernelGGL((conv_rows_kernel<LOGR, MAXLEN, false, true>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((conv_rows_kernel<LOGR, MAXLEN, false, false>), grid, block, 0, st, a);
+  if (j.fp) hipLaunchKernelGGL((conv_rows_kernel<LOGR, MAXLEN, true, true, READY>), grid, block, 0, st, j.a);
+  else if (j.narrow) hipLaunchKernelGGL((conv_rows_kernel<LOGR, MAXLEN, false, true, READY>), grid, block, 0, st, j.a);
+  else hipLaunchKernelGGL((conv_rows_kernel<LOGR, MAXLEN, false, false, READY>), grid, block, 0, st, j.a);
 }
+#define CONV_READY_MIN_SRC 6
 template <int LOGR>
-void launch_conv_of(const ConvArgs& a, bool fp, bool narrow, dim3 grid, hipStream_t st) {
-  if (a.alpha <= 4) launch_conv_len<LOGR, 4>(a, fp, narrow, grid, st);
-  else if (a.alpha <= 6) launch_conv_len<LOGR, 6>(a, fp, narrow, grid, st);
-  else launch_conv_len<LOGR, 8>(a, fp, narrow, grid, st);
+void launch_conv_of(const ConvJob& j, dim3 grid, hipStream_t st) {
+  if (j.a.alpha <= 4) launch_conv_len<LOGR, 4, false>(j, grid, st);
+  else if (j.a.alpha <= 6 && j.ready) launch_conv_len<LOGR, 6, true>(j, grid, st);
+  else if (j.a.alpha <= 6) launch_conv_len<LOGR, 6, false>(j, grid, st);
+  else if (j.ready) launch_conv_len<LOGR, 8, true>(j, grid, st);
+  else launch_conv_len<LOGR, 8, false>(j, grid, st);
 }
-// a: everything but the tables of the ring, the target lists and nsplit; target_id(slot) = modulus id of a target slot.
+// Modelled time of a conversion whose targets are dealt to n workgroups (shares) per (polynomial, tile): two fit a compute unit, and
+// a lone one runs at two thirds of their joint rate. Every share repeats what is done for the sources (wsrc). Weights are
+// instructions per limb of work, in hundreds.
+inline u64 conv_cost(u64 groups, u32 wsrc, u32 wtargets, u32 n) {
+  const u64 per_cu = (groups * n + 255) / 256;
+  return (per_cu / 2 * 8 + per_cu % 2 * 6) * (wsrc + (wtargets + n - 1) / n);
+}
+// The number of shares: a call on few ciphertexts needs several to fill the chip. What the shares repeat costs a caller nothing
+// while the chip is his alone, but costs the others when several calls are in flight: the fewest shares within a
+// quarter of the best time that leave no round of workgroups under three quarters full, one share within 10 % (the best, for
+// calls that occupy under a quarter of the chip anyway).
+u32 conv_shares(u64 groups, u32 wsrc, u32 wtargets, u32 targets) {
+  u64 best = ~0ull;
+  u32 at = 1;
+  for (u32 n = 1; n <= targets; n++) {
+    const u64 cost = conv_cost(groups, wsrc, wtargets, n);
+    if (cost < best) best = cost, at = n;
+  }
+  if (groups <= 64) return at;
+  if (conv_cost(groups, wsrc, wtargets, 1) * 100 <= best * 110) return 1;
+  for (u32 n = 2; n < at; n++) {
+    const u64 rounds = (groups * n + 255) / 256;
+    if (conv_cost(groups, wsrc, wtargets, n) * 100 <= best * 125 && groups * n * 4 >= rounds * 256 * 3) return n;
+  }
+  return at;
+}
+// job.a: everything but the tables of the ring, the target lists and nsplit; target_id(slot) = modulus id of a target slot.
 template <class TargetId>
-int launch_conv_rows(const ckks_ctx* c, ConvArgs a, u32 npoly, bool narrow, TargetId target_id, hipStream_t st) {
+void conv_plan(const ckks_ctx* c, ConvJob& job, TargetId target_id) {
+  ConvArgs& a = job.a;
   a.tw = c->d_tw_fwd;
   a.twi = c->d_tw_inv;
   a.twfp = c->d_twfp_fwd;
@@ -859,35 +895,43 @@ int launch_conv_rows(const ckks_ctx* c, ConvArgs a, u32 npoly, bool narrow, Targ
       if (fp) a.nfp++;
       else a.nint++;
     }
-  // Shares of the targets per (polynomial, tile): every share repeats the inverse pass of the sources, but a call on few
-  // ciphertexts has fewer workgroups than the chip holds (two per compute unit, of which a lone one runs at three quarters
-  // of their joint rate). Weights are instructions per limb of work, in hundreds.
-  const bool fp = host_class(c, c->mod[a.src_id0]) == 0;
-  const u32 own = a.skip_own ? std::min(a.alpha, a.src_nlimbs) : 0;   // not converted, of the sources' kind
-  const u32 nfp = a.nfp - (fp ? own : 0), nint = a.nint - (fp ? 0 : own);
-  const u32 tiles = c->N / CONV_TILE, wsrc = a.alpha * (fp ? 4 : 6), wfp = nfp * (fp ? 4 : 5), wint = nint * 8;
-  const u64 groups = (u64)npoly * tiles;
-  u64 best = ~0ull;
-  a.nsplit = 1;
-  for (u32 n = 1; n <= nfp + nint; n++) {
-    const u64 per_cu = (groups * n + 255) / 256, cost = (per_cu / 2 * 8 + per_cu % 2 * 6) * (wsrc + (wfp + wint + n - 1) / n);
-    if (cost < best) best = cost, a.nsplit = n;
-  }
-  if (groups * a.nsplit > 0x7FFFFFFFull) return fail(CKKS_ESHAPE, "batch too large for one launch");
-  const dim3 grid((u32)(groups * a.nsplit));
+  job.fp = host_class(c, c->mod[a.src_id0]) == 0;
+  const u32 len = std::min(a.alpha, a.src_nlimbs), own = a.skip_own ? len : 0;   // own limbs: of the sources' kind, not converted
+  const u32 targets = a.nfp + a.nint - own, wtargets = (a.nfp - (job.fp ? own : 0)) * (job.fp ? 4 : 5) + (a.nint - (job.fp ? 0 : own)) * 8;
+  const u64 groups = (u64)job.npoly * (c->N / CONV_TILE);
+  // From 6 sources on, and where one share would take over a tenth longer than several (a quarter with double-precision sources,
+  // whose inverse pass is cheaper), the sources' inverse row pass runs by itself before the shares instead of in each of them
+  // (else its launch costs more than the repeats: 3 products of 11 limbs, 8 special primes 219 us, 205 without). us, the inverse
+  // pass in every share and the best number of them | this: one rotation of 24 limbs, 3 digits, 8 special primes 159 | 151, of
+  // 16 + 8 60-bit limbs 147 | 132, 3 products of 8 of these limbs 209 | 189; four rotations on four streams 542 | 471, 402 | 361,
+  // of 12 + 4 60-bit limbs 307 | 278, of 20 + 5 limbs 410 | 385; with kernels of their own for every step these four took 525,
+  // 352, 302 and 411.
+  const u32 wsrc = len * (job.fp ? 4 : 6);
+  u32 n = conv_shares(groups, wsrc, wtargets, targets);
+  const u64 one = conv_cost(groups, wsrc, wtargets, 1), several = conv_cost(groups, wsrc, wtargets, n);
+  job.ready = len >= CONV_READY_MIN_SRC && one * 100 > several * (job.fp ? 125 : 110);
+  if (job.ready) n = conv_shares(groups, len, wtargets, targets);
+  a.nsplit = n;
+}
+int launch_conv_rows(const ckks_ctx* c, const ConvJob& job, hipStream_t st) {
+  const u64 blocks = (u64)job.npoly * (c->N / CONV_TILE) * job.a.nsplit;
+  if (blocks > 0x7FFFFFFFull) return fail(CKKS_ESHAPE, "batch too large for one launch");
+  const dim3 grid((u32)blocks);
   ProfScope ps(c, PK_CONV_ROWS, st);
   switch (c->logN) {
-    case 13: launch_conv_of<5>(a, fp, narrow, grid, st); break;
-    case 14: launch_conv_of<6>(a, fp, narrow, grid, st); break;
-    case 15: launch_conv_of<7>(a, fp, narrow, grid, st); break;
-    default: launch_conv_of<8>(a, fp, narrow, grid, st); break;
+    case 13: launch_conv_of<5>(job, grid, st); break;
+    case 14: launch_conv_of<6>(job, grid, st); break;
+    case 15: launch_conv_of<7>(job, grid, st); break;
+    default: launch_conv_of<8>(job, grid, st); break;
   }
   HIP_TRY(hipGetLastError());
   return CKKS_OK;
 }
-// ModUp on the two-pass path, from the inverse block pass of the polynomial (in dcoef) to ext after the row pass.
-int ks16_conv_up(const ckks_ctx* c, const LevelTables* lt, const u64* dcoef, u64* ext, u32 B, u32 nlimbs, hipStream_t st) {
-  ConvArgs a;
+// ModUp on the two-pass path, from the inverse block pass of the polynomial (in dcoef; its row pass too if the plan says ready)
+// to ext after the row pass.
+ConvJob conv_up_job(const ckks_ctx* c, const LevelTables* lt, const u64* dcoef, u64* ext, u32 B, u32 nlimbs) {
+  ConvJob job;
+  ConvArgs& a = job.a;
   a.src = dcoef;
   a.dst = ext;
   a.src_poly_stride = (u64)nlimbs * c->N;
@@ -903,7 +947,34 @@ int ks16_conv_up(const ckks_ctx* c, const LevelTables* lt, const u64* dcoef, u64
   a.off = lt->up_off;
   a.matd = lt->up_matd;
   a.scale = lt->up_scale;
-  return launch_conv_rows(c, a, B * lt->beta, lt->narrow_up, [&](u32 s) { return s < nlimbs ? s : s - nlimbs + c->nq; }, st);
+  job.npoly = B * lt->beta;
+  job.narrow = lt->narrow_up;
+  conv_plan(c, job, [&](u32 s) { return s < nlimbs ? s : s - nlimbs + c->nq; });
+  return job;
+}
+// ModDown: both accumulators' special limbs to tq.
+ConvJob conv_down_job(const ckks_ctx* c, const LevelTables* lt, const u64* acc, u64* tq, u32 B, u32 nlimbs) {
+  ConvJob job;
+  ConvArgs& a = job.a;
+  a.src = acc;
+  a.dst = tq;
+  a.src_poly_stride = (u64)lt->next * c->N;
+  a.dst_poly_stride = (u64)nlimbs * c->N;
+  a.src_slot0 = nlimbs;
+  a.src_id0 = c->nq;
+  a.src_nlimbs = a.alpha = c->np;
+  a.beta = 1;
+  a.skip_own = 0;
+  a.ntarget = nlimbs;
+  a.pitch = lt->dn_pitch;
+  a.mat = lt->dn_mat_plain;
+  a.off = lt->dn_off;
+  a.matd = lt->dn_matd;
+  a.scale = lt->dn_scale;
+  job.npoly = B * 2;
+  job.narrow = lt->narrow_dn;
+  conv_plan(c, job, [](u32 s) { return s; });
+  return job;
 }
 
 // ModDown's conversion and the first forward pass of its result on the two-pass path: the special limbs of both
@@ -919,27 +990,13 @@ int ks16_moddown_rows(ckks_ctx* c, const LevelTables* lt, u32 B, u32 nlimbs, u64
   NttOpts o3;
   o3.scale = lt->dn_scale;
   o3.split_out = fused;
-  o3.blocks_only = conv;
-  if ((rc = launch_ntt(c, true, acc, (u64)next * N, acc, (u64)next * N, B * 2, nlimbs, K, pmap, 0, 0, st, o3))) return rc;
+  ConvJob job;
   if (conv) {
-    ConvArgs a;
-    a.src = acc;
-    a.dst = tq;
-    a.src_poly_stride = (u64)next * N;
-    a.dst_poly_stride = (u64)nlimbs * N;
-    a.src_slot0 = nlimbs;
-    a.src_id0 = c->nq;
-    a.src_nlimbs = a.alpha = K;
-    a.beta = 1;
-    a.skip_own = 0;
-    a.ntarget = nlimbs;
-    a.pitch = lt->dn_pitch;
-    a.mat = lt->dn_mat_plain;
-    a.off = lt->dn_off;
-    a.matd = lt->dn_matd;
-    a.scale = lt->dn_scale;
-    return launch_conv_rows(c, a, B * 2, lt->narrow_dn, [](u32 s) { return s; }, st);
+    job = conv_down_job(c, lt, acc, tq, B, nlimbs);
+    o3.blocks_only = !job.ready;
   }
+  if ((rc = launch_ntt(c, true, acc, (u64)next * N, acc, (u64)next * N, B * 2, nlimbs, K, pmap, 0, 0, st, o3))) return rc;
+  if (conv) return launch_conv_rows(c, job, st);
   if (!fused) {
     {
       ModDownArgs a{acc, tq, c->d_mods, lt->dn_inv, lt->dn_mat_plain, c->logN, nlimbs, c->nq, K, next, nlimbs, c->nq};
@@ -1070,7 +1127,11 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
   o1.galois_pc = io.galois_pc;
   o1.scale = lt->up_scale;
   o1.split_out = fused_up;
-  o1.blocks_only = conv_up;
+  ConvJob up;
+  if (conv_up) {
+    up = conv_up_job(c, lt, dcoef, ext, B, nlimbs);
+    o1.blocks_only = !up.ready;
+  }
   const u64 polyN = (u64)nlimbs * N;
   if (io.prod_a) o1.src_b = io.prod_b + polyN;
   if ((rc = launch_ntt(c, true, io.prod_a ? io.prod_a + polyN : io.d, io.prod_a ? 2 * polyN : io.d_stride, dcoef, polyN, B, 0,
@@ -1081,7 +1142,7 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
   const bool fork = any_fp && any_int && !special_fp && !acc_add && !conv_up && c->tune[4] == 0;
   hipStream_t sb = st;
   if (conv_up) {
-    if ((rc = ks16_conv_up(c, lt, dcoef, ext, B, nlimbs, st))) return rc;
+    if ((rc = launch_conv_rows(c, up, st))) return rc;
   } else if (!fused_up) {
     ModUpArgs a{dcoef, ext, c->d_mods, lt->up_inv, lt->up_mat, c->logN, nlimbs, c->nq, c->alpha, beta, next};
     ProfScope ps(c, PK_MODUP, st);
@@ -1247,10 +1308,15 @@ static int hoist_front16(ckks_ctx* c, const LevelTables* lt, const u64* ct_in, u
   const u64* c1 = ct_in + polyN;
   NttOpts o1, of;
   o1.scale = lt->up_scale;
-  o1.blocks_only = of.blocks_only = conv_fits(c, 0, nlimbs, c->alpha, lt->narrow_up);
+  of.blocks_only = conv_fits(c, 0, nlimbs, c->alpha, lt->narrow_up);
+  ConvJob up;
+  if (of.blocks_only) {
+    up = conv_up_job(c, lt, dcoef, ext, B, nlimbs);
+    o1.blocks_only = !up.ready;
+  }
   if ((rc = launch_ntt(c, true, c1, 2 * polyN, dcoef, polyN, B, 0, nlimbs, qmap, 0, 0, st, o1))) return rc;
-  if (o1.blocks_only) {
-    if ((rc = ks16_conv_up(c, lt, dcoef, ext, B, nlimbs, st))) return rc;
+  if (of.blocks_only) {
+    if ((rc = launch_conv_rows(c, up, st))) return rc;
   } else {
     ModUpArgs a{dcoef, ext, c->d_mods, lt->up_inv, lt->up_mat, c->logN, nlimbs, c->nq, c->alpha, beta, next};
     ProfScope ps(c, PK_MODUP, st);

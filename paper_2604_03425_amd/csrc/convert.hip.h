@@ -1,7 +1,8 @@
 // Base conversion fused with the transform passes on both sides of it (ModUp and ModDown, N = 2^13 .. 2^16, at most 8
 // source limbs): second inverse pass of the sources, conversion, first forward pass of every target. Only the sources are
 // read and only the targets, after their row pass, are written; as separate kernels the same step moved the sources three
-// times more and the targets two times more.
+// times more and the targets two times more. Where several workgroups share the targets of a tile, the inverse pass may be a
+// kernel of its own before this one (READY, chosen in conv_plan).
 //
 // A conversion needs all sources of a position in one lane and a row pass all rows of a column in one workgroup. A workgroup
 // of 512 lanes takes R rows x NC = 2048 / R columns, four positions per lane, and keeps the converted form of all sources
@@ -361,7 +362,8 @@ __device__ __forceinline__ void conv_each(F f) {
 
 // One workgroup per (polynomial, tile, share of the targets), tiles fastest. The 64-byte row pieces of two adjacent tiles
 // (N = 2^16) make one line: the XCD-contiguous order keeps them on one L2.
-template <int LOGR, int MAXLEN, bool SRC_FP, bool NARROW>
+// READY: src holds what the inverse row pass makes of the sources (canonical residues, scaled).
+template <int LOGR, int MAXLEN, bool SRC_FP, bool NARROW, bool READY>
 __global__ void __launch_bounds__(CONV_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4))) conv_rows_kernel(ConvArgs a) {
   __shared__ u64 sm[2 * CONV_TILE_WORDS];
   constexpr int L = 11 - LOGR, LOGN = LOGR + 8;
@@ -373,10 +375,13 @@ __global__ void __launch_bounds__(CONV_THREADS) __attribute__((amdgpu_waves_per_
   const u32 e0 = conv_elem(L, 0), pos = (e0 >> L) * 256 + (tile << L) + (e0 & ((1u << L) - 1));
   const u64* src = a.src + (size_t)(poly / a.beta) * a.src_poly_stride + ((size_t)(a.src_slot0 + lo) << LOGN);
   u64* dst = a.dst + (size_t)poly * a.dst_poly_stride;
+  // the sources' positions: READY in the first round's layout, in which the targets start
+  const u32 from = READY ? (threadIdx.x >> L) * 256 + (tile << L) + (threadIdx.x & ((1u << L) - 1)) : pos;
+  constexpr u32 step = READY ? (CONV_THREADS >> L) * 256 : 256;
   ConvWord y[MAXLEN][4];   // doubles from double-precision sources, until the integer targets
   u64 ahead[4];   // the next source's words are requested before the current one is transformed
 #pragma unroll
-  for (int i = 0; i < 4; i++) ahead[i] = src[pos + i * 256];
+  for (int i = 0; i < 4; i++) ahead[i] = src[from + i * step];
   conv_each<MAXLEN>([&](auto kc) {
     constexpr int k = decltype(kc)::value;
     if ((u32)k >= len) {   // uniform
@@ -387,34 +392,43 @@ __global__ void __launch_bounds__(CONV_THREADS) __attribute__((amdgpu_waves_per_
     const u32 id = a.src_id0 + lo + k;
     const ModInfo mi = conv_mod(a.mods, id);
     ulonglong2 sc;
-    conv_fetch(sc, a.scale, lo + k);
-    const u64* s = src + ((size_t)min((u32)k + 1, len - 1) << LOGN) + pos;
+    if (!READY) conv_fetch(sc, a.scale, lo + k);
+    const u64* s = src + ((size_t)min((u32)k + 1, len - 1) << LOGN) + from;
     u64 now[4];
 #pragma unroll
     for (int i = 0; i < 4; i++) now[i] = ahead[i];
 #pragma unroll
-    for (int i = 0; i < 4; i++) ahead[i] = s[i * 256];
+    for (int i = 0; i < 4; i++) ahead[i] = s[i * step];
     if (SRC_FP) {
       double x[4];
+      if (READY) {
 #pragma unroll
-      for (int i = 0; i < 4; i++) x[i] = __longlong_as_double((long long)now[i]);
-      conv_inv_rows<LOGR>(x, a.twifp + ((size_t)id << LOGN), mi.qd, mi.qinv, (double*)sm);
+        for (int i = 0; i < 4; i++) x[i] = u2d(now[i]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; i++) x[i] = __longlong_as_double((long long)now[i]);
+        conv_inv_rows<LOGR>(x, a.twifp + ((size_t)id << LOGN), mi.qd, mi.qinv, (double*)sm);
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+          x[i] = fp_mulmod_const(x[i], __longlong_as_double((long long)sc.x), __longlong_as_double((long long)sc.y), mi.qd);
+      }
       const double h = (mi.qd - 1.0) * 0.5;
 #pragma unroll
       for (int i = 0; i < 4; i++) {
-        double v = fp_mulmod_const(x[i], __longlong_as_double((long long)sc.x), __longlong_as_double((long long)sc.y), mi.qd);
-        v = v > h ? v - mi.qd : v;
+        const double v = x[i] > h ? x[i] - mi.qd : x[i];
         y[k][i].set(v < -h ? v + mi.qd : v);
       }
     } else {
       u64 x[4];
 #pragma unroll
       for (int i = 0; i < 4; i++) x[i] = now[i];
-      conv_inv_rows<LOGR>(x, a.twi + ((size_t)id << LOGN), mi.m, sm);
+      if (!READY) {
+        conv_inv_rows<LOGR>(x, a.twi + ((size_t)id << LOGN), mi.m, sm);
 #pragma unroll
-      for (int i = 0; i < 4; i++) {
-        y[k][i].split(csub(shoup(x[i], sc.x, sc.y, mi.m) + (mi.m >> 1), mi.m));
+        for (int i = 0; i < 4; i++) x[i] = shoup(x[i], sc.x, sc.y, mi.m);
       }
+#pragma unroll
+      for (int i = 0; i < 4; i++) y[k][i].split(csub(x[i] + (mi.m >> 1), mi.m));
     }
   });
   lds_barrier();   // the last inverse exchange has been read everywhere

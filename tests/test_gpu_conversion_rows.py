@@ -16,7 +16,7 @@ SHAPES = [
     ((13, 8, 60, 8, 60, 1), 8, 1),     # 60-bit primes on both sides: the general reduction
     ((14, 4, 51, 4, 60, 1), 4, 2),     # 51-bit sources
     ((13, 6, 50, 3, 50, 2), 6, 2),     # double precision on both sides, special primes too
-    ((13, 3, 30, 2, 50, 2), 3, 40),    # small primes, more workgroups than the chip holds
+    ((13, 3, 30, 2, 50, 2), 3, 40),    # 30-bit targets: the general reduction, which keeps the separate kernels
 ]
 
 
@@ -24,6 +24,48 @@ SHAPES = [
 @pytest.mark.parametrize("shape,nl,B", SHAPES)
 def test_calls_around_the_fused_conversion(shape, nl, B):
     calls.test_calls_on_the_smaller_two_pass_rings(shape, nl, B)
+
+
+def _kernels_of(gpu, gc, call):
+    gpu.ckks_prof_reset(gc)
+    gpu.ckks_prof_enable(gc, True)
+    call()
+    gpu.ckks_prof_enable(gc, False)
+    return {k: n for k, (ms, n) in gpu.ckks_prof_collect(gc).items()}
+
+
+@gpu_only
+@pytest.mark.parametrize("shape,B,alone", [
+    # (logN nq qbits np pbits dnum), B, whether the sources' inverse row pass runs in a kernel of its own
+    ((13, 6, 50, 2, 60, 3), 96, False),    # one share a tile: a workgroup walks over all targets of both kinds
+    ((13, 6, 60, 2, 50, 3), 96, False),    # the same from integer sources
+    ((13, 6, 50, 3, 50, 2), 96, False),
+    ((14, 14, 50, 7, 60, 2), 32, False),   # seven sources
+    ((15, 6, 50, 3, 60, 2), 20, False),
+    ((15, 12, 60, 6, 50, 2), 16, False),
+    ((14, 6, 50, 2, 60, 3), 24, False),    # shares of a few targets
+    ((14, 14, 50, 7, 60, 2), 1, True),
+    ((13, 12, 60, 6, 50, 2), 2, True),
+])
+def test_shares_of_the_targets(shape, B, alone):
+    import torch
+    import paper_2604_03425_amd as gpu
+    from ckks_inputs import galois_element, make_params, uniform_residues
+    from gpu_util import assert_same, to_dev, to_host
+    from oracle import ref
+    p = make_params(*shape)
+    rc, gc, nl = ref.RefContext(p), gpu.Context(p), len(p.q)
+    ct, ct2 = (uniform_residues(40 + i, p.q, (B, 2), p.N) for i in range(2))
+    evk, g, some = uniform_residues(42, p.moduli, (p.dnum, 2), p.N), galois_element(9, p.logN), sorted({0, B // 2, B - 1})
+    d_ct, d_ct2, d_evk = to_dev(ct), to_dev(ct2), to_dev(evk)
+    out, ws = torch.empty_like(d_ct), gc.workspace(gpu.OP_HROT, B, nl)
+    ran = _kernels_of(gpu, gc, lambda: gpu.ckks_hrot(gc, out, d_ct, B, nl, g, d_evk, ws))
+    assert ran["conv_rows_kernel"] == 2, ran
+    assert any(k.startswith("ntt16_inv_rows") for k in ran) == alone, ran
+    assert_same(to_host(out)[some], rc.hrot(ct[some], g, evk), "hrot")
+    gpu.ckks_hmult_relin(gc, out, d_ct, d_ct2, B, nl, d_evk, ws)
+    assert_same(to_host(out)[some], rc.hmult_relin(ct[some], ct2[some], evk), "hmult_relin")
+    gc.close()
 
 
 def test_double_precision_conversion_is_exact_at_its_bounds():
