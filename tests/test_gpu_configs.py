@@ -470,7 +470,8 @@ def test_tuning_knobs_do_not_change_results(gpu):
     d_ct, d_evk = to_dev(ct), to_dev(evk)
     d_rev = d_ct.flip(0).contiguous()
     for knobs in ({0: 0}, {0: 1}, {0: 2}, {0: 3}, {0: 4}, {3: 1}, {3: 1, 4: 0}, {4: 0}, {1: 1}, {1: 1, 3: 1}, {5: 1},
-                  {5: 1, 4: 0}, {2: 1}, {2: 1, 4: 0}, {2: 1, 5: 1}, {2: 1, 1: 1}, {2: 1, 3: 1}):
+                  {5: 1, 4: 0}, {2: 1}, {2: 1, 4: 0}, {2: 1, 5: 1}, {2: 1, 1: 1}, {2: 1, 3: 1}, {2: 2}, {2: 2, 4: 0},
+                  {2: 2, 3: 1, 4: 0}):
         gc = gpu.Context(p)
         for k, v in knobs.items():
             gpu.ckks_tune_set(gc, k, v)
@@ -649,7 +650,8 @@ def test_pcmm_schedules_under_knobs(gpu):
     ref.set_threads(1)
     d_ct, d_pte, d_pt = to_dev(ct), to_dev(pte), to_dev(pt)
     dbk, dgk = [to_dev(k) for k in bk], [to_dev(k) for k in gk]
-    for knobs in [{1: 1}, {5: 1}, {6: 1}, {0: 0}, {0: 2}, {3: 1}, {4: 0}, {2: 1}, {1: 1, 5: 1, 6: 1}]:
+    for knobs in [{1: 1}, {5: 1}, {6: 1}, {0: 0}, {0: 2}, {3: 1}, {4: 0}, {2: 1}, {2: 2}, {2: 2, 4: 0}, {2: 2, 3: 1, 4: 0},
+                  {1: 1, 5: 1, 6: 1}]:
         gc = gpu.Context(p)
         for k, v in knobs.items():
             gpu.ckks_tune_set(gc, k, v)
