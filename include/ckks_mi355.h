@@ -308,7 +308,8 @@ int ckks_prof_enable(ckks_ctx* ctx, int on);
  * writes them to dst (device pointers, multiples of 16 bytes, not overlapping) and nothing else. */
 int ckks_prof_copy(ckks_ctx* ctx, void* dst, const void* src, size_t bytes, void* stream);
 /* Tuning knobs for experiments (defaults in brackets):
- * knob 0 [-1] workgroup-to-tile mapping of the N = 2^16 kernels: 0..4 forces one mapping everywhere, -1 chooses per kernel;
+ * knob 0 [-1] workgroup-to-tile mapping of the kernels for N = 2^13 .. 2^16: 0..4 forces one mapping, -1 chooses per kernel (no
+ *             effect on the conversions of knob 2 = 0 and on hoisted sums of several double-precision rotations);
  * knob 1 [0]  != 0 turns the double-precision bodies for primes < 2^50 off (integer bodies everywhere);
  * knob 2 [0]  base conversions of ModUp and ModDown: 0 = with the row passes on both sides of them in one kernel, where a
  *             conversion has at most 8 sources of one arithmetic kind (2 otherwise); 1 = inside the following row pass only;
@@ -317,7 +318,8 @@ int ckks_prof_copy(ckks_ctx* ctx, void* dst, const void* src, size_t bytes, void
  *             component, block pass of the ModDown correction and final assembly in one kernel; 1 = plain block
  *             pass, streaming product and a separate assembly kernel;
  * knob 4 [1]  0 lets a key switch run the double-precision row pass of the converted digits on a second stream
- *             owned by the context, beside the special-prime chain, joined before the result is assembled;
+ *             owned by the context, beside the special-prime chain, joined before the result is assembled (only where
+ *             that pass is a kernel of its own, see knob 2);
  * knob 5 [0]  != 0 makes every base conversion use the general four-sum accumulation with a 128-bit Montgomery
  *             reduction, also where the bit sizes of the bases allow the shorter three-sum form;
  * knob 6 [0]  != 0 computes the inner sums of ckks_pcmm_bsgs with the integer kernel on every limb;

@@ -157,9 +157,10 @@ struct ProfRec {
 
 struct ckks_ctx {
   // Tuning knobs (ckks_tune_set; meanings in the public header). 0: workgroup mapping of the two-pass kernels (-1: per
-  // kernel); 1: integer bodies everywhere; 2: 1 = base conversions inside the row passes; 3: 2 = inner product fused
-  // with the final assembly on double-precision main limbs, 1 = separate kernels; 4: 0 = fork part of a key switch onto
-  // the second stream; 5: general base-conversion reduction; 6: integer PCMM inner sums; 7: cap on giant steps per pass.
+  // kernel); 1: integer bodies everywhere; 2: base conversions with the row passes on both sides of them (0, where they fit),
+  // inside the following one (1) or kernels of their own (2); 3: 2 = inner product fused with the final assembly on
+  // double-precision main limbs, 1 = separate kernels; 4: 0 = fork a row pass that is a kernel of its own onto the second
+  // stream; 5: general base-conversion reduction; 6: integer PCMM inner sums; 7: cap on giant steps per pass.
   int tune[8] = {-1, 0, 0, 2, 1, 0, 0, 0};
   bool prof_on = false;
   std::vector<ProfRec> prof_recs;
@@ -819,8 +820,9 @@ int launch_bconv_rows(const ckks_ctx* c, BconvRowsArgs a, u32 npoly, bool narrow
 }
 
 // Whether the conversion of digits of `alpha` limbs with modulus ids [id0, id0 + n) runs inside the transform passes around it
-// (conv_rows_kernel): the kernel keeps up to 8 sources per position in registers, all of one arithmetic kind, and converts
-// double-precision sources to integer targets in the three-sum form only. Knob 2 = 0 (the default) allows it.
+// (conv_rows_kernel): the kernel keeps up to 8 sources per position, all of one arithmetic kind, and converts
+// double-precision sources to integer targets in the three-sum form only. Knob 2 = 0 (the default) allows it. One prime of
+// another kind among the main limbs leaves the whole polynomial to the separate kernels, also its digits of one kind.
 bool conv_fits(const ckks_ctx* c, u32 id0, u32 n, u32 alpha, bool narrow) {
   if (c->tune[2] != 0 || alpha > CONV_MAX_SRC) return false;
   const bool fp = host_class(c, c->mod[id0]) == 0;
@@ -1094,8 +1096,8 @@ void launch_inner_c(const ckks_ctx* c, u32 B, u32 nslots, const FwdInnerArgs& a,
 //      correction + (sum - correction) / P + addends] in one kernel, so their accumulators never reach memory;
 //      integer-class main limbs take the assembly kernel on the accumulators of step 3.
 // With knob 3 = 1 the double-precision slots take a plain block pass, a streaming product and the assembly kernel
-// instead of step 5's fusion. With knob 4 = 0 the double-precision part of step 2 runs on the context's second stream
-// beside steps 3 and 4, which do not depend on it, and is joined before step 5.
+// instead of step 5's fusion. With knob 4 = 0 the double-precision row pass of step 2, where it is a kernel of its own, runs on
+// the context's second stream beside steps 3 and 4, which do not depend on it, and is joined before step 5.
 // acc_add != null (knob 3 at its default only): the sequence stops before ModDown and ADDS the two accumulators, plus
 // P * sigma(io.add_src component 0) on the main primes of the first, to acc_add ([B][2][next][N]).
 int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B, u32 nlimbs, const u64* evk, char* ws,
@@ -2060,7 +2062,8 @@ int ckks_hmult_relin(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_a, const 
   // Two-pass rings, double-precision main primes: the products are formed where they are read (first inverse pass, own
   // digits, assembly), which takes 6 passes over a limb vector where a product kernel of its own and the reads of its
   // results took 11: 32 products of 24 limbs at 2^16 3328 -> 3099 us, 3 of 11 limbs 230 -> 216, 8 of 13 limbs at 2^15
-  // 308 -> 293. Integer-class primes keep it: their kernels are bound by instructions, and a product costs 40.
+  // 308 -> 293. Integer-class primes keep it: their kernels are bound by instructions, and a product costs 40. One such prime
+  // among the main limbs keeps it for all of them.
   bool all_fp = two_pass(c) && c->tune[3] != 1;
   for (u32 i = 0; i < nlimbs; i++) all_fp = all_fp && host_class(c, c->mod[i]) == 0;
   if (all_fp) {

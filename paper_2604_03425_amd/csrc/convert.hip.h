@@ -6,7 +6,8 @@
 //
 // A conversion needs all sources of a position in one lane and a row pass all rows of a column in one workgroup. A workgroup
 // of 512 lanes takes R rows x NC = 2048 / R columns, four positions per lane, and keeps the converted form of all sources
-// (8 x 4 words = 64 registers) there while it walks over the targets. Four positions per lane is what makes the sources fit
+// (8 x 4 words = 64 registers) there while it walks over the targets (integer sources that are transformed here: a quarter
+// of the words in scratch memory, stored once and reloaded once per target list; the compiler does not promote them). Four positions per lane is what makes the sources fit
 // beside a transform at 4 waves per SIMD; the row pass is then radix-4 rounds with up to three exchanges through LDS (two
 // of them across waves), whose two tiles alternate so that an exchange costs one barrier. Two workgroups share a compute
 // unit, so one computes while the other waits.
@@ -16,7 +17,7 @@
 // only the first LOGR stages are done. The last round has s = 11 - LOGR, a lane then holds four adjacent rows of a column;
 // for odd LOGR only the second of its two stages is left to do.
 //
-// What bounds it: instruction issue (about three quarters of the vector peak; 1.9 TB/s). Per target and position the conversion
+// What bounds it: instruction issue (0.66 of the vector peak by executed instructions; 2.2 TB/s). Per target and position the conversion
 // of 8 double-precision sources costs 41 FP64 instructions (see convert_fp), its row pass about 45; an integer target about
 // twice that. N = 2^16, 64 ciphertexts of 24 limbs, 3 digits of 8, 8 special primes: inverse row pass, ModUp and row passes as
 // four kernels 2030 us, here 1600; the same for ModDown's three 1440 and 1120. One such ciphertext: 62 -> 50 and 49 -> 43 us.
@@ -349,8 +350,8 @@ __device__ __forceinline__ void convert_int(u64 (&x)[4], const ConvWord (&y)[MAX
   }
 }
 
-// f(0), .., f(N - 1) with constant indices: unrolled before the optimiser sees it, so that an array indexed in f stays in
-// registers (with an unrolled loop of this size it went to scratch memory).
+// f(0), .., f(N - 1) with constant indices: unrolled before the optimiser sees it, so that an array indexed in f can stay in
+// registers (with an unrolled loop of this size all of it went to scratch memory).
 template <class F, int... K>
 __device__ __forceinline__ void conv_each_of(F f, std::integer_sequence<int, K...>) {
   (f(std::integral_constant<int, K>{}), ...);
