@@ -63,6 +63,8 @@ def keyswitch_model(p, B, nl, hrot, hmult, fp_inner=2, bconv=0):
     """Algorithmic bytes and lane-ops per kernel kind for ONE key-switch call on a batch of B (N = 2^16 path:
     double-precision bodies on primes < 2^50, with their inner product as a separate streaming kernel)."""
     N, K, alpha = p.N, len(p.p), p.alpha
+    if bconv == 0 and max(alpha, K) > 8:
+        bconv = 2    # more sources than the fused conversion takes (parameter sets with alpha = K on both sides of it)
     nxt, beta = nl + K, p.beta(nl)
     ext_mod = list(p.q[:nl]) + list(p.p)
     fp = [m < (1 << 50) for m in ext_mod]
