@@ -208,7 +208,7 @@ __device__ __forceinline__ void conv_inv_rows(double (&x)[4], const double* __re
   radix4_inv(x, w0, q, qinv);
   reduce4(x, q, qinv);
 }
-// ---- integer classes, Harvey's ranges for every prime below 2^60: [0,8q) forward, [0,4q) inverse ----
+// ---- integer classes, Harvey's ranges for every prime below 2^60: [0,16q) forward, [0,4q) inverse ----
 template <int LOGR>
 __device__ __forceinline__ void conv_fwd_rows(u64 (&x)[4], const ConvTwiddles<ulonglong2>& w,
                                               const ulonglong2* __restrict__ tw, u64 q, u64* sm) {
@@ -229,7 +229,7 @@ __device__ __forceinline__ void conv_fwd_rows(u64 (&x)[4], const ConvTwiddles<ul
   if (LOGR == 8) radix4_fwd<true>(x, w3, q, q2);
   if (LOGR & 1) {
 #pragma unroll
-    for (int p = 0; p < 2; p++) bf_fwd<true>(x[2 * p], x[2 * p + 1], wl[p], q, q2);
+    for (int p = 0; p < 2; p++) bf_fwd<true, true>(x[2 * p], x[2 * p + 1], wl[p], q, q2);
   }
 }
 template <int LOGR>

@@ -78,15 +78,16 @@ __device__ __forceinline__ u64 neg_opaque(u64 m) {
   asm("" : "+s"(nm));
   return nm;
 }
-__device__ __forceinline__ u64 shoup_lazy4(u64 x, u64 w, u64 ws, u64 m) {
-  const u64 nm = neg_opaque(m);
+// nm = 2^64 - m; the product is added to s, whose words start the multiply-add chains (modulo 2^64).
+__device__ __forceinline__ u64 shoup_lazy4_add(u64 s, u64 x, u64 w, u64 ws, u64 nm) {
   const u32 x0 = (u32)x, x1 = (u32)(x >> 32), p0 = (u32)ws, p1 = (u32)(ws >> 32);
   const u64 qt = (u64)x1 * p1 + __umulhi(x1, p0) + __umulhi(x0, p1);
   const u32 q0 = (u32)qt, q1 = (u32)(qt >> 32), w0 = (u32)w, w1 = (u32)(w >> 32), n0 = (u32)nm, n1 = (u32)(nm >> 32);
-  const u64 t = (u64)x0 * w0 + (u64)q0 * n0;   // modulo 2^64
+  const u64 t = s + (u64)x0 * w0 + (u64)q0 * n0;
   const u32 hi = (u32)(t >> 32) + x0 * w1 + x1 * w0 + q0 * n1 + q1 * n0;
   return ((u64)hi << 32) | (u32)t;
 }
+__device__ __forceinline__ u64 shoup_lazy4(u64 x, u64 w, u64 ws, u64 m) { return shoup_lazy4_add(0, x, w, ws, neg_opaque(m)); }
 // x - m if x >= m, computed as x + (2^64 - m): one 64-bit add, no borrow chain.
 __device__ __forceinline__ u64 csub_neg(u64 x, u64 m) {
   const u64 d = x + neg_opaque(m);

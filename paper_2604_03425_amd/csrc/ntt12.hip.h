@@ -38,11 +38,7 @@ __device__ __forceinline__ void ntt12_fwd_int(const u64* __restrict__ src, u64* 
   for (int c = 0; c < 16; c++) x[c] = sm[i0 * 272 + l * 17 + c];
   radix16_fwd<BIG>(x, q, q2, [&](int s, int g) { return tw[(256 << s) + (R << s) + g]; });
 #pragma unroll
-  for (int c = 0; c < 16; c++) {
-    u64 v = x[c];
-    v = BIG ? csub(csub(v, q2), 2 * q) : barrett_lazy(v, mu, q);
-    x[c] = csub(v, q);
-  }
+  for (int c = 0; c < 16; c++) x[c] = csub(fwd_settle<BIG>(x[c], mu, q), q);
   // back to one column per lane, so that 16 adjacent lanes store one 128-byte line
   wave_lds_sync();
 #pragma unroll

@@ -10,7 +10,8 @@
 // pass around is 4q. SMALL primes (q < 2^52): forward butterflies never correct, values grow by 4q per
 // stage (< 65q < 2^59 after 16 stages from canonical input) and are reduced once at the end; inverse
 // butterflies let sums double for the 8 stages of a pass (inputs < 4q -> < 1024q). BIG primes (q < 2^60)
-// use Harvey's butterflies: values are kept in [0,8q) (forward) / [0,4q) (inverse).
+// use Harvey's butterflies: 16q fits 64 bits, so forward values are kept in [0,16q) with a correction by 8q in every other stage
+// (the first of a round; below 12q after it, 16q after the next), inverse ones in [0,4q).
 #pragma once
 #include "modarith.hip.h"
 
@@ -20,13 +21,22 @@
 // ---- butterflies ----
 template <bool BIG>
 __device__ __forceinline__ u64 lazy_const(u64 q) { return 4 * q; }
-// Forward (Cooley-Tukey), q2 = 4q. BIG: inputs and outputs in [0,8q). SMALL: values grow by 4q per stage.
-template <bool BIG>
+// Forward (Cooley-Tukey), q2 = 4q. SMALL: values grow by 4q per stage. BIG: CORRECT takes inputs below 16q to outputs below 12q,
+// without it inputs below 12q go to outputs below 16q. X + T is formed in the product's own multiply-add chain. Correcting every
+// other stage and adding there: 18 vector instructions on average instead of 22; 4 products of
+// 12 + 4 60-bit limbs at 2^16 322 -> 314 us, 12 rotations of 6 + 2 limbs at 2^14 99 -> 97.
+template <bool BIG, bool CORRECT>
 __device__ __forceinline__ void bf_fwd(u64& X, u64& Y, ulonglong2 w, u64 q, u64 q2) {
-  if (BIG) X = csub_neg(X, q2);
-  u64 T = shoup_lazy4(Y, w.x, w.y, q);
-  Y = X + q2 - T;
-  X = X + T;
+  if (BIG && CORRECT) X = csub_neg(X, 2 * q2);
+  const u64 s = shoup_lazy4_add(X, Y, w.x, w.y, neg_opaque(q));
+  Y = (X << 1) + q2 - s;
+  X = s;
+}
+// The stages of a round are corrected alternately, from the first one (s = 0) on.
+template <bool BIG>
+__device__ __forceinline__ void bf_fwd(u64& X, u64& Y, ulonglong2 w, u64 q, u64 q2, int s) {
+  if (s & 1) bf_fwd<BIG, false>(X, Y, w, q, q2);
+  else bf_fwd<BIG, true>(X, Y, w, q, q2);
 }
 // Inverse (Gentleman-Sande). BIG: c = 4q, inputs in [0,4q), outputs in [0,4q). SMALL: inputs < c (a multiple of q,
 // at least 4q), X' < 2c, Y' < 4q.
@@ -49,7 +59,7 @@ __device__ __forceinline__ void radix16_fwd(u64 (&x)[16], u64 q, u64 q2, TW tw) 
     for (int g = 0; g < (1 << s); g++) {
       ulonglong2 w = tw(s, g);
 #pragma unroll
-      for (int p = 0; p < half; p++) bf_fwd<BIG>(x[g * 2 * half + p], x[g * 2 * half + p + half], w, q, q2);
+      for (int p = 0; p < half; p++) bf_fwd<BIG>(x[g * 2 * half + p], x[g * 2 * half + p + half], w, q, q2, s);
     }
   }
 }
@@ -82,7 +92,7 @@ __device__ __forceinline__ void radix16_fwd_staged(u64 (&x)[16], u64 q, u64 q2, 
     for (int g = 0; g < (1 << s); g++) {
       ulonglong2 w = tw(s, g);
 #pragma unroll
-      for (int p = 0; p < half; p++) bf_fwd<BIG>(x[g * 2 * half + p], x[g * 2 * half + p + half], w, q, q2);
+      for (int p = 0; p < half; p++) bf_fwd<BIG>(x[g * 2 * half + p], x[g * 2 * half + p + half], w, q, q2, s);
     }
     after(s);
   }
@@ -116,7 +126,7 @@ __device__ __forceinline__ void radix_groups_fwd(u64 (&x)[16], u64 q, u64 q2, TW
 #pragma unroll
       for (int k = 0; k < 16; k += 1 << LG)
 #pragma unroll
-        for (int p = 0; p < half; p++) bf_fwd<BIG>(x[k + g * 2 * half + p], x[k + g * 2 * half + p + half], w, q, q2);
+        for (int p = 0; p < half; p++) bf_fwd<BIG>(x[k + g * 2 * half + p], x[k + g * 2 * half + p + half], w, q, q2, s);
     }
   }
 }
@@ -155,6 +165,11 @@ __device__ __forceinline__ void ntt16_load_stage(ulonglong2 (&t)[15], const ulon
 }
 
 __device__ __forceinline__ u64 barrett_lazy(u64 v, u64 mu, u64 q) { return v - mul_hi64(v, mu) * q; }  // [0,2q)
+// The end of a forward transform: below 2q.
+template <bool BIG>
+__device__ __forceinline__ u64 fwd_settle(u64 v, u64 mu, u64 q) {
+  return BIG ? csub_neg(csub_neg(csub_neg(v, 8 * q), 4 * q), 2 * q) : barrett_lazy(v, mu, q);
+}
 
 // ---- pass bodies. `base` points at one limb-vector of N words, `tw` at that modulus' table. ----
 
@@ -175,7 +190,7 @@ struct RowTile {
   }
 };
 
-// Forward, stages 0..LOGR-1. In: canonical (or < 2q). Out: SMALL < 33q (+in), BIG < 8q. `x` holds the first round's layout.
+// Forward, stages 0..LOGR-1. In: canonical (or < 2q). Out: SMALL < 33q (+in), BIG < 16q. `x` holds the first round's layout.
 template <bool BIG, int LOGR>
 __device__ __forceinline__ void ntt16_fwd_rows_loaded(u64 (&x)[16], u64* __restrict__ dst, const ulonglong2* __restrict__ tw,
                                                       u64 q, u32 tile, u64* sm) {
@@ -240,9 +255,7 @@ __device__ __forceinline__ void ntt16_fwd_blocks_loaded(u64 (&x)[16], const ulon
   radix16_fwd<BIG>(x, q, q2, [&](int s, int g) { return twb[NTT16_TW_INDEX(s, g)]; });
 #pragma unroll
   for (int j = 0; j < 16; j++) {
-    u64 v = x[j];
-    if (BIG) v = csub(csub(v, q2), 2 * q);
-    else v = barrett_lazy(v, mu, q);
+    const u64 v = fwd_settle<BIG>(x[j], mu, q);
     x[j] = CANON ? csub(v, q) : v;
   }
   wave_lds_sync();
@@ -264,10 +277,11 @@ __device__ __forceinline__ void ntt16_fwd_blocks(u64 (&x)[16], const u64* __rest
 }
 
 // Forward, the last 8 stages of one 256-element block h of R by 32 adjacent lanes with 8 values each (radix-8, exchange, radix-8, exchange, radix-4; LDS rows of pitch 35 words per 32 elements,
-// all exchanges inside the half-wave). In: x[i] = element i*32 + l, lazy (BIG: < 8q). Out: x[c] = element
-// (l >> 2)*32 + (l & 3)*8 + c, below 2q. `between` runs after the first exchange has been written.
+// all exchanges inside the half-wave). In: x[i] = element i*32 + l, lazy (BIG: < 16q). Out: x[c] = element
+// (l >> 2)*32 + (l & 3)*8 + c, lazy (BIG: < 16q, SMALL: < 65q). `between` runs after the first exchange has been written.
 #define NTT8_PITCH_I 35
 #define NTT8_BLOCK_LDS_I (8 * NTT8_PITCH_I)
+// (the second of two radix-8 rounds: three stages came before, the first of these is not corrected)
 template <bool BIG, class TW>
 __device__ __forceinline__ void radix8_fwd(u64 (&x)[8], u64 q, u64 q2, TW tw) {
 #pragma unroll
@@ -277,7 +291,7 @@ __device__ __forceinline__ void radix8_fwd(u64 (&x)[8], u64 q, u64 q2, TW tw) {
     for (int g = 0; g < (1 << s); g++) {
       const ulonglong2 w = tw(s, g);
 #pragma unroll
-      for (int p = 0; p < half; p++) bf_fwd<BIG>(x[g * 2 * half + p], x[g * 2 * half + p + half], w, q, q2);
+      for (int p = 0; p < half; p++) bf_fwd<BIG>(x[g * 2 * half + p], x[g * 2 * half + p + half], w, q, q2, s + 1);
     }
   }
 }
@@ -290,13 +304,13 @@ __device__ __forceinline__ void radix8_fwd_staged(u64 (&x)[8], u64 q, u64 q2, TW
     for (int g = 0; g < (1 << s); g++) {
       const ulonglong2 w = tw(s, g);
 #pragma unroll
-      for (int p = 0; p < half; p++) bf_fwd<BIG>(x[g * 2 * half + p], x[g * 2 * half + p + half], w, q, q2);
+      for (int p = 0; p < half; p++) bf_fwd<BIG>(x[g * 2 * half + p], x[g * 2 * half + p + half], w, q, q2, s);
     }
     after(s);
   }
 }
 template <bool BIG, class BETWEEN>
-__device__ __forceinline__ void ntt256_fwd_blocks_int8(u64 (&x)[8], const ulonglong2* __restrict__ tw, u64 q, u64 mu, u32 h,
+__device__ __forceinline__ void ntt256_fwd_blocks_int8(u64 (&x)[8], const ulonglong2* __restrict__ tw, u64 q, u32 h,
                                                        u32 R, u32 l, u64* smb, BETWEEN between) {
   const u32 a = l >> 2, b = l & 3;
   const u64 q2 = lazy_const<BIG>(q);
@@ -347,12 +361,10 @@ __device__ __forceinline__ void ntt256_fwd_blocks_int8(u64 (&x)[8], const ulongl
 #pragma unroll
   for (int u = 0; u < 2; u++) {   // stage 14: pairs (c, c + 2) inside each half
 #pragma unroll
-    for (int p = 0; p < 2; p++) bf_fwd<BIG>(x[u * 4 + p], x[u * 4 + p + 2], t3[u], q, q2);
+    for (int p = 0; p < 2; p++) bf_fwd<BIG, true>(x[u * 4 + p], x[u * 4 + p + 2], t3[u], q, q2);
   }
 #pragma unroll
-  for (int k = 0; k < 4; k++) bf_fwd<BIG>(x[2 * k], x[2 * k + 1], t3[2 + k], q, q2);   // stage 15: pairs (2k, 2k + 1)
-#pragma unroll
-  for (int c = 0; c < 8; c++) x[c] = BIG ? csub(csub(x[c], q2), 2 * q) : barrett_lazy(x[c], mu, q);
+  for (int k = 0; k < 4; k++) bf_fwd<BIG, false>(x[2 * k], x[2 * k + 1], t3[2 + k], q, q2);   // stage 15: pairs (2k, 2k + 1)
 }
 
 // Inverse, the first 8 stages, on contiguous blocks. In: x holds, for lane (hb, j0), the values at positions i*16 + j0

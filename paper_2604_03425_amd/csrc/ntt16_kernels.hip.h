@@ -715,7 +715,7 @@ ntt16_fwd_blocks_inner8_kernel(FwdInnerArgs a) {
     u32 jnext = jn + 1;
     if (jnext == jo) jnext++;
     const u32 jcur = jn;
-    ntt256_fwd_blocks_int8<BIG>(x, tw, q, mi.mu64, h, 1u << (a.logN - 8), l, smb, [&] { request_key(jcur); });
+    ntt256_fwd_blocks_int8<BIG>(x, tw, q, h, 1u << (a.logN - 8), l, smb, [&] { request_key(jcur); });
     __builtin_amdgcn_sched_barrier(0);
     // younger than every load the products wait for, so it stays in flight across them (the current tile again when
     // nothing follows: the same static wait counts on every path)

@@ -36,7 +36,7 @@ __device__ __forceinline__ void radix4_fwd(u64 (&x)[4], const ulonglong2 (&w)[3]
 #pragma unroll
   for (int s = 0; s < 2; s++)
 #pragma unroll
-    for (int p = 0; p < 2; p++) bf_fwd<BIG>(x[s == 0 ? p : 2 * p], x[s == 0 ? p + 2 : 2 * p + 1], s == 0 ? w[0] : w[1 + p], q, q2);
+    for (int p = 0; p < 2; p++) bf_fwd<BIG>(x[s == 0 ? p : 2 * p], x[s == 0 ? p + 2 : 2 * p + 1], s == 0 ? w[0] : w[1 + p], q, q2, s);
 }
 // c: bound of the inputs (BIG: 4q). SMALL: outputs below 4c.
 template <bool BIG>
@@ -155,7 +155,7 @@ __device__ __forceinline__ void wl_fwd(u64 (&x)[4], const WlTwiddles<ulonglong2>
   wl_exchange<4, 5>(x, sm);
   radix4_fwd<BIG>(x, w.w[5], q, q2);
 #pragma unroll
-  for (int i = 0; i < 4; i++) x[i] = csub(BIG ? csub(csub(x[i], q2), 2 * q) : barrett_lazy(x[i], mu, q), q);
+  for (int i = 0; i < 4; i++) x[i] = csub(fwd_settle<BIG>(x[i], mu, q), q);
   wl_exchange<5, 2>(x, sm);
 }
 template <bool BIG>

@@ -97,3 +97,31 @@ def test_inverse_ranges():
         vals = sorted(vals, key=lambda vb: -vb[1])    # pair the largest bounds with each other: the worst case
         vals = _stage(vals, m, False, rng, False)
     assert max(b for _, b in vals) <= 1024 * m < (1 << 62)
+
+
+def test_forward_ranges_with_every_other_stage_corrected():
+    """60-bit primes: a stage corrected by 8m takes values below 16m to below 12m, the next one, uncorrected, back to below
+    16m <= 2^64; X + T is summed in the product's chain modulo 2^64 and the difference formed from that sum."""
+    rng = random.Random(7)
+    m = top_prime_like(60)
+    assert 16 * m <= 1 << 64
+    top = [16 * m - 1, 8 * m, 8 * m - 1, 0, 12 * m]
+    vals = [rng.choice(top) for _ in range(64)]
+    for stage in range(16):
+        limit = 16 * m if stage % 2 == 0 else 12 * m
+        rng.shuffle(vals)
+        out = []
+        for X, Y in zip(vals[::2], vals[1::2]):
+            assert X < limit and Y < limit
+            w = rng.randrange(m)
+            if stage % 2 == 0 and X >= 8 * m:
+                X -= 8 * m
+            T = approx_product(Y, w, (w << 64) // m, m)
+            s = (X + T) & M64
+            d = (2 * X + 4 * m - s) & M64
+            assert s == X + T and d == X + 4 * m - T
+            out += [s, d]
+        vals = out
+        assert max(vals) < (12 * m if stage % 2 == 0 else 16 * m)
+        # a Montgomery product with a canonical word takes the largest value to below 2m
+        assert (16 * m - 1) * (m - 1) // (1 << 64) + m <= 2 * m
