@@ -632,6 +632,213 @@ __global__ void __launch_bounds__(256) pmacc_int_kernel(PmaccArgs a) {
   }
 }
 
+// ---- the inner sums of large calls: words staged through LDS ----
+// The kernels above are bound by the caches: every lane loads P + NG words for P * NG multiply-adds, several workgroups load
+// the same ones, and beyond about 12 TB/s of L2 reads more waves or cheaper arithmetic change nothing (three sums instead of
+// four, half the FP64 instructions and 24 instead of 48 sums a lane all measured within 8 %). Here the WP x WG waves of a
+// workgroup hold the sums of WP * P polynomials x WG * NG giant steps at the same 64 positions, and each baby step's words,
+// one row of 64 per polynomial and giant step, are copied into LDS once for all of them, PMACC_SLOTS - 1 baby steps ahead and
+// without passing through registers. One barrier a baby step: a wave that passes it has read the step before, whose slot is
+// then free for the next copy, and its own share of this step's rows has landed. 16 polynomials x 12 giant steps x 64 baby
+// steps at 2^16: 24 50-bit limbs 6840 -> 6400 us, 8 60-bit limbs 3180 -> 2350. What bounds them: neither side alone (8 50-bit
+// limbs: the copies without the sums 1770 us, the sums without the copies 1820, both 2050).
+#define PMACC_SLOTS 3
+template <int P, int NG, int WP, int WG>
+struct PmaccStage {
+  static constexpr int PT = P * WP, GT = NG * WG, ROWS = PT + GT, WAVES = WP * WG;
+  // a wave copies two rows with one instruction, 16 bytes a lane; the last pair is copied again where the waves do not divide
+  // them, so that all waves have the same number of copies in flight
+  static constexpr int PAIRS = ROWS / 2, SHARE = (PAIRS + WAVES - 1) / WAVES, LDS_WORDS = PMACC_SLOTS * ROWS * 64;
+  static_assert(PT % 2 == 0 && GT % 2 == 0, "rows are copied in pairs of one kind");
+  u32 i, id, poly0, giant0, lane;   // limb, modulus, the wave's first polynomial and first giant step within the launch
+  size_t at, ct_sz, pt_k;           // offset of the workgroup's positions inside a polynomial, baby-step strides
+  size_t off[SHARE];
+  u32 pair[SHARE], lds, slot = 0;
+  u64* img;
+
+  // grid.x = polynomial tiles x giant tiles x (N / 64) x limbs, a multiple of 8: the tiles of one position follow each other on
+  // one XCD, whose L2 then serves the words they share
+  __device__ __forceinline__ void init(const PmaccArgs& a, u64* img_) {
+    img = img_;
+    const u32 N = 1u << a.logN, npoly = 2 * a.B, npt = (npoly + PT - 1) / PT, tiles = npt * a.ngt;
+    const u32 lin = (blockIdx.x & 7) * (gridDim.x / 8) + (blockIdx.x >> 3), tile = lin % tiles, group = lin / tiles;
+    const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), p0 = tile % npt * PT, g0 = tile / npt * GT;
+    lane = threadIdx.x & 63;
+    i = __builtin_amdgcn_readfirstlane(a.limbs[group / (N / 64)]), id = __builtin_amdgcn_readfirstlane(a.mod_ids[group / (N / 64)]);
+    poly0 = p0 + wave % WP * P, giant0 = g0 + wave / WP * NG;
+    at = (size_t)i * N + group % (N / 64) * 64;
+    pt_k = (size_t)a.nlimbs * N, ct_sz = npoly * pt_k;
+#pragma unroll
+    for (int c = 0; c < SHARE; c++) {   // rows past the last polynomial or giant step repeat it; their sums are not stored
+      pair[c] = min(wave + c * WAVES, (u32)PAIRS - 1);
+      const u32 row = 2 * pair[c] + (lane >> 5);
+      off[c] = at + (lane & 31) * 2 + (is_ct(c) ? min(p0 + row, npoly - 1) * pt_k : (a.g0 + min(g0 + row - PT, a.ng - 1)) * (a.n1 * pt_k));
+    }
+    lds = (u32)(uintptr_t)(__attribute__((address_space(3))) u64*)img + lane * 8;
+    for (u32 k = 0; k < PMACC_SLOTS - 1; k++) request(a, k, k);
+  }
+  __device__ __forceinline__ bool is_ct(int c) const { return pair[c] < PT / 2; }   // uniform
+  __device__ __forceinline__ void request(const PmaccArgs& a, u32 k, u32 to) {
+    k = min(k, a.n1 - 1);   // past the end the last step again: the same number of copies in flight on every path
+    const u64* ct = k == 0 ? a.ct_in : a.baby + (k - 1) * ct_sz;
+    const u64* pt = a.pt + k * pt_k;
+#pragma unroll
+    for (int c = 0; c < SHARE; c++)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) u32*)((is_ct(c) ? ct : pt) + off[c]),
+                                       (__attribute__((address_space(3))) u32*)(img + to * (ROWS * 64) + pair[c] * 128), 16, 0, 0);
+  }
+  // Baby step k's words of the wave. The copies of step k + 1 stay in flight.
+  __device__ __forceinline__ void take(const PmaccArgs& a, u32 k, u64 (&x)[P], u64 (&c)[NG]) {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"((PMACC_SLOTS - 2) * SHARE) : "memory");
+    request(a, k + PMACC_SLOTS - 1, slot == 0 ? PMACC_SLOTS - 1 : slot - 1);
+    const u32 rows = lds + slot * (ROWS * 512), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    read(c, rows + (PT + wave / WP * NG) * 512);
+    read(x, rows + wave % WP * P * 512);
+    slot = slot == PMACC_SLOTS - 1 ? 0 : slot + 1;
+  }
+  __device__ __forceinline__ void drain() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+  // R rows from LDS. As instructions, with their wait: an ordinary load would first wait for every copy in flight.
+  typedef u32 Row2 __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ void unpack(u64* w, Row2 v) { w[0] = (u64)v.y << 32 | v.x, w[1] = (u64)v.w << 32 | v.z; }
+  static __device__ __forceinline__ void read(u64 (&w)[2], u32 addr) {
+    Row2 a;
+    asm volatile("ds_read2st64_b64 %0, %1 offset0:0 offset1:1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(a) : "v"(addr) : "memory");
+    unpack(w, a);
+  }
+  static __device__ __forceinline__ void read(u64 (&w)[3], u32 addr) {
+    Row2 a;
+    asm volatile("ds_read2st64_b64 %0, %2 offset0:0 offset1:1\n\tds_read_b64 %1, %2 offset:1024\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(a), "=&v"(w[2]) : "v"(addr) : "memory");
+    unpack(w, a);
+  }
+  static __device__ __forceinline__ void read(u64 (&w)[4], u32 addr) {
+    Row2 a, b;
+    asm volatile("ds_read2st64_b64 %0, %2 offset0:0 offset1:1\n\tds_read2st64_b64 %1, %2 offset0:2 offset1:3\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(a), "=&v"(b) : "v"(addr) : "memory");
+    unpack(w, a), unpack(w + 2, b);
+  }
+  static __device__ __forceinline__ void read(u64 (&w)[6], u32 addr) {
+    Row2 a, b, c;
+    asm volatile("ds_read2st64_b64 %0, %3 offset0:0 offset1:1\n\tds_read2st64_b64 %1, %3 offset0:2 offset1:3\n\t"
+                 "ds_read2st64_b64 %2, %3 offset0:4 offset1:5\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(a), "=&v"(b), "=&v"(c) : "v"(addr) : "memory");
+    unpack(w, a), unpack(w + 2, b), unpack(w + 4, c);
+  }
+  // where the sum of the wave's polynomial p and giant step g goes; null for one that is not wanted
+  __device__ __forceinline__ u64* dest(const PmaccArgs& a, u32 p, u32 g) const {
+    const u32 rel = giant0 + g;
+    if (poly0 + p >= 2 * a.B || rel >= a.ng) return nullptr;
+    return (rel == 0 ? a.out0 : a.out_rest + (rel - 1) * ct_sz) + (poly0 + p) * pt_k + at + lane;
+  }
+};
+
+// Double-precision limbs. The products x c', c' = c - h centred with h = (q - 1) / 2, are summed exactly as H + L: H starts at
+// 1.5 * 2^103, in whose binade adding a product rounds it to a multiple of 2^51, and the rest of the product, an integer of
+// magnitude at most 2^50, goes to L. Five products (below 2^99 each) leave H in the binade; then H + L is reduced into L
+// with a quotient off by at most 0.95, so L starts below 1.45 q and every value of a fold stays below 7.9 * 2^50 < 2^53. The
+// sum of the x, times h, is added once at the end. 4 FP64 instructions a product and 6 a fold, against 7 and 3.
+template <int P, int NG, int WP, int WG>
+__global__ void __launch_bounds__(64 * WP * WG) pmacc_fp_staged_kernel(PmaccArgs a) {
+  typedef PmaccStage<P, NG, WP, WG> Stage;
+  __shared__ __attribute__((aligned(16))) u64 img[Stage::LDS_WORDS];
+  Stage st;
+  st.init(a, img);
+  const ModInfo mi = a.mods[st.id];
+  const double q = mi.qd, qinv = mi.qinv, half = (q - 1.0) * 0.5;
+  constexpr double M = 1.5 * 10141204801825835211973625643008.0;   // 1.5 * 2^103
+  double H[P][NG], L[P][NG], sx[P];
+#pragma unroll
+  for (int p = 0; p < P; p++) {
+    sx[p] = 0.0;
+#pragma unroll
+    for (int g = 0; g < NG; g++) H[p][g] = M, L[p][g] = 0.0;
+  }
+  for (u32 k = 0, pending = 0; k < a.n1; k++) {
+    u64 xr[P], cr[NG];
+    st.take(a, k, xr, cr);
+    double c[NG];
+#pragma unroll
+    for (int g = 0; g < NG; g++) c[g] = __longlong_as_double((long long)(cr[g] | 0x4330000000000000ull)) - (4503599627370496.0 + half);
+#pragma unroll
+    for (int p = 0; p < P; p++) {
+      const double x = u2d(xr[p]);
+      sx[p] += x;
+#pragma unroll
+      for (int g = 0; g < NG; g++) {
+        const double Hn = __builtin_fma(x, c[g], H[p][g]), h = Hn - H[p][g];
+        L[p][g] += __builtin_fma(x, c[g], -h);
+        H[p][g] = Hn;
+      }
+    }
+    if (++pending == 5 || k == a.n1 - 1) {   // wave-uniform
+      pending = 0;
+#pragma unroll
+      for (int p = 0; p < P; p++) {
+        sx[p] = fp_reduce(sx[p], qinv, q);
+#pragma unroll
+        for (int g = 0; g < NG; g++) {
+          const double h = H[p][g] - M, t = __builtin_rint(__builtin_fma(L[p][g], qinv, h * qinv));
+          L[p][g] = __builtin_fma(-t, q, h) + L[p][g];
+          H[p][g] = M;
+        }
+      }
+    }
+  }
+  st.drain();
+#pragma unroll
+  for (int p = 0; p < P; p++) {
+    const double s = fp_mulmod_var(sx[p], half, qinv, q);
+#pragma unroll
+    for (int g = 0; g < NG; g++)
+      if (u64* dst = st.dest(a, p, g)) *dst = d2u_canon(fp_reduce(L[p][g] + s, qinv, q), q);
+  }
+}
+
+// Integer limbs: the four sums of 30-bit partial products of the kernel above. After 11 baby steps what the three lower ones
+// hold above 30 bits moves up to the highest, which alone is reduced (below 4 q: with 11 more products and what moves up
+// below 2^64): 24 instructions a fold instead of the 60 of a canonical residue of all four.
+template <int P, int NG, int WP, int WG>
+__global__ void __launch_bounds__(64 * WP * WG) pmacc_int_staged_kernel(PmaccArgs a) {
+  typedef PmaccStage<P, NG, WP, WG> Stage;
+  __shared__ __attribute__((aligned(16))) u64 img[Stage::LDS_WORDS];
+  Stage st;
+  st.init(a, img);
+  const ModInfo mi = a.mods[st.id];
+  const u32 m0 = __builtin_amdgcn_readfirstlane((u32)mi.m), m1 = __builtin_amdgcn_readfirstlane((u32)(mi.m >> 32));
+  const u64 nm = neg_opaque((u64)m1 << 32 | m0);
+  Dot30 dd[P][NG];
+#pragma unroll
+  for (int p = 0; p < P; p++)
+#pragma unroll
+    for (int g = 0; g < NG; g++) dot30_init(dd[p][g]);
+  for (u32 k = 0, pending = 0; k < a.n1; k++) {
+    u64 xr[P], cr[NG];
+    st.take(a, k, xr, cr);
+    u32 c0[NG], c1[NG];
+#pragma unroll
+    for (int g = 0; g < NG; g++) c0[g] = (u32)cr[g] & M30, c1[g] = (u32)(cr[g] >> 30);
+#pragma unroll
+    for (int p = 0; p < P; p++) {
+      const u32 x0 = (u32)xr[p] & M30, x1 = (u32)(xr[p] >> 30);
+#pragma unroll
+      for (int g = 0; g < NG; g++) dot30_mac(dd[p][g], x0, x1, c0[g], c1[g]);
+    }
+    if (++pending == 11) {   // wave-uniform
+      pending = 0;
+#pragma unroll
+      for (int p = 0; p < P; p++)
+#pragma unroll
+        for (int g = 0; g < NG; g++) dot30_settle(dd[p][g], mi.mu64, nm);
+    }
+  }
+  st.drain();
+#pragma unroll
+  for (int p = 0; p < P; p++)
+#pragma unroll
+    for (int g = 0; g < NG; g++)
+      if (u64* dst = st.dest(a, p, g)) *dst = reduce128(dot30_value(dd[p][g]), mi);
+}
+
 // out = out + in (mod q_i) on [npoly][nlimbs][N]
 struct AddArgs {
   u64* out;

@@ -130,6 +130,20 @@ __device__ __forceinline__ void dot30_mac(Dot30& d, u32 y0, u32 y1, u32 c0, u32 
   d.s10 += (u64)y1 * c0;
   d.s11 += (u64)y1 * c1;
 }
+// The same value with s00, s01, s10 below 2^30 and s11 below 4m: what they hold above 30 bits moves up (s01, s10 + 2^34 and
+// s11 + 2^36 must fit 64 bits), then s11 loses an estimate of its quotient that is short by at most 3 (as shoup_lazy4). nm = 2^64 - m, hidden from the compiler.
+__device__ __forceinline__ void dot30_settle(Dot30& d, u64 mu64, u64 nm) {
+  d.s01 += d.s00 >> 30;
+  d.s11 += (d.s01 >> 30) + (d.s10 >> 30);
+  d.s00 = (u32)d.s00 & 0x3FFFFFFFu;
+  d.s01 = (u32)d.s01 & 0x3FFFFFFFu;
+  d.s10 = (u32)d.s10 & 0x3FFFFFFFu;
+  const u32 x0 = (u32)d.s11, x1 = (u32)(d.s11 >> 32), p0 = (u32)mu64, p1 = (u32)(mu64 >> 32);
+  const u64 qt = (u64)x1 * p1 + __umulhi(x1, p0) + __umulhi(x0, p1);
+  const u32 q0 = (u32)qt, q1 = (u32)(qt >> 32), n0 = (u32)nm, n1 = (u32)(nm >> 32);
+  const u64 t = d.s11 + (u64)q0 * n0;
+  d.s11 = (u64)((u32)(t >> 32) + q0 * n1 + q1 * n0) << 32 | (u32)t;
+}
 __device__ __forceinline__ Acc128 dot30_value(const Dot30& d) {
   Acc128 v;
   u64 mid = d.s01 + d.s10;

@@ -1,0 +1,57 @@
+"""GPU parity of the diagonal matrix product's inner sums where they go through LDS (4 ciphertexts and 7 giant steps on):
+tiles of 8 polynomials x 12 or x 8 giant steps, short last tiles, folds of 5 and 11 terms, both arithmetic kinds; bit-exact."""
+import numpy as np
+import pytest
+
+from ckks_inputs import make_params, uniform_residues
+from oracle import ref
+
+pytestmark = pytest.mark.gpu
+
+FP, INT, SMALL = (12, 3, 50, 2, 50, 2), (12, 3, 60, 2, 60, 2), (12, 3, 40, 2, 50, 2)
+CASES = [
+    # shape, B, n1, n2
+    (FP, 4, 5, 12),      # one whole tile, one whole fold
+    (FP, 5, 6, 9),       # a last tile of one ciphertext, a tile of 12 three quarters full, one term past a fold
+    (FP, 4, 1, 7),       # one baby step: less than the copies in flight
+    (FP, 4, 2, 8),
+    (FP, 4, 11, 21),     # two tiles of 12 in one launch, the second short
+    (FP, 4, 3, 27),      # giant steps beyond what the workspace holds at once: 24, then 3
+    (SMALL, 7, 16, 10),
+    (INT, 4, 11, 12),
+    (INT, 5, 12, 9),
+    (INT, 4, 1, 7),
+    (INT, 4, 23, 8),
+    (INT, 9, 2, 20),     # tiles of 6 and one of 8
+]
+
+
+@pytest.mark.parametrize("largest", [False, True])
+@pytest.mark.parametrize("shape,B,n1,n2", CASES)
+def test_inner_sums_through_lds(shape, B, n1, n2, largest):
+    import torch
+    import paper_2604_03425_amd as gpu
+    from gpu_util import assert_same, to_dev, to_host
+    p = make_params(*shape)
+    rc, gc, nl = ref.RefContext(p), gpu.Context(p), len(p.q)
+    ct, pt = uniform_residues(1, p.q, (B, 2), p.N), uniform_residues(2, p.q, (n2, n1), p.N)
+    if largest:       # the residues that the range arguments are made for
+        top = np.array(p.q, dtype=np.uint64)[:, None] - np.uint64(1)
+        ct[:], pt[:] = top, top
+    baby = [uniform_residues(10 + i, p.moduli, (p.dnum, 2), p.N) for i in range(n1 - 1)]
+    giant = [uniform_residues(50 + i, p.moduli, (p.dnum, 2), p.N) for i in range(n2 - 1)]
+    ref.set_threads(8)
+    want = rc.pcmm_bsgs(ct, pt, n1, n2, 1, baby, giant)
+    ref.set_threads(1)
+    d_ct, d_pt = to_dev(ct), to_dev(pt)
+    args = (n1, n2, 1, [to_dev(k) for k in baby], [to_dev(k) for k in giant], gc.workspace(gpu.OP_PCMM_BSGS, B, nl, n1))
+    out = torch.empty_like(d_ct)
+    gpu.ckks_pcmm_bsgs(gc, out, d_ct, B, nl, d_pt, *args)
+    assert_same(to_host(out), want, "inner sums")
+    # rows that 16-byte copies cannot start at take the kernels without LDS: the same bits
+    shifted = torch.empty(d_pt.numel() + 1, dtype=torch.int64, device="cuda")[1:].view_as(d_pt)
+    shifted.copy_(d_pt)
+    out.zero_()
+    gpu.ckks_pcmm_bsgs(gc, out, d_ct, B, nl, shifted, *args)
+    assert_same(to_host(out), want, "inner sums, plaintexts on an odd word")
+    gc.close()
