@@ -116,6 +116,8 @@ struct LevelTables {
   ulonglong2* up_scale = nullptr;  // [nlimbs]  (Q_j/q_i)^-1 / N mod q_i
   ulonglong2* dn_scale = nullptr;  // [K]       2^64 (P/p_k)^-1 / N mod p_k
   u64* dn_mat_plain = nullptr;     // dn_mat without the Montgomery factor
+  u64 *up_conv = nullptr, *up_conv_off = nullptr;   // up_mat, up_off as conv_rows_kernel takes them: scaled by 2^60 where
+  u64 *dn_conv = nullptr, *dn_conv_off = nullptr;   // those are scaled by 2^90; the same for dn_mat_plain, dn_off
   u64* up_off = nullptr;           // [beta][next] -sum_i ((q_i-1)/2) (Q_j/q_i) mod m_t, scaled like up_mat
   double* up_matd = nullptr;       // [beta][next][up_pitch - 1] centred (Q_j/q_i) mod m_t on double-precision targets
   double* dn_matd = nullptr;       // [nlimbs][dn_pitch - 1] centred (P/p_k) mod q_i on double-precision targets
@@ -173,7 +175,7 @@ struct ckks_ctx {
   ModInfo* d_mods = nullptr;
   ulonglong2* d_tw_fwd = nullptr;
   ulonglong2* d_tw_inv = nullptr;
-  double* d_twfp_fwd = nullptr;  // N = 2^12 .. 2^16: the twiddles as doubles for moduli < 2^50
+  double* d_twfp_fwd = nullptr;  // N = 2^12 .. 2^16: the twiddles as doubles in [-q/2, q/2] for moduli < 2^50
   double* d_twfp_inv = nullptr;
   hipStream_t side = nullptr;       // second stream for the fork/join inside a key switch (default priority)
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -381,6 +383,16 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
       dn_scale[k] = ulonglong2{w, h_shoup(w, m)};
     }
   }
+  std::vector<u64> up_conv(up_mat), up_conv_off(up_off), dn_conv(dn_mat_plain), dn_conv_off(dn_off);
+  auto by_30_less = [&](std::vector<u64>& v, u32 per_target, u32 targets) {   // (target s: modulus ext_mod(s))
+    for (u32 s = 0; s < targets; s++) {
+      const u64 m = ext_mod(s), r = h_inv((1ull << 30) % m, m);
+      for (size_t at = (size_t)s * per_target; at < v.size(); at += (size_t)targets * per_target)
+        for (u32 k = 0; k < per_target; k++) v[at + k] = h_mul(v[at + k], r, m);
+    }
+  };
+  if (t.narrow_up) by_30_less(up_conv, R + 1, next), by_30_less(up_conv_off, 1, next);
+  if (t.narrow_dn) by_30_less(dn_conv, RK + 1, nlimbs), by_30_less(dn_conv_off, 1, nlimbs);
   std::vector<ulonglong2> rs_one(1), rs_qinv(nlimbs > 1 ? nlimbs - 1 : 0), rs_qinv16(rs_qinv.size());
   std::vector<u64> rs_mat(rs_qinv.size() * 5, 0);
   rs_one[0] = ulonglong2{1, 0};  // floor(1 * 2^64 / q) is filled per use below; with x < q the product x*1 needs no reduction
@@ -402,6 +414,10 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
   t.up_scale = arena.add(up_scale);
   t.dn_scale = arena.add(dn_scale);
   t.dn_mat_plain = arena.add(dn_mat_plain);
+  t.up_conv = arena.add(up_conv);
+  t.up_conv_off = arena.add(up_conv_off);
+  t.dn_conv = arena.add(dn_conv);
+  t.dn_conv_off = arena.add(dn_conv_off);
   t.up_off = arena.add(up_off);
   t.up_matd = arena.add(up_matd);
   t.dn_off = arena.add(dn_off);
@@ -435,6 +451,7 @@ int build_levels(ckks_ctx* c) {
     LevelTables& t = lv[nl];
     rebase(t.up_inv); rebase(t.up_mat); rebase(t.dn_inv); rebase(t.dn_mat); rebase(t.pinv);
     rebase(t.up_scale); rebase(t.dn_scale); rebase(t.dn_mat_plain); rebase(t.pinv2);
+    rebase(t.up_conv); rebase(t.up_conv_off); rebase(t.dn_conv); rebase(t.dn_conv_off);
     rebase(t.up_off); rebase(t.up_matd); rebase(t.dn_matd); rebase(t.dn_off);
     rebase(t.rs_one); rebase(t.rs_mat); rebase(t.rs_qinv); rebase(t.rs_qinv16);
   }
@@ -945,8 +962,8 @@ ConvJob conv_up_job(const ckks_ctx* c, const LevelTables* lt, const u64* dcoef, 
   a.skip_own = 1;
   a.ntarget = lt->next;
   a.pitch = lt->up_pitch;
-  a.mat = lt->up_mat;
-  a.off = lt->up_off;
+  a.mat = lt->up_conv;
+  a.off = lt->up_conv_off;
   a.matd = lt->up_matd;
   a.scale = lt->up_scale;
   job.npoly = B * lt->beta;
@@ -969,8 +986,8 @@ ConvJob conv_down_job(const ckks_ctx* c, const LevelTables* lt, const u64* acc, 
   a.skip_own = 0;
   a.ntarget = nlimbs;
   a.pitch = lt->dn_pitch;
-  a.mat = lt->dn_mat_plain;
-  a.off = lt->dn_off;
+  a.mat = lt->dn_conv;
+  a.off = lt->dn_conv_off;
   a.matd = lt->dn_matd;
   a.scale = lt->dn_scale;
   job.npoly = B * 2;
@@ -1720,6 +1737,7 @@ int ckks_ctx_create(ckks_ctx** out, uint32_t logN, const uint64_t* q, uint32_t n
     mi.qinv = 1.0 / (double)m;
     mi.ninvd = (double)mi.ninv;
     mi.ninvq = (double)mi.ninv / (double)m;
+    auto centred = [m](u64 v) { return v > m / 2 ? -(double)(m - v) : (double)v; };
     pw[0] = 1;
     for (u64 k = 1; k < N; k++) pw[k] = h_mul(pw[k - 1], c->psi[i], m);
     for (u32 k = 0; k < N; k++) {
@@ -1730,8 +1748,8 @@ int ckks_ctx_create(ckks_ctx** out, uint32_t logN, const uint64_t* q, uint32_t n
       u64 wi = e == 0 ? 1 : m - pw[N - e];
       inv[(size_t)i * N + k] = ulonglong2{wi, h_shoup(wi, m)};
       if (!fwdfp.empty() && (m >> 50) == 0) {
-        fwdfp[(size_t)i * N + k] = (double)w;
-        invfp[(size_t)i * N + k] = (double)wi;
+        fwdfp[(size_t)i * N + k] = centred(w);
+        invfp[(size_t)i * N + k] = centred(wi);
       }
     }
   }

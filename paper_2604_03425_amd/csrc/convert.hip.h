@@ -137,7 +137,8 @@ __device__ __forceinline__ void conv_twiddles_last(TW (&w)[2], const TW* __restr
 
 // ---- double precision: forward and inverse row passes ----
 // A forward pass gets its first rounds' twiddles (ConvTwiddles) from the caller, who requests them ahead of the conversion;
-// the later ones' are requested as the registers for them become free.
+// the later ones' are requested as the registers for them become free. In: |x| <= 1.5 q. Out: at most 2.64 q (three stages
+// from a reduced value), which the block passes take: one reduction, after four or five stages.
 template <class TW>
 struct ConvTwiddles {
   TW w0[3], w1[3];
@@ -157,10 +158,10 @@ __device__ __forceinline__ void conv_fwd_rows(double (&x)[4], const ConvTwiddles
   if (LOGR == 8) conv_twiddles(w3, tw, 3);
   if (LOGR & 1) conv_twiddles_last<LOGR>(wl, tw);
   radix4_fwd(x, w.w1, q, qinv);
-  reduce4(x, q, qinv);
+  if (LOGR < 8) reduce4(x, q, qinv);
   if (LOGR >= 6) {
     conv_exchange<7, 5>(x, sm);
-    radix4_fwd(x, w2, q, qinv);
+    radix4_fwd<LOGR == 8>(x, w2, q, qinv);
   }
   if (LOGR != 6) conv_exchange<(LOGR >= 6 ? 5 : 7), L>(x, sm);
   if (LOGR == 8) radix4_fwd(x, w3, q, qinv);
@@ -172,8 +173,8 @@ __device__ __forceinline__ void conv_fwd_rows(double (&x)[4], const ConvTwiddles
       x[2 * p] = x[2 * p] + T;
     }
   }
-  reduce4(x, q, qinv);
 }
+// In and out: |x| <= q/2; at most four stages between reductions.
 template <int LOGR>
 __device__ __forceinline__ void conv_inv_rows(double (&x)[4], const double* __restrict__ twi, double q, double qinv, double* sm) {
   constexpr int L = 11 - LOGR;
@@ -190,20 +191,16 @@ __device__ __forceinline__ void conv_inv_rows(double (&x)[4], const double* __re
       x[2 * p] = x[2 * p] + x[2 * p + 1];
       x[2 * p + 1] = fp_mulmod_var(D, wl[p], qinv, q);
     }
-    reduce4(x, q, qinv);
   }
-  if (LOGR == 8) {
-    radix4_inv(x, w3, q, qinv);
-    reduce4(x, q, qinv);
-  }
+  if (LOGR == 8) radix4_inv(x, w3, q, qinv);
   if (LOGR != 6) conv_exchange<L, (LOGR >= 6 ? 5 : 7)>(x, sm);
   if (LOGR >= 6) {
     radix4_inv(x, w2, q, qinv);
-    reduce4(x, q, qinv);
+    if (LOGR >= 7) reduce4(x, q, qinv);
     conv_exchange<5, 7>(x, sm);
   }
   radix4_inv(x, w1, q, qinv);
-  reduce4(x, q, qinv);
+  if (LOGR <= 6) reduce4(x, q, qinv);
   conv_exchange<7, 9>(x, sm);
   radix4_inv(x, w0, q, qinv);
   reduce4(x, q, qinv);
@@ -294,9 +291,9 @@ __device__ __forceinline__ void conv_mad(u64& acc, u32 y, u32 c) {
 // Double-precision sources (centred integers, |y| < 2^49) to a double-precision target with centred constants |c| < 2^49:
 // the products are summed exactly as H + L. H starts at 1.5 * 2^102, in whose binade adding a product rounds it to a
 // multiple of 2^50; what that adds to H is exact (both lie in the binade: at most 8 products of 2^98), and so is the rest of
-// the product, an integer of magnitude at most 2^49, which goes to L (at most 2^52). Then H - 1.5 * 2^102 = c q + r with the
-// quotient off by at most one. 4 FP64 instructions a term and 9 at the end, against 4 multiply-adds a term and 27 for the
-// sum of 30-bit pieces. Out: |x| <= q/2.
+// the product, an integer of magnitude at most 2^49, which goes to L (at most 2^52). Then H - 1.5 * 2^102 + L = c q + x with the
+// quotient off by at most 1.25, so that H - 1.5 * 2^102 - c q = x - L stays below 2^53. 4 FP64 instructions a term and 6 at the
+// end, against 4 multiply-adds a term and 19 for the sum of 30-bit pieces. Out: |x| <= 1.3 q.
 template <int MAXLEN>
 __device__ __forceinline__ void convert_fp(double (&x)[4], const ConvWord (&y)[MAXLEN][4], const ConvTarget<MAXLEN>& tg) {
   const double q = tg.qd, qinv = tg.qinv;
@@ -318,19 +315,20 @@ __device__ __forceinline__ void convert_fp(double (&x)[4], const ConvWord (&y)[M
 #pragma unroll
   for (int i = 0; i < 4; i++) {
     const double h = H[i] - M;
-    x[i] = fp_reduce(__builtin_fma(-__builtin_rint(h * qinv), q, h) + L[i], qinv, q);
+    x[i] = __builtin_fma(-__builtin_rint(__builtin_fma(L[i], qinv, h * qinv)), q, h) + L[i];
   }
 }
-// Split-form sources to any target, canonical.
+// Split-form sources to any target. NARROW: below 9m, plus `bias` (a multiple of m modulo 2^64); otherwise canonical.
 template <int MAXLEN, bool NARROW>
-__device__ __forceinline__ void convert_int(u64 (&x)[4], const ConvWord (&y)[MAXLEN][4], const ConvTarget<MAXLEN>& tg) {
+__device__ __forceinline__ void convert_int(u64 (&x)[4], const ConvWord (&y)[MAXLEN][4], const ConvTarget<MAXLEN>& tg, u64 bias) {
   Dot30N n[4];
   Dot30 g[4];
 #pragma unroll
   for (int i = 0; i < 4; i++) {
     n[i].a = g[i].s00 = (u32)tg.off & BCONV_M30;
     n[i].b = g[i].s01 = tg.off >> 30;
-    n[i].c = g[i].s10 = g[i].s11 = 0;
+    g[i].s10 = g[i].s11 = 0;
+    n[i].c = bias;
   }
 #pragma unroll
   for (int k = 0; k < MAXLEN; k++) {
@@ -345,7 +343,7 @@ __device__ __forceinline__ void convert_int(u64 (&x)[4], const ConvWord (&y)[MAX
   }
 #pragma unroll
   for (int i = 0; i < 4; i++) {   // one position at a time: folding all four side by side would spill
-    x[i] = csub(NARROW ? dot30n_redc90(n[i], tg.m, tg.minv) : redc(dot30_value(g[i]), tg.m, tg.minv), tg.m);
+    x[i] = NARROW ? dot30n_redc60(n[i], tg.m, tg.minv) : csub(redc(dot30_value(g[i]), tg.m, tg.minv), tg.m);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
@@ -413,12 +411,9 @@ __global__ void __launch_bounds__(CONV_THREADS) __attribute__((amdgpu_waves_per_
         for (int i = 0; i < 4; i++)
           x[i] = fp_mulmod_const(x[i], __longlong_as_double((long long)sc.x), __longlong_as_double((long long)sc.y), mi.qd);
       }
-      const double h = (mi.qd - 1.0) * 0.5;
+      // |x| <= q, and (q + 1) / 2 is 2^-51 or more away from q/2 in units of q: no rounding of x / q can pass one half
 #pragma unroll
-      for (int i = 0; i < 4; i++) {
-        const double v = x[i] > h ? x[i] - mi.qd : x[i];
-        y[k][i].set(v < -h ? v + mi.qd : v);
-      }
+      for (int i = 0; i < 4; i++) y[k][i].set(fp_reduce(x[i], mi.qinv, mi.qd));
     } else {
       u64 x[4];
 #pragma unroll
@@ -463,10 +458,10 @@ __global__ void __launch_bounds__(CONV_THREADS) __attribute__((amdgpu_waves_per_
     if (SRC_FP) {
       convert_fp<MAXLEN>(x, y, tg);
     } else {
-      u64 v[4];
-      convert_int<MAXLEN, NARROW>(v, y, tg);
+      u64 v[4];   // in [-4m, 5m), below 2^53 in magnitude, as an offset from 2^62
+      convert_int<MAXLEN, NARROW>(v, y, tg, (1ull << 62) - 4 * tg.m);
 #pragma unroll
-      for (int i = 0; i < 4; i++) x[i] = u2d(v[i]);
+      for (int i = 0; i < 4; i++) x[i] = NARROW ? fp_reduce(u2d_biased62(v[i]), tg.qinv, tg.qd) : u2d(v[i]);
     }
     conv_fwd_rows<LOGR>(x, w, tw, tg.qd, tg.qinv, (double*)sm);
     double* d = (double*)dst + ((size_t)tg.slot << LOGN) + pos;
@@ -493,7 +488,7 @@ __global__ void __launch_bounds__(CONV_THREADS) __attribute__((amdgpu_waves_per_
     w.load(tw);
     __builtin_amdgcn_sched_barrier(0);
     u64 x[4];
-    convert_int<MAXLEN, NARROW>(x, y, tg);
+    convert_int<MAXLEN, NARROW>(x, y, tg, 0);
     conv_fwd_rows<LOGR>(x, w, tw, tg.m, sm);
     u64* d = dst + ((size_t)tg.slot << LOGN) + pos;
 #pragma unroll

@@ -4,10 +4,13 @@
 // integer below 2^53. Same tiles, lane layouts and LDS transposes as the integer bodies.
 //
 // Twiddles are single doubles (the quotient estimate uses the rounded product and 1/q, so no companion constant
-// is stored). Ranges (in units of q): a multiply returns at most (0.5 + 0.375 |y|) q, so a radix-16 round of four
-// forward stages takes |x| <= 1 to |x| <= 7.0 < 8; values are brought back to |x| <= 0.5 after every round. Inverse rounds double the
-// sums, so they are brought back after every two stages. Between the two passes of a transform the data lives in
-// global memory as reduced doubles.
+// is stored) in [-q/2, q/2]. Ranges (in units of q): a multiply by one returns at most 0.5 + 0.1875 |y|, so a forward stage takes
+// A to 1.1875 A + 0.5: from 0.5 seven stages stay below 7.88 < 8, from 1 and from 1.5 six and five, from 2.64 (where three
+// stages from 0.5 end) four. A radix-16 round takes at most 2.64 and ends with bringing all values back to 0.5. An inverse stage
+// doubles the sums and leaves the differences at 0.5 + 0.1875 times theirs: from 0.5 four stages end at 8 (which is below
+// 2^53, q being below 2^50), from 1 they do if the two sums of eight values are brought back first; every round ends with all
+// values at 0.5. Between the two passes of a transform the data lives in global memory as doubles of at most 2.64 (forward,
+// from the conversions), 0.5 (otherwise).
 #pragma once
 #include "ntt16.hip.h"
 
@@ -49,15 +52,14 @@ __device__ __forceinline__ void radix16_inv_fp(double (&x)[16], double q, double
         Y = fp_mulmod_var(D, w, qinv, q);
       }
     }
-    if (s == 2 || s == 0) {
-#pragma unroll
-      for (int i = 0; i < 16; i++) x[i] = fp_reduce(x[i], qinv, q);
-    }
+    if (s == 1) x[0] = fp_reduce(x[0], qinv, q), x[8] = fp_reduce(x[8], qinv, q);
   }
+#pragma unroll
+  for (int i = 0; i < 16; i++) x[i] = fp_reduce(x[i], qinv, q);
 }
 
-// The first LG stages only, on 16 >> LG groups of 2^LG adjacent registers sharing the twiddles; reduced at the end
-// (forward) / after every two stages and at the end (inverse).
+// The first LG stages only, on 16 >> LG groups of 2^LG adjacent registers sharing the twiddles; reduced at the end. The
+// inverse takes |x| <= 0.5.
 template <int LG, class TW>
 __device__ __forceinline__ void radix_groups_fwd_fp(double (&x)[16], double q, double qinv, TW tw) {
 #pragma unroll
@@ -100,11 +102,9 @@ __device__ __forceinline__ void radix_groups_inv_fp(double (&x)[16], double q, d
           Y = fp_mulmod_var(D, w, qinv, q);
         }
     }
-    if (((LG - s) & 1) == 0 || s == 0) {
-#pragma unroll
-      for (int i = 0; i < 16; i++) x[i] = fp_reduce(x[i], qinv, q);
-    }
   }
+#pragma unroll
+  for (int i = 0; i < 16; i++) x[i] = fp_reduce(x[i], qinv, q);
 }
 
 // Forward, stages 0..LOGR-1. `x` holds integers of magnitude at most q (residues as doubles) in the first round's layout
@@ -140,7 +140,7 @@ __device__ __forceinline__ void ntt16_fwd_rows_fp(const u64* __restrict__ src, d
   ntt16_fwd_rows_fp_loaded<LOGR>(x, dst, tw, q, qinv, tile, sm);
 }
 
-// Forward, the last 8 stages of a limb of R blocks, on reduced doubles. Leaves x (|x| <= q/2) in the i-layout of ntt16_fwd_blocks.
+// Forward, the last 8 stages of a limb of R blocks, on doubles of at most 2.64 q. Leaves x (|x| <= q/2) in the i-layout of ntt16_fwd_blocks.
 // `x` must already hold the tile in the i-layout (lane (hb, j0) holds positions i*16 + j0 of block h).
 // `between` runs after the first round (its twiddles are dead by then), e.g. to request data the caller needs
 // after the transform.

@@ -5,10 +5,17 @@
 #pragma once
 #include "ntt16fp.hip.h"
 
-// Two forward stages: (0,2),(1,3) by w[0], then (0,1) by w[1] and (2,3) by w[2]. Ranges as for radix16_fwd(_fp).
+__device__ __forceinline__ void reduce4(double (&x)[4], double q, double qinv) {
+#pragma unroll
+  for (int i = 0; i < 4; i++) x[i] = fp_reduce(x[i], qinv, q);
+}
+// Two forward stages: (0,2),(1,3) by w[0], then (0,1) by w[1] and (2,3) by w[2]; reduced between them if BETWEEN. Ranges as
+// for radix16_fwd(_fp).
+template <bool BETWEEN = false>
 __device__ __forceinline__ void radix4_fwd(double (&x)[4], const double (&w)[3], double q, double qinv) {
 #pragma unroll
-  for (int s = 0; s < 2; s++)
+  for (int s = 0; s < 2; s++) {
+    if (BETWEEN && s == 1) reduce4(x, q, qinv);
 #pragma unroll
     for (int p = 0; p < 2; p++) {
       double& X = x[s == 0 ? p : 2 * p];
@@ -17,6 +24,7 @@ __device__ __forceinline__ void radix4_fwd(double (&x)[4], const double (&w)[3],
       Y = X - T;
       X = X + T;
     }
+  }
 }
 // Two inverse stages in the reverse order.
 __device__ __forceinline__ void radix4_inv(double (&x)[4], const double (&w)[3], double q, double qinv) {
@@ -47,10 +55,6 @@ __device__ __forceinline__ void radix4_inv(u64 (&x)[4], const ulonglong2 (&w)[3]
     for (int p = 0; p < 2; p++) bf_inv<BIG>(x[s == 0 ? p : 2 * p], x[s == 0 ? p + 2 : 2 * p + 1], s == 0 ? w[0] : w[1 + p], q, c);
     if (!BIG) c <<= 1;
   }
-}
-__device__ __forceinline__ void reduce4(double (&x)[4], double q, double qinv) {
-#pragma unroll
-  for (int i = 0; i < 4; i++) x[i] = fp_reduce(x[i], qinv, q);
 }
 
 // ---- a limb of 4096 values in 1024 lanes ----
@@ -97,17 +101,16 @@ struct WlTwiddles {
   }
 };
 
-// Round-0 layout, |x| <= q  ->  round-2 layout, |x| <= q/2.
+// Round-0 layout, |x| <= q  ->  round-2 layout, |x| <= q/2. Six stages between reductions.
 __device__ __forceinline__ void wl_fwd(double (&x)[4], const WlTwiddles<double>& w, double q, double qinv, double* sm) {
   radix4_fwd(x, w.w[0], q, qinv);
   wl_exchange<0, 1>(x, sm);
   radix4_fwd(x, w.w[1], q, qinv);
-  reduce4(x, q, qinv);
   wl_exchange<1, 2>(x, sm);
   radix4_fwd(x, w.w[2], q, qinv);
+  reduce4(x, q, qinv);
   wl_exchange<2, 3>(x, sm);
   radix4_fwd(x, w.w[3], q, qinv);
-  reduce4(x, q, qinv);
   wl_exchange<3, 4>(x, sm);
   radix4_fwd(x, w.w[4], q, qinv);
   wl_exchange<4, 5>(x, sm);
@@ -115,7 +118,7 @@ __device__ __forceinline__ void wl_fwd(double (&x)[4], const WlTwiddles<double>&
   reduce4(x, q, qinv);
   wl_exchange<5, 2>(x, sm);
 }
-// Round-2 layout, |x| <= q  ->  round-0 layout, times sc, in (-q, q).
+// Round-2 layout, |x| <= q  ->  round-0 layout, times sc, in (-q, q). Two stages to the first reduction, four between others.
 __device__ __forceinline__ void wl_inv(double (&x)[4], const WlTwiddles<double>& w, double q, double qinv, double sc, double scq,
                                        double* sm) {
   wl_exchange<2, 5>(x, sm);
@@ -123,13 +126,11 @@ __device__ __forceinline__ void wl_inv(double (&x)[4], const WlTwiddles<double>&
   reduce4(x, q, qinv);
   wl_exchange<5, 4>(x, sm);
   radix4_inv(x, w.w[4], q, qinv);
-  reduce4(x, q, qinv);
   wl_exchange<4, 3>(x, sm);
   radix4_inv(x, w.w[3], q, qinv);
   reduce4(x, q, qinv);
   wl_exchange<3, 2>(x, sm);
   radix4_inv(x, w.w[2], q, qinv);
-  reduce4(x, q, qinv);
   wl_exchange<2, 1>(x, sm);
   radix4_inv(x, w.w[1], q, qinv);
   reduce4(x, q, qinv);

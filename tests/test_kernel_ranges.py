@@ -125,3 +125,110 @@ def test_forward_ranges_with_every_other_stage_corrected():
         assert max(vals) < (12 * m if stage % 2 == 0 else 16 * m)
         # a Montgomery product with a canonical word takes the largest value to below 2m
         assert (16 * m - 1) * (m - 1) // (1 << 64) + m <= 2 * m
+
+
+# ---- double precision: every value an integer of magnitude at most 2^53 (in integers, rounding where the kernels round) ----
+def _fp_prime(bits):
+    q = (1 << bits) - 1
+    while q % 131072 != 1 or any(q % d == 0 for d in (3, 5, 7, 11, 13)):
+        q -= 2
+    return q
+
+
+def _fp_reduce(x, q):
+    r = x - round(float(x) * (1.0 / q)) * q      # round() of a float: half to even, as the instruction
+    assert abs(x) <= 1 << 53
+    return r
+
+
+def _fp_mulmod(a, w, q):
+    h = int(float(a * w))
+    c = round(float(h) * (1.0 / q))
+    assert abs(a) <= 1 << 53 and abs(h - c * q) <= 1 << 53 and abs(a * w - h) <= 1 << 53
+    return a * w - c * q
+
+
+def _fp_worst_stage(top, q, rng, inverse):
+    """The largest magnitude after one stage on values of at most `top`, tried at the ends of the range."""
+    best = 0
+    for _ in range(300):
+        X, Y = (rng.choice((-1, 1)) * (top - rng.choice((0, 1, rng.randrange(1 << 20)))) for _ in range(2))
+        w = rng.choice((-1, 1)) * (q // 2 - rng.choice((0, 1, rng.randrange(q // 2))))
+        if inverse:
+            assert abs(X - Y) <= 1 << 53
+            T = _fp_mulmod(X - Y, w, q)
+            out = (X + Y, T)
+        else:
+            T = _fp_mulmod(Y, w, q)
+            out = (X + T, X - T)
+        assert max(map(abs, out)) <= 1 << 53
+        best = max(best, *map(abs, out))
+    return best
+
+
+def test_double_precision_forward_ranges():
+    """1.1875 A + 0.5 a stage: seven stages from 0.5 q, six from q, five from 1.5 q, four from 2.64 q stay within 2^53."""
+    rng = random.Random(11)
+    for bits in (50, 45):
+        q = _fp_prime(bits)
+        for start, stages in ((0.5, 7), (1.0, 6), (1.5, 5), (2.64, 4)):
+            bound, top = start, int(start * q)
+            for _ in range(stages):
+                top, bound = min(_fp_worst_stage(top, q, rng, False), int((1.1875 * bound + 0.5) * q) + 2), 1.1875 * bound + 0.5
+                assert top <= bound * q + 2 and bound < 8
+        assert ((0.5 * 1.1875 + 0.5) * 1.1875 + 0.5) * 1.1875 + 0.5 < 2.64
+
+
+def test_double_precision_inverse_ranges():
+    """Four stages from 0.5 q end at 8 q < 2^53, their differences at 2 q; from q the round of four does so too if the two
+    sums of eight values are reduced before its last stage."""
+    rng = random.Random(12)
+    q = _fp_prime(50)
+    top = q // 2
+    for stage in range(4):
+        _fp_worst_stage(top, q, rng, True)
+        top *= 2
+    assert top <= 8 * q < 1 << 53
+    # bounds of the 16 values of a round, in units of q
+    x = [1.0] * 16
+    for half in (1, 2, 4, 8):
+        if half == 8:
+            x[0] = x[8] = 0.5
+        for g in range(0, 16, 2 * half):
+            for p in range(g, g + half):
+                s = x[p] + x[p + half]
+                assert s <= 8
+                x[p], x[p + half] = s, 0.5 + 0.1875 * s
+
+
+def test_centred_representative_by_rounding():
+    """x - rint(x / q) q is the centred representative for |x| <= q, up to its ends."""
+    for bits in (50, 49, 40):
+        q = _fp_prime(bits)
+        h = (q - 1) // 2
+        for x in (0, 1, h - 1, h, h + 1, h + 2, q - 1, q):
+            for v in (x, -x):
+                r = _fp_reduce(v, q)
+                assert (r - v) % q == 0 and abs(r) <= h
+
+
+def test_conversion_of_eight_double_precision_sources():
+    """H + L of eight products of 2^98, reduced with one rounded quotient: exact, at most 1.3 q."""
+    rng = random.Random(13)
+    for bits in (50, 40):
+        q, M = _fp_prime(bits), 3 << 101
+        for _ in range(200):
+            H, L, want = M, 0, 0
+            for _ in range(8):
+                y = rng.choice((-1, 1)) * ((1 << 49) - 1 - rng.choice((0, rng.randrange(1 << 48))))
+                c = rng.choice((1, 1, -1)) * (q // 2 - rng.choice((0, rng.randrange(q // 2))))
+                want += y * c
+                Hn = int(float(H + y * c))
+                L += y * c - (Hn - H)
+                H = Hn
+                assert abs(L) <= 1 << 53
+            h = H - M
+            t = round(float(L * (1.0 / q) + float(h) * (1.0 / q)))
+            assert abs(h - t * q) <= 1 << 53
+            x = h - t * q + L
+            assert (x - want) % q == 0 and abs(x) <= 1.3 * q
