@@ -205,7 +205,7 @@ __device__ __forceinline__ void conv_inv_rows(double (&x)[4], const double* __re
   radix4_inv(x, w0, q, qinv);
   reduce4(x, q, qinv);
 }
-// ---- integer classes, Harvey's ranges for every prime below 2^60: [0,16q) forward, [0,4q) inverse ----
+// ---- integer classes, Harvey's ranges for every prime below 2^60: [0,16q) forward, [0,8q) inverse ----
 template <int LOGR>
 __device__ __forceinline__ void conv_fwd_rows(u64 (&x)[4], const ConvTwiddles<ulonglong2>& w,
                                               const ulonglong2* __restrict__ tw, u64 q, u64* sm) {

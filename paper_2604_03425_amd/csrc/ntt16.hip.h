@@ -11,7 +11,7 @@
 // stage (< 65q < 2^59 after 16 stages from canonical input) and are reduced once at the end; inverse
 // butterflies let sums double for the 8 stages of a pass (inputs < 4q -> < 1024q). BIG primes (q < 2^60)
 // use Harvey's butterflies: 16q fits 64 bits, so forward values are kept in [0,16q) with a correction by 8q in every other stage
-// (the first of a round; below 12q after it, 16q after the next), inverse ones in [0,4q).
+// (the first of a round; below 12q after it, 16q after the next), inverse ones in [0,8q).
 #pragma once
 #include "modarith.hip.h"
 
@@ -38,15 +38,23 @@ __device__ __forceinline__ void bf_fwd(u64& X, u64& Y, ulonglong2 w, u64 q, u64 
   if (s & 1) bf_fwd<BIG, false>(X, Y, w, q, q2);
   else bf_fwd<BIG, true>(X, Y, w, q, q2);
 }
-// Inverse (Gentleman-Sande). BIG: c = 4q, inputs in [0,4q), outputs in [0,4q). SMALL: inputs < c (a multiple of q,
-// at least 4q), X' < 2c, Y' < 4q.
-template <bool BIG>
+// Inverse (Gentleman-Sande). BIG: c = 4q, inputs and outputs in [0,8q); PRODUCTS: both inputs are products of the stage
+// before, below 4q, whose sum needs no correction. SMALL: inputs < c (a multiple of q, at least 4q), X' < 2c, Y' < 4q.
+template <bool BIG, bool PRODUCTS = false>
 __device__ __forceinline__ void bf_inv(u64& X, u64& Y, ulonglong2 w, u64 q, u64 c) {
   u64 S = X + Y;
-  u64 D = X + c - Y;
-  if (BIG) S = csub_neg(S, c);  // c == 4q
+  u64 D = X + (BIG && !PRODUCTS ? 2 * c : c) - Y;
+  if (BIG && !PRODUCTS) S = csub_neg(S, 2 * c);
   X = S;
   Y = shoup_lazy4(D, w.x, w.y, q);
+}
+
+// Pair p of a stage whose pairs are `half` registers apart: of the stage before, half / 2 apart, it holds two sums or, every
+// other half / 2 of them, two products. Half the corrections of all but a round's first stage fall away.
+template <bool BIG>
+__device__ __forceinline__ void bf_inv_pair(u64& X, u64& Y, ulonglong2 w, u64 q, u64 c, int half, int p) {
+  if (p & (half >> 1)) bf_inv<BIG, true>(X, Y, w, q, c);
+  else bf_inv<BIG>(X, Y, w, q, c);
 }
 
 // Four forward stages on 16 registers: stage s pairs (a, a + (8>>s)); tw(s, g) is the twiddle of group g.
@@ -74,7 +82,7 @@ __device__ __forceinline__ void radix16_inv(u64 (&x)[16], u64 q, u64 c0, TW tw) 
     for (int g = 0; g < (1 << s); g++) {
       ulonglong2 w = tw(s, g);
 #pragma unroll
-      for (int p = 0; p < half; p++) bf_inv<BIG>(x[g * 2 * half + p], x[g * 2 * half + p + half], w, q, c);
+      for (int p = 0; p < half; p++) bf_inv_pair<BIG>(x[g * 2 * half + p], x[g * 2 * half + p + half], w, q, c, half, p);
     }
     if (!BIG) c <<= 1;
   }
@@ -107,7 +115,7 @@ __device__ __forceinline__ void radix16_inv_staged(u64 (&x)[16], u64 q, u64 c0, 
     for (int g = 0; g < (1 << s); g++) {
       ulonglong2 w = tw(s, g);
 #pragma unroll
-      for (int p = 0; p < half; p++) bf_inv<BIG>(x[g * 2 * half + p], x[g * 2 * half + p + half], w, q, c);
+      for (int p = 0; p < half; p++) bf_inv_pair<BIG>(x[g * 2 * half + p], x[g * 2 * half + p + half], w, q, c, half, p);
     }
     if (!BIG) c <<= 1;
     after(s);
@@ -142,7 +150,7 @@ __device__ __forceinline__ void radix_groups_inv(u64 (&x)[16], u64 q, u64 c0, TW
 #pragma unroll
       for (int k = 0; k < 16; k += 1 << LG)
 #pragma unroll
-        for (int p = 0; p < half; p++) bf_inv<BIG>(x[k + g * 2 * half + p], x[k + g * 2 * half + p + half], w, q, c);
+        for (int p = 0; p < half; p++) bf_inv_pair<BIG>(x[k + g * 2 * half + p], x[k + g * 2 * half + p + half], w, q, c, half, p);
     }
     if (!BIG) c <<= 1;
   }
@@ -410,7 +418,7 @@ __device__ __forceinline__ void ntt16_inv_blocks(u64 (&x)[16], const ulonglong2*
 }
 
 // Inverse, stages LOGR-1..0 on R rows x NC columns, then multiplication by the constant (sc, scs) (N^-1, possibly
-// merged with another per-limb constant) and canonical output. In: < 2q (BIG: < 4q). x receives the first round's layout
+// merged with another per-limb constant) and canonical output. In: < 2q (BIG: < 8q). x receives the first round's layout
 // of the row tile.
 template <bool BIG, int LOGR>
 __device__ __forceinline__ void ntt16_inv_rows(u64 (&x)[16], const u64* __restrict__ src, const ulonglong2* __restrict__ twi,

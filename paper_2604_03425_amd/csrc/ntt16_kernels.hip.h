@@ -507,7 +507,7 @@ __device__ __forceinline__ void fwd_inner_c_body_fp(const FwdInnerArgs& a, u32 b
     // (a pointer rebuilt from scalar halves has lost its address space: say "global", or the loads become flat
     // loads, which wait for the prefetch in case it lands where they read)
     const global_u64_ptr k = (global_u64_ptr)(evk + (size_t)jn * 2 * a.nm * N + lane_pos());
-    ntt16_fwd_blocks_fp_words(
+    ntt16_fwd_blocks_fp_words<false>(
         x, tw, q, qinv, tile, R, ex, twl,
         [&] {
           // always issued (the current tile again when nothing follows), so that the waits of the two rounds are
@@ -521,7 +521,8 @@ __device__ __forceinline__ void fwd_inner_c_body_fp(const FwdInnerArgs& a, u32 b
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < 16; i++) acc[i] += fp_mulmod_var(x[i], u2d(e[i]), qinv, q);
-    if ((++cnt & 3) == 0) {   // each product is below 0.75 q: fold before the sum can reach 2^53
+    // values of at most 3.64 q times key words below q: products of at most 1.87 q, four of them and a folded sum stay below 8 q
+    if ((++cnt & 3) == 0) {
 #pragma unroll
       for (int i = 0; i < 16; i++) acc[i] = fp_reduce(acc[i], qinv, q);
     }
@@ -534,7 +535,7 @@ __device__ __forceinline__ void fwd_inner_c_body_fp(const FwdInnerArgs& a, u32 b
     const u64* a2 = a.fin_add2 + (a2poly * a.nlimbs + t) * N;
     const u64* as = a.fin_add_src + ((size_t)bc * a.nlimbs + t) * N;
     take(x);
-    ntt16_fwd_blocks_fp_words(x, tw, q, qinv, tile, R, ex, twl, [] {}, [&] {
+    ntt16_fwd_blocks_fp_words<true>(x, tw, q, qinv, tile, R, ex, twl, [] {}, [&] {
       const u32 pos = lane_pos();
       if (mode & 1) {
 #pragma unroll

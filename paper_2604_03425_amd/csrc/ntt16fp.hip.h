@@ -14,7 +14,7 @@
 #pragma once
 #include "ntt16.hip.h"
 
-template <class TW>
+template <bool REDUCE = true, class TW>
 __device__ __forceinline__ void radix16_fwd_fp(double (&x)[16], double q, double qinv, TW tw) {
 #pragma unroll
   for (int s = 0; s < 4; s++) {
@@ -32,8 +32,10 @@ __device__ __forceinline__ void radix16_fwd_fp(double (&x)[16], double q, double
       }
     }
   }
+  if (REDUCE) {
 #pragma unroll
-  for (int i = 0; i < 16; i++) x[i] = fp_reduce(x[i], qinv, q);
+    for (int i = 0; i < 16; i++) x[i] = fp_reduce(x[i], qinv, q);
+  }
 }
 template <class TW>
 __device__ __forceinline__ void radix16_inv_fp(double (&x)[16], double q, double qinv, TW tw) {
@@ -216,7 +218,7 @@ __device__ __forceinline__ void ntt16_twl_store(double v, double* twl) {
   const u32 t = threadIdx.x, L = t & 63;
   if (L < 60) twl[((t >> 6) * 4 + L / 15) * NTT16_TWL_PITCH + L % 15] = v;
 }
-template <class LOADED, class BETWEEN>
+template <bool REDUCE, class LOADED, class BETWEEN>   // without REDUCE: out at most 3.64 q
 __device__ __forceinline__ void ntt16_fwd_blocks_fp_words(double (&x)[16], const double* __restrict__ tw, double q,
                                                           double qinv, u32 tile, u32 R, u32* ex, const double* twl, LOADED loaded,
                                                           BETWEEN between) {
@@ -238,7 +240,7 @@ __device__ __forceinline__ void ntt16_fwd_blocks_fp_words(double (&x)[16], const
   // element (i, j0) -> lane i0 = i holds (i0, j): written at i*17 + j0, read at i0*17 + j
   fp_transpose16_words(x, grp, 17, j0, 1, i0 * 17);
   between();
-  radix16_fwd_fp(x, q, qinv, [&](int s, int g) { return twb[(1 << s) - 1 + g]; });
+  radix16_fwd_fp<REDUCE>(x, q, qinv, [&](int s, int g) { return twb[(1 << s) - 1 + g]; });
   // and back: written at i0*17 + j, read at i*17 + j0
   fp_transpose16_words(x, grp, 1, i0 * 17, 17, j0);
 }

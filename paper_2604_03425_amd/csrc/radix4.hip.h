@@ -46,13 +46,16 @@ __device__ __forceinline__ void radix4_fwd(u64 (&x)[4], const ulonglong2 (&w)[3]
 #pragma unroll
     for (int p = 0; p < 2; p++) bf_fwd<BIG>(x[s == 0 ? p : 2 * p], x[s == 0 ? p + 2 : 2 * p + 1], s == 0 ? w[0] : w[1 + p], q, q2, s);
 }
-// c: bound of the inputs (BIG: 4q). SMALL: outputs below 4c.
+// c: bound of the inputs (BIG: 4q, inputs and outputs below 8q). SMALL: outputs below 4c.
 template <bool BIG>
 __device__ __forceinline__ void radix4_inv(u64 (&x)[4], const ulonglong2 (&w)[3], u64 q, u64 c) {
 #pragma unroll
   for (int s = 1; s >= 0; s--) {
 #pragma unroll
-    for (int p = 0; p < 2; p++) bf_inv<BIG>(x[s == 0 ? p : 2 * p], x[s == 0 ? p + 2 : 2 * p + 1], s == 0 ? w[0] : w[1 + p], q, c);
+    for (int p = 0; p < 2; p++) {
+      if (s == 0) bf_inv_pair<BIG>(x[p], x[p + 2], w[0], q, c, 2, p);
+      else bf_inv<BIG>(x[2 * p], x[2 * p + 1], w[1 + p], q, c);
+    }
     if (!BIG) c <<= 1;
   }
 }

@@ -232,3 +232,25 @@ def test_conversion_of_eight_double_precision_sources():
             assert abs(h - t * q) <= 1 << 53
             x = h - t * q + L
             assert (x - want) % q == 0 and abs(x) <= 1.3 * q
+
+
+def test_inverse_ranges_with_products_left_alone():
+    """60-bit primes: sums corrected by 8m stay below 8m; the sum of two products (below 4m) needs no correction."""
+    rng = random.Random(14)
+    m = top_prime_like(60)
+    for start in (8 * m - 1, m - 1):
+        x = [rng.choice((start, start - rng.randrange(start), 0)) for _ in range(16)]
+        for half in (1, 2, 4, 8):
+            for g in range(0, 16, 2 * half):
+                for p in range(half):
+                    X, Y, w = x[g + p], x[g + p + half], rng.randrange(m)
+                    products = bool(p & (half >> 1))
+                    assert max(X, Y) < (4 * m if products else 8 * m)
+                    S, D = X + Y, X + (4 if products else 8) * m - Y
+                    assert 0 < D <= M64 and S <= M64
+                    if not products and S >= 8 * m:
+                        S -= 8 * m
+                    T = approx_product(D, w, (w << 64) // m, m)
+                    assert S < 8 * m and T < 4 * m
+                    assert (S - X - Y) % m == 0 and (T - w * (X - Y)) % m == 0
+                    x[g + p], x[g + p + half] = S, T
