@@ -667,14 +667,10 @@ ntt16_fwd_blocks_inner8_kernel(FwdInnerArgs a) {
       const u64 eb[2] = {e0[v].x, e0[v].y}, ea[2] = {e1[v].x, e1[v].y};
 #pragma unroll
       for (int k = 0; k < 2; k++) {
-        const u64 xv = x[2 * v + k];
-        Acc128 p0, p1;
-        p0.lo = xv * eb[k];
-        p0.hi = mul_hi64(xv, eb[k]);
-        p1.lo = xv * ea[k];
-        p1.hi = mul_hi64(xv, ea[k]);
-        acc0[2 * v + k] = csub(acc0[2 * v + k] + redc(p0, q, mi.minv), q2);
-        acc1[2 * v + k] = csub(acc1[2 * v + k] + redc(p1, q, mi.minv), q2);
+        const u64 xv = BIG ? csub_neg(x[2 * v + k], 8 * q) : x[2 * v + k];   // below 2^63
+        acc0[2 * v + k] = csub_neg(acc0[2 * v + k] + mont_mul63(xv, eb[k], q, mi.minv), q2);
+        acc1[2 * v + k] = csub_neg(acc1[2 * v + k] + mont_mul63(xv, ea[k], q, mi.minv), q2);
+        __builtin_amdgcn_sched_barrier(0);   // more products side by side spill
       }
     }
   };
@@ -1378,8 +1374,7 @@ struct IntSum<false> {
   u64 s;   // below 2q
   __device__ __forceinline__ void init(u64 v) { s = v; }
   __device__ __forceinline__ void mac(u64 x, u64 e, const ModInfo& mi) {
-    const Acc128 p = {x * e, mul_hi64(x, e)};
-    s = csub(s + redc(p, mi.m, mi.minv), 2 * mi.m);
+    s = csub(s + mont_mul63(x, e, mi.m, mi.minv), 2 * mi.m);
   }
   __device__ __forceinline__ void fold(bool, const ModInfo&) {}
   __device__ __forceinline__ u64 value(const ModInfo& mi) const { return csub(s, mi.m); }

@@ -254,3 +254,33 @@ def test_inverse_ranges_with_products_left_alone():
                     assert S < 8 * m and T < 4 * m
                     assert (S - X - Y) % m == 0 and (T - w * (X - Y)) % m == 0
                     x[g + p], x[g + p + half] = S, T
+
+
+def test_montgomery_product_by_words():
+    """x < 2^63, e and m below 2^60: two 32-bit Montgomery words whose middle sum, with both carries, fits 64 bits."""
+    rng = random.Random(15)
+    M32 = (1 << 32) - 1
+    for bits in (60, 53, 50):
+        m = top_prime_like(bits)
+        mi = -pow(m, -1, 1 << 32) & M32
+        m0, m1 = m & M32, m >> 32
+        for _ in range(3000):
+            x = rng.choice(((1 << 63) - 1, min(8 * m, 1 << 63) - 1, rng.getrandbits(63)))
+            e = rng.choice((m - 1, rng.randrange(m)))
+            x0, x1, e0, e1 = x & M32, x >> 32, e & M32, e >> 32
+            p = x0 * e0
+            mid = x0 * e1 + (x1 * e0 + (p >> 32))
+            assert mid <= M64
+            u0 = (p & M32) * mi & M32
+            v0 = u0 * m0 + (p & M32)
+            assert v0 <= M64 and v0 & M32 == 0
+            mid = u0 * m1 + mid + (v0 >> 32)
+            assert mid <= M64
+            u1 = (mid & M32) * mi & M32
+            v1 = u1 * m0 + (mid & M32)
+            r = x1 * e1 + (u1 * m1 + (mid >> 32)) + (v1 >> 32)
+            assert v1 <= M64 and v1 & M32 == 0 and r <= M64
+            assert (r * (1 << 64) - x * e) % m == 0
+            assert r <= x * e // (1 << 64) + m
+            if x < 8 * m:
+                assert r < 2 * m
