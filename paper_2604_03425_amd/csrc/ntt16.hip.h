@@ -232,7 +232,7 @@ __device__ __forceinline__ void ntt16_fwd_rows(const u64* __restrict__ src, u64*
   ntt16_fwd_rows_loaded<BIG, LOGR>(x, dst, tw, q, tile, sm);
 }
 
-// Forward, the last 8 stages of a limb of R blocks, then canonical (CANON) or < 2q. `x` is left holding, for lane (hb = t>>4, j0 = t&15), the 16 values at
+// Forward, the last 8 stages of a limb of R blocks, then canonical (CANON) or lazy (BIG: < 8q, SMALL: < 67q). `x` is left holding, for lane (hb = t>>4, j0 = t&15), the 16 values at
 // block h = tile*16 + hb, positions i*16 + j0 (i = 0..15), ready for a coalesced store or a fused epilogue.
 template <bool BIG, bool CANON = true>
 __device__ __forceinline__ void ntt16_fwd_blocks_loaded(u64 (&x)[16], const ulonglong2* __restrict__ tw, u64 q, u64 mu,
@@ -263,8 +263,8 @@ __device__ __forceinline__ void ntt16_fwd_blocks_loaded(u64 (&x)[16], const ulon
   radix16_fwd<BIG>(x, q, q2, [&](int s, int g) { return twb[NTT16_TW_INDEX(s, g)]; });
 #pragma unroll
   for (int j = 0; j < 16; j++) {
-    const u64 v = fwd_settle<BIG>(x[j], mu, q);
-    x[j] = CANON ? csub(v, q) : v;
+    if (CANON) x[j] = csub(fwd_settle<BIG>(x[j], mu, q), q);
+    else if (BIG) x[j] = csub_neg(x[j], 8 * q);
   }
   wave_lds_sync();
 #pragma unroll

@@ -779,7 +779,7 @@ template <bool BIG>
 __device__ __forceinline__ void fwd_final_body(const FwdFinalArgs& a, u32 bc, u32 tile, u32 i_limb, const ModInfo& mi, u64* sm) {
   const u32 tid = threadIdx.x, j0 = tid & 15, h = tile * 16 + (tid >> 4);
   const size_t N = (size_t)1 << a.logN;
-  const u64 q = mi.m, q2 = 2 * mi.m;
+  const u64 q = mi.m, above = BIG ? 8 * q : 128 * q;   // a multiple of q above what the transform leaves
   u64 x[16];
   ntt16_fwd_blocks<BIG, false>(x, a.tq + ((size_t)bc * a.nlimbs + i_limb) * N, a.tw + (size_t)i_limb * N, q, mi.mu64, tile,
                                1u << (a.logN - 8), sm);
@@ -792,7 +792,7 @@ __device__ __forceinline__ void fwd_final_body(const FwdFinalArgs& a, u32 bc, u3
   const u32 g = a.multi ? a.galois_pc[__builtin_amdgcn_readfirstlane(bc >> 1)] : a.galois;
 #pragma unroll
   for (int i = 0; i < 16; i++) {
-    u64 r = shoup(ac[i * 16] + q2 - x[i], pv.x, pv.y, q);
+    u64 r = shoup(ac[i * 16] + above - x[i], pv.x, pv.y, q);
     if (mode & 1) r = addmod(r, a2[i * 16], q);
     if (mode & 2) r = addmod(r, as[galois_src_index(h * 256 + i * 16 + j0, g, a.logN)], q);
     o[i * 16] = r;
