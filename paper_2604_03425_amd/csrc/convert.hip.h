@@ -18,9 +18,11 @@
 // for odd LOGR only the second of its two stages is left to do.
 //
 // What bounds it: instruction issue (0.66 of the vector peak by executed instructions; 2.2 TB/s). Per target and position the conversion
-// of 8 double-precision sources costs 41 FP64 instructions (see convert_fp), its row pass about 45; an integer target about
+// of 8 double-precision sources costs 38 FP64 instructions (see convert_fp), its row pass 35; an integer target about
 // twice that. N = 2^16, 64 ciphertexts of 24 limbs, 3 digits of 8, 8 special primes: inverse row pass, ModUp and row passes as
-// four kernels 2030 us, here 1600; the same for ModDown's three 1440 and 1120. One such ciphertext: 62 -> 50 and 49 -> 43 us.
+// four kernels 2030 us, here 1476 (1551 with canonical results of the integer sums, 9 instructions at the end of a
+// double-precision one and two reductions a row pass); the same for ModDown's three 1440 and 1090 (1148). One such ciphertext: 62 ->
+// 46 and 49 -> 34 us.
 #pragma once
 #include "radix4.hip.h"
 #include "ntt16_kernels.hip.h"

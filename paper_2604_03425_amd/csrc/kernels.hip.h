@@ -640,7 +640,7 @@ __global__ void __launch_bounds__(256) pmacc_int_kernel(PmaccArgs a) {
 // one row of 64 per polynomial and giant step, are copied into LDS once for all of them, PMACC_SLOTS - 1 baby steps ahead and
 // without passing through registers. One barrier a baby step: a wave that passes it has read the step before, whose slot is
 // then free for the next copy, and its own share of this step's rows has landed. 16 polynomials x 12 giant steps x 64 baby
-// steps at 2^16: 24 50-bit limbs 6840 -> 6400 us, 8 60-bit limbs 3180 -> 2350. What bounds them: neither side alone (8 50-bit
+// steps at 2^16: 24 50-bit limbs 6840 -> 6320 us, 8 60-bit limbs 3180 -> 2220. What bounds them: neither side alone (8 50-bit
 // limbs: the copies without the sums 1770 us, the sums without the copies 1820, both 2050).
 #define PMACC_SLOTS 3
 template <int P, int NG, int WP, int WG>

@@ -1100,6 +1100,8 @@ __global__ void __launch_bounds__(256) inner16_rot_fp_kernel(FwdInnerArgs a, u32
 
 // The same for integer-class moduli: products go through a Montgomery reduction (factor 2^-64, as in the
 // one-rotation kernel), P * c0 likewise.
+// The products are summed as 128-bit values: as 30-bit partial products, with a fifth fewer instructions, 8 ciphertexts of 8
+// limbs and 63 rotations took 2020 us, here 1650.
 template <int MAXB>
 __global__ void __launch_bounds__(256) inner16_rot_int_kernel(FwdInnerArgs a, u32 B) {
   constexpr int CB = INNER16_ROT_CB;

@@ -1,7 +1,7 @@
 """Range arguments of the integer butterflies, replayed with Python integers (no GPU).
 
 The HIP kernels keep lazy values in 64-bit words: the twiddle product estimates its quotient from three of the four
-32 x 32 partial products (result below 4q), 60-bit primes use Harvey-style butterflies on [0,8q) / [0,4q), primes below
+32 x 32 partial products (result below 4q), 60-bit primes use Harvey-style butterflies on [0,16q) / [0,8q), primes below
 2^52 never correct on the way forward and let sums double on the way back. These tests follow the same recurrences at
 the largest moduli each form accepts and check that nothing reaches 2^64 and that every value stays congruent to the
 exact product. They model the arithmetic statement, not the kernels' code: bit-exactness of the kernels themselves is
