@@ -37,7 +37,7 @@ OPS_BUTTERFLY, OPS_MAC, OPS_REDUCE, OPS_SHOUP, OPS_ADD = 24, 8, 16, 14, 4
 OPS_BUTTERFLY_FP, OPS_MULRED_FP, OPS_SHOUP_FP = 9.5, 7, 6
 # Base-conversion dot product on 30-bit operand halves: 4 multiply-adds per term, and per output a base-2^30
 # Montgomery reduction of the three sums (22) plus the final correction (5).
-OPS_DOT30, OPS_REDUCE90 = 4, 27
+OPS_DOT30, OPS_REDUCE90, OPS_REDUCE60, OPS_PAIR_FP = 4, 27, 12, 4 + 6 / 5
 
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "keyswitch_micro_traffic.json")
@@ -98,13 +98,14 @@ def keyswitch_model(p, B, nl, hrot, hmult, fp_inner=2, bconv=0):
     fp_t, int_t = [t for t in range(nxt) if fp[t]], [t for t in range(nxt) if not fp[t]]
     dn_fp, dn_int = 2 * own_fp, 2 * own_int     # ModDown targets per ciphertext
     if bconv == 0:
-        # inverse row pass of the sources, conversion (4 FP64 instructions per term and 9 per output between
-        # double-precision limbs, else 4 multiply-adds per term and 27), row pass of the targets; sources read and targets
-        # written once
-        new_ops = sum(sum(len(dg) * OPS_DOT30 + (9 if fp[t] and all(fp[i] for i in dg) else OPS_REDUCE90)
+        # inverse row pass of the sources, conversion (4 FP64 instructions per term and 6 per output between
+        # double-precision limbs, else 4 multiply-adds per term and 12, or 19 to a double-precision target), row pass of the
+        # targets; sources read and targets written once
+        from_int = lambda t: OPS_REDUCE60 + (7 if fp[t] else 0)
+        new_ops = sum(sum(len(dg) * OPS_DOT30 + (6 if fp[t] and all(fp[i] for i in dg) else from_int(t))
                           for t in range(nxt) if t not in dg) for dg in digits)
         put("conv_rows_kernel", None, (B * (nl + new_limbs) + 2 * B * (K + nl)) * limb,
-            inv_rows_ops + B * N * (new_ops + 2 * nl * (K * OPS_DOT30 + OPS_REDUCE90)) +
+            inv_rows_ops + B * N * (new_ops + 2 * sum(K * OPS_DOT30 + from_int(t) for t in range(nl))) +
             B * ((new_fp + dn_fp) * bf_pass_fp + (new_int + dn_int) * bf_pass))
     elif bconv == 2:
         # base conversion, as executed: 4 multiply-adds per term on 30-bit halves + a 27-instruction reduction per output
@@ -350,14 +351,14 @@ def other_workloads(args):
                 del wsc
             checked = "ciphertext %d of the plain and the hoisted call equals the oracle's BSGS (%.0f s on %d threads)" % (b1, t_or, threads)
         rots = Bc * (n1 - 1 + n2 - 1)
-        # inner sums on the double-precision limbs: 7 FP64 instructions per multiply-add (exact product in two
-        # parts, quotient, remainder, accumulate), against the chip's FP64 vector issue rate
+        # inner sums on the double-precision limbs: 4 FP64 instructions per multiply-add (the product added to an exact
+        # pair of sums) and 6 every fifth, against the chip's FP64 vector issue rate
         nfp = sum(1 for m in p.q if m < (1 << 50))
         macs = Bc * 2 * nfp * N * n1 * n2
         pm_ms = prof.get("pmacc_fp_kernel", 0.0)
         pm_roof = None
         if pm_ms:
-            tops = macs * OPS_MULRED_FP / (pm_ms * 1e-3) / 1e12
+            tops = macs * OPS_PAIR_FP / (pm_ms * 1e-3) / 1e12
             pm_roof = {"bound": "alu", "kernel": "pmacc_fp_kernel", "achieved": round(tops, 2), "peak": round(PEAK_ALU_TOPS, 1),
                        "unit": "T lane-instructions/s", "frac": round(tops / PEAK_ALU_TOPS, 3)}
         print(json.dumps({"workload": "pcmm_ffn_share", "gpu_matches_oracle_on_sample": checked, "inner_sum_roofline": pm_roof, "ciphertexts_per_call": Bc, "seconds_per_call": round(dt, 4),

@@ -17,7 +17,7 @@
 // only the first LOGR stages are done. The last round has s = 11 - LOGR, a lane then holds four adjacent rows of a column;
 // for odd LOGR only the second of its two stages is left to do.
 //
-// What bounds it: instruction issue (0.66 of the vector peak by executed instructions; 2.2 TB/s). Per target and position the conversion
+// What bounds it: instruction issue (0.62 of the vector peak by executed instructions at 2.3 TB/s). Per target and position the conversion
 // of 8 double-precision sources costs 38 FP64 instructions (see convert_fp), its row pass 35; an integer target about
 // twice that. N = 2^16, 64 ciphertexts of 24 limbs, 3 digits of 8, 8 special primes: inverse row pass, ModUp and row passes as
 // four kernels 2030 us, here 1476 (1551 with canonical results of the integer sums, 9 instructions at the end of a
