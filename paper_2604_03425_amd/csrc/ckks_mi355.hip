@@ -386,7 +386,10 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
   std::vector<u64> up_conv(up_mat), up_conv_off(up_off), dn_conv(dn_mat_plain), dn_conv_off(dn_off);
   auto by_30_less = [&](std::vector<u64>& v, u32 per_target, u32 targets) {   // (target s: modulus ext_mod(s))
     for (u32 s = 0; s < targets; s++) {
-      const u64 m = ext_mod(s), r = h_inv((1ull << 30) % m, m);
+      const u64 m = ext_mod(s);
+      u64 inv = 1;   // m^-1 modulo 2^64; then 2^-30 mod m = (1 + m k) / 2^30 with k = -m^-1 mod 2^30
+      for (int it = 0; it < 6; it++) inv *= 2 - m * inv;
+      const u64 r = (u64)((1 + (u128)m * ((0 - inv) & 0x3FFFFFFFull)) >> 30);
       for (size_t at = (size_t)s * per_target; at < v.size(); at += (size_t)targets * per_target)
         for (u32 k = 0; k < per_target; k++) v[at + k] = h_mul(v[at + k], r, m);
     }
