@@ -148,34 +148,31 @@ def _fp_mulmod(a, w, q):
     return a * w - c * q
 
 
-def _fp_worst_stage(top, q, rng, inverse):
-    """The largest magnitude after one stage on values of at most `top`, tried at the ends of the range."""
-    best = 0
-    for _ in range(300):
-        X, Y = (rng.choice((-1, 1)) * (top - rng.choice((0, 1, rng.randrange(1 << 20)))) for _ in range(2))
+def _fp_stage(top_x, top_y, q, rng, inverse, trials=300):
+    """One stage on values up to top_x, top_y (integers) in magnitude, tried at the ends of both ranges: no value passes 2^53
+    and each product is within 0.5 + 0.1875 |factor| / q of zero, in units of q."""
+    for _ in range(trials):
+        X, Y = (rng.choice((-1, 1)) * (t - rng.choice((0, 1, rng.randrange(1 << 20)))) for t in (top_x, top_y))
         w = rng.choice((-1, 1)) * (q // 2 - rng.choice((0, 1, rng.randrange(q // 2))))
-        if inverse:
-            assert abs(X - Y) <= 1 << 53
-            T = _fp_mulmod(X - Y, w, q)
-            out = (X + Y, T)
-        else:
-            T = _fp_mulmod(Y, w, q)
-            out = (X + T, X - T)
-        assert max(map(abs, out)) <= 1 << 53
-        best = max(best, *map(abs, out))
-    return best
+        factor = X - Y if inverse else Y
+        T = _fp_mulmod(factor, w, q)
+        assert abs(T) <= (0.5 + 0.1875 * abs(factor) / q) * q + 2
+        for out in (X + Y, T) if inverse else (X + T, X - T):
+            assert abs(out) <= 1 << 53
 
 
 def test_double_precision_forward_ranges():
-    """1.1875 A + 0.5 a stage: seven stages from 0.5 q, six from q, five from 1.5 q, four from 2.64 q stay within 2^53."""
+    """1.1875 A + 0.5 a stage: seven stages from 0.5 q, six from q, five from 1.5 q, four from 2.64 q stay within 2^53. Each
+    stage is entered with the bound itself, whatever the sampled values of the one before reached."""
     rng = random.Random(11)
     for bits in (50, 45):
         q = _fp_prime(bits)
         for start, stages in ((0.5, 7), (1.0, 6), (1.5, 5), (2.64, 4)):
-            bound, top = start, int(start * q)
+            bound = start
             for _ in range(stages):
-                top, bound = min(_fp_worst_stage(top, q, rng, False), int((1.1875 * bound + 0.5) * q) + 2), 1.1875 * bound + 0.5
-                assert top <= bound * q + 2 and bound < 8
+                _fp_stage(int(bound * q), int(bound * q), q, rng, False)
+                bound = 1.1875 * bound + 0.5
+                assert bound < 8
         assert ((0.5 * 1.1875 + 0.5) * 1.1875 + 0.5) * 1.1875 + 0.5 < 2.64
 
 
@@ -184,20 +181,22 @@ def test_double_precision_inverse_ranges():
     sums of eight values are reduced before its last stage."""
     rng = random.Random(12)
     q = _fp_prime(50)
-    top = q // 2
-    for stage in range(4):
-        _fp_worst_stage(top, q, rng, True)
-        top *= 2
-    assert top <= 8 * q < 1 << 53
-    # bounds of the 16 values of a round, in units of q
+    for bound in (0.5, 1.0, 2.0, 4.0):
+        assert 2 * bound * q <= 1 << 53 and 0.5 + 0.1875 * 2 * bound <= 2
+        _fp_stage(int(bound * q), int(bound * q), q, rng, True)
+    # the 16 values of a round from q, bounds in units of q
     x = [1.0] * 16
     for half in (1, 2, 4, 8):
         if half == 8:
-            x[0] = x[8] = 0.5
+            assert x[0] == x[8] == 8
+            for at in (0, 8):
+                assert abs(_fp_reduce(int(x[at] * q), q)) <= q // 2 + 1
+                x[at] = 0.5
         for g in range(0, 16, 2 * half):
             for p in range(g, g + half):
                 s = x[p] + x[p + half]
                 assert s <= 8
+                _fp_stage(int(x[p] * q), int(x[p + half] * q), q, rng, True, 30)
                 x[p], x[p + half] = s, 0.5 + 0.1875 * s
 
 
