@@ -39,23 +39,24 @@ def test_approximate_product_is_below_4m_and_congruent():
 
 
 def _stage(values, m, corrected, rng, forward):
-    """One butterfly stage on a list of (value, bound) pairs; returns the new pairs and checks the 64-bit words."""
+    """One butterfly stage on a list of (value, bound) pairs; returns the new pairs and checks the 64-bit words. Corrected:
+    by 8m, a 60-bit prime's forward stage of an even number or inverse stage."""
     out = []
-    q4 = 4 * m
+    q4, q8 = 4 * m, 8 * m
     for k in range(0, len(values), 2):
         (X, bx), (Y, by) = values[k], values[k + 1]
         w = rng.randrange(m)
         ws = (w << 64) // m
         if forward:
             if corrected:
-                assert bx <= 8 * m
-                X = X - q4 if X >= q4 else X
-                bx = q4
+                assert max(bx, by) <= 16 * m
+                X = X - q8 if X >= q8 else X
+                bx = q8
             T = approx_product(Y, w, ws, m)
             assert X + q4 <= M64
             out += [(X + T, bx + q4), (X + q4 - T, bx + q4)]
         else:
-            c = q4 if corrected else max(bx, by)
+            c = q8 if corrected else max(bx, by)
             assert c % m == 0 and by <= c
             S, D = X + Y, X + c - Y
             assert S <= M64 and D <= M64
@@ -74,22 +75,22 @@ def test_forward_ranges():
     for bits, corrected, stages in ((60, True, 16), (52, False, 16), (52, False, 17)):
         m = top_prime_like(bits)
         vals = [(m - 1, m)] * 32          # canonical inputs at the maximum
-        for _ in range(stages):
+        for stage in range(stages):
             rng.shuffle(vals)
-            vals = _stage(vals, m, corrected, rng, True)
+            vals = _stage(vals, m, corrected and stage % 2 == 0, rng, True)
         bound = max(b for _, b in vals)
-        assert bound <= (8 * m if corrected else (1 + 4 * stages) * m)
+        assert bound <= (16 * m if corrected else (1 + 4 * stages) * m)
 
 
 def test_inverse_ranges():
     rng = random.Random(6)
-    # 60-bit primes: inputs below 4q stay below 4q through any number of stages
+    # 60-bit primes: inputs below 8q stay below 8q through any number of stages
     m = top_prime_like(60)
-    vals = [(4 * m - 1, 4 * m)] * 32
+    vals = [(8 * m - 1, 8 * m)] * 32
     for _ in range(16):
         rng.shuffle(vals)
         vals = _stage(vals, m, True, rng, False)
-    assert max(b for _, b in vals) <= 4 * m
+    assert max(b for _, b in vals) <= 8 * m
     # primes below 2^52: sums double for the 8 stages of a pass, from inputs below 4q
     m = top_prime_like(52)
     vals = [(4 * m - 1, 4 * m)] * 32
