@@ -298,6 +298,7 @@ __device__ __forceinline__ void conv_mad(u64& acc, u32 y, u32 c) {
 // end, against 4 multiply-adds a term and 19 for the sum of 30-bit pieces. Out: |x| <= 1.3 q.
 template <int MAXLEN>
 __device__ __forceinline__ void convert_fp(double (&x)[4], const ConvWord (&y)[MAXLEN][4], const ConvTarget<MAXLEN>& tg) {
+  static_assert(MAXLEN <= 8, "more products leave the binade of H");
   const double q = tg.qd, qinv = tg.qinv;
   constexpr double M = 1.5 * 5070602400912917605986812821504.0;   // 1.5 * 2^102
   double H[4], L[4];
@@ -323,6 +324,7 @@ __device__ __forceinline__ void convert_fp(double (&x)[4], const ConvWord (&y)[M
 // Split-form sources to any target. NARROW: below 9m, plus `bias` (a multiple of m modulo 2^64); otherwise canonical.
 template <int MAXLEN, bool NARROW>
 __device__ __forceinline__ void convert_int(u64 (&x)[4], const ConvWord (&y)[MAXLEN][4], const ConvTarget<MAXLEN>& tg, u64 bias) {
+  static_assert(MAXLEN <= 8, "the transforms that follow take values below 9m");
   Dot30N n[4];
   Dot30 g[4];
 #pragma unroll

@@ -8,6 +8,7 @@ exact product. They model the arithmetic statement, not the kernels' code: bit-e
 what the GPU parity tests check.
 """
 import random
+from fractions import Fraction
 
 M64 = (1 << 64) - 1
 
@@ -284,3 +285,166 @@ def test_montgomery_product_by_words():
             assert r <= x * e // (1 << 64) + m
             if x < 8 * m:
                 assert r < 2 * m
+
+
+def _narrow_ok(n, bs, bt, bt_min):
+    """The host's rule for three sums of 30-bit partial products: n sources below 2^bs, targets below 2^bt, at least 2^(bt_min - 1)."""
+    if bs > 60 or bt > 60 or bt_min < 36:
+        return False
+    w, y1, c1 = (1 << 30) - 1, 1 << max(0, bs - 30), 1 << max(0, bt - 30)
+    amax = n * w * w + n * w + w * w
+    bmax = n * (w * c1 + y1 * w) + n * c1 + (1 << 34) + w * c1 + w * w
+    cmax = n * y1 * c1 + (1 << 34) + w * c1 + w * w
+    return max(amax, bmax, cmax) < 1 << 64
+
+
+def _odd_below(bits):
+    return (1 << bits) - 59
+
+
+def _redc60(sums, m):
+    """Two words of the base-2^30 Montgomery reduction of a + b 2^30 + c 2^60; no word may pass 2^64."""
+    M30 = (1 << 30) - 1
+    a, b, c = sums
+    q0, q1, qi = m & M30, m >> 30, -pow(m, -1, 1 << 30) & M30
+    u = (a & M30) * qi & M30
+    a += u * q0
+    assert a <= M64 and a & M30 == 0
+    b += (a >> 30) + u * q1
+    assert b <= M64
+    u = (b & M30) * qi & M30
+    b += u * q0
+    assert b <= M64 and b & M30 == 0
+    c += (b >> 30) + u * q1
+    assert c <= M64
+    return c
+
+
+def test_conversion_of_split_sources():
+    """At most 8 sources: V / 2^60 modulo m below V / 2^60 + m <= 9m. To a double-precision target the result goes through
+    an offset, 2^62 - 4m in the top sum: what is left of it after subtracting 2^62 is exact in doubles and below 2^53."""
+    rng = random.Random(16)
+    M30, tried = (1 << 30) - 1, 0
+    for bs in (60, 55, 51, 50, 36, 30):
+        for bt in (60, 52, 50, 45, 36):
+            for n in range(1, 9):
+                if not _narrow_ok(n, bs, bt, bt):
+                    continue
+                tried += 1
+                m = _odd_below(bt)
+                for trial in range(20):
+                    worst = trial % 2 == 0
+                    ys = [(1 << bs) - 1 if worst else rng.getrandbits(bs) for _ in range(n)]
+                    cs = [m - 1 if worst else rng.randrange(m) for _ in range(n)]
+                    off = m - 1 if worst else rng.randrange(m)
+                    V = off + sum(y * c for y, c in zip(ys, cs))
+                    a, b, c = off & M30, off >> 30, 0
+                    for y, k in zip(ys, cs):
+                        a += (y & M30) * (k & M30)
+                        b += (y & M30) * (k >> 30) + (y >> 30) * (k & M30)
+                        c += (y >> 30) * (k >> 30)
+                    assert max(a, b, c) <= M64
+                    r = _redc60((a, b, c), m)
+                    assert (r * (1 << 60) - V) % m == 0 and r <= V // (1 << 60) + m and r < 9 * m
+                    if bt <= 50:
+                        v = _redc60((a, b, c + (1 << 62) - 4 * m), m)
+                        assert v == r + (1 << 62) - 4 * m and -4 * m <= v - (1 << 62) < 5 * m <= 1 << 53
+                        hi, lo = 2.0 ** 84 + 2.0 ** 32 * (v >> 32), 2.0 ** 52 + (v & 0xFFFFFFFF)
+                        assert int(hi) == (1 << 84) + (v >> 32 << 32)
+                        big = 2.0 ** 84 + 2.0 ** 62 + 2.0 ** 52
+                        assert int(big) == (1 << 84) + (1 << 62) + (1 << 52)
+                        x = (hi - big) + lo
+                        assert int(x) == v - (1 << 62)
+                        assert abs(_fp_reduce(int(x), m)) <= m // 2
+    assert tried > 150
+
+
+def test_integer_inner_sums_carry_into_their_top_word():
+    """Four sums of 30-bit partial products, settled after every 11 terms: nothing passes 2^64, the value modulo m stays, the
+    top sum returns below 4m and the others below 2^30."""
+    M30 = (1 << 30) - 1
+    rng = random.Random(17)
+    for m in (_odd_below(60), _odd_below(52), _odd_below(50), _odd_below(30), _odd_below(20)):
+        mu = (1 << 64) // m
+        for worst in (True, False):
+            s00 = s01 = s10 = s11 = want = 0
+            for k in range(1, 45):
+                x, c = (m - 1, m - 1) if worst else (rng.randrange(m), rng.randrange(m))
+                want += x * c
+                s00 += (x & M30) * (c & M30)
+                s01 += (x & M30) * (c >> 30)
+                s10 += (x >> 30) * (c & M30)
+                s11 += (x >> 30) * (c >> 30)
+                assert max(s00, s01, s10, s11) <= M64
+                if k % 11 == 0:
+                    s01 += s00 >> 30
+                    assert s01 <= M64
+                    s11 += (s01 >> 30) + (s10 >> 30)
+                    assert s11 <= M64
+                    s00, s01, s10 = s00 & M30, s01 & M30, s10 & M30
+                    x0, x1, p0, p1 = s11 & 0xFFFFFFFF, s11 >> 32, mu & 0xFFFFFFFF, mu >> 32
+                    qt = x1 * p1 + (x1 * p0 >> 32) + (x0 * p1 >> 32)
+                    s11 -= qt * m
+                    assert 0 <= s11 < 4 * m
+                V = s00 + ((s01 + s10) << 30) + (s11 << 60)
+                assert V < 1 << 128 and (V - want) % m == 0
+        # the highest a term-by-term argument can reach: a settled value and 11 products of the largest halves
+        assert 11 * M30 * M30 + M30 + (1 << 34) <= M64 and 11 * M30 * M30 + 4 * _odd_below(60) + (1 << 36) <= M64
+
+
+def test_double_precision_inner_sums_in_two_parts():
+    """Products of a residue and a centred word added to H in the binade of 1.5 * 2^103, what that rounds off to L, both folded
+    into L after every fifth: exact, at most 1.45 q after a fold, below 7.9 * 2^50 throughout."""
+    rng = random.Random(18)
+    for bits in (50, 49, 40, 30):
+        q, M = _fp_prime(bits), 3 << 102
+        half, qinv = (q - 1) // 2, 1.0 / q
+        for x_of, c_of in ((lambda: q - 1, lambda: q - 1), (lambda: q - 1, lambda: 0),
+                           (lambda: rng.choice((q - 1, rng.randrange(q))), lambda: rng.choice((0, q - 1, rng.randrange(q))))):
+            H, L, sx, want = M, 0, 0, 0
+            for k in range(1, 41):
+                x, c = x_of(), c_of()
+                want += x * c
+                sx += x
+                p = x * (c - half)
+                Hn = int(float(H + p))
+                assert 1 << 103 <= Hn < 1 << 104
+                rest = p - (Hn - H)
+                assert abs(rest) <= 1 << 50
+                L, H = L + rest, Hn
+                assert abs(L) <= 7.9 * 2 ** 50 and sx <= 1 << 53
+                if k % 5 == 0 or k == 40:
+                    h = H - M
+                    t = round(float(Fraction(L) * Fraction(qinv) + Fraction(float(h) * qinv)))   # one fma
+                    r = h - t * q
+                    assert abs(r) <= 1 << 53 and int(float(h)) == h
+                    L, H, sx = r + L, M, _fp_reduce(sx, q)
+                    assert abs(L) <= 1.45 * q
+            total = L + _fp_mulmod(sx, half, q)
+            assert abs(_fp_reduce(total, q)) <= q // 2 + 1 and (total - want) % q == 0
+
+
+def test_unreduced_digits_of_the_fused_inner_product():
+    """A round of four stages from q/2 is left as it is, at most 3.64 q; its product with a key word is at most 1.87 q, and
+    four of them with a folded sum stay below 8 q."""
+    rng = random.Random(19)
+    q = _fp_prime(50)
+    bound = 0.5
+    for _ in range(4):
+        bound = 1.1875 * bound + 0.5
+    assert bound <= 3.64
+    largest = 0.5 + 0.375 * 3.64
+    assert largest <= 1.87 and 4 * 1.87 + 0.5 < 8
+    top = int(3.64 * q)
+    for _ in range(100):
+        acc = rng.choice((-1, 1)) * (q // 2)
+        for k in range(4):
+            x = rng.choice((-1, 1)) * (top - rng.choice((0, 1, rng.randrange(1 << 20))))
+            T = _fp_mulmod(x, q - 1 - rng.choice((0, rng.randrange(1 << 20))), q)
+            assert abs(T) <= 1.87 * q
+            acc += T
+            assert abs(acc) <= 1 << 53
+        assert abs(_fp_reduce(acc, q)) <= q // 2 + 1
+    # and at the bound itself, which sampled products do not reach
+    for sign in (-1, 1):
+        assert abs(_fp_reduce(sign * int((4 * 1.87 + 0.5) * q), q)) <= q // 2 + 1
