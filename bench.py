@@ -351,15 +351,17 @@ def other_workloads(args):
                 del wsc
             checked = "ciphertext %d of the plain and the hoisted call equals the oracle's BSGS (%.0f s on %d threads)" % (b1, t_or, threads)
         rots = Bc * (n1 - 1 + n2 - 1)
-        # inner sums on the double-precision limbs: 4 FP64 instructions per multiply-add (the product added to an exact
-        # pair of sums) and 6 every fifth, against the chip's FP64 vector issue rate
+        # inner sums on the double-precision limbs against the chip's FP64 vector issue rate: staged through LDS 4 FP64
+        # instructions per multiply-add (the product added to an exact pair of sums) and 6 every fifth, in register tiles 7
+        # (exact product in two parts, quotient, remainder, accumulate)
         nfp = sum(1 for m in p.q if m < (1 << 50))
         macs = Bc * 2 * nfp * N * n1 * n2
-        pm_ms = prof.get("pmacc_fp_kernel", 0.0)
+        ran = [(k, ops) for k, ops in (("pmacc_fp_staged_kernel", OPS_PAIR_FP), ("pmacc_fp_kernel", OPS_MULRED_FP)) if prof.get(k)]
         pm_roof = None
-        if pm_ms:
-            tops = macs * OPS_PAIR_FP / (pm_ms * 1e-3) / 1e12
-            pm_roof = {"bound": "alu", "kernel": "pmacc_fp_kernel", "achieved": round(tops, 2), "peak": round(PEAK_ALU_TOPS, 1),
+        if len(ran) == 1:   # (of two the event times do not say how the multiply-adds were shared)
+            pm_kernel, pm_ops = ran[0]
+            tops = macs * pm_ops / (prof[pm_kernel] * 1e-3) / 1e12
+            pm_roof = {"bound": "alu", "kernel": pm_kernel, "achieved": round(tops, 2), "peak": round(PEAK_ALU_TOPS, 1),
                        "unit": "T lane-instructions/s", "frac": round(tops / PEAK_ALU_TOPS, 3)}
         print(json.dumps({"workload": "pcmm_ffn_share", "gpu_matches_oracle_on_sample": checked, "inner_sum_roofline": pm_roof, "ciphertexts_per_call": Bc, "seconds_per_call": round(dt, 4),
                           "seconds_for_128_ciphertexts": round(dt * total / Bc, 3), "hrot_per_s": round(rots / dt, 1),

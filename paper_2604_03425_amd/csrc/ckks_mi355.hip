@@ -139,7 +139,7 @@ enum ProfKind {
   PK_FWD_ROWS, PK_FWD_BLOCKS = PK_FWD_ROWS + 3, PK_INV_BLOCKS = PK_FWD_BLOCKS + 3, PK_INV_ROWS = PK_INV_BLOCKS + 3,
   PK_FWD_FINAL = PK_INV_ROWS + 3,
   PK_AUTOMORPH = PK_FWD_FINAL + 3, PK_MODUP, PK_INNER, PK_INNER16, PK_INNER16_INT, PK_INNER_C, PK_INNER8, PK_INNER8_BIG, PK_BCONV_ROWS, PK_MODDOWN = PK_BCONV_ROWS + 3, PK_FINAL, PK_TENSOR, PK_PMACC, PK_PMACC_FP, PK_ADD,
-  PK_KS12_FRONT, PK_KS12_DIGITS, PK_KS12_SPECIAL, PK_KS12_FINAL, PK_CONV_ROWS, PK_COPY, PK_COUNT
+  PK_KS12_FRONT, PK_KS12_DIGITS, PK_KS12_SPECIAL, PK_KS12_FINAL, PK_CONV_ROWS, PK_COPY, PK_PMACC_STAGED, PK_PMACC_FP_STAGED, PK_COUNT
 };
 static const char* const kProfNames[PK_COUNT] = {
     "ntt_fwd_pass", "ntt_inv_pass",
@@ -151,7 +151,8 @@ static const char* const kProfNames[PK_COUNT] = {
     "automorph_kernel", "modup_kernel", "inner_kernel", "inner16_fp_kernel", "inner16_int_kernel", "ntt16_fwd_blocks_inner_c_kernel", "ntt16_fwd_blocks_inner8_kernel<1>", "ntt16_fwd_blocks_inner8_kernel<2>",
     "ntt16_bconv_rows_kernel<0>", "ntt16_bconv_rows_kernel<1>", "ntt16_bconv_rows_kernel<2>", "moddown_kernel", "ks_final_kernel", "tensor_kernel",
     "pmacc_int_kernel", "pmacc_fp_kernel", "addto_kernel",
-    "ks12_front_kernel", "ks12_digits_kernel", "ks12_special_kernel", "ks12_final_kernel", "conv_rows_kernel", "copy"};
+    "ks12_front_kernel", "ks12_digits_kernel", "ks12_special_kernel", "ks12_final_kernel", "conv_rows_kernel", "copy",
+    "pmacc_int_staged_kernel", "pmacc_fp_staged_kernel"};
 struct ProfRec {
   int kind;
   hipEvent_t start, stop;
@@ -2395,7 +2396,7 @@ static int pcmm_impl(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint3
       if (staged && g0 + ng - h0 >= 7) {
         const bool big = g0 + ng - h0 >= 9;
         const dim3 grid = staged_tiles(fa, h0, big ? 12 : 8, nfp);
-        ProfScope ps(c, PK_PMACC_FP, st);
+        ProfScope ps(c, PK_PMACC_FP_STAGED, st);
         if (big) hipLaunchKernelGGL((pmacc_fp_staged_kernel<4, 6, 2, 2>), grid, dim3(256), 0, st, fa);
         else hipLaunchKernelGGL((pmacc_fp_staged_kernel<4, 4, 2, 2>), grid, dim3(256), 0, st, fa);
         HIP_TRY(hipGetLastError());
@@ -2428,7 +2429,7 @@ static int pcmm_impl(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint3
       if (staged && g0 + ng - h0 >= 7) {
         const bool big = g0 + ng - h0 >= 9;
         const dim3 grid = staged_tiles(ia, h0, big ? 6 : 8, nint);
-        ProfScope ps(c, PK_PMACC, st);
+        ProfScope ps(c, PK_PMACC_STAGED, st);
         if (big) hipLaunchKernelGGL((pmacc_int_staged_kernel<4, 3, 2, 2>), grid, dim3(256), 0, st, ia);
         else hipLaunchKernelGGL((pmacc_int_staged_kernel<4, 2, 2, 4>), grid, dim3(512), 0, st, ia);
         HIP_TRY(hipGetLastError());

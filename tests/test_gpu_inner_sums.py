@@ -55,3 +55,25 @@ def test_inner_sums_through_lds(shape, B, n1, n2, largest):
     gpu.ckks_pcmm_bsgs(gc, out, d_ct, B, nl, shifted, *args)
     assert_same(to_host(out), want, "inner sums, plaintexts on an odd word")
     gc.close()
+
+
+@pytest.mark.parametrize("shape,kind", [(FP, "pmacc_fp"), (INT, "pmacc_int")])
+def test_profile_names_the_kernel_that_ran(shape, kind):
+    import torch
+    import paper_2604_03425_amd as gpu
+    from gpu_util import to_dev
+    p = make_params(*shape)
+    gc, nl, B, n1, n2 = gpu.Context(p), len(p.q), 4, 3, 8
+    d_ct, d_pt = to_dev(uniform_residues(1, p.q, (B, 2), p.N)), to_dev(uniform_residues(2, p.q, (n2, n1), p.N))
+    key = to_dev(uniform_residues(3, p.moduli, (p.dnum, 2), p.N))
+    shifted = torch.empty(d_pt.numel() + 1, dtype=torch.int64, device="cuda")[1:].view_as(d_pt)
+    shifted.copy_(d_pt)
+    out, ws = torch.empty_like(d_ct), gc.workspace(gpu.OP_PCMM_BSGS, B, nl, n1)
+    for pt, ran, other in ((d_pt, "_staged_kernel", "_kernel"), (shifted, "_kernel", "_staged_kernel")):
+        gpu.ckks_prof_reset(gc)
+        gpu.ckks_prof_enable(gc, True)
+        gpu.ckks_pcmm_bsgs(gc, out, d_ct, B, nl, pt, n1, n2, 1, [key] * (n1 - 1), [key] * (n2 - 1), ws)
+        gpu.ckks_prof_enable(gc, False)
+        times = gpu.ckks_prof_collect(gc)
+        assert kind + ran in times and kind + other not in times, times
+    gc.close()
