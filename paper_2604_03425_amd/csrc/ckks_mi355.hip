@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <string>
 #include <vector>
@@ -1662,6 +1663,60 @@ int check_ids(const ckks_ctx* c, const uint32_t* ids, u32 n, LimbMap* out) {
   return CKKS_OK;
 }
 
+// Launch forms of a matrix product's inner sums and what a launch takes, in us, for the choice between them:
+//   4 + wait * n1 + limbs * N / 65536 * (issue^4 + traffic^4)^(1/4)
+//   issue = groups * (tiles * tile + count * giant) * (n1 + rest), traffic = word * (n1 * (2B + count) + 2B * count)
+// for `count` giant steps in tiles of `giants` and 2B polynomials in groups of `polys`: instructions or, where one group shares
+// nothing with another, each word once (5.6 TB/s in register tiles, 4.9 staged). Each form was timed alone, 1 .. 64 baby steps and
+// 4 .. 32 ciphertexts; the constants fit 24 and 4 limbs at 2^16 (rms 4 .. 6 %, lone tiles of 1 .. 4 giant steps 9 .. 14 %), `wait`, a
+// lone workgroup's time a step, 2^12 .. 2^14. Why a choice and not a size: a staged tile costs the most of a whole one when it is
+// short, and half as much again beyond its baby steps, while the register-tiled kernels pay for a tile of 4, 3, 2 or 1 giant steps
+// most of what one of 6 (integer limbs 3) costs and read the baby steps again for each launch. 24 limbs at 2^16, in register tiles
+// and staged, us: 8 ciphertexts, 12 giant x 64 baby steps 6582 and 6205 (integer limbs 8614 and 6306), 12 x 1 549 and 699, 7 x 8
+// 1052 and 820, 18 x 8 1713 and 2090; 5 ciphertexts 9 x 8 882 and 956 (integer limbs 840 and 1068). The launches chosen take 0.5 %
+// more than the best of the forms on average over 14 counts of giant steps at each of those sizes, 12 % less than register tiles.
+struct SumForm {
+  u32 giants, polys;
+  double tile, giant, rest, word, wait;
+};
+struct SumForms {
+  SumForm tiled[5];    // pmacc_*_kernel: whole tiles only, largest first down to 1, as many of each as fit
+  SumForm staged[2];   // pmacc_*_staged_kernel
+};
+constexpr SumForms kSumsFp = {{{6, PMACC_FP_P, .89, 0, 3.6, .093, .72}, {4, PMACC_FP_P, .73, 0, .6, .093, .48},
+                               {3, PMACC_FP_P, .65, 0, .3, .093, .36}, {2, PMACC_FP_P, .63, 0, 0, .093, .24},
+                               {1, PMACC_FP_P, .56, 0, 0, .093, .12}},
+                              {{12, 8, 1.28, .026, 5.6, .108, .25}, {8, 8, .89, .024, 5.4, .108, .25}}};
+constexpr SumForms kSumsInt = {{{3, PMACC_INT_P, .29, 0, 5.8, .093, .36}, {2, PMACC_INT_P, .33, 0, 2.5, .093, .24},
+                                {1, PMACC_INT_P, .25, 0, 0, .093, .12}},
+                               {{6, 8, .55, .039, 8.7, .108, .25}, {8, 8, .99, .032, 8.0, .108, .25}}};
+struct SumPlan {
+  double us;
+  int staged;   // what the next launch is: a staged form, or -1 for register tiles to the end
+  u32 count;    // giant steps it covers
+};
+// The next launch for `left` giant steps of `work` = limbs * N / 65536: everything left in register tiles, everything in staged
+// tiles of either size (the last one short), or 12 steps in the large ones and then the best for the others. Up to 6 steps and
+// below 4 ciphertexts register tiles, against which the staged kernels were not measured.
+SumPlan sum_plan(const SumForms& f, u32 left, u32 B, u32 n1, double work) {
+  auto us = [&](const SumForm& m, u32 count) {
+    const u32 groups = (2 * B + m.polys - 1) / m.polys, tiles = (count + m.giants - 1) / m.giants;
+    const double issue = groups * (tiles * m.tile + count * m.giant) * (n1 + m.rest);
+    const double traffic = m.word * ((double)n1 * (2 * B + count) + 2.0 * B * count);
+    return 4 + m.wait * n1 + work * std::sqrt(std::hypot(issue * issue, traffic * traffic));
+  };
+  SumPlan best{0, -1, left};
+  u32 rest = left;
+  for (u32 i = 0; rest; rest %= f.tiled[i++].giants)
+    if (rest >= f.tiled[i].giants) best.us += us(f.tiled[i], rest / f.tiled[i].giants * f.tiled[i].giants);
+  if (left < 7 || B < 4) return best;
+  auto consider = [&](double t, int staged, u32 count) {
+    if (t < best.us) best = {t, staged, count};
+  };
+  for (int i = 0; i < 2; i++) consider(us(f.staged[i], left), i, left);
+  if (left > 12) consider(us(f.staged[0], 12) + sum_plan(f, left - 12, B, n1, work).us, 0, 12);
+  return best;
+}
 }  // namespace
 
 extern "C" {
@@ -2382,22 +2437,23 @@ static int pcmm_impl(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint3
       a.g0 = first_g;
       a.ng = count;
     };
-    // The kernels that stage their words through LDS take tiles of 8 polynomials x 12 giant steps (integer limbs 6), or x 8
-    // where at most 8 are left: from 4 ciphertexts and 7 giant steps on (fewer leave waves of a workgroup without sums), and
-    // rows that 16-byte copies can start at. 4 ciphertexts, 8 x 8 steps, 24 50-bit limbs at 2^16: 640 -> 492 us.
-    const bool staged = B >= 4 && (((uintptr_t)pt | (uintptr_t)baby | (uintptr_t)(dh ? first : (const u64*)ct_in)) & 15) == 0;
-    auto staged_tiles = [&](PmaccArgs& a, u32 h0, u32 per_tile, u32 limbs) {
-      const u32 left = g0 + ng - h0;
-      fill(a, h0, left < 9 ? left : std::min(left, (left + 3) / 12 * 12));   // 9 .. 12 go in tiles of 12
-      a.ngt = (a.ng + per_tile - 1) / per_tile;
-      return dim3((2 * B + 7) / 8 * a.ngt * (N / 64) * limbs);
+    // the kernels that stage their words through LDS copy 16 bytes a lane
+    const bool staged_ok = (((uintptr_t)pt | (uintptr_t)baby | (uintptr_t)(dh ? first : (const u64*)ct_in)) & 15) == 0;
+    auto plan = [&](const SumForms& f, u32 h0, u32 limbs) {
+      return staged_ok ? sum_plan(f, g0 + ng - h0, B, n1, (double)limbs * N / 65536) : SumPlan{0, -1, g0 + ng - h0};
+    };
+    // (2^32 lanes, which a grid may not pass, take a workspace larger than the memory)
+    auto staged_tiles = [&](PmaccArgs& a, u32 h0, const SumPlan& p, const SumForm& m, u32 limbs) {
+      fill(a, h0, p.count);
+      a.ngt = (p.count + m.giants - 1) / m.giants;
+      return dim3((2 * B + m.polys - 1) / m.polys * a.ngt * (N / 64) * limbs);
     };
     for (u32 h0 = g0; nfp && h0 < g0 + ng;) {
-      if (staged && g0 + ng - h0 >= 7) {
-        const bool big = g0 + ng - h0 >= 9;
-        const dim3 grid = staged_tiles(fa, h0, big ? 12 : 8, nfp);
+      const SumPlan next = plan(kSumsFp, h0, nfp);
+      if (next.staged >= 0) {
+        const dim3 grid = staged_tiles(fa, h0, next, kSumsFp.staged[next.staged], nfp);
         ProfScope ps(c, PK_PMACC_FP_STAGED, st);
-        if (big) hipLaunchKernelGGL((pmacc_fp_staged_kernel<4, 6, 2, 2>), grid, dim3(256), 0, st, fa);
+        if (next.staged == 0) hipLaunchKernelGGL((pmacc_fp_staged_kernel<4, 6, 2, 2>), grid, dim3(256), 0, st, fa);
         else hipLaunchKernelGGL((pmacc_fp_staged_kernel<4, 4, 2, 2>), grid, dim3(256), 0, st, fa);
         HIP_TRY(hipGetLastError());
         h0 += fa.ng;
@@ -2426,11 +2482,11 @@ static int pcmm_impl(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint3
       h0 += cnt * ngt;
     }
     for (u32 h0 = g0; nint && h0 < g0 + ng;) {
-      if (staged && g0 + ng - h0 >= 7) {
-        const bool big = g0 + ng - h0 >= 9;
-        const dim3 grid = staged_tiles(ia, h0, big ? 6 : 8, nint);
+      const SumPlan next = plan(kSumsInt, h0, nint);
+      if (next.staged >= 0) {
+        const dim3 grid = staged_tiles(ia, h0, next, kSumsInt.staged[next.staged], nint);
         ProfScope ps(c, PK_PMACC_STAGED, st);
-        if (big) hipLaunchKernelGGL((pmacc_int_staged_kernel<4, 3, 2, 2>), grid, dim3(256), 0, st, ia);
+        if (next.staged == 0) hipLaunchKernelGGL((pmacc_int_staged_kernel<4, 3, 2, 2>), grid, dim3(256), 0, st, ia);
         else hipLaunchKernelGGL((pmacc_int_staged_kernel<4, 2, 2, 4>), grid, dim3(512), 0, st, ia);
         HIP_TRY(hipGetLastError());
         h0 += ia.ng;

@@ -77,3 +77,42 @@ def test_profile_names_the_kernel_that_ran(shape, kind):
         times = gpu.ckks_prof_collect(gc)
         assert kind + ran in times and kind + other not in times, times
     gc.close()
+
+
+@pytest.mark.parametrize("shape,B,n1,n2,staged", [
+    (FP, 8, 1, 18, False),      # three whole register tiles in one launch
+    (FP, 8, 1, 24, False),
+    (FP, 4, 8, 8, True),
+    (FP, 5, 8, 13, True),       # two tiles of 8
+    (FP, 4, 16, 23, True),      # two tiles of 12, the last one short
+    (FP, 3, 16, 8, False),
+    (FP, 4, 16, 6, False),
+    (INT, 5, 3, 18, False),     # six register tiles of 3
+    (INT, 5, 8, 9, False),
+    (INT, 5, 5, 7, True),
+    (INT, 4, 4, 13, True),      # three tiles of 6, one giant step in the last
+    (INT, 4, 16, 22, True),     # four tiles of 6, the last one short
+])
+def test_kernels_of_the_inner_sums(shape, B, n1, n2, staged):
+    """Staged through LDS only where that was measured faster than whole register tiles; the bits are the oracle's."""
+    import torch
+    import paper_2604_03425_amd as gpu
+    from gpu_util import assert_same, to_dev, to_host
+    p = make_params(*shape)
+    rc, gc, nl, some = ref.RefContext(p), gpu.Context(p), len(p.q), [0, B - 1]
+    ct, pt = uniform_residues(1, p.q, (B, 2), p.N), uniform_residues(2, p.q, (n2, n1), p.N)
+    key = uniform_residues(3, p.moduli, (p.dnum, 2), p.N)
+    d_ct, d_pt, d_key = to_dev(ct), to_dev(pt), to_dev(key)
+    out, ws = torch.empty_like(d_ct), gc.workspace(gpu.OP_PCMM_BSGS, B, nl, n1)
+    gpu.ckks_prof_reset(gc)
+    gpu.ckks_prof_enable(gc, True)
+    gpu.ckks_pcmm_bsgs(gc, out, d_ct, B, nl, d_pt, n1, n2, 1, [d_key] * (n1 - 1), [d_key] * (n2 - 1), ws)
+    gpu.ckks_prof_enable(gc, False)
+    ran = {k for k in gpu.ckks_prof_collect(gc) if k.startswith("pmacc")}
+    kind = "pmacc_fp" if shape is FP else "pmacc_int"
+    assert ran == {kind + ("_staged_kernel" if staged else "_kernel")}
+    ref.set_threads(8)
+    want = rc.pcmm_bsgs(ct[some], pt, n1, n2, 1, [key] * (n1 - 1), [key] * (n2 - 1))
+    ref.set_threads(1)
+    assert_same(to_host(out)[some], want, "inner sums")
+    gc.close()
