@@ -57,6 +57,14 @@ def test_inner_sums_through_lds(shape, B, n1, n2, largest):
     gc.close()
 
 
+def _ran(gpu, gc, call):
+    gpu.ckks_prof_reset(gc)
+    gpu.ckks_prof_enable(gc, True)
+    call()
+    gpu.ckks_prof_enable(gc, False)
+    return {k for k in gpu.ckks_prof_collect(gc) if k.startswith("pmacc")}
+
+
 @pytest.mark.parametrize("shape,kind", [(FP, "pmacc_fp"), (INT, "pmacc_int")])
 def test_profile_names_the_kernel_that_ran(shape, kind):
     import torch
@@ -70,11 +78,7 @@ def test_profile_names_the_kernel_that_ran(shape, kind):
     shifted.copy_(d_pt)
     out, ws = torch.empty_like(d_ct), gc.workspace(gpu.OP_PCMM_BSGS, B, nl, n1)
     for pt, ran, other in ((d_pt, "_staged_kernel", "_kernel"), (shifted, "_kernel", "_staged_kernel")):
-        gpu.ckks_prof_reset(gc)
-        gpu.ckks_prof_enable(gc, True)
-        gpu.ckks_pcmm_bsgs(gc, out, d_ct, B, nl, pt, n1, n2, 1, [key] * (n1 - 1), [key] * (n2 - 1), ws)
-        gpu.ckks_prof_enable(gc, False)
-        times = gpu.ckks_prof_collect(gc)
+        times = _ran(gpu, gc, lambda: gpu.ckks_pcmm_bsgs(gc, out, d_ct, B, nl, pt, n1, n2, 1, [key] * (n1 - 1), [key] * (n2 - 1), ws))
         assert kind + ran in times and kind + other not in times, times
     gc.close()
 
@@ -104,15 +108,61 @@ def test_kernels_of_the_inner_sums(shape, B, n1, n2, staged):
     key = uniform_residues(3, p.moduli, (p.dnum, 2), p.N)
     d_ct, d_pt, d_key = to_dev(ct), to_dev(pt), to_dev(key)
     out, ws = torch.empty_like(d_ct), gc.workspace(gpu.OP_PCMM_BSGS, B, nl, n1)
-    gpu.ckks_prof_reset(gc)
-    gpu.ckks_prof_enable(gc, True)
-    gpu.ckks_pcmm_bsgs(gc, out, d_ct, B, nl, d_pt, n1, n2, 1, [d_key] * (n1 - 1), [d_key] * (n2 - 1), ws)
-    gpu.ckks_prof_enable(gc, False)
-    ran = {k for k in gpu.ckks_prof_collect(gc) if k.startswith("pmacc")}
+    ran = _ran(gpu, gc, lambda: gpu.ckks_pcmm_bsgs(gc, out, d_ct, B, nl, d_pt, n1, n2, 1, [d_key] * (n1 - 1), [d_key] * (n2 - 1), ws))
     kind = "pmacc_fp" if shape is FP else "pmacc_int"
     assert ran == {kind + ("_staged_kernel" if staged else "_kernel")}
     ref.set_threads(8)
     want = rc.pcmm_bsgs(ct[some], pt, n1, n2, 1, [key] * (n1 - 1), [key] * (n2 - 1))
     ref.set_threads(1)
     assert_same(to_host(out)[some], want, "inner sums")
+    gc.close()
+
+
+@pytest.mark.parametrize("B,n1,n2", [
+    (4, 3, 7),       # tiles of 8 for both kinds of limbs
+    (4, 3, 11),      # one tile of 12, two of 6
+    (5, 12, 11),     # past a fold of either kind
+])
+def test_inner_sums_through_lds_in_the_extended_basis(B, n1, n2):
+    """Main limbs below the top level and special ones after them (a limb's modulus is not its index), both arithmetic kinds
+    writing to the same sums."""
+    import torch
+    import paper_2604_03425_amd as gpu
+    from gpu_util import assert_same, to_dev, to_host
+    p, nl = make_params(16, 4, 50, 2, 60, 2), 3
+    rc, gc, some = ref.RefContext(p), gpu.Context(p), [0, B - 1]
+    ct, pt = uniform_residues(1, p.q[:nl], (B, 2), p.N), uniform_residues(2, list(p.q[:nl]) + list(p.p), (n2, n1), p.N)
+    keys = [uniform_residues(3 + i, p.moduli, (p.dnum, 2), p.N) for i in range(3)]
+    baby, giant = [keys[i % 3] for i in range(n1 - 1)], [keys[(i + 1) % 3] for i in range(n2 - 1)]
+    d_ct, d_pt, d_keys = to_dev(ct), to_dev(pt), [to_dev(k) for k in keys]
+    d_baby, d_giant = [d_keys[i % 3] for i in range(n1 - 1)], [d_keys[(i + 1) % 3] for i in range(n2 - 1)]
+    out, ws = torch.empty_like(d_ct), gc.workspace(gpu.OP_PCMM_BSGS_DH, B, nl, n1)
+    ran = _ran(gpu, gc, lambda: gpu.ckks_pcmm_bsgs_double_hoisted(gc, out, d_ct, B, nl, d_pt, n1, n2, 1, d_baby, d_giant, ws))
+    assert ran == {"pmacc_fp_staged_kernel", "pmacc_int_staged_kernel"}
+    ref.set_threads(8)
+    want = rc.pcmm_bsgs_double_hoisted(ct[some], pt, n1, n2, 1, baby, giant)
+    ref.set_threads(1)
+    assert_same(to_host(out)[some], want, "extended basis")
+    gc.close()
+
+
+@pytest.mark.parametrize("logN,B,n1,n2", [(13, 5, 6, 11), (12, 4, 12, 8)])
+def test_inner_sums_through_lds_on_mixed_primes(logN, B, n1, n2):
+    import torch
+    import paper_2604_03425_amd as gpu
+    from gpu_util import assert_same, to_dev, to_host
+    from test_gpu_mixed_primes import mixed_params
+    p, nl = mixed_params(logN, [60, 50, 50, 60], [60, 60], 2), 3
+    rc, gc = ref.RefContext(p), gpu.Context(p)
+    ct, pt = uniform_residues(1, p.q[:nl], (B, 2), p.N), uniform_residues(2, p.q[:nl], (n2, n1), p.N)
+    baby = [uniform_residues(10 + i, p.moduli, (p.dnum, 2), p.N) for i in range(n1 - 1)]
+    giant = [uniform_residues(50 + i, p.moduli, (p.dnum, 2), p.N) for i in range(n2 - 1)]
+    d_ct, d_pt, d_baby, d_giant = to_dev(ct), to_dev(pt), [to_dev(k) for k in baby], [to_dev(k) for k in giant]
+    out, ws = torch.empty_like(d_ct), gc.workspace(gpu.OP_PCMM_BSGS, B, nl, n1)
+    ran = _ran(gpu, gc, lambda: gpu.ckks_pcmm_bsgs(gc, out, d_ct, B, nl, d_pt, n1, n2, 1, d_baby, d_giant, ws))
+    assert ran == {"pmacc_fp_staged_kernel", "pmacc_int_staged_kernel"}
+    ref.set_threads(8)
+    want = rc.pcmm_bsgs(ct, pt, n1, n2, 1, baby, giant)
+    ref.set_threads(1)
+    assert_same(to_host(out), want, "mixed primes")
     gc.close()
