@@ -87,9 +87,10 @@ def test_pcmm_ffn_share_real_shape_against_oracle_digests(gpu):
     """The FFN-layer workload at its real shape: N=2^16, 24 limbs, dnum=3, 32 baby x 24 giant steps, a batch of 8.
     SHA-256 of every output ciphertext equals the digest the oracle wrote (tests/golden/pcmm_ffn_digests.txt, made
     by make_pcmm_ffn_digests.py from the same seeded inputs), for the one-rotation-at-a-time schedule and for the
-    hoisted one, which is bit-identical by definition. This is the shape at which the N=2^16 schedule runs whole
-    tiles of 24 giant steps (6-giant-step launches of the double-precision inner sums, 3-giant-step integer ones),
-    accumulates the giant steps in place, and packs the hoisted baby steps' accumulators into the inner-sum region."""
+    hoisted one, which is bit-identical by definition. This is the shape at which the N=2^16 schedule holds whole
+    tiles of 24 giant steps (double-precision inner sums through LDS, 12 giant steps a workgroup), accumulates the giant
+    steps in place, and packs the hoisted baby steps' accumulators into the inner-sum region. A slice of 3 ciphertexts
+    takes the register-tiled inner sums, 6 giant steps a tile, to the same digests."""
     import hashlib
     import importlib.util
     import os
@@ -115,11 +116,18 @@ def test_pcmm_ffn_share_real_shape_against_oracle_digests(gpu):
     d_baby, d_giant = [to_dev(k) for k in baby], [to_dev(k) for k in giant]
     del baby, giant
     ws = gc.workspace(gpu.OP_PCMM_BSGS, B, nl, n1)
-    for name, fn in (("plain", gpu.ckks_pcmm_bsgs), ("hoisted", gpu.ckks_pcmm_bsgs_hoisted)):
-        out = torch.zeros((B, 2, nl, p.N), dtype=torch.int64, device="cuda")
-        fn(gc, out, d_ct, B, nl, d_pt, n1, n2, 1, d_baby, d_giant, ws)
+    for name, fn, b0 in (("plain", gpu.ckks_pcmm_bsgs, 0), ("hoisted", gpu.ckks_pcmm_bsgs_hoisted, 0),
+                         ("hoisted", gpu.ckks_pcmm_bsgs_hoisted, B - 3)):
+        out = torch.zeros((B - b0, 2, nl, p.N), dtype=torch.int64, device="cuda")
+        gpu.ckks_prof_reset(gc)
+        gpu.ckks_prof_enable(gc, True)
+        fn(gc, out, d_ct[b0:], B - b0, nl, d_pt, n1, n2, 1, d_baby, d_giant, ws)
+        gpu.ckks_prof_enable(gc, False)
+        sums = {k for k in gpu.ckks_prof_collect(gc) if k.startswith("pmacc")}
+        assert sums == {"pmacc_fp_kernel" if b0 else "pmacc_fp_staged_kernel"}
         got = to_host(out)
-        bad = [b for b in range(B) if hashlib.sha256(np.ascontiguousarray(got[b]).tobytes()).hexdigest() != want[b]]
+        bad = [b for b in range(b0, B)
+               if hashlib.sha256(np.ascontiguousarray(got[b - b0]).tobytes()).hexdigest() != want[b]]
         assert not bad, "%s schedule: ciphertexts %s differ from the oracle's digests" % (name, bad)
     gc.close()
 
