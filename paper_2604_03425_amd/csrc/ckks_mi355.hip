@@ -2139,8 +2139,8 @@ int ckks_hmult_relin(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_a, const 
   // Two-pass rings, double-precision main primes: the products are formed where they are read (first inverse pass, own
   // digits, assembly), which takes 6 passes over a limb vector where a product kernel of its own and the reads of its
   // results took 11: 32 products of 24 limbs at 2^16 3328 -> 3099 us, 3 of 11 limbs 230 -> 216, 8 of 13 limbs at 2^15
-  // 308 -> 293. Integer-class primes keep it: their kernels are bound by instructions, and a product costs 40. One such prime
-  // among the main limbs keeps it for all of them.
+  // 308 -> 293. Integer-class primes keep it: their inner product takes neither the inputs of a product nor the assembly. One
+  // such prime among the main limbs keeps it for all of them.
   bool all_fp = two_pass(c) && c->tune[3] != 1;
   for (u32 i = 0; i < nlimbs; i++) all_fp = all_fp && host_class(c, c->mod[i]) == 0;
   if (all_fp) {

@@ -47,8 +47,9 @@ struct ConvArgs {
   u32 nfp, nint;             // targets by arithmetic kind: tslot[0 .. nfp), tslot[nfp .. nfp + nint)
   u32 nsplit;                // workgroups that share the targets of a (polynomial, tile)
   u32 pitch;                 // constants per target in mat
-  const u64* mat;            // integer conversion: as BconvRowsArgs
-  const u64* off;
+  // integer conversion: [beta][ntarget][pitch] constants (C/c_k) mod m_t and [beta][ntarget] the offset of the shifted sources,
+  // scaled by 2^60 under NARROW (by 2^64 otherwise): LevelTables::up_conv, dn_conv and their _off, not up_mat, dn_mat_plain
+  const u64 *mat, *off;
   const double* matd;        // [beta][ntarget][pitch - 1] centred constants (double-precision sources and targets)
   const ulonglong2* scale;   // [src_nlimbs] per source (Q_j/q_i)^-1 / N, in the form of its class
   const ulonglong2 *tw, *twi;
@@ -321,7 +322,8 @@ __device__ __forceinline__ void convert_fp(double (&x)[4], const ConvWord (&y)[M
     x[i] = __builtin_fma(-__builtin_rint(__builtin_fma(L[i], qinv, h * qinv)), q, h) + L[i];
   }
 }
-// Split-form sources to any target. NARROW: below 9m, plus `bias` (a multiple of m modulo 2^64); otherwise canonical.
+// Split-form sources to any target. NARROW: below 9m, plus `bias`: 0, or 2^62 less a multiple of m, which leaves the residue to a
+// caller that takes 2^62 away again. Otherwise canonical.
 template <int MAXLEN, bool NARROW>
 __device__ __forceinline__ void convert_int(u64 (&x)[4], const ConvWord (&y)[MAXLEN][4], const ConvTarget<MAXLEN>& tg, u64 bias) {
   static_assert(MAXLEN <= 8, "the transforms that follow take values below 9m");

@@ -477,7 +477,7 @@ struct PmaccArgs {
 
 // Inner sums on double-precision moduli (q < 2^50), register-tiled like a small matrix product: a lane owns
 // one coefficient position and keeps the running sums of PMACC_FP_P polynomials x NG giant steps (one double each:
-// every product is reduced on the spot with 5 FP64 instructions), so per baby step it loads P ciphertext words and
+// every product is reduced on the spot with 6 FP64 instructions and added with one), so per baby step it loads P ciphertext words and
 // NG plaintext words for P * NG multiply-adds: 8/P + 8/NG bytes per multiply-add instead of 16. grid =
 // (ceil(2B / P) * ngt, N / 256, limbs of the class): polynomial groups innermost, then the ngt tiles of NG giant
 // steps, so the workgroups that share a plaintext tile or a set of baby-step words run together on one XCD and

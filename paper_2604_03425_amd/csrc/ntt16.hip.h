@@ -376,7 +376,7 @@ __device__ __forceinline__ void ntt256_fwd_blocks_int8(u64 (&x)[8], const ulongl
 }
 
 // Inverse, the first 8 stages, on contiguous blocks. In: x holds, for lane (hb, j0), the values at positions i*16 + j0
-// of block h (any value < 2q). Out: < 2q (BIG: < 4q), same lane layout, ready for a coalesced store.
+// of block h (any value < 2q). Out: < 2q (BIG: < 8q), same lane layout, ready for a coalesced store.
 template <bool BIG>
 __device__ __forceinline__ void ntt16_inv_blocks(u64 (&x)[16], const ulonglong2* __restrict__ twi, u64 q, u64 mu, u32 tile,
                                                  u32 R, u64* sm) {
