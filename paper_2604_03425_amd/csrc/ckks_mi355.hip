@@ -2405,8 +2405,8 @@ static int pcmm_impl(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint3
       if (rc) return rc;
     }
   }
-  // limbs by arithmetic kind: the double-precision kernel computes up to 6 giant steps x 8 polynomials per pass
-  // over the baby-step ciphertexts, the integer kernel up to 3 giant steps x 4 polynomials
+  // limbs by arithmetic kind: each has kernels of its own. In register tiles the double-precision ones take up to 6 giant
+  // steps x 8 polynomials per pass over the baby-step ciphertexts, the integer ones up to 3 x 4
   PmaccArgs fa, ia;
   u32 nfp = 0, nint = 0;
   for (u32 i = 0; i < pl_limbs; i++) {

@@ -1,5 +1,6 @@
-"""GPU parity of the diagonal matrix product's inner sums where they go through LDS (4 ciphertexts and 7 giant steps on):
-tiles of 8 polynomials x 12 or x 8 giant steps, short last tiles, folds of 5 and 11 terms, both arithmetic kinds; bit-exact."""
+"""GPU parity of the diagonal matrix product's inner sums from 4 ciphertexts and 7 giant steps on, where they go through LDS if
+that is estimated to be faster: tiles of 8 polynomials x 12 (integer limbs x 6) or x 8 giant steps, short last tiles, folds of
+5 and 11 terms, both arithmetic kinds; bit-exact."""
 import numpy as np
 import pytest
 
@@ -19,7 +20,7 @@ CASES = [
     (FP, 4, 3, 27),      # giant steps beyond what the workspace holds at once: 24, then 3
     (SMALL, 7, 16, 10),
     (INT, 4, 11, 12),
-    (INT, 5, 12, 9),
+    (INT, 5, 12, 9),     # register tiles
     (INT, 4, 1, 7),
     (INT, 4, 23, 8),
     (INT, 9, 2, 20),     # tiles of 6 and one of 8
