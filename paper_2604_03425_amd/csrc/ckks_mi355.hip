@@ -117,11 +117,9 @@ struct LevelTables {
   ulonglong2* up_scale = nullptr;  // [nlimbs]  (Q_j/q_i)^-1 / N mod q_i
   ulonglong2* dn_scale = nullptr;  // [K]       2^64 (P/p_k)^-1 / N mod p_k
   u64* dn_mat_plain = nullptr;     // dn_mat without the Montgomery factor
-  u64 *up_conv = nullptr, *up_conv_off = nullptr;   // up_mat, up_off as conv_rows_kernel takes them: scaled by 2^60 where
-  u64 *dn_conv = nullptr, *dn_conv_off = nullptr;   // those are scaled by 2^90; the same for dn_mat_plain, dn_off
+  uint4* up_pieces = nullptr;      // [beta][next], [nlimbs] matrices of bytes of (Q_j/q_i) mod m_t, (P/p_k) mod q_i for
+  uint4* dn_pieces = nullptr;      // conv_rows_kernel (ConvRows; at most 8 sources); dn: with 2^-64 on integer-class targets
   u64* up_off = nullptr;           // [beta][next] -sum_i ((q_i-1)/2) (Q_j/q_i) mod m_t, scaled like up_mat
-  double* up_matd = nullptr;       // [beta][next][up_pitch - 1] centred (Q_j/q_i) mod m_t on double-precision targets
-  double* dn_matd = nullptr;       // [nlimbs][dn_pitch - 1] centred (P/p_k) mod q_i on double-precision targets
   u64* dn_off = nullptr;           // [nlimbs]     -sum_k ((p_k-1)/2) (P/p_k) mod q_i, scaled like dn_mat_plain
   u32 up_pitch = 0, dn_pitch = 0;  // constants per target in up_mat / dn_mat_plain
   ulonglong2* pinv2 = nullptr;     // [nlimbs]  2^64 / P mod q_i
@@ -186,6 +184,7 @@ struct ckks_ctx {
   // or 5 changes): levels[nlimbs] points into one device allocation, d_levels.
   std::vector<LevelTables> levels;
   char* d_levels = nullptr;
+  ConvReduction* d_conv_red = nullptr;   // [nm], inside d_levels
   void* scratch_ptr = nullptr;  // this device's address of `scratch` (hipGetSymbolAddress at context creation)
 };
 
@@ -253,6 +252,22 @@ struct LevelArena {
   }
 };
 
+// The rows of one target in conv_rows_kernel's matrix of bytes (layout: ConvRows), for sources with constants c[0 .. n)
+// that have `bytes` bytes (double-precision ones 7: the kernel leaves their signs in the eighth).
+void conv_rows_of(std::vector<unsigned char>& out, size_t row, u32 groups, const u64* c, u32 n, u32 bytes, u64 m) {
+  for (u32 k = 0; k < n; k++) {
+    u64 v = c[k];
+    for (u32 i = 0; i < bytes; i++) {
+      const u64 w = ((v > m / 2 ? v - m : v) + 0x8080808080808080ull) ^ 0x8080808080808080ull;   // bytes in [-128, 127]
+      for (u32 p = 0; p < CONV_PIECES; p++)
+        out[(((row * groups + k / 4) * 2 + k / 2 % 2) * CONV_PIECES + p) * 16 + k % 2 * 8 + i] = (unsigned char)(w >> (8 * p));
+      v = h_mul(v, 256, m);
+    }
+  }
+}
+// Number of groups of 4 sources of a fused conversion (0: too many sources for it).
+inline u32 conv_groups(u32 n) { return n <= 4 ? 1 : n <= CONV_MAX_SRC ? 2 : 0; }
+
 // Constants for ciphertexts at `nlimbs` limbs, appended to the arena (pointers are offsets into it).
 LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
   const bool fp_on = c->tune[1] == 0;
@@ -278,7 +293,9 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
   auto mont_rs = [&](u64 v, u64 m) { return t.narrow_rs ? h_mont90(v, m) : h_mont(v, m); };
   std::vector<ulonglong2> up_inv((size_t)t.beta * alpha, ulonglong2{0, 0});
   std::vector<u64> up_mat((size_t)t.beta * next * (R + 1), 0), up_off((size_t)t.beta * next, 0);
-  std::vector<double> up_matd((size_t)t.beta * next * R, 0.0);
+  const u32 up_groups = conv_groups(alpha), dn_groups = conv_groups(K);
+  const size_t group_bytes = 2 * CONV_PIECES * 16;
+  std::vector<unsigned char> up_pieces((size_t)t.beta * next * up_groups * group_bytes, 0), dn_pieces(nlimbs * dn_groups * group_bytes, 0);
   t.up_pitch = R + 1;
   t.dn_pitch = RK + 1;
   for (u32 j = 0; j < t.beta; j++) {
@@ -294,8 +311,17 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
         for (u32 k = lo; k < hi; k++)
           if (k != i) v = h_mul(v, c->mod[k] % m, m);
         up_mat[((size_t)j * next + s) * (R + 1) + (i - lo)] = mont_up(v, m);
-        if (is_fp(m)) up_matd[((size_t)j * next + s) * R + (i - lo)] = v > m / 2 ? -(double)(m - v) : (double)v;
       }
+    }
+    for (u32 s = 0; up_groups && s < next; s++) {
+      const u64 m = ext_mod(s);
+      u64 plain[CONV_MAX_SRC];
+      for (u32 i = lo; i < hi; i++) {
+        plain[i - lo] = 1;
+        for (u32 k = lo; k < hi; k++)
+          if (k != i) plain[i - lo] = h_mul(plain[i - lo], c->mod[k] % m, m);
+      }
+      conv_rows_of(up_pieces, (size_t)j * next + s, up_groups, plain, hi - lo, is_fp(c->mod[lo]) ? 7 : CONV_PIECES, m);
     }
     for (u32 s = 0; s < next; s++) {
       u64 m = ext_mod(s), v = 1;
@@ -314,7 +340,6 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
   }
   std::vector<ulonglong2> dn_inv(K), pinv(nlimbs);
   std::vector<u64> dn_mat((size_t)nlimbs * (RK + 1), 0);
-  std::vector<double> dn_matd((size_t)nlimbs * RK, 0.0);
   for (u32 k = 0; k < K; k++) {
     u64 pk = c->mod[c->nq + k], h = 1;
     for (u32 r = 0; r < K; r++)
@@ -326,7 +351,6 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
       for (u32 r = 0; r < K; r++)
         if (r != k) v = h_mul(v, c->mod[c->nq + r] % m, m);
       dn_mat[(size_t)i * (RK + 1) + k] = mont_dn(v, m);
-      if (is_fp(m)) dn_matd[(size_t)i * RK + k] = v > m / 2 ? -(double)(m - v) : (double)v;
     }
   }
   for (u32 i = 0; i < nlimbs; i++) {
@@ -385,19 +409,16 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
       dn_scale[k] = ulonglong2{w, h_shoup(w, m)};
     }
   }
-  std::vector<u64> up_conv(up_mat), up_conv_off(up_off), dn_conv(dn_mat_plain), dn_conv_off(dn_off);
-  auto by_30_less = [&](std::vector<u64>& v, u32 per_target, u32 targets) {   // (target s: modulus ext_mod(s))
-    for (u32 s = 0; s < targets; s++) {
-      const u64 m = ext_mod(s);
-      u64 inv = 1;   // m^-1 modulo 2^64; then 2^-30 mod m = (1 + m k) / 2^30 with k = -m^-1 mod 2^30
-      for (int it = 0; it < 6; it++) inv *= 2 - m * inv;
-      const u64 r = (u64)((1 + (u128)m * ((0 - inv) & 0x3FFFFFFFull)) >> 30);
-      for (size_t at = (size_t)s * per_target; at < v.size(); at += (size_t)targets * per_target)
-        for (u32 k = 0; k < per_target; k++) v[at + k] = h_mul(v[at + k], r, m);
+  for (u32 i = 0; dn_groups && i < nlimbs; i++) {
+    const u64 m = c->mod[i], first = is_fp(m) ? 1 : h_inv(h_mont(1, m), m);
+    u64 plain[CONV_MAX_SRC];
+    for (u32 k = 0; k < K; k++) {
+      plain[k] = first;
+      for (u32 r = 0; r < K; r++)
+        if (r != k) plain[k] = h_mul(plain[k], c->mod[c->nq + r] % m, m);
     }
-  };
-  if (t.narrow_up) by_30_less(up_conv, R + 1, next), by_30_less(up_conv_off, 1, next);
-  if (t.narrow_dn) by_30_less(dn_conv, RK + 1, nlimbs), by_30_less(dn_conv_off, 1, nlimbs);
+    conv_rows_of(dn_pieces, i, dn_groups, plain, K, is_fp(c->mod[c->nq]) ? 7 : CONV_PIECES, m);
+  }
   std::vector<ulonglong2> rs_one(1), rs_qinv(nlimbs > 1 ? nlimbs - 1 : 0), rs_qinv16(rs_qinv.size());
   std::vector<u64> rs_mat(rs_qinv.size() * 5, 0);
   rs_one[0] = ulonglong2{1, 0};  // floor(1 * 2^64 / q) is filled per use below; with x < q the product x*1 needs no reduction
@@ -419,14 +440,10 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
   t.up_scale = arena.add(up_scale);
   t.dn_scale = arena.add(dn_scale);
   t.dn_mat_plain = arena.add(dn_mat_plain);
-  t.up_conv = arena.add(up_conv);
-  t.up_conv_off = arena.add(up_conv_off);
-  t.dn_conv = arena.add(dn_conv);
-  t.dn_conv_off = arena.add(dn_conv_off);
+  t.up_pieces = (uint4*)arena.add(up_pieces);
+  t.dn_pieces = (uint4*)arena.add(dn_pieces);
   t.up_off = arena.add(up_off);
-  t.up_matd = arena.add(up_matd);
   t.dn_off = arena.add(dn_off);
-  t.dn_matd = arena.add(dn_matd);
   t.pinv2 = arena.add(pinv2);
   t.up_inv = arena.add(up_inv);
   t.up_mat = arena.add(up_mat);
@@ -442,6 +459,13 @@ int build_levels(ckks_ctx* c) {
   LevelArena arena;
   std::vector<LevelTables> lv(c->nq + 1);
   for (u32 nl = 1; nl <= c->nq; nl++) lv[nl] = build_level(c, nl, arena);
+  std::vector<ConvReduction> red(c->nm);   // (read on integer targets of 2^36 or more)
+  for (u32 i = 0; i < c->nm; i++) {
+    const u64 m = c->mod[i];
+    const u32 e = h_bits(m), sh = e > 51 ? e - 51 : 0;
+    red[i] = ConvReduction{sh, e > CONV_INT_MIN_BITS ? -(int)((((u128)1 << (64 + sh)) + m / 2) / m) : 0};
+  }
+  ConvReduction* d_red = arena.add(red);
   DeviceGuard guard(c->device);
   if (!guard.ok) return fail(CKKS_EHIP, "cannot select the context's device");
   char* dev = nullptr;
@@ -456,8 +480,7 @@ int build_levels(ckks_ctx* c) {
     LevelTables& t = lv[nl];
     rebase(t.up_inv); rebase(t.up_mat); rebase(t.dn_inv); rebase(t.dn_mat); rebase(t.pinv);
     rebase(t.up_scale); rebase(t.dn_scale); rebase(t.dn_mat_plain); rebase(t.pinv2);
-    rebase(t.up_conv); rebase(t.up_conv_off); rebase(t.dn_conv); rebase(t.dn_conv_off);
-    rebase(t.up_off); rebase(t.up_matd); rebase(t.dn_matd); rebase(t.dn_off);
+    rebase(t.up_pieces); rebase(t.dn_pieces); rebase(t.up_off); rebase(t.dn_off);
     rebase(t.rs_one); rebase(t.rs_mat); rebase(t.rs_qinv); rebase(t.rs_qinv16);
   }
   if (c->d_levels) {
@@ -466,6 +489,7 @@ int build_levels(ckks_ctx* c) {
     (void)hipFree(c->d_levels);
   }
   c->d_levels = dev;
+  c->d_conv_red = (ConvReduction*)(dev + (size_t)d_red);
   c->levels.swap(lv);
   return CKKS_OK;
 }
@@ -842,41 +866,40 @@ int launch_bconv_rows(const ckks_ctx* c, BconvRowsArgs a, u32 npoly, bool narrow
 }
 
 // Whether the conversion of digits of `alpha` limbs with modulus ids [id0, id0 + n) runs inside the transform passes around it
-// (conv_rows_kernel): the kernel keeps up to 8 sources per position, all of one arithmetic kind, and converts
-// double-precision sources to integer targets in the three-sum form only. Knob 2 = 0 (the default) allows it. One prime of
-// another kind among the main limbs leaves the whole polynomial to the separate kernels, also its digits of one kind.
-bool conv_fits(const ckks_ctx* c, u32 id0, u32 n, u32 alpha, bool narrow) {
+// (conv_rows_kernel): the kernel keeps up to 8 sources per position, all of one arithmetic kind. Knob 2 = 0 (the default) allows it. One prime of
+// another kind among the main limbs leaves the whole polynomial to the separate kernels, also its digits of one kind. So does an
+// integer target below 2^36 (only where knob 1 makes it one), which the reduction of the sums does not take.
+bool conv_fits(const ckks_ctx* c, u32 id0, u32 n, u32 alpha) {
   if (c->tune[2] != 0 || alpha > CONV_MAX_SRC) return false;
   const bool fp = host_class(c, c->mod[id0]) == 0;
   for (u32 i = 1; i < n; i++)
     if ((host_class(c, c->mod[id0 + i]) == 0) != fp) return false;
-  return narrow || !fp;
+  for (u32 i = 0; i < c->nm; i++)
+    if (host_class(c, c->mod[i]) != 0 && h_bits(c->mod[i]) <= CONV_INT_MIN_BITS) return false;
+  return true;
 }
 // A fused conversion about to be launched. READY: the sources' inverse row pass runs in a kernel of its own before it.
 struct ConvJob {
   ConvArgs a;
   u32 npoly;
-  bool fp, narrow, ready;
+  bool fp, ready;
 };
 template <int LOGR, int MAXLEN, bool READY>
 void launch_conv_len(const ConvJob& j, dim3 grid, hipStream_t st) {
   const dim3 block(CONV_THREADS);
-  if (j.fp) hipLaunchKernelGGL((conv_rows_kernel<LOGR, MAXLEN, true, true, READY>), grid, block, 0, st, j.a);
-  else if (j.narrow) hipLaunchKernelGGL((conv_rows_kernel<LOGR, MAXLEN, false, true, READY>), grid, block, 0, st, j.a);
-  else hipLaunchKernelGGL((conv_rows_kernel<LOGR, MAXLEN, false, false, READY>), grid, block, 0, st, j.a);
+  if (j.fp) hipLaunchKernelGGL((conv_rows_kernel<LOGR, MAXLEN, true, READY>), grid, block, 0, st, j.a);
+  else hipLaunchKernelGGL((conv_rows_kernel<LOGR, MAXLEN, false, READY>), grid, block, 0, st, j.a);
 }
 #define CONV_READY_MIN_SRC 6
 template <int LOGR>
 void launch_conv_of(const ConvJob& j, dim3 grid, hipStream_t st) {
   if (j.a.alpha <= 4) launch_conv_len<LOGR, 4, false>(j, grid, st);
-  else if (j.a.alpha <= 6 && j.ready) launch_conv_len<LOGR, 6, true>(j, grid, st);
-  else if (j.a.alpha <= 6) launch_conv_len<LOGR, 6, false>(j, grid, st);
   else if (j.ready) launch_conv_len<LOGR, 8, true>(j, grid, st);
   else launch_conv_len<LOGR, 8, false>(j, grid, st);
 }
 // Modelled time of a conversion whose targets are dealt to n workgroups (shares) per (polynomial, tile): two fit a compute unit, and
 // a lone one runs at two thirds of their joint rate. Every share repeats what is done for the sources (wsrc). Weights are
-// instructions per limb of work, in hundreds.
+// relative numbers of instructions per limb: a target 4 (217 vector instructions a lane) or, integer, 7 (384), a source 4 or 6.
 inline u64 conv_cost(u64 groups, u32 wsrc, u32 wtargets, u32 n) {
   const u64 per_cu = (groups * n + 255) / 256;
   return (per_cu / 2 * 8 + per_cu % 2 * 6) * (wsrc + (wtargets + n - 1) / n);
@@ -909,6 +932,7 @@ void conv_plan(const ckks_ctx* c, ConvJob& job, TargetId target_id) {
   a.twfp = c->d_twfp_fwd;
   a.twifp = c->d_twfp_inv;
   a.mods = c->d_mods;
+  a.red = c->d_conv_red;
   a.nfp = a.nint = 0;
   for (int fp = 1; fp >= 0; fp--)
     for (u32 s = 0; s < a.ntarget; s++) {
@@ -921,7 +945,7 @@ void conv_plan(const ckks_ctx* c, ConvJob& job, TargetId target_id) {
     }
   job.fp = host_class(c, c->mod[a.src_id0]) == 0;
   const u32 len = std::min(a.alpha, a.src_nlimbs), own = a.skip_own ? len : 0;   // own limbs: of the sources' kind, not converted
-  const u32 targets = a.nfp + a.nint - own, wtargets = (a.nfp - (job.fp ? own : 0)) * (job.fp ? 4 : 5) + (a.nint - (job.fp ? 0 : own)) * 8;
+  const u32 targets = a.nfp + a.nint - own, wtargets = (a.nfp - (job.fp ? own : 0)) * 4 + (a.nint - (job.fp ? 0 : own)) * 7;
   const u64 groups = (u64)job.npoly * (c->N / CONV_TILE);
   // From 6 sources on, and where one share would take over a tenth longer than several (a quarter with double-precision sources,
   // whose inverse pass is cheaper), the sources' inverse row pass runs by itself before the shares instead of in each of them
@@ -966,13 +990,9 @@ ConvJob conv_up_job(const ckks_ctx* c, const LevelTables* lt, const u64* dcoef, 
   a.beta = lt->beta;
   a.skip_own = 1;
   a.ntarget = lt->next;
-  a.pitch = lt->up_pitch;
-  a.mat = lt->up_conv;
-  a.off = lt->up_conv_off;
-  a.matd = lt->up_matd;
+  a.pieces = lt->up_pieces;
   a.scale = lt->up_scale;
   job.npoly = B * lt->beta;
-  job.narrow = lt->narrow_up;
   conv_plan(c, job, [&](u32 s) { return s < nlimbs ? s : s - nlimbs + c->nq; });
   return job;
 }
@@ -990,13 +1010,9 @@ ConvJob conv_down_job(const ckks_ctx* c, const LevelTables* lt, const u64* acc, 
   a.beta = 1;
   a.skip_own = 0;
   a.ntarget = nlimbs;
-  a.pitch = lt->dn_pitch;
-  a.mat = lt->dn_conv;
-  a.off = lt->dn_conv_off;
-  a.matd = lt->dn_matd;
+  a.pieces = lt->dn_pieces;
   a.scale = lt->dn_scale;
   job.npoly = B * 2;
-  job.narrow = lt->narrow_dn;
   conv_plan(c, job, [](u32 s) { return s; });
   return job;
 }
@@ -1008,7 +1024,7 @@ int ks16_moddown_rows(ckks_ctx* c, const LevelTables* lt, u32 B, u32 nlimbs, u64
   int rc;
   const u32 N = c->N, next = lt->next, K = c->np;
   const bool fused = c->tune[2] == 1 && c->logN == 16;
-  const bool conv = conv_fits(c, c->nq, K, K, lt->narrow_dn);
+  const bool conv = conv_fits(c, c->nq, K, K);
   LimbMap pmap;
   for (u32 k = 0; k < CKKS_MAX_SLOTS; k++) pmap.id[k] = (unsigned char)(k < K ? c->nq + k : 0);
   NttOpts o3;
@@ -1144,7 +1160,7 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
     if (s_ >= nlimbs) special_fp |= fp;
   }
   const bool fused_up = c->tune[2] == 1 && c->logN == 16;
-  const bool conv_up = conv_fits(c, 0, nlimbs, c->alpha, lt->narrow_up);
+  const bool conv_up = conv_fits(c, 0, nlimbs, c->alpha);
   // 1.
   NttOpts o1;
   o1.galois = io.d_galois;
@@ -1332,7 +1348,7 @@ static int hoist_front16(ckks_ctx* c, const LevelTables* lt, const u64* ct_in, u
   const u64* c1 = ct_in + polyN;
   NttOpts o1, of;
   o1.scale = lt->up_scale;
-  of.blocks_only = conv_fits(c, 0, nlimbs, c->alpha, lt->narrow_up);
+  of.blocks_only = conv_fits(c, 0, nlimbs, c->alpha);
   ConvJob up;
   if (of.blocks_only) {
     up = conv_up_job(c, lt, dcoef, ext, B, nlimbs);

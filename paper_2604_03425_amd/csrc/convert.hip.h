@@ -4,25 +4,25 @@
 // times more and the targets two times more. Where several workgroups share the targets of a tile, the inverse pass may be a
 // kernel of its own before this one (READY, chosen in conv_plan).
 //
-// A conversion needs all sources of a position in one lane and a row pass all rows of a column in one workgroup. A workgroup
-// of 512 lanes takes R rows x NC = 2048 / R columns, four positions per lane, and keeps the converted form of all sources
-// (8 x 4 words = 64 registers) there while it walks over the targets (integer sources that are transformed here: a quarter
-// of the words in scratch memory, stored once and reloaded once per target list; the compiler does not promote them). Four positions per lane is what makes the sources fit
-// beside a transform at 4 waves per SIMD; the row pass is then radix-4 rounds with up to three exchanges through LDS (two
-// of them across waves), whose two tiles alternate so that an exchange costs one barrier. Two workgroups share a compute
-// unit, so one computes while the other waits.
+// A conversion needs all sources of a position and a row pass all rows of a column in one workgroup. A workgroup of 512 lanes
+// takes R rows x NC = 2048 / R columns, four positions per lane, and keeps all sources (8 x 4 words = 64 registers) while it walks
+// over the targets. The conversion is a product of small integers on the matrix cores (see below), for two targets at a time: the
+// second one's values wait in LDS (registers where there are four sources or fewer) while the first is transformed. Four positions
+// per lane is what makes the sources fit beside a transform at 4 waves per SIMD; the row pass is then radix-4 rounds with up to
+// three exchanges through LDS (two of them across waves), whose two tiles alternate so that an exchange costs one barrier. Two
+// workgroups share a compute unit, so one computes while the other waits.
 //
 // Element e = row * NC + column of the tile; round K (stages 2K, 2K+1) holds, in lane t, the elements
 // (t >> s) << (s + 2) | i << s | (t mod 2^s), s = 9 - 2K: the linear layout of a radix-4 transform of 2048 values of which
 // only the first LOGR stages are done. The last round has s = 11 - LOGR, a lane then holds four adjacent rows of a column;
 // for odd LOGR only the second of its two stages is left to do.
 //
-// What bounds it: instruction issue (0.62 of the vector peak by executed instructions at 2.3 TB/s). Per target and position the conversion
-// of 8 double-precision sources costs 38 FP64 instructions (see convert_fp), its row pass 35; an integer target about
-// twice that. N = 2^16, 64 ciphertexts of 24 limbs, 3 digits of 8, 8 special primes: inverse row pass, ModUp and row passes as
-// four kernels 2030 us, here 1476 (1551 with canonical results of the integer sums, 9 instructions at the end of a
-// double-precision one and two reductions a row pass); the same for ModDown's three 1440 and 1090 (1148). One such ciphertext: 62 ->
-// 46 and 49 -> 34 us.
+// What bounds it: instruction issue, at a clock rate that falls with the power the instructions take (1.65 - 1.75 GHz here).
+// Vector instructions per target and position: 17 for the conversion (20 to an integer target), 38 and 74 for the row pass, LDS
+// addresses included; on the vector units alone the conversion of 8 sources took 38 (double precision on both sides), 56 (integer
+// sources) and 50 (integer targets). N = 2^16, 64 ciphertexts of 24 limbs, 3 digits of 8, 8 special primes: ModUp 1394 -> 1303 us,
+// ModDown 1034 -> 893; one such ciphertext 35.5 -> 31.6 and 24.1 -> 22.2 (inverse pass apart). The conversion, row passes and
+// inverse pass as kernels of their own took 2030 and 1440 us.
 #pragma once
 #include "radix4.hip.h"
 #include "ntt16_kernels.hip.h"
@@ -35,6 +35,13 @@
 #define CONV_TILE 2048
 #define CONV_MAX_SRC 8
 
+// Reduction constants of an integer target m < 2^e: sh = max(0, e - 51), mu = -2^(64 + sh) / m to the nearest integer.
+#define CONV_INT_MIN_BITS 36   // integer targets have more bits
+struct ConvReduction {
+  u32 sh;
+  int mu;
+};
+
 struct ConvArgs {
   const u64* src;            // sources after the inverse block pass (reduced doubles / lazy integers, by class)
   u64* dst;                  // targets after the row pass
@@ -46,11 +53,8 @@ struct ConvArgs {
   u32 ntarget;               // targets of a digit in the constant tables
   u32 nfp, nint;             // targets by arithmetic kind: tslot[0 .. nfp), tslot[nfp .. nfp + nint)
   u32 nsplit;                // workgroups that share the targets of a (polynomial, tile)
-  u32 pitch;                 // constants per target in mat
-  // integer conversion: [beta][ntarget][pitch] constants (C/c_k) mod m_t and [beta][ntarget] the offset of the shifted sources,
-  // scaled by 2^60 under NARROW (by 2^64 otherwise): LevelTables::up_conv, dn_conv and their _off, not up_mat, dn_mat_plain
-  const u64 *mat, *off;
-  const double* matd;        // [beta][ntarget][pitch - 1] centred constants (double-precision sources and targets)
+  const uint4* pieces;       // [beta][ntarget] matrices of bytes of the constants (layout: conv_request_rows)
+  const ConvReduction* red;     // [nm] per modulus id, read on integer targets
   const ulonglong2* scale;   // [src_nlimbs] per source (Q_j/q_i)^-1 / N, in the form of its class
   const ulonglong2 *tw, *twi;
   const double *twfp, *twifp;
@@ -140,7 +144,8 @@ __device__ __forceinline__ void conv_twiddles_last(TW (&w)[2], const TW* __restr
 
 // ---- double precision: forward and inverse row passes ----
 // A forward pass gets its first rounds' twiddles (ConvTwiddles) from the caller, who requests them ahead of the conversion;
-// the later ones' are requested as the registers for them become free. In: |x| <= 1.5 q. Out: at most 2.64 q (three stages
+// the later ones' are requested as the registers for them become free. `freed` runs when the first
+// ones are dead. In: |x| <= 1.5 q. Out: at most 2.64 q (three stages
 // from a reduced value), which the block passes take: one reduction, after four or five stages.
 template <class TW>
 struct ConvTwiddles {
@@ -150,9 +155,9 @@ struct ConvTwiddles {
     conv_twiddles(w1, tw, 1);
   }
 };
-template <int LOGR>
+template <int LOGR, class FREED>
 __device__ __forceinline__ void conv_fwd_rows(double (&x)[4], const ConvTwiddles<double>& w, const double* __restrict__ tw,
-                                              double q, double qinv, double* sm) {
+                                              double q, double qinv, double* sm, FREED freed) {
   constexpr int L = 11 - LOGR;
   double w2[3], w3[3], wl[2];
   if (LOGR >= 6) conv_twiddles(w2, tw, 2);
@@ -161,6 +166,7 @@ __device__ __forceinline__ void conv_fwd_rows(double (&x)[4], const ConvTwiddles
   if (LOGR == 8) conv_twiddles(w3, tw, 3);
   if (LOGR & 1) conv_twiddles_last<LOGR>(wl, tw);
   radix4_fwd(x, w.w1, q, qinv);
+  freed();
   if (LOGR < 8) reduce4(x, q, qinv);
   if (LOGR >= 6) {
     conv_exchange<7, 5>(x, sm);
@@ -209,9 +215,9 @@ __device__ __forceinline__ void conv_inv_rows(double (&x)[4], const double* __re
   reduce4(x, q, qinv);
 }
 // ---- integer classes, Harvey's ranges for every prime below 2^60: [0,16q) forward, [0,8q) inverse ----
-template <int LOGR>
+template <int LOGR, class FREED>
 __device__ __forceinline__ void conv_fwd_rows(u64 (&x)[4], const ConvTwiddles<ulonglong2>& w,
-                                              const ulonglong2* __restrict__ tw, u64 q, u64* sm) {
+                                              const ulonglong2* __restrict__ tw, u64 q, u64* sm, FREED freed) {
   constexpr int L = 11 - LOGR;
   const u64 q2 = lazy_const<true>(q);
   ulonglong2 w2[3], w3[3], wl[2];
@@ -219,6 +225,7 @@ __device__ __forceinline__ void conv_fwd_rows(u64 (&x)[4], const ConvTwiddles<ul
   conv_exchange<9, 7>(x, sm);
   if (LOGR >= 6) conv_twiddles(w2, tw, 2);
   radix4_fwd<true>(x, w.w1, q, q2);
+  freed();
   if (LOGR & 1) conv_twiddles_last<LOGR>(wl, tw);
   if (LOGR >= 6) {
     conv_exchange<7, 5>(x, sm);
@@ -257,100 +264,180 @@ __device__ __forceinline__ void conv_inv_rows(u64 (&x)[4], const ulonglong2* __r
   radix4_inv<true>(x, w0, q, q2);
 }
 
-// ---- conversions at the lane's four positions ----
-// What is uniform about a target: its modulus and row of constants (zero beyond the digit's length). Fetched one target
-// ahead, its place in the list two ahead, so that no target starts by waiting for a chain of scalar loads.
-template <int MAXLEN>
+// ---- conversions on the matrix cores ----
+// A source y (centred, below 2^60 in magnitude) is cut into 8 bytes y = sum_i y_i 2^(8 i), each in [-128, 127]; on the other
+// side stand the bytes of C_ki = c_k 2^(8 i) mod m, centred. Then
+//   sum_k y_k c_k  =  sum_p 2^(8 p) S_p  (mod m),   S_p = sum_(k,i) y_ki (byte p of C_ki),
+// a product of an 8-row matrix of bytes per target with 8 bytes per source and position: at most 64 products of 2^14 to a sum,
+// exact in 32 bits. What is left for the vector units is to put eight sums together, modulo m: the whole is below 2^12 m.
+// v_mfma_i32_32x32x32_i8 takes four sources: lane (h, n) = (lane / 32, lane % 32) supplies 16 bytes, sources 2h and 2h + 1 of
+// position n in the second operand, of row n in the first, and receives rows 8b + 4h + r of column n. Rows are dealt so that lane
+// half h gets the 8 sums (b, r) = (p / 4, p % 4) of target h of a pair; the upper 16 rows of the product are not used (a full
+// one would serve four targets, whose results do not fit the registers; the matrix cores are idle nine tenths of the time). A lane's four
+// positions of all sources become the operands of 2 x 4 products by swaps of half-waves, in place.
+typedef int conv_i32x4 __attribute__((ext_vector_type(4)));
+typedef const __attribute__((address_space(3))) u32* lds_const_ptr;
+typedef int conv_i32x16 __attribute__((ext_vector_type(16)));
+#define CONV_PIECES 8   // bytes of a constant, and of a source
+
+// A source at one position: its 8 bytes, as a word.
+// |v| < 2^49, an integer. 1.5 * 2^52 + v + 0x808080808080: the low 48 bits are the lower six bytes plus 128 each, the four above
+// them the next byte (what is left there after taking away the exponent and 2^51); byte 7 meets zeros.
+__device__ __forceinline__ u64 conv_cut(double v) {
+  const double t = v + (6755399441055744.0 + 141289400074368.0);
+  const u32 lo = (u32)__double2loint(t) ^ 0x80808080u, hi = ((u32)__double2hiint(t) ^ 0x8080u) - 0x43380000u;
+  return (u64)hi << 32 | lo;
+}
+// shifted = v + h in [0, 2^60); off8 = 0x8080808080808080 - h
+__device__ __forceinline__ u64 conv_cut(u64 shifted, u64 off8) { return (shifted + off8) ^ 0x8080808080808080ull; }
+// Swaps the upper half-wave of x with the lower one of y.
+__device__ __forceinline__ void conv_swap32(u32& x, u32& y) {
+  const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+  x = r[0];
+  y = r[1];
+}
+// a * b + c in 64 bits, one instruction. (Not as an asm statement: next to matrix instructions the compiler has to see what
+// writes a register, or it gives out one that a product in flight has yet to write.)
+__device__ __forceinline__ long long conv_mad(int a, int b, long long c) { return (long long)a * b + c; }
+// b, hidden from the compiler, which would make shifts of a product by a power of two
+__device__ __forceinline__ int conv_opaque(int b) {
+  asm("" : "+s"(b));
+  return b;
+}
+// What is uniform about a target. Fetched one pair of targets ahead, its place in the list two ahead, so that no target starts
+// by waiting for a chain of scalar loads.
 struct ConvTarget {
-  u32 slot, id;
-  u64 m, minv, off, c[MAXLEN];
+  u32 slot, id, sh;
+  int mu;
+  u64 m;
   double qd, qinv;
-  template <bool CHAIN>   // the constants of convert_fp
-  __device__ __forceinline__ void fetch(const ConvArgs& a, u32 target, u32 j) {
+  __device__ __forceinline__ void fetch(const ConvArgs& a, u32 target) {
     slot = target & 255;
     id = target >> 8;
     const ModInfo mi = conv_mod(a.mods, id);
-    m = mi.m, minv = mi.minv, qd = mi.qd, qinv = mi.qinv;
-    const size_t row = (size_t)j * a.ntarget + slot;
-    const_u64_ptr p = CHAIN ? conv_const(a.matd + row * (a.pitch - 1)) : conv_const(a.mat + row * a.pitch);
-#pragma unroll
-    for (int k = 0; k < MAXLEN; k++) c[k] = p[k];
-    off = CHAIN ? 0 : *conv_const(a.off + row);
+    m = mi.m, qd = mi.qd, qinv = mi.qinv;
+    const u64 red = conv_const(a.red)[id];
+    sh = (u32)red;
+    mu = (int)(red >> 32);
   }
 };
-// A source at one position: the centred double, or the 30-bit halves of (y + (q-1)/2) mod q that the integer conversion
-// reads; zero beyond the digit's length.
-struct ConvWord {
-  u32 lo, hi;
-  __device__ __forceinline__ void set(double v) { lo = (u32)__double2loint(v), hi = (u32)__double2hiint(v); }
-  __device__ __forceinline__ double value() const { return __hiloint2double((int)hi, (int)lo); }
-  __device__ __forceinline__ void split(u64 v) { lo = (u32)v & BCONV_M30, hi = (u32)(v >> 30); }
-};
-// acc += y * c for a constant c that is the same in all lanes. As an instruction: written as a 64-bit product the widened y
-// is hoisted out of the target loop, which doubles the registers of the sources.
-__device__ __forceinline__ void conv_mad(u64& acc, u32 y, u32 c) {
-  asm("v_mad_u64_u32 %0, vcc, %1, %2, %0" : "+v"(acc) : "v"(y), "s"(c) : "vcc");
-}
-// Double-precision sources (centred integers, |y| < 2^49) to a double-precision target with centred constants |c| < 2^49:
-// the products are summed exactly as H + L. H starts at 1.5 * 2^102, in whose binade adding a product rounds it to a
-// multiple of 2^50; what that adds to H is exact (both lie in the binade: at most 8 products of 2^98), and so is the rest of
-// the product, an integer of magnitude at most 2^49, which goes to L (at most 2^52). Then H - 1.5 * 2^102 + L = c q + x with the
-// quotient off by at most 1.25, so that H - 1.5 * 2^102 - c q = x - L stays below 2^53. 4 FP64 instructions a term and 6 at the
-// end, against 4 multiply-adds a term and 19 for the sum of 30-bit pieces. Out: |x| <= 1.3 q.
+// The lanes' rows of a pair of targets: lane (h, n) has bytes of sources 4g + 2h and 4g + 2h + 1 (byte p of every C_ki, i
+// ascending), p = 4 * bit 3 of n + the two lowest bits of n, of target bit 2 of n. Wave g < MAXLEN / 4 copies the rows of group g
+// straight into LDS, 16 bytes a lane.
+#define CONV_ROWS_WORDS(MAXLEN) ((MAXLEN) / 4 * 256)
 template <int MAXLEN>
-__device__ __forceinline__ void convert_fp(double (&x)[4], const ConvWord (&y)[MAXLEN][4], const ConvTarget<MAXLEN>& tg) {
-  static_assert(MAXLEN <= 8, "more products leave the binade of H");
-  const double q = tg.qd, qinv = tg.qinv;
-  constexpr double M = 1.5 * 5070602400912917605986812821504.0;   // 1.5 * 2^102
-  double H[4], L[4];
-#pragma unroll
-  for (int i = 0; i < 4; i++) H[i] = M, L[i] = 0.0;
-#pragma unroll
-  for (int k = 0; k < MAXLEN; k++) {
-    const double ck = __longlong_as_double((long long)tg.c[k]);
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const double yk = y[k][i].value(), Hn = __builtin_fma(yk, ck, H[i]);
-      const double h = Hn - H[i];
-      L[i] += __builtin_fma(yk, ck, -h);
-      H[i] = Hn;
-    }
+__device__ __forceinline__ void conv_request_rows(const ConvArgs& a, u32 first_row, u32 slot0, u32 slot1, u32* image) {
+  const u32 g = conv_uniform(threadIdx.x >> 6);
+  if (g >= MAXLEN / 4) return;
+  u32 l = threadIdx.x & 63;
+  asm volatile("" : "+v"(l));
+  const u32 h = l >> 5, p = (l & 3) + 4 * ((l >> 3) & 1), row = first_row + ((l & 4) ? slot1 : slot0);
+  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)a.pieces, 0, (int)(a.beta * a.ntarget * (MAXLEN / 4) * 2 * CONV_PIECES * 16), 0x00020000);
+  // (beyond the table, so read as zeros, for the unused rows: they would cost power, which is what the clock rate depends on)
+  const int at = (l & 16) ? 0x7FFFFFF0 : (int)((((row * (MAXLEN / 4) + g) * 2 + h) * CONV_PIECES + p) * 16);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)(image + g * 256), 16, at, 0, 0, 0);
+}
+// All vector memory requests of the wave are back, said so that the compiler knows.
+__device__ __forceinline__ void conv_wait_vector_memory() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+  asm volatile("" ::: "memory");
+}
+template <int MAXLEN>
+struct ConvRows {
+  conv_i32x4 a[MAXLEN / 4];
+  // As an asm statement with its own wait: the compiler, which does not see the barriers that order it after the copy, would wait
+  // for everything requested since, stores included. (No product is in flight here whose registers it could be given.)
+  __device__ __forceinline__ void take(const u32* image) {
+    const u32 at = (u32)(size_t)(lds_const_ptr)image + (threadIdx.x & 63) * 16;
+    if (MAXLEN == 4) asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(a[0]) : "v"(at) : "memory");
+    else
+      asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:1024\n\ts_waitcnt lgkmcnt(0)"
+                   : "=&v"(a[0]), "=&v"(a[MAXLEN / 4 - 1]) : "v"(at) : "memory");
   }
+};
+// The eight sums of a target at the lane's column, put together: lo + hi 2^32 (mod m), lo < 2^32.
+__device__ __forceinline__ void conv_join(u32& lo, long long& hi, const conv_i32x16& d) {
+  const int a0 = d[0] + (d[1] << 8), a1 = d[2] + (d[3] << 8), a2 = d[4] + (d[5] << 8), a3 = d[6] + (d[7] << 8);
+  const int w = conv_opaque(65536);
+  const long long l = conv_mad(a1, w, a0), h = conv_mad(a3, w, a2);
+  lo = (u32)l;
+  hi = h + (l >> 32);
+}
+// The same where the whole is below 2^62 (m < 2^50), so that hi fits 32 bits.
+__device__ __forceinline__ void conv_join(u32& lo, int& hi, const conv_i32x16& d) {
+  const int a0 = d[0] + (d[1] << 8), a1 = d[2] + (d[3] << 8), a2 = d[4] + (d[5] << 8), a3 = d[6] + (d[7] << 8);
+  const long long l = conv_mad(a1, conv_opaque(65536), a0);
+  lo = (u32)l;
+  hi = (int)((u32)(l >> 32) + (u32)a2 + ((u32)a3 << 16));
+}
+// |x| <= q / 2 (and a rounding): lo + hi 2^32 less its nearest multiple of q; the difference before lo is added is below 2^53.
+__device__ __forceinline__ double conv_settle(u32 lo, int hi, double q, double qinv) {
+  const double l = (double)lo, h = (double)hi;
+  const double c = __builtin_rint(__builtin_fma(l, qinv, h * (qinv * 4294967296.0)));
+  return __builtin_fma(__builtin_fma(-c, q * (1.0 / 4294967296.0), h), 4294967296.0, l);
+}
+// V = lo + hi 2^32, |V| <= 2^12 m: V + s m with s = 2 + floor((hi >> sh) mu / 2^32), which is within [-V / m + 0.75, -V / m + 2.33] (mu
+// is off by a half, hi >> sh below 2^31 by one): in [0.75 m, 2.33 m]. Needs 2^36 <= m < 2^60.
+__device__ __forceinline__ u64 conv_settle(u32 lo, long long hi, const ConvTarget& tg) {
+  const int t = (int)__builtin_amdgcn_alignbit((u32)(hi >> 32), (u32)hi, tg.sh);
+  const int s = __mulhi(t, tg.mu) + 2;
+  const int m0 = (int)(u32)tg.m;
+  const u32 m1 = (u32)(tg.m >> 32) + ((u32)tg.m >> 31);
+  const u64 v = (u64)conv_mad(s, m0, (long long)((u64)(u32)hi << 32 | lo));
+  return (u64)((u32)(v >> 32) + (u32)s * m1) << 32 | (u32)v;
+}
+// All sources at the lane's four positions as operands: y[i][f][g], columns = positions i of lane half f, sources 4g .. 4g + 3.
+template <int MAXLEN>
+struct ConvSources {
+  conv_i32x4 y[4][2][MAXLEN / 4];
+};
+template <int MAXLEN>
+__device__ __forceinline__ conv_i32x16 conv_product(const ConvRows<MAXLEN>& r, const conv_i32x4 (&y)[MAXLEN / 4]) {
+  conv_i32x16 d = {};
+#pragma unroll
+  for (int g = 0; g < MAXLEN / 4; g++) d = __builtin_amdgcn_mfma_i32_32x32x32_i8(r.a[g], y[g], d, 0, 0, 0);
+  return d;
+}
+// A pair of double-precision targets at the lane's four positions: |x| <= q / 2. x1 takes the second one's.
+template <int MAXLEN, class X1>
+__device__ __forceinline__ void convert(double (&x0)[4], X1 x1, const ConvSources<MAXLEN>& y, const ConvRows<MAXLEN>& r,
+                                        const ConvTarget& t0, const ConvTarget& t1) {
 #pragma unroll
   for (int i = 0; i < 4; i++) {
-    const double h = H[i] - M;
-    x[i] = __builtin_fma(-__builtin_rint(__builtin_fma(L[i], qinv, h * qinv)), q, h) + L[i];
+    u32 lo[2], hi[2];
+#pragma unroll
+    for (int f = 0; f < 2; f++) {
+      int h;
+      conv_join(lo[f], h, conv_product<MAXLEN>(r, y.y[i][f]));
+      hi[f] = (u32)h;
+    }
+    conv_swap32(lo[0], lo[1]);
+    conv_swap32(hi[0], hi[1]);
+    x0[i] = conv_settle(lo[0], (int)hi[0], t0.qd, t0.qinv);
+    x1(i, conv_settle(lo[1], (int)hi[1], t1.qd, t1.qinv));
   }
 }
-// Split-form sources to any target. NARROW: below 9m, plus `bias`: 0, or 2^62 less a multiple of m, which leaves the residue to a
-// caller that takes 2^62 away again. Otherwise canonical.
-template <int MAXLEN, bool NARROW>
-__device__ __forceinline__ void convert_int(u64 (&x)[4], const ConvWord (&y)[MAXLEN][4], const ConvTarget<MAXLEN>& tg, u64 bias) {
-  static_assert(MAXLEN <= 8, "the transforms that follow take values below 9m");
-  Dot30N n[4];
-  Dot30 g[4];
+// A pair of integer targets: below 2.34 m.
+template <int MAXLEN, class X1>
+__device__ __forceinline__ void convert(u64 (&x0)[4], X1 x1, const ConvSources<MAXLEN>& y, const ConvRows<MAXLEN>& r,
+                                        const ConvTarget& t0, const ConvTarget& t1) {
 #pragma unroll
   for (int i = 0; i < 4; i++) {
-    n[i].a = g[i].s00 = (u32)tg.off & BCONV_M30;
-    n[i].b = g[i].s01 = tg.off >> 30;
-    g[i].s10 = g[i].s11 = 0;
-    n[i].c = bias;
-  }
+    u32 lo[2], mid[2], hi[2];
 #pragma unroll
-  for (int k = 0; k < MAXLEN; k++) {
-    const u32 c0 = (u32)tg.c[k] & BCONV_M30, c1 = (u32)(tg.c[k] >> 30);
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      conv_mad(NARROW ? n[i].a : g[i].s00, y[k][i].lo, c0);
-      conv_mad(NARROW ? n[i].b : g[i].s01, y[k][i].lo, c1);
-      conv_mad(NARROW ? n[i].b : g[i].s10, y[k][i].hi, c0);
-      conv_mad(NARROW ? n[i].c : g[i].s11, y[k][i].hi, c1);
+    for (int f = 0; f < 2; f++) {
+      long long h;
+      conv_join(lo[f], h, conv_product<MAXLEN>(r, y.y[i][f]));
+      mid[f] = (u32)h;
+      hi[f] = (u32)(h >> 32);
     }
-  }
-#pragma unroll
-  for (int i = 0; i < 4; i++) {   // one position at a time: folding all four side by side would spill
-    x[i] = NARROW ? dot30n_redc60(n[i], tg.m, tg.minv) : csub(redc(dot30_value(g[i]), tg.m, tg.minv), tg.m);
-    __builtin_amdgcn_sched_barrier(0);
+    conv_swap32(lo[0], lo[1]);
+    conv_swap32(mid[0], mid[1]);
+    conv_swap32(hi[0], hi[1]);
+    x0[i] = conv_settle(lo[0], (long long)((u64)hi[0] << 32 | mid[0]), t0);
+    x1(i, conv_settle(lo[1], (long long)((u64)hi[1] << 32 | mid[1]), t1));
   }
 }
 
@@ -368,9 +455,11 @@ __device__ __forceinline__ void conv_each(F f) {
 // One workgroup per (polynomial, tile, share of the targets), tiles fastest. The 64-byte row pieces of two adjacent tiles
 // (N = 2^16) make one line: the XCD-contiguous order keeps them on one L2.
 // READY: src holds what the inverse row pass makes of the sources (canonical residues, scaled).
-template <int LOGR, int MAXLEN, bool SRC_FP, bool NARROW, bool READY>
+template <int LOGR, int MAXLEN, bool SRC_FP, bool READY>
 __global__ void __launch_bounds__(CONV_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4))) conv_rows_kernel(ConvArgs a) {
   __shared__ u64 sm[2 * CONV_TILE_WORDS];
+  __shared__ u64 second[MAXLEN == 4 ? 1 : CONV_TILE];
+  __shared__ __attribute__((aligned(16))) u32 rows_image[2 * CONV_ROWS_WORDS(MAXLEN)];
   constexpr int L = 11 - LOGR, LOGN = LOGR + 8;
   constexpr u32 TILES = 1u << (LOGN - 11);
   const u32 lin = xcd_swizzled_linear_id();
@@ -383,7 +472,7 @@ __global__ void __launch_bounds__(CONV_THREADS) __attribute__((amdgpu_waves_per_
   // the sources' positions: READY in the first round's layout, in which the targets start
   const u32 from = READY ? (threadIdx.x >> L) * 256 + (tile << L) + (threadIdx.x & ((1u << L) - 1)) : pos;
   constexpr u32 step = READY ? (CONV_THREADS >> L) * 256 : 256;
-  ConvWord y[MAXLEN][4];   // doubles from double-precision sources, until the integer targets
+  u64 y[MAXLEN][4];
   u64 ahead[4];   // the next source's words are requested before the current one is transformed
 #pragma unroll
   for (int i = 0; i < 4; i++) ahead[i] = src[from + i * step];
@@ -391,7 +480,7 @@ __global__ void __launch_bounds__(CONV_THREADS) __attribute__((amdgpu_waves_per_
     constexpr int k = decltype(kc)::value;
     if ((u32)k >= len) {   // uniform
 #pragma unroll
-      for (int i = 0; i < 4; i++) y[k][i].lo = y[k][i].hi = 0;
+      for (int i = 0; i < 4; i++) y[k][i] = 0;
       return;
     }
     const u32 id = a.src_id0 + lo + k;
@@ -419,7 +508,7 @@ __global__ void __launch_bounds__(CONV_THREADS) __attribute__((amdgpu_waves_per_
       }
       // |x| <= q, and (q + 1) / 2 is 2^-51 or more away from q/2 in units of q: no rounding of x / q can pass one half
 #pragma unroll
-      for (int i = 0; i < 4; i++) y[k][i].set(fp_reduce(x[i], mi.qinv, mi.qd));
+      for (int i = 0; i < 4; i++) y[k][i] = conv_cut(fp_reduce(x[i], mi.qinv, mi.qd));
     } else {
       u64 x[4];
 #pragma unroll
@@ -429,14 +518,31 @@ __global__ void __launch_bounds__(CONV_THREADS) __attribute__((amdgpu_waves_per_
 #pragma unroll
         for (int i = 0; i < 4; i++) x[i] = shoup(x[i], sc.x, sc.y, mi.m);
       }
+      const u64 h = mi.m >> 1, off8 = 0x8080808080808080ull - h;
 #pragma unroll
-      for (int i = 0; i < 4; i++) y[k][i].split(csub(x[i] + (mi.m >> 1), mi.m));
+      for (int i = 0; i < 4; i++) y[k][i] = conv_cut(csub(x[i] + h, mi.m), off8);
     }
   });
-  lds_barrier();   // the last inverse exchange has been read everywhere
-  // targets n, n + nsplit, .. of list [first, first + count) less the digit's own limbs, which stand together in the list of
-  // their kind (lists are in the order of the slots): `body` does one
-  auto walk = [&](u32 first, u32 count, bool own_kind, u32 n, auto chain, auto body) {
+  ConvSources<MAXLEN> ys;
+#pragma unroll
+  for (int i = 0; i < 4; i++)
+#pragma unroll
+    for (int g = 0; g < MAXLEN / 4; g++) {
+      u32 p[2][4];
+#pragma unroll
+      for (int f = 0; f < 2; f++)
+#pragma unroll
+        for (int k = 0; k < 2; k++) p[f][2 * k] = (u32)y[4 * g + 2 * f + k][i], p[f][2 * k + 1] = (u32)(y[4 * g + 2 * f + k][i] >> 32);
+#pragma unroll
+      for (int w = 0; w < 4; w++) conv_swap32(p[0][w], p[1][w]);
+#pragma unroll
+      for (int f = 0; f < 2; f++) ys.y[i][f][g] = conv_i32x4{(int)p[f][0], (int)p[f][1], (int)p[f][2], (int)p[f][3]};
+    }
+  // Targets n, n + nsplit, .. of list [first, first + count) less the digit's own limbs, which stand together in the list of
+  // their kind (lists are in the order of the slots), in pairs. `zero`: of the type of their values.
+  auto walk = [&](u32 first, u32 count, bool own_kind, u32 n, auto* tables, auto zero, auto transform) {
+    typedef decltype(zero) V;
+    typedef std::remove_const_t<std::remove_pointer_t<decltype(tables)>> TW;
     const u32 skip = own_kind && a.skip_own ? len : 0;
     count -= skip;
     if (n >= count) return;
@@ -444,60 +550,60 @@ __global__ void __launch_bounds__(CONV_THREADS) __attribute__((amdgpu_waves_per_
       i = min(i, count - 1);
       return a.target[first + i + (i >= lo ? skip : 0)];
     };
-    ConvTarget<MAXLEN> cur, next;
-    cur.template fetch<decltype(chain)::value>(a, at(n), j);
-    u32 info = at(n + a.nsplit);
+    u32 i0 = at(n), i1 = at(n + a.nsplit), buffer = 0;
+    ConvTarget t0, t1, n0, n1;
+    conv_request_rows<MAXLEN>(a, j * a.ntarget, i0 & 255, i1 & 255, rows_image);
+    n0.fetch(a, i0);
+    n1.fetch(a, i1);
+    i0 = at(n + 2 * a.nsplit);
+    i1 = at(n + 3 * a.nsplit);
+    conv_wait_vector_memory();
+    lds_barrier();   // (the last inverse exchange has been read everywhere, too)
 #pragma nounroll
-    for (; n < count; n += a.nsplit) {
-      next.template fetch<decltype(chain)::value>(a, info, j);
-      info = at(n + 2 * a.nsplit);
-      body(cur);
-      cur = next;
-    }
-  };
-  auto fp_target = [&](const ConvTarget<MAXLEN>& tg) {
-    const double* tw = a.twfp + ((size_t)tg.id << LOGN);
-    ConvTwiddles<double> w;
-    w.load(tw);
-    __builtin_amdgcn_sched_barrier(0);
-    double x[4];
-    if (SRC_FP) {
-      convert_fp<MAXLEN>(x, y, tg);
-    } else {
-      u64 v[4];   // in [-4m, 5m), below 2^53 in magnitude, as an offset from 2^62
-      convert_int<MAXLEN, NARROW>(v, y, tg, (1ull << 62) - 4 * tg.m);
-#pragma unroll
-      for (int i = 0; i < 4; i++) x[i] = NARROW ? fp_reduce(u2d_biased62(v[i]), tg.qinv, tg.qd) : u2d(v[i]);
-    }
-    conv_fwd_rows<LOGR>(x, w, tw, tg.qd, tg.qinv, (double*)sm);
-    double* d = (double*)dst + ((size_t)tg.slot << LOGN) + pos;
-#pragma unroll
-    for (int i = 0; i < 4; i++) d[i * 256] = x[i];
-  };
-  if (SRC_FP) walk(0, a.nfp, true, share, std::true_type{}, fp_target);
-  else walk(0, a.nfp, false, share, std::false_type{}, fp_target);
-  if (a.nint == 0) return;
-  if (SRC_FP) {
-    conv_each<MAXLEN>([&](auto kc) {
-      constexpr int k = decltype(kc)::value;
-      const double h = (u32)k < len ? (conv_mod(a.mods, a.src_id0 + lo + min((u32)k, len - 1)).qd - 1.0) * 0.5 : 0.0;
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-        y[k][i].split((u64)__double_as_longlong(y[k][i].value() + h + 4503599627370496.0) & 0x000FFFFFFFFFFFFFull);
+    for (; n < count; n += 2 * a.nsplit) {
+      t0 = n0, t1 = n1;
+      ConvTwiddles<TW> w;
+      w.load(tables + ((size_t)t0.id << LOGN));
+      __builtin_amdgcn_sched_barrier(0);
+      V x[4], y1[4], *later = (V*)second + threadIdx.x;   // the second target's values wait in LDS
+      {
+        ConvRows<MAXLEN> rows;
+        rows.take(rows_image + buffer);
+        convert<MAXLEN>(x, [&](int i, V v) { if (MAXLEN == 4) y1[i] = v; else later[i * CONV_THREADS] = v; }, ys, rows, t0, t1);
       }
-    });
-  }
-  // the shares that got one double-precision target more are the last to get an integer one
-  walk(a.nfp, a.nint, !SRC_FP, a.nsplit - 1 - share, std::false_type{}, [&](const ConvTarget<MAXLEN>& tg) {
-    const ulonglong2* tw = a.tw + ((size_t)tg.id << LOGN);
-    ConvTwiddles<ulonglong2> w;
-    w.load(tw);
-    __builtin_amdgcn_sched_barrier(0);
-    u64 x[4];
-    convert_int<MAXLEN, NARROW>(x, y, tg, 0);
-    conv_fwd_rows<LOGR>(x, w, tw, tg.m, sm);
-    u64* d = dst + ((size_t)tg.slot << LOGN) + pos;
+      buffer ^= CONV_ROWS_WORDS(MAXLEN);
+      // Into the image that the pair before was read from, ahead of its barriers. Wave 0 or 1 waits for them before the first
+      // target's stores (everything requested later has been waited for by then); the second's barriers show them to all.
+      conv_request_rows<MAXLEN>(a, j * a.ntarget, i0 & 255, i1 & 255, rows_image + buffer);
+      ConvTwiddles<TW> w1;
+      transform(x, t0, w, [&] {
+        w1.load(tables + ((size_t)t1.id << LOGN));
+        n0.fetch(a, i0);
+        n1.fetch(a, i1);
+        i0 = at(n + 4 * a.nsplit);
+        i1 = at(n + 5 * a.nsplit);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      conv_wait_vector_memory();
+      auto store = [&](u32 slot) {
+        V* d = (V*)dst + ((size_t)slot << LOGN) + pos;
 #pragma unroll
-    for (int i = 0; i < 4; i++) d[i * 256] = x[i];
+        for (int i = 0; i < 4; i++) d[i * 256] = x[i];
+      };
+      store(t0.slot);
+      if (n + a.nsplit >= count) return;
+#pragma unroll
+      for (int i = 0; i < 4; i++) x[i] = MAXLEN == 4 ? y1[i] : later[i * CONV_THREADS];
+      transform(x, t1, w1, [] {});
+      store(t1.slot);
+    }
+  };
+  walk(0, a.nfp, SRC_FP, share, a.twfp, 0.0, [&](double (&x)[4], const ConvTarget& tg, const ConvTwiddles<double>& w, auto freed) {
+    conv_fwd_rows<LOGR>(x, w, a.twfp + ((size_t)tg.id << LOGN), tg.qd, tg.qinv, (double*)sm, freed);
   });
+  // the shares that got one double-precision target more are the last to get an integer one
+  walk(a.nfp, a.nint, !SRC_FP, a.nsplit - 1 - share, a.tw, (u64)0,
+       [&](u64 (&x)[4], const ConvTarget& tg, const ConvTwiddles<ulonglong2>& w, auto freed) {
+         conv_fwd_rows<LOGR>(x, w, a.tw + ((size_t)tg.id << LOGN), tg.m, sm, freed);
+       });
 }

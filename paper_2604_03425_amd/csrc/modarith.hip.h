@@ -47,12 +47,6 @@ __device__ __forceinline__ double fp_reduce(double x, double qinv, double q) {  
 __device__ __forceinline__ double u2d(u64 v) {  // exact for v < 2^52
   return __longlong_as_double((long long)(v | 0x4330000000000000ull)) - 4503599627370496.0;
 }
-// exact for any u64 v with |v - 2^62| < 2^53: that difference
-__device__ __forceinline__ double u2d_biased62(u64 v) {
-  const double hi = __hiloint2double(0x45300000, (int)(u32)(v >> 32));   // 2^84 + 2^32 * high word
-  const double lo = __hiloint2double(0x43300000, (int)(u32)v);           // 2^52 + low word
-  return (hi - (19342813113834066795298816.0 + 4611686018427387904.0 + 4503599627370496.0)) + lo;
-}
 __device__ __forceinline__ u64 d2u_canon(double r, double q) {  // r an integer in (-q, 2q) -> canonical residue
   r = r < 0.0 ? r + q : r;
   r = r >= q ? r - q : r;
@@ -192,22 +186,6 @@ __device__ __forceinline__ u64 dot30n_redc90(const Dot30N& d, u64 m, u64 minv) {
   u = ((u32)c * qi) & 0x3FFFFFFFu;
   c += (u64)u * q0;
   return (c >> 30) + (u64)u * q1;
-}
-// The first two words of it: V * 2^-60 mod m in [0, V / 2^60 + m). With at most 8 terms of 60-bit sources and constants below
-// m (which carry 2^60) that is below 9m: enough for a forward transform in the integers, and half of what a canonical residue
-// costs.
-__device__ __forceinline__ u64 dot30n_redc60(const Dot30N& d, u64 m, u64 minv) {
-  const u32 q0 = (u32)m & 0x3FFFFFFFu, q1 = (u32)(m >> 30), qi = (u32)minv & 0x3FFFFFFFu;
-  u64 a = d.a, b = d.b, c = d.c;
-  u32 u = ((u32)a * qi) & 0x3FFFFFFFu;
-  a += (u64)u * q0;
-  b += a >> 30;
-  b += (u64)u * q1;
-  u = ((u32)b * qi) & 0x3FFFFFFFu;
-  b += (u64)u * q0;
-  c += b >> 30;
-  c += (u64)u * q1;
-  return c;
 }
 // Montgomery reduction: V * 2^-64 mod m, in [0, V/2^64 + m). minv = -m^-1 mod 2^64.
 __device__ __forceinline__ u64 redc(Acc128 v, u64 m, u64 minv) {
