@@ -12,8 +12,8 @@
 #include "kernels.hip.h"
 #include "convert.hip.h"
 #include "ks12.hip.h"
-#include "ntt12.hip.h"
 #include "ntt16_kernels.hip.h"
+#include "ntt_limb.hip.h"
 
 typedef unsigned __int128 u128;
 
@@ -175,7 +175,7 @@ struct ckks_ctx {
   ModInfo* d_mods = nullptr;
   ulonglong2* d_tw_fwd = nullptr;
   ulonglong2* d_tw_inv = nullptr;
-  double* d_twfp_fwd = nullptr;  // N = 2^12 .. 2^16: the twiddles as doubles in [-q/2, q/2] for moduli < 2^50
+  double* d_twfp_fwd = nullptr;  // N = 2^10 .. 2^16: the twiddles as doubles in [-q/2, q/2] for moduli < 2^50
   double* d_twfp_inv = nullptr;
   hipStream_t side = nullptr;       // second stream for the fork/join inside a key switch (default priority)
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -612,12 +612,57 @@ struct NttOpts {
   bool raw_out = false;               // with blocks_only: leave reduced doubles on double-precision moduli
   int only_class = -1;                // >= 0: touch only the slots of this modulus class
   int exclude_class = -1;             // >= 0: leave the slots of this modulus class alone
+  // a whole transform of all slots, canonical residues in and out
+  bool plain() const {
+    return !galois && !src_b && !galois_pc && !scale && !split_out && !rows_only && !blocks_only && only_class < 0 && exclude_class < 0;
+  }
 };
+// Whole transforms of rings up to this one hold a limb per workgroup (ntt_limb.hip.h).
+#define LIMB_MAX_LOGN 14
+template <int LOGN>
+void launch_limb_kernel(bool inverse, dim3 grid, hipStream_t st, const LimbArgs& a) {
+  if (inverse) hipLaunchKernelGGL((ntt_limb_kernel<LOGN, true>), grid, dim3(Limb<LOGN>::THREADS), 0, st, a);
+  else hipLaunchKernelGGL((ntt_limb_kernel<LOGN, false>), grid, dim3(Limb<LOGN>::THREADS), 0, st, a);
+}
+int launch_limbs(const ckks_ctx* c, bool inverse, const u64* src, u64 src_stride, u64* dst, u64 dst_stride, u32 npoly, u32 slot0,
+                 u32 nslots, const LimbMap& ids_from_slot0, u32 skip_beta, u32 skip_nq, hipStream_t st) {
+  LimbArgs a;
+  a.src = src + (size_t)slot0 * c->N;
+  a.dst = dst + (size_t)slot0 * c->N;
+  a.tw = inverse ? c->d_tw_inv : c->d_tw_fwd;
+  a.twfp = inverse ? c->d_twfp_inv : c->d_twfp_fwd;
+  a.mods = c->d_mods;
+  a.src_poly_stride = src_stride;
+  a.dst_poly_stride = dst_stride;
+  a.skip_beta = skip_beta;
+  a.skip_alpha = c->alpha;
+  a.skip_nq = skip_nq;
+  a.fp_on = c->tune[1] == 0 ? 1u : 0u;
+  for (u32 i = 0; i < 128; i++) a.id[i] = ids_from_slot0.id[i];
+  const u32 chunk = 65535 - (skip_beta ? 65535 % skip_beta : 0);   // whole digit groups
+  for (u32 p0 = 0; p0 < npoly; p0 += chunk) {
+    LimbArgs b = a;
+    b.src += (size_t)p0 * src_stride;
+    b.dst += (size_t)p0 * dst_stride;
+    const dim3 grid(std::min<u32>(chunk, npoly - p0), nslots);
+    ProfScope ps(c, inverse ? PK_NTT_INV : PK_NTT_FWD, st);
+    switch (c->logN) {
+      case 10: launch_limb_kernel<10>(inverse, grid, st, b); break;
+      case 11: launch_limb_kernel<11>(inverse, grid, st, b); break;
+      case 12: launch_limb_kernel<12>(inverse, grid, st, b); break;
+      case 13: launch_limb_kernel<13>(inverse, grid, st, b); break;
+      default: launch_limb_kernel<14>(inverse, grid, st, b); break;
+    }
+  }
+  HIP_TRY(hipGetLastError());
+  return CKKS_OK;
+}
 int launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, u64 src_stride, u64* dst, u64 dst_stride, u32 npoly,
                u32 slot0, u32 nslots, const LimbMap& ids_from_slot0, u32 skip_beta, u32 skip_nq, hipStream_t st,
                const NttOpts& opt = NttOpts()) {
   if (npoly == 0 || nslots == 0) return CKKS_OK;
   const int kind = inverse ? PK_NTT_INV : PK_NTT_FWD;
+  if (c->logN <= LIMB_MAX_LOGN && opt.plain()) return launch_limbs(c, inverse, src, src_stride, dst, dst_stride, npoly, slot0, nslots, ids_from_slot0, skip_beta, skip_nq, st);
   if (two_pass(c)) {
     Ntt16Args a;
     a.logN = c->logN;
@@ -665,34 +710,6 @@ int launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, u64 src_stride, 
       launch_by_class(c, PK_INV_BLOCKS, a, npoly, nslots, cls_of, st,
                       [&](int cls, dim3 grid) { LAUNCH_CLASS_KERNEL(ntt16_inv_blocks_kernel, cls, grid, st, a); });
       if (!opt.blocks_only) rows(b, PK_INV_ROWS);
-    }
-    HIP_TRY(hipGetLastError());
-    return CKKS_OK;
-  }
-  if (c->logN == 12) {
-    // the whole limb in one workgroup: all 12 stages in one pass over memory, in or out of place
-    Ntt12Args a;
-    a.src = src + (size_t)slot0 * c->N;
-    a.dst = dst + (size_t)slot0 * c->N;
-    a.tw = inverse ? c->d_tw_inv : c->d_tw_fwd;
-    a.twfp = inverse ? c->d_twfp_inv : c->d_twfp_fwd;
-    a.mods = c->d_mods;
-    a.src_poly_stride = src_stride;
-    a.dst_poly_stride = dst_stride;
-    a.skip_beta = skip_beta;
-    a.skip_alpha = c->alpha;
-    a.skip_nq = skip_nq;
-    a.fp_on = c->tune[1] == 0 ? 1u : 0u;
-    for (u32 i = 0; i < 128; i++) a.id[i] = ids_from_slot0.id[i];
-    const u32 chunk = 65535 - (skip_beta ? 65535 % skip_beta : 0);   // grid.x carries the polynomial index; whole digit groups
-    for (u32 p0 = 0; p0 < npoly; p0 += chunk) {
-      const u32 np_ = std::min<u32>(chunk, npoly - p0);
-      Ntt12Args b = a;
-      b.src += (size_t)p0 * src_stride;
-      b.dst += (size_t)p0 * dst_stride;
-      ProfScope ps(c, kind, st);
-      if (inverse) hipLaunchKernelGGL(ntt12_kernel<true>, dim3(np_, nslots), dim3(256), 0, st, b);
-      else hipLaunchKernelGGL(ntt12_kernel<false>, dim3(np_, nslots), dim3(256), 0, st, b);
     }
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
@@ -1784,7 +1801,7 @@ int ckks_ctx_create(ckks_ctx** out, uint32_t logN, const uint64_t* q, uint32_t n
   std::vector<ModInfo> mods(c->nm);
   std::vector<ulonglong2> fwd((size_t)c->nm * N), inv((size_t)c->nm * N);
   std::vector<double> fwdfp, invfp;
-  if (logN >= 12 && logN <= 16) {   // the rings with double-precision bodies
+  if (logN <= 16) {   // the rings with double-precision bodies
     fwdfp.assign((size_t)c->nm * N, 0.0);
     invfp.assign((size_t)c->nm * N, 0.0);
   }
