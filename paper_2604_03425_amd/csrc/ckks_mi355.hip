@@ -614,7 +614,8 @@ struct NttOpts {
   int exclude_class = -1;             // >= 0: leave the slots of this modulus class alone
   // a whole transform of all slots, canonical residues in and out
   bool plain() const {
-    return !galois && !src_b && !galois_pc && !scale && !split_out && !rows_only && !blocks_only && only_class < 0 && exclude_class < 0;
+    return !galois && !src_b && !galois_pc && !scale && !split_out && !rows_only && !blocks_only && !raw_out && only_class < 0 &&
+           exclude_class < 0;
   }
 };
 // Whole transforms of rings up to this one hold a limb per workgroup (ntt_limb.hip.h).
