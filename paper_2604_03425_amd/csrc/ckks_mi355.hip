@@ -607,7 +607,7 @@ struct NttOpts {
   const u32* galois_pc = nullptr;     // same, one element per polynomial (host array, npoly <= KS_MULTI_MAX entries)
   const ulonglong2* scale = nullptr;  // two-pass inverse only: per-slot constants (from slot0) replacing N^-1
   bool split_out = false;             // N = 2^16 inverse only: write the shifted, split form the fused base conversion reads
-  bool rows_only = false;             // two-pass forward only: stop after the row pass (a fused kernel does the rest)
+  bool rows_only = false;             // two-pass only: only the row pass (forward: a fused kernel does the rest; inverse: one did the block pass)
   bool blocks_only = false;           // two-pass only: only the block pass (forward: in place on dst)
   bool raw_out = false;               // with blocks_only: leave reduced doubles on double-precision moduli
   int only_class = -1;                // >= 0: touch only the slots of this modulus class
@@ -708,8 +708,9 @@ int launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, u64 src_stride, 
         launch_by_class(c, PK_FWD_BLOCKS, b, npoly, nslots, cls_of, st,
                         [&](int cls, dim3 grid) { LAUNCH_CLASS_KERNEL(ntt16_fwd_blocks_kernel, cls, grid, st, b); });
     } else {
-      launch_by_class(c, PK_INV_BLOCKS, a, npoly, nslots, cls_of, st,
-                      [&](int cls, dim3 grid) { LAUNCH_CLASS_KERNEL(ntt16_inv_blocks_kernel, cls, grid, st, a); });
+      if (!opt.rows_only)
+        launch_by_class(c, PK_INV_BLOCKS, a, npoly, nslots, cls_of, st,
+                        [&](int cls, dim3 grid) { LAUNCH_CLASS_KERNEL(ntt16_inv_blocks_kernel, cls, grid, st, a); });
       if (!opt.blocks_only) rows(b, PK_INV_ROWS);
     }
     HIP_TRY(hipGetLastError());
@@ -1038,7 +1039,9 @@ ConvJob conv_down_job(const ckks_ctx* c, const LevelTables* lt, const u64* acc, 
 // ModDown's conversion and the first forward pass of its result on the two-pass path: the special limbs of both
 // accumulators back to coefficient form (scaled by (P/p_k)^-1 / N), P -> Q_l, stages 0..7; tq receives the converted
 // limbs in row-pass form. Knob 2 = 1 does the conversion inside the row pass (ntt16_bconv_rows_kernel).
-int ks16_moddown_rows(ckks_ctx* c, const LevelTables* lt, u32 B, u32 nlimbs, u64* acc, u64* tq, hipStream_t st) {
+// int_blocks_done: the integer-class special limbs have been through their inverse block pass.
+int ks16_moddown_rows(ckks_ctx* c, const LevelTables* lt, u32 B, u32 nlimbs, u64* acc, u64* tq, hipStream_t st,
+                      bool int_blocks_done = false) {
   int rc;
   const u32 N = c->N, next = lt->next, K = c->np;
   const bool fused = c->tune[2] == 1 && c->logN == 16;
@@ -1053,7 +1056,19 @@ int ks16_moddown_rows(ckks_ctx* c, const LevelTables* lt, u32 B, u32 nlimbs, u64
     job = conv_down_job(c, lt, acc, tq, B, nlimbs);
     o3.blocks_only = !job.ready;
   }
-  if ((rc = launch_ntt(c, true, acc, (u64)next * N, acc, (u64)next * N, B * 2, nlimbs, K, pmap, 0, 0, st, o3))) return rc;
+  auto inverse = [&](const NttOpts& o) {
+    return launch_ntt(c, true, acc, (u64)next * N, acc, (u64)next * N, B * 2, nlimbs, K, pmap, 0, 0, st, o);
+  };
+  if (int_blocks_done) {
+    NttOpts blocks = o3, rows = o3;
+    blocks.blocks_only = true;
+    blocks.only_class = 0;
+    rows.rows_only = true;
+    if ((rc = inverse(blocks))) return rc;
+    if (!o3.blocks_only && (rc = inverse(rows))) return rc;
+  } else if ((rc = inverse(o3))) {
+    return rc;
+  }
   if (conv) return launch_conv_rows(c, job, st);
   if (!fused) {
     {
@@ -1147,7 +1162,9 @@ void launch_inner_c(const ckks_ctx* c, u32 B, u32 nslots, const FwdInnerArgs& a,
 //   2. ModUp conversion and row pass of every slot a digit does not own
 //      (1's row pass and 2 are one kernel where conv_fits; else kernels of their own, knob 2 = 1: one fused kernel for 2)
 //   3. integer-class slots (the special primes): [block pass + evk inner product] (x 2^-64 from the Montgomery products)
-//   4. INTT of the special limbs with 2^64 (P/p_k)^-1 / N folded in; ModDown conversion and row pass (as step 2)
+//   4. INTT of the special limbs with 2^64 (P/p_k)^-1 / N folded in (of the integer-class ones step 3 has done the block pass, in
+//      the registers that hold the sums: one launch and a write and read of both accumulators less; 64 rotations with their own
+//      keys 5623 -> 5383 us, one rotation 147 -> 139); ModDown conversion and row pass (as step 2)
 //   5. double-precision main limbs: [block pass of the digits + evk inner product + block pass of the ModDown
 //      correction + (sum - correction) / P + addends] in one kernel, so their accumulators never reach memory;
 //      integer-class main limbs take the assembly kernel on the accumulators of step 3.
@@ -1280,7 +1297,8 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
     ia.c0 = io.add_src;
     ia.c0_poly_stride = 2 * (u64)nlimbs * N;
   }
-  // 3. integer-class slots, 8 values per lane (grid.y = tiles of 8 blocks)
+  // 3. integer-class slots, 8 values per lane (grid.y = tiles of 8 blocks); the special ones go on through their inverse block pass
+  if (!acc_add) ia.twi = c->d_tw_inv;
   for (int cls = 1; cls <= 2; cls++) {
     FwdInnerArgs a = ia;
     u32 cnt = 0;
@@ -1322,7 +1340,7 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
   }
   if (acc_add) return CKKS_OK;
   // 4.
-  if ((rc = ks16_moddown_rows(c, lt, B, nlimbs, acc, tq, st))) return rc;
+  if ((rc = ks16_moddown_rows(c, lt, B, nlimbs, acc, tq, st, true))) return rc;
   if (fork) HIP_TRY(hipStreamWaitEvent(st, c->ev_join, 0));
   // 5.
   if (fused_fp && any_fp) {

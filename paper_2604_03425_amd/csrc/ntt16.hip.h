@@ -375,6 +375,75 @@ __device__ __forceinline__ void ntt256_fwd_blocks_int8(u64 (&x)[8], const ulongl
   for (int k = 0; k < 4; k++) bf_fwd<BIG, false>(x[2 * k], x[2 * k + 1], t3[2 + k], q, q2);   // stage 15: pairs (2k, 2k + 1)
 }
 
+// The way back for two polynomials at once, which share the twiddles: the first 8 inverse stages of block h. In: x[k][c] = element
+// (l >> 2)*32 + (l & 3)*8 + c, below 2q. Out: x[k][i] = element i*32 + l, below 2q (BIG: 8q).
+template <bool BIG, class TW>
+__device__ __forceinline__ void radix8_inv(u64 (&x)[8], u64 q, u64 c0, TW tw) {
+  u64 c = c0;
+#pragma unroll
+  for (int s = 2; s >= 0; s--) {
+    const int half = 4 >> s;
+#pragma unroll
+    for (int g = 0; g < (1 << s); g++) {
+      const ulonglong2 w = tw(s, g);
+#pragma unroll
+      for (int p = 0; p < half; p++) bf_inv_pair<BIG>(x[g * 2 * half + p], x[g * 2 * half + p + half], w, q, c, half, p);
+    }
+    if (!BIG) c <<= 1;
+  }
+}
+template <bool BIG>
+__device__ __forceinline__ void ntt256_inv_blocks_int8(u64 (&x)[2][8], const ulonglong2* __restrict__ twi, u64 q, u64 mu, u32 h, u32 R,
+                                                       u32 l, u64* smb) {
+  const u32 a = l >> 2, b = l & 3;
+  const u64 q2 = lazy_const<BIG>(q);
+  ulonglong2 t1[7], t2[7], t3[6];
+#pragma unroll
+  for (int u = 0; u < 2; u++) t3[u] = twi[(R << 6) + (h << 6) + (a << 3) + (b << 1) + u];
+#pragma unroll
+  for (int k = 0; k < 4; k++) t3[2 + k] = twi[(R << 7) + (h << 7) + (a << 4) + (b << 2) + k];
+#pragma unroll
+  for (int s = 0; s < 3; s++)
+#pragma unroll
+    for (int g = 0; g < (1 << s); g++) t2[(1 << s) - 1 + g] = twi[(R << (3 + s)) + (h << (3 + s)) + (a << s) + g];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int e = 0; e < 2; e++) {
+#pragma unroll
+    for (int k = 0; k < 4; k++) bf_inv<BIG>(x[e][2 * k], x[e][2 * k + 1], t3[2 + k], q, q2);
+#pragma unroll
+    for (int u = 0; u < 2; u++)
+#pragma unroll
+      for (int p = 0; p < 2; p++) bf_inv_pair<BIG>(x[e][u * 4 + p], x[e][u * 4 + p + 2], t3[u], q, BIG ? q2 : q2 << 1, 2, p);
+  }
+#pragma unroll
+  for (int s = 0; s < 3; s++)
+#pragma unroll
+    for (int g = 0; g < (1 << s); g++) t1[(1 << s) - 1 + g] = twi[(R << s) + (h << s) + g];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int e = 0; e < 2; e++) {
+    wave_lds_sync();
+#pragma unroll
+    for (int c = 0; c < 8; c++) smb[a * NTT8_PITCH_I + b * 8 + c] = x[e][c];
+    wave_lds_sync();
+#pragma unroll
+    for (int r = 0; r < 8; r++) x[e][r] = smb[a * NTT8_PITCH_I + r * 4 + b];
+    radix8_inv<BIG>(x[e], q, BIG ? q2 : q2 << 2, [&](int s, int g) { return t2[(1 << s) - 1 + g]; });
+    wave_lds_sync();
+#pragma unroll
+    for (int r = 0; r < 8; r++) smb[a * NTT8_PITCH_I + r * 4 + b] = x[e][r];
+    wave_lds_sync();
+#pragma unroll
+    for (int i = 0; i < 8; i++) x[e][i] = smb[i * NTT8_PITCH_I + l];
+    radix8_inv<BIG>(x[e], q, BIG ? q2 : q2 << 5, [&](int s, int g) { return t1[(1 << s) - 1 + g]; });
+    if (!BIG) {
+#pragma unroll
+      for (int i = 0; i < 8; i++) x[e][i] = barrett_lazy(x[e][i], mu, q);
+    }
+  }
+}
+
 // Inverse, the first 8 stages, on contiguous blocks. In: x holds, for lane (hb, j0), the values at positions i*16 + j0
 // of block h (any value < 2q). Out: < 2q (BIG: < 8q), same lane layout, ready for a coalesced store.
 template <bool BIG>

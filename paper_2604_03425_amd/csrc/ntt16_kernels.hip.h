@@ -364,6 +364,9 @@ struct FwdInnerArgs {
   const ulonglong2* tw;
   const double* twfp; 
   const ModInfo* mods;
+  // ntt16_fwd_blocks_inner8_kernel only: != null takes the accumulators of the special limbs through the inverse block pass
+  // before it stores them (ModDown goes on with the inverse row pass)
+  const ulonglong2* twi = nullptr;
   u32 logN, nlimbs, nq, nm, alpha, beta, next, map_mode, galois;
   u32 ext_galois;            // streaming kernels only: != 0 reads ext through the Galois map too (hoisted digits:
                              // ext holds the transform of the un-rotated polynomial, shared by many rotations)
@@ -722,6 +725,18 @@ ntt16_fwd_blocks_inner8_kernel(FwdInnerArgs a) {
     jn = jnext;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no copy into LDS may outlive the workgroup
+  if (a.twi && t >= a.nlimbs) {   // uniform
+    u64 y[2][8];
+#pragma unroll
+    for (int c = 0; c < 8; c++) y[0][c] = acc0[c], y[1][c] = acc1[c];
+    ntt256_inv_blocks_int8<BIG>(y, a.twi + (size_t)id * N, q, mi.mu64, h, 1u << (a.logN - 8), l, smb);
+    u64* o = a.acc + ((size_t)b * 2 * a.next + t) * N + h * 256 + l;
+#pragma unroll
+    for (int e = 0; e < 2; e++)
+#pragma unroll
+      for (int i = 0; i < 8; i++) o[(size_t)e * a.next * N + i * 32] = y[e][i];
+    return;
+  }
   u64* o0 = a.acc + (((size_t)b * 2 + 0) * a.next + t) * N + posC;
   u64* o1 = o0 + (size_t)a.next * N;
   if (a.accumulate) {   // a rotation kept in the extended basis, added to what acc holds (wave-uniform branch)
