@@ -11,6 +11,7 @@
 
 #include "kernels.hip.h"
 #include "convert.hip.h"
+#include "convert_wide.hip.h"
 #include "ks12.hip.h"
 #include "ntt16_kernels.hip.h"
 #include "ntt_limb.hip.h"
@@ -101,7 +102,8 @@ struct Pass {
   u32 s0, k, logC, tile_log;
 };
 
-// Number of source rows the base-conversion kernels are instantiated for (the smallest that covers n).
+// Rows of constants per target in up_mat / dn_mat (the smallest of these that covers n): what the kernels that read them are
+// instantiated for (4, 8) or walk over.
 inline u32 bconv_rows(u32 n) { return n <= 4 ? 4 : n <= 8 ? 8 : n <= 15 ? 15 : n <= 24 ? 24 : n <= 36 ? 36 : 45; }
 
 // Base-conversion constants for ciphertexts at one limb count.
@@ -117,8 +119,9 @@ struct LevelTables {
   ulonglong2* up_scale = nullptr;  // [nlimbs]  (Q_j/q_i)^-1 / N mod q_i
   ulonglong2* dn_scale = nullptr;  // [K]       2^64 (P/p_k)^-1 / N mod p_k
   u64* dn_mat_plain = nullptr;     // dn_mat without the Montgomery factor
-  uint4* up_pieces = nullptr;      // [beta][next], [nlimbs] matrices of bytes of (Q_j/q_i) mod m_t, (P/p_k) mod q_i for
-  uint4* dn_pieces = nullptr;      // conv_rows_kernel (ConvRows; at most 8 sources); dn: with 2^-64 on integer-class targets
+  // matrices of bytes of (Q_j/q_i) mod m_t ([beta][next]) and (P/p_k) mod q_i ([nlimbs]; on two-pass rings with 2^-64 on
+  // integer-class targets), for conv_rows_kernel (at most 8 sources) or conv_wide_kernel
+  uint4 *up_pieces = nullptr, *dn_pieces = nullptr;
   u64* up_off = nullptr;           // [beta][next] -sum_i ((q_i-1)/2) (Q_j/q_i) mod m_t, scaled like up_mat
   u64* dn_off = nullptr;           // [nlimbs]     -sum_k ((p_k-1)/2) (P/p_k) mod q_i, scaled like dn_mat_plain
   u32 up_pitch = 0, dn_pitch = 0;  // constants per target in up_mat / dn_mat_plain
@@ -184,7 +187,7 @@ struct ckks_ctx {
   // or 5 changes): levels[nlimbs] points into one device allocation, d_levels.
   std::vector<LevelTables> levels;
   char* d_levels = nullptr;
-  ConvReduction* d_conv_red = nullptr;   // [nm], inside d_levels
+  ConvReduction *d_conv_red = nullptr, *d_wide_red = nullptr;   // [nm] each, inside d_levels
   void* scratch_ptr = nullptr;  // this device's address of `scratch` (hipGetSymbolAddress at context creation)
 };
 
@@ -265,8 +268,21 @@ void conv_rows_of(std::vector<unsigned char>& out, size_t row, u32 groups, const
     }
   }
 }
-// Number of groups of 4 sources of a fused conversion (0: too many sources for it).
-inline u32 conv_groups(u32 n) { return n <= 4 ? 1 : n <= CONV_MAX_SRC ? 2 : 0; }
+// The same for target `slot` of digit j in conv_wide_kernel's matrices (layout there).
+void wide_rows_of(std::vector<unsigned char>& out, u32 j, u32 slot, u32 quads, u32 groups, const u64* c, u32 n, u64 m) {
+  for (u32 k = 0; k < n; k++) {
+    u64 v = c[k];
+    const size_t at = (((size_t)j * quads + slot / 4) * groups + k / 4) * 64 + k / 2 % 2 * 32;
+    for (u32 i = 0; i < CONV_PIECES; i++) {
+      const u64 w = ((v > m / 2 ? v - m : v) + 0x8080808080808080ull) ^ 0x8080808080808080ull;
+      for (u32 p = 0; p < CONV_PIECES; p++)
+        out[(at + (slot / 2 % 2 * 2 + p / 4) * 8 + slot % 2 * 4 + p % 4) * 16 + k % 2 * 8 + i] = (unsigned char)(w >> (8 * p));
+      v = h_mul(v, 256, m);
+    }
+  }
+}
+// Groups of 4 sources that a conversion of n of them is done for: by conv_rows_kernel up to 8, by conv_wide_kernel beyond.
+inline u32 conv_groups(u32 n) { return n <= 4 ? 1 : n <= CONV_MAX_SRC ? 2 : n <= 12 ? 3 : n <= 16 ? 4 : n <= 24 ? 6 : n <= 36 ? 9 : 12; }
 
 // Constants for ciphertexts at `nlimbs` limbs, appended to the arena (pointers are offsets into it).
 LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
@@ -294,8 +310,13 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
   std::vector<ulonglong2> up_inv((size_t)t.beta * alpha, ulonglong2{0, 0});
   std::vector<u64> up_mat((size_t)t.beta * next * (R + 1), 0), up_off((size_t)t.beta * next, 0);
   const u32 up_groups = conv_groups(alpha), dn_groups = conv_groups(K);
-  const size_t group_bytes = 2 * CONV_PIECES * 16;
-  std::vector<unsigned char> up_pieces((size_t)t.beta * next * up_groups * group_bytes, 0), dn_pieces(nlimbs * dn_groups * group_bytes, 0);
+  const bool up_wide = alpha > CONV_MAX_SRC, dn_wide = K > CONV_MAX_SRC;
+  auto pieces_bytes = [](u32 digits, u32 targets, u32 groups, bool wide) {
+    return wide ? (size_t)digits * ((targets + 3) / 4) * groups * 1024 : (size_t)digits * targets * groups * 2 * CONV_PIECES * 16;
+  };
+  std::vector<unsigned char> up_pieces(pieces_bytes(t.beta, next, up_groups, up_wide), 0);
+  std::vector<unsigned char> dn_pieces(pieces_bytes(1, nlimbs, dn_groups, dn_wide), 0);
+  std::vector<u64> up_plain((size_t)next * alpha), dn_plain((size_t)nlimbs * K);   // (Q_j/q_i) mod m_t of one digit, (P/p_k) mod q_i
   t.up_pitch = R + 1;
   t.dn_pitch = RK + 1;
   for (u32 j = 0; j < t.beta; j++) {
@@ -310,18 +331,14 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
         u64 m = ext_mod(s), v = 1;
         for (u32 k = lo; k < hi; k++)
           if (k != i) v = h_mul(v, c->mod[k] % m, m);
+        up_plain[(size_t)s * alpha + (i - lo)] = v;
         up_mat[((size_t)j * next + s) * (R + 1) + (i - lo)] = mont_up(v, m);
       }
     }
-    for (u32 s = 0; up_groups && s < next; s++) {
-      const u64 m = ext_mod(s);
-      u64 plain[CONV_MAX_SRC];
-      for (u32 i = lo; i < hi; i++) {
-        plain[i - lo] = 1;
-        for (u32 k = lo; k < hi; k++)
-          if (k != i) plain[i - lo] = h_mul(plain[i - lo], c->mod[k] % m, m);
-      }
-      conv_rows_of(up_pieces, (size_t)j * next + s, up_groups, plain, hi - lo, is_fp(c->mod[lo]) ? 7 : CONV_PIECES, m);
+    for (u32 s = 0; s < next; s++) {
+      const u64* plain = &up_plain[(size_t)s * alpha];
+      if (up_wide) wide_rows_of(up_pieces, j, s, (next + 3) / 4, up_groups, plain, hi - lo, ext_mod(s));
+      else conv_rows_of(up_pieces, (size_t)j * next + s, up_groups, plain, hi - lo, is_fp(c->mod[lo]) ? 7 : CONV_PIECES, ext_mod(s));
     }
     for (u32 s = 0; s < next; s++) {
       u64 m = ext_mod(s), v = 1;
@@ -329,12 +346,8 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
       up_mat[((size_t)j * next + s) * (R + 1) + R] = mont_up(v ? m - v : 0, m);
       // offset of the shifted-residue form: -sum_i h_i (Q_j/q_i), h_i = (q_i - 1) / 2
       u64 sum = 0;
-      for (u32 i = lo; i < hi; i++) {
-        u64 w = 1;
-        for (u32 k = lo; k < hi; k++)
-          if (k != i) w = h_mul(w, c->mod[k] % m, m);
-        sum = (u64)(((u128)sum + h_mul(w, ((c->mod[i] - 1) / 2) % m, m)) % m);
-      }
+      for (u32 i = lo; i < hi; i++)
+        sum = (u64)(((u128)sum + h_mul(up_plain[(size_t)s * alpha + (i - lo)], ((c->mod[i] - 1) / 2) % m, m)) % m);
       up_off[(size_t)j * next + s] = mont_up(sum ? m - sum : 0, m);
     }
   }
@@ -350,6 +363,7 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
       u64 m = c->mod[i], v = 1;
       for (u32 r = 0; r < K; r++)
         if (r != k) v = h_mul(v, c->mod[c->nq + r] % m, m);
+      dn_plain[(size_t)i * K + k] = v;
       dn_mat[(size_t)i * (RK + 1) + k] = mont_dn(v, m);
     }
   }
@@ -377,12 +391,8 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
     u64 r64_inv = h_inv(h_mont(1, m), m);
     {
       u64 sum = 0;   // -sum_k h_k (P/p_k) mod m, then scaled like the row of constants below
-      for (u32 k = 0; k < K; k++) {
-        u64 w = 1;
-        for (u32 r = 0; r < K; r++)
-          if (r != k) w = h_mul(w, c->mod[c->nq + r] % m, m);
-        sum = (u64)(((u128)sum + h_mul(w, ((c->mod[c->nq + k] - 1) / 2) % m, m)) % m);
-      }
+      for (u32 k = 0; k < K; k++)
+        sum = (u64)(((u128)sum + h_mul(dn_plain[(size_t)i * K + k], ((c->mod[c->nq + k] - 1) / 2) % m, m)) % m);
       const u64 neg = mont_dn(sum ? m - sum : 0, m);
       dn_off[i] = is_fp(m) ? neg : h_mul(neg, r64_inv, m);
     }
@@ -409,15 +419,13 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
       dn_scale[k] = ulonglong2{w, h_shoup(w, m)};
     }
   }
-  for (u32 i = 0; dn_groups && i < nlimbs; i++) {
-    const u64 m = c->mod[i], first = is_fp(m) ? 1 : h_inv(h_mont(1, m), m);
-    u64 plain[CONV_MAX_SRC];
-    for (u32 k = 0; k < K; k++) {
-      plain[k] = first;
-      for (u32 r = 0; r < K; r++)
-        if (r != k) plain[k] = h_mul(plain[k], c->mod[c->nq + r] % m, m);
-    }
-    conv_rows_of(dn_pieces, i, dn_groups, plain, K, is_fp(c->mod[c->nq]) ? 7 : CONV_PIECES, m);
+  for (u32 i = 0; i < nlimbs; i++) {
+    const u64 m = c->mod[i];
+    u64* plain = &dn_plain[(size_t)i * K];
+    if (!is_fp(m) && c->logN >= 13 && c->logN <= 16)
+      for (u32 k = 0; k < K; k++) plain[k] = h_mul(plain[k], h_inv(h_mont(1, m), m), m);
+    if (dn_wide) wide_rows_of(dn_pieces, 0, i, (nlimbs + 3) / 4, dn_groups, plain, K, m);
+    else if (K) conv_rows_of(dn_pieces, i, dn_groups, plain, K, is_fp(c->mod[c->nq]) ? 7 : CONV_PIECES, m);
   }
   std::vector<ulonglong2> rs_one(1), rs_qinv(nlimbs > 1 ? nlimbs - 1 : 0), rs_qinv16(rs_qinv.size());
   std::vector<u64> rs_mat(rs_qinv.size() * 5, 0);
@@ -459,13 +467,18 @@ int build_levels(ckks_ctx* c) {
   LevelArena arena;
   std::vector<LevelTables> lv(c->nq + 1);
   for (u32 nl = 1; nl <= c->nq; nl++) lv[nl] = build_level(c, nl, arena);
-  std::vector<ConvReduction> red(c->nm);   // (read on integer targets of 2^36 or more)
+  std::vector<ConvReduction> red(c->nm), wide(c->nm);   // (read on integer targets of 2^36, 2^50 or more)
   for (u32 i = 0; i < c->nm; i++) {
     const u64 m = c->mod[i];
     const u32 e = h_bits(m), sh = e > 51 ? e - 51 : 0;
     red[i] = ConvReduction{sh, e > CONV_INT_MIN_BITS ? -(int)((((u128)1 << (64 + sh)) + m / 2) / m) : 0};
   }
-  ConvReduction* d_red = arena.add(red);
+  for (u32 i = 0; i < c->nm; i++) {
+    const u64 m = c->mod[i];
+    const u32 e = h_bits(m), sh = e > 50 ? e - 48 : 0;
+    wide[i] = ConvReduction{sh, e > 50 ? -(int)((((u128)1 << (64 + sh)) + m / 2) / m) : 0};
+  }
+  ConvReduction *d_red = arena.add(red), *d_wide = arena.add(wide);
   DeviceGuard guard(c->device);
   if (!guard.ok) return fail(CKKS_EHIP, "cannot select the context's device");
   char* dev = nullptr;
@@ -490,6 +503,7 @@ int build_levels(ckks_ctx* c) {
   }
   c->d_levels = dev;
   c->d_conv_red = (ConvReduction*)(dev + (size_t)d_red);
+  c->d_wide_red = (ConvReduction*)(dev + (size_t)d_wide);
   c->levels.swap(lv);
   return CKKS_OK;
 }
@@ -794,41 +808,79 @@ KsLayout ks_layout(const ckks_ctx* c, u32 B, u32 nlimbs) {
   return L;
 }
 
-// Base-conversion launches: two adjacent coefficients per lane up to 24 sources, one beyond (register budget).
+// Base-conversion launches, two adjacent coefficients per lane.
 template <bool PRESCALED, bool NARROW>
 void launch_modup_n(const ckks_ctx* c, const ModUpArgs& a, u32 beta, u32 B, hipStream_t st) {
-  dim3 block(BCONV_THREADS), g2(c->N / BCONV_THREADS / 2, beta, B), g1(c->N / BCONV_THREADS, beta, B);
-#define LAUNCH_MODUP(LEN, EPT, GRID) \
-  hipLaunchKernelGGL((modup_kernel<LEN, PRESCALED, EPT, NARROW>), GRID, block, 0, st, a, a.dcoef, a.ext, a.mods, a.mat)
-  if (c->alpha <= 4) LAUNCH_MODUP(4, 2, g2);
-  else if (c->alpha <= 8) LAUNCH_MODUP(8, 2, g2);
-  else if (c->alpha <= 15) LAUNCH_MODUP(15, 2, g2);
-  else if (c->alpha <= 24) LAUNCH_MODUP(24, 2, g2);
-  else if (c->alpha <= 36) LAUNCH_MODUP(36, 1, g1);
-  else LAUNCH_MODUP(45, 1, g1);
-#undef LAUNCH_MODUP
+  dim3 block(BCONV_THREADS), grid(c->N / BCONV_THREADS / 2, beta, B);
+  if (c->alpha <= 4) hipLaunchKernelGGL((modup_kernel<4, PRESCALED, NARROW>), grid, block, 0, st, a, a.dcoef, a.ext, a.mods, a.mat);
+  else hipLaunchKernelGGL((modup_kernel<8, PRESCALED, NARROW>), grid, block, 0, st, a, a.dcoef, a.ext, a.mods, a.mat);
+}
+// Conversions of more than 8 sources, on the matrix cores.
+void launch_wide(const WideArgs& a, u32 digits, u32 npoly, hipStream_t st) {
+  const dim3 block(WIDE_THREADS), grid(std::max(1u, (1u << a.logN) / WIDE_THREADS), digits, npoly);
+  switch (conv_groups(a.alpha)) {
+    case 3: hipLaunchKernelGGL(conv_wide_kernel<3>, grid, block, 0, st, a); break;
+    case 4: hipLaunchKernelGGL(conv_wide_kernel<4>, grid, block, 0, st, a); break;
+    case 6: hipLaunchKernelGGL(conv_wide_kernel<6>, grid, block, 0, st, a); break;
+    case 9: hipLaunchKernelGGL(conv_wide_kernel<9>, grid, block, 0, st, a); break;
+    default: hipLaunchKernelGGL(conv_wide_kernel<12>, grid, block, 0, st, a); break;
+  }
 }
 template <bool PRESCALED>
-void launch_modup(const ckks_ctx* c, const ModUpArgs& a, u32 beta, u32 B, bool narrow, hipStream_t st) {
+void launch_modup(const ckks_ctx* c, const LevelTables* lt, const ModUpArgs& a, u32 beta, u32 B, hipStream_t st) {
+  const bool narrow = lt->narrow_up;
+  if (c->alpha > CONV_MAX_SRC) {
+    WideArgs w;
+    w.src = a.dcoef;
+    w.dst = a.ext;
+    w.src_poly_stride = (u64)a.nlimbs << a.logN;
+    w.dst_poly_stride = (u64)a.next << a.logN;
+    w.pieces = lt->up_pieces;
+    w.red = c->d_wide_red;
+    w.mods = c->d_mods;
+    w.inv = PRESCALED ? nullptr : lt->up_inv;
+    w.logN = a.logN;
+    w.src_slot0 = w.src_id0 = 0;
+    w.src_nlimbs = a.nlimbs;
+    w.alpha = c->alpha;
+    w.beta = beta;
+    w.skip_own = 1;
+    w.ntarget = a.next;
+    w.main = a.nlimbs;
+    w.special = c->nq;
+    return launch_wide(w, beta, B, st);
+  }
   if (narrow) launch_modup_n<PRESCALED, true>(c, a, beta, B, st);
   else launch_modup_n<PRESCALED, false>(c, a, beta, B, st);
 }
 template <bool PRESCALED, bool NARROW>
 void launch_moddown_n(const ckks_ctx* c, const ModDownArgs& a, u32 B2, hipStream_t st) {
-  dim3 block(BCONV_THREADS), g2(c->N / BCONV_THREADS / 2, B2), g1(c->N / BCONV_THREADS, B2);
-  const u32 K = a.K;
-#define LAUNCH_MODDOWN(LEN, EPT, GRID) \
-  hipLaunchKernelGGL((moddown_kernel<LEN, PRESCALED, EPT, NARROW>), GRID, block, 0, st, a, a.acc, a.tq, a.mods, a.mat)
-  if (K <= 4) LAUNCH_MODDOWN(4, 2, g2);
-  else if (K <= 8) LAUNCH_MODDOWN(8, 2, g2);
-  else if (K <= 15) LAUNCH_MODDOWN(15, 2, g2);
-  else if (K <= 24) LAUNCH_MODDOWN(24, 2, g2);
-  else if (K <= 36) LAUNCH_MODDOWN(36, 1, g1);
-  else LAUNCH_MODDOWN(45, 1, g1);
-#undef LAUNCH_MODDOWN
+  dim3 block(BCONV_THREADS), grid(c->N / BCONV_THREADS / 2, B2);
+  if (a.K <= 4) hipLaunchKernelGGL((moddown_kernel<4, PRESCALED, NARROW>), grid, block, 0, st, a, a.acc, a.tq, a.mods, a.mat);
+  else hipLaunchKernelGGL((moddown_kernel<8, PRESCALED, NARROW>), grid, block, 0, st, a, a.acc, a.tq, a.mods, a.mat);
 }
 template <bool PRESCALED>
-void launch_moddown(const ckks_ctx* c, const ModDownArgs& a, u32 B2, bool narrow, hipStream_t st) {
+void launch_moddown(const ckks_ctx* c, const LevelTables* lt, const ModDownArgs& a, u32 B2, bool narrow, hipStream_t st) {
+  if (a.K > CONV_MAX_SRC) {
+    WideArgs w;
+    w.src = a.acc;
+    w.dst = a.tq;
+    w.src_poly_stride = (u64)a.next << a.logN;
+    w.dst_poly_stride = (u64)a.nlimbs << a.logN;
+    w.pieces = lt->dn_pieces;
+    w.red = c->d_wide_red;
+    w.mods = c->d_mods;
+    w.inv = PRESCALED ? nullptr : lt->dn_inv;
+    w.logN = a.logN;
+    w.src_slot0 = a.src_slot;
+    w.src_id0 = a.src_id0;
+    w.src_nlimbs = w.alpha = a.K;
+    w.beta = 1;
+    w.skip_own = 0;
+    w.ntarget = w.main = a.nlimbs;
+    w.special = 0;
+    return launch_wide(w, 1, B2, st);
+  }
   if (narrow) launch_moddown_n<PRESCALED, true>(c, a, B2, st);
   else launch_moddown_n<PRESCALED, false>(c, a, B2, st);
 }
@@ -1074,7 +1126,7 @@ int ks16_moddown_rows(ckks_ctx* c, const LevelTables* lt, u32 B, u32 nlimbs, u64
     {
       ModDownArgs a{acc, tq, c->d_mods, lt->dn_inv, lt->dn_mat_plain, c->logN, nlimbs, c->nq, K, next, nlimbs, c->nq};
       ProfScope ps(c, PK_MODDOWN, st);
-      launch_moddown<true>(c, a, B * 2, lt->narrow_dn, st);
+      launch_moddown<true>(c, lt, a, B * 2, lt->narrow_dn, st);
       HIP_TRY(hipGetLastError());
     }
     NttOpts o2;
@@ -1221,7 +1273,7 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
   } else if (!fused_up) {
     ModUpArgs a{dcoef, ext, c->d_mods, lt->up_inv, lt->up_mat, c->logN, nlimbs, c->nq, c->alpha, beta, next};
     ProfScope ps(c, PK_MODUP, st);
-    launch_modup<true>(c, a, beta, B, lt->narrow_up, st);
+    launch_modup<true>(c, lt, a, beta, B, st);
     HIP_TRY(hipGetLastError());
   }
   if (fork) {
@@ -1396,7 +1448,7 @@ static int hoist_front16(ckks_ctx* c, const LevelTables* lt, const u64* ct_in, u
   } else {
     ModUpArgs a{dcoef, ext, c->d_mods, lt->up_inv, lt->up_mat, c->logN, nlimbs, c->nq, c->alpha, beta, next};
     ProfScope ps(c, PK_MODUP, st);
-    launch_modup<true>(c, a, beta, B, lt->narrow_up, st);
+    launch_modup<true>(c, lt, a, beta, B, st);
     HIP_TRY(hipGetLastError());
   }
   of.raw_out = true;  // reduced doubles on double-precision moduli, canonical residues elsewhere
@@ -1617,7 +1669,7 @@ int keyswitch_impl(ckks_ctx* c, const KsIo& io, u32 B, u32 nlimbs, const u64* ev
   {
     ModUpArgs a{dcoef, ext, c->d_mods, lt->up_inv, lt->up_mat, c->logN, nlimbs, c->nq, c->alpha, beta, next};
     ProfScope ps(c, PK_MODUP, st);
-    launch_modup<false>(c, a, beta, B, lt->narrow_up, st);
+    launch_modup<false>(c, lt, a, beta, B, st);
     HIP_TRY(hipGetLastError());
   }
   // 3. forward transform of the converted slots
@@ -1639,7 +1691,7 @@ int keyswitch_impl(ckks_ctx* c, const KsIo& io, u32 B, u32 nlimbs, const u64* ev
   {
     ModDownArgs a{acc, tq, c->d_mods, lt->dn_inv, lt->dn_mat, c->logN, nlimbs, c->nq, K, next, nlimbs, c->nq};
     ProfScope ps(c, PK_MODDOWN, st);
-    launch_moddown<false>(c, a, B * 2, lt->narrow_dn, st);
+    launch_moddown<false>(c, lt, a, B * 2, lt->narrow_dn, st);
     HIP_TRY(hipGetLastError());
   }
   // 7. its forward transform, 8. subtract, scale by P^-1, assemble
@@ -2635,7 +2687,7 @@ int ckks_rescale(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_in, uint32_t 
   {
     ModDownArgs a{last, tq, c->d_mods, lt->rs_one, lt->rs_mat, c->logN, nl1, c->nq, 1, 1, 0, nl1};
     ProfScope ps(c, PK_MODDOWN, st);
-    launch_moddown<true>(c, a, B * 2, lt->narrow_rs, st);
+    launch_moddown<true>(c, lt, a, B * 2, lt->narrow_rs, st);
     HIP_TRY(hipGetLastError());
   }
   // 3. back to the evaluation domain, subtract, divide by q_last

@@ -311,15 +311,16 @@ struct ConvTarget {
   int mu;
   u64 m;
   double qd, qinv;
-  __device__ __forceinline__ void fetch(const ConvArgs& a, u32 target) {
-    slot = target & 255;
-    id = target >> 8;
-    const ModInfo mi = conv_mod(a.mods, id);
+  __device__ __forceinline__ void fetch(const ModInfo* mods, const ConvReduction* red, u32 slot_, u32 id_) {
+    slot = slot_;
+    id = id_;
+    const ModInfo mi = conv_mod(mods, id);
     m = mi.m, qd = mi.qd, qinv = mi.qinv;
-    const u64 red = conv_const(a.red)[id];
-    sh = (u32)red;
-    mu = (int)(red >> 32);
+    const u64 r = conv_const(red)[id];
+    sh = (u32)r;
+    mu = (int)(r >> 32);
   }
+  __device__ __forceinline__ void fetch(const ConvArgs& a, u32 target) { fetch(a.mods, a.red, target & 255, target >> 8); }
 };
 // The lanes' rows of a pair of targets: lane (h, n) has bytes of sources 4g + 2h and 4g + 2h + 1 (byte p of every C_ki, i
 // ascending), p = 4 * bit 3 of n + the two lowest bits of n, of target bit 2 of n. Wave g < MAXLEN / 4 copies the rows of group g

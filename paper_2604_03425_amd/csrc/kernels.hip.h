@@ -133,53 +133,24 @@ __global__ void __launch_bounds__(256) automorph_kernel(AutoArgs a) {
 template <int MAXLEN, bool NARROW>
 __device__ __forceinline__ u64 bconv_dot(const u32 (&y0)[MAXLEN], const u32 (&y1)[MAXLEN], u32 nneg,
                                          const u64* __restrict__ crow, const ModInfo& mi) {
+  static_assert(MAXLEN <= 15, "more terms leave 64 bits");
+  const u64 neg = crow[MAXLEN];
   if (NARROW) {
-    u64 r = 0;
+    Dot30N dd;
+    dot30n_init(dd);
 #pragma unroll
-    for (int i0 = 0; i0 < MAXLEN; i0 += 15) {
-      Dot30N dd;
-      dot30n_init(dd);
-#pragma unroll
-      for (int i = i0; i < i0 + 15 && i < MAXLEN; i++) {
-        const u64 c = crow[i];
-        dot30n_mac(dd, y0[i], y1[i], (u32)c & M30, (u32)(c >> 30));
-      }
-      if (i0 == 0) {
-        const u64 c = crow[MAXLEN];
-        dd.a += (u64)nneg * ((u32)c & M30);
-        dd.b += (u64)nneg * (u32)(c >> 30);
-      }
-      r += dot30n_redc90(dd, mi.m, mi.minv);   // each part < m + 2^34
-    }
-    if (MAXLEN > 15) r = csub(r, 2 * mi.m);   // three chunks: r < 4m
-    return csub(r, mi.m);
+    for (int i = 0; i < MAXLEN; i++) dot30n_mac(dd, y0[i], y1[i], (u32)crow[i] & M30, (u32)(crow[i] >> 30));
+    dd.a += (u64)nneg * ((u32)neg & M30);
+    dd.b += (u64)nneg * (u32)(neg >> 30);
+    return csub(dot30n_redc90(dd, mi.m, mi.minv), mi.m);
   }
-  Acc128 V = {0, 0};
+  Dot30 dd;
+  dot30_init(dd);
 #pragma unroll
-  for (int i0 = 0; i0 < MAXLEN; i0 += 15) {
-    Dot30 dd;
-    dot30_init(dd);
-#pragma unroll
-    for (int i = i0; i < i0 + 15 && i < MAXLEN; i++) {
-      const u64 c = crow[i];
-      dot30_mac(dd, y0[i], y1[i], (u32)c & M30, (u32)(c >> 30));
-    }
-    if (i0 == 0) {
-      const u64 c = crow[MAXLEN];
-      dd.s00 += (u64)nneg * ((u32)c & M30);
-      dd.s01 += (u64)nneg * (u32)(c >> 30);
-    }
-    Acc128 part = dot30_value(dd);
-    if (i0 == 0) {
-      V = part;
-    } else {
-      V.lo += part.lo;
-      V.hi += part.hi + (V.lo < part.lo ? 1ull : 0ull);
-    }
-  }
-  u64 r = redc(V, mi.m, mi.minv);
-  if (MAXLEN > 15) r = csub(r, 2 * mi.m);  // three chunks of 15 products: r < 4m
-  return csub(r, mi.m);
+  for (int i = 0; i < MAXLEN; i++) dot30_mac(dd, y0[i], y1[i], (u32)crow[i] & M30, (u32)(crow[i] >> 30));
+  dd.s00 += (u64)nneg * ((u32)neg & M30);
+  dd.s01 += (u64)nneg * (u32)(neg >> 30);
+  return csub(redc(dot30_value(dd), mi.m, mi.minv), mi.m);
 }
 
 // ModUp: for digit j (limbs [lo_j, hi_j) of the coefficient-domain input), write every other slot of the extended
@@ -194,39 +165,33 @@ struct ModUpArgs {
   u32 logN, nlimbs, nq, alpha, beta, next;
 };
 // PRESCALED: the input already holds y_i (the inverse transform folded (Q_j/q_i)^-1 into its 1/N scaling).
-// EPT: adjacent coefficients per lane (16-byte accesses for EPT = 2); the constants of an output are fetched once
-// per lane through scalar loads and reused for all of them.
+// Two adjacent coefficients per lane (16-byte accesses); the constants of an output are fetched once per lane through scalar
+// loads and reused for both. Up to 8 sources; more go to conv_wide_kernel.
 // The tables and buffers are also passed as separate no-alias parameters: only then can the compiler see that the
 // stores never touch the constants and fetch those through wave-uniform scalar loads (splitting them on the
 // scalar unit as well).
-template <int MAXLEN, bool PRESCALED, int EPT, bool NARROW>
+template <int MAXLEN, bool PRESCALED, bool NARROW>
 __global__ void __launch_bounds__(BCONV_THREADS) modup_kernel(ModUpArgs a, const u64* __restrict__ dcoef,
                                                               u64* __restrict__ ext, const ModInfo* __restrict__ mods,
                                                               const u64* __restrict__ matrix) {
   const u32 N = 1u << a.logN;
-  const u32 n = (blockIdx.x * BCONV_THREADS + threadIdx.x) * EPT;
+  const u32 n = (blockIdx.x * BCONV_THREADS + threadIdx.x) * 2;
   const u32 j = blockIdx.y, b = blockIdx.z;
   const u32 lo = j * a.alpha, hi = min(lo + a.alpha, a.nlimbs), len = hi - lo;
   const u64* d = dcoef + ((size_t)b * a.nlimbs + lo) * N + n;
-  u32 y0[EPT][MAXLEN], y1[EPT][MAXLEN], nneg[EPT];
+  u32 y0[2][MAXLEN], y1[2][MAXLEN], nneg[2];
 #pragma unroll
-  for (int e = 0; e < EPT; e++) nneg[e] = 0;
+  for (int e = 0; e < 2; e++) nneg[e] = 0;
 #pragma unroll
   for (int i = 0; i < MAXLEN; i++) {
 #pragma unroll
-    for (int e = 0; e < EPT; e++) y0[e][i] = y1[e][i] = 0;
+    for (int e = 0; e < 2; e++) y0[e][i] = y1[e][i] = 0;
     if ((u32)i < len) {
       const u64 m = mods[lo + i].m;
-      u64 yv[EPT];
-      if (EPT == 2) {
-        const ulonglong2 v = *(const ulonglong2*)(d + (size_t)i * N);
-        yv[0] = v.x;
-        yv[EPT - 1] = v.y;
-      } else {
-        yv[0] = d[(size_t)i * N];
-      }
+      const ulonglong2 v = *(const ulonglong2*)(d + (size_t)i * N);
+      const u64 yv[2] = {v.x, v.y};
 #pragma unroll
-      for (int e = 0; e < EPT; e++) {
+      for (int e = 0; e < 2; e++) {
         u64 y = yv[e];
         if (!PRESCALED) {
           ulonglong2 c = a.inv[j * a.alpha + i];
@@ -244,11 +209,10 @@ __global__ void __launch_bounds__(BCONV_THREADS) modup_kernel(ModUpArgs a, const
     if (t >= lo && t < hi) continue;
     const u32 id = t < a.nlimbs ? t : t - a.nlimbs + a.nq;
     const ModInfo mi = mods[id];
-    u64 r[EPT];
+    u64 r[2];
 #pragma unroll
-    for (int e = 0; e < EPT; e++) r[e] = bconv_dot<MAXLEN, NARROW>(y0[e], y1[e], nneg[e], mat + (size_t)t * (MAXLEN + 1), mi);
-    if (EPT == 2) *(ulonglong2*)(out + (size_t)t * N) = ulonglong2{r[0], r[EPT - 1]};
-    else out[(size_t)t * N] = r[0];
+    for (int e = 0; e < 2; e++) r[e] = bconv_dot<MAXLEN, NARROW>(y0[e], y1[e], nneg[e], mat + (size_t)t * (MAXLEN + 1), mi);
+    *(ulonglong2*)(out + (size_t)t * N) = ulonglong2{r[0], r[1]};
   }
 }
 
@@ -294,33 +258,27 @@ struct ModDownArgs {
   u32 src_slot;           // slot of the first source limb inside a row of `acc` (nlimbs for a key switch)
   u32 src_id0;            // modulus id of the first source limb (nq for a key switch)
 };
-template <int MAXLEN, bool PRESCALED, int EPT, bool NARROW>
+template <int MAXLEN, bool PRESCALED, bool NARROW>
 __global__ void __launch_bounds__(BCONV_THREADS) moddown_kernel(ModDownArgs a, const u64* __restrict__ acc,
                                                                 u64* __restrict__ tq, const ModInfo* __restrict__ mods,
                                                                 const u64* __restrict__ matrix) {
   const u32 N = 1u << a.logN;
-  const u32 n = (blockIdx.x * BCONV_THREADS + threadIdx.x) * EPT;
+  const u32 n = (blockIdx.x * BCONV_THREADS + threadIdx.x) * 2;
   const u32 bc = blockIdx.y;
   const u64* x = acc + ((size_t)bc * a.next + a.src_slot) * N + n;
-  u32 y0[EPT][MAXLEN], y1[EPT][MAXLEN], nneg[EPT];
+  u32 y0[2][MAXLEN], y1[2][MAXLEN], nneg[2];
 #pragma unroll
-  for (int e = 0; e < EPT; e++) nneg[e] = 0;
+  for (int e = 0; e < 2; e++) nneg[e] = 0;
 #pragma unroll
   for (int k = 0; k < MAXLEN; k++) {
 #pragma unroll
-    for (int e = 0; e < EPT; e++) y0[e][k] = y1[e][k] = 0;
+    for (int e = 0; e < 2; e++) y0[e][k] = y1[e][k] = 0;
     if ((u32)k < a.K) {
       const u64 m = mods[a.src_id0 + k].m;
-      u64 yv[EPT];
-      if (EPT == 2) {
-        const ulonglong2 v = *(const ulonglong2*)(x + (size_t)k * N);
-        yv[0] = v.x;
-        yv[EPT - 1] = v.y;
-      } else {
-        yv[0] = x[(size_t)k * N];
-      }
+      const ulonglong2 v = *(const ulonglong2*)(x + (size_t)k * N);
+      const u64 yv[2] = {v.x, v.y};
 #pragma unroll
-      for (int e = 0; e < EPT; e++) {
+      for (int e = 0; e < 2; e++) {
         u64 y = yv[e];
         if (!PRESCALED) {
           ulonglong2 c = a.inv[k];
@@ -335,11 +293,10 @@ __global__ void __launch_bounds__(BCONV_THREADS) moddown_kernel(ModDownArgs a, c
   u64* out = tq + (size_t)bc * a.nlimbs * N + n;
   for (u32 i = 0; i < a.nlimbs; i++) {
     const ModInfo mi = mods[i];
-    u64 r[EPT];
+    u64 r[2];
 #pragma unroll
-    for (int e = 0; e < EPT; e++) r[e] = bconv_dot<MAXLEN, NARROW>(y0[e], y1[e], nneg[e], matrix + (size_t)i * (MAXLEN + 1), mi);
-    if (EPT == 2) *(ulonglong2*)(out + (size_t)i * N) = ulonglong2{r[0], r[EPT - 1]};
-    else out[(size_t)i * N] = r[0];
+    for (int e = 0; e < 2; e++) r[e] = bconv_dot<MAXLEN, NARROW>(y0[e], y1[e], nneg[e], matrix + (size_t)i * (MAXLEN + 1), mi);
+    *(ulonglong2*)(out + (size_t)i * N) = ulonglong2{r[0], r[1]};
   }
 }
 
