@@ -1152,9 +1152,8 @@ int ks16_moddown_rows(ckks_ctx* c, const LevelTables* lt, u32 B, u32 nlimbs, u64
 }
 
 // Last kernel of a key switch on the two-pass path: block pass of tq fused with (acc - tq) / P and the addends.
-// exclude_class >= 0 leaves the limbs of that modulus class to another kernel.
 int ks16_assemble(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B, u32 nlimbs, const u64* acc, const u64* tq,
-                  hipStream_t st, int exclude_class = -1) {
+                  hipStream_t st) {
   FwdFinalArgs a;
   a.tq = tq;
   a.acc = acc;
@@ -1177,10 +1176,7 @@ int ks16_assemble(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B, u32
     for (u32 i = 0; i < B; i++) a.galois_pc[i] = io.galois_pc[i];
   }
   a.map_mode = map_mode_pass(c);
-  auto cls_of = [&](u32 s) {
-    const int k = host_class(c, c->mod[s]);
-    return k == exclude_class ? -1 : k;
-  };
+  auto cls_of = [&](u32 s) { return host_class(c, c->mod[s]); };
   launch_by_class(c, PK_FWD_FINAL, a, B * 2, nlimbs, cls_of, st,
                   [&](int cls, dim3 grid) { LAUNCH_CLASS_KERNEL(ntt16_fwd_blocks_final_kernel, cls, grid, st, a); });
   HIP_TRY(hipGetLastError());
@@ -1349,18 +1345,24 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
     ia.c0 = io.add_src;
     ia.c0_poly_stride = 2 * (u64)nlimbs * N;
   }
-  // 3. integer-class slots, 8 values per lane (grid.y = tiles of 8 blocks); the special ones go on through their inverse block pass
+  // 3. integer-class slots, 8 values per lane (grid.y = tiles of 8 blocks): the special ones, which go on through their inverse
+  // block pass, and the main ones where their accumulators are needed in memory
   if (!acc_add) ia.twi = c->d_tw_inv;
-  for (int cls = 1; cls <= 2; cls++) {
-    FwdInnerArgs a = ia;
-    u32 cnt = 0;
-    for (u32 s_ = 0; s_ < next; s_++)
-      if (ext_class(s_) == cls) a.slots[cnt++] = (unsigned char)s_;
-    if (!cnt) continue;
-    ProfScope ps(c, PK_INNER8 + cls - 1, st);
-    if (cls == 1) hipLaunchKernelGGL(ntt16_fwd_blocks_inner8_kernel<1>, dim3(B, N / 2048, cnt), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL(ntt16_fwd_blocks_inner8_kernel<2>, dim3(B, N / 2048, cnt), dim3(256), 0, st, a);
-  }
+  auto launch_inner8 = [&](FwdInnerArgs a, bool special, bool main_slots, bool fin) {
+    for (int cls = 1; cls <= 2; cls++) {
+      u32 cnt = 0;
+      for (u32 s_ = 0; s_ < next; s_++)
+        if (ext_class(s_) == cls && (s_ >= nlimbs ? special : main_slots)) a.slots[cnt++] = (unsigned char)s_;
+      if (!cnt) continue;
+      ProfScope ps(c, PK_INNER8 + cls - 1, st);
+      const dim3 grid(B, N / 2048, cnt), block(256);
+      if (fin && cls == 1) hipLaunchKernelGGL((ntt16_fwd_blocks_inner8_kernel<1, true>), grid, block, 0, st, a);
+      else if (fin) hipLaunchKernelGGL((ntt16_fwd_blocks_inner8_kernel<2, true>), grid, block, 0, st, a);
+      else if (cls == 1) hipLaunchKernelGGL((ntt16_fwd_blocks_inner8_kernel<1, false>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((ntt16_fwd_blocks_inner8_kernel<2, false>), grid, block, 0, st, a);
+    }
+  };
+  launch_inner8(ia, true, acc_add || !fused_fp, false);
   HIP_TRY(hipGetLastError());
   // double-precision slots whose accumulators are needed in memory: the special ones always (ModDown reads them),
   // the main ones when the result is accumulated or when the fusion of step 5 is switched off
@@ -1395,29 +1397,29 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
   if ((rc = ks16_moddown_rows(c, lt, B, nlimbs, acc, tq, st, true))) return rc;
   if (fork) HIP_TRY(hipStreamWaitEvent(st, c->ev_join, 0));
   // 5.
-  if (fused_fp && any_fp) {
-    FwdInnerArgs a = ia;
-    u32 cnt = 0;
-    for (u32 s_ = 0; s_ < nlimbs; s_++)
-      if (ext_class(s_) == 0) a.slots[cnt++] = (unsigned char)s_;
-    if (cnt) {
-      a.fin_tq = tq;
-      a.fin_out = io.out;
-      a.fin_add_src = io.add_src;
-      a.fin_add2 = io.add2 ? io.add2 : io.out;
-      a.fin_add2_three = io.add2 && io.add2_three ? 1u : 0u;
-      a.fin_pinv = lt->pinv2;
-      a.fin_mode0 = io.mode[0];
-      a.fin_mode1 = io.mode[1];
-      a.fin_galois = io.add_galois;
-      a.prod_a = io.prod_a;
-      a.prod_b = io.prod_b;
-      ProfScope ps(c, PK_INNER_C, st);
-      launch_inner_c(c, B, cnt, a, st);
-      HIP_TRY(hipGetLastError());
-    }
+  if (!fused_fp) return ks16_assemble(c, lt, io, B, nlimbs, acc, tq, st);
+  FwdInnerArgs a = ia;
+  a.fin_tq = tq;
+  a.fin_out = io.out;
+  a.fin_add_src = io.add_src;
+  a.fin_add2 = io.add2 ? io.add2 : io.out;
+  a.fin_add2_three = io.add2 && io.add2_three ? 1u : 0u;
+  a.fin_pinv = lt->pinv2;
+  a.fin_mode0 = io.mode[0];
+  a.fin_mode1 = io.mode[1];
+  a.fin_galois = io.add_galois;
+  a.prod_a = io.prod_a;
+  a.prod_b = io.prod_b;
+  u32 cnt = 0;
+  for (u32 s_ = 0; s_ < nlimbs; s_++)
+    if (ext_class(s_) == 0) a.slots[cnt++] = (unsigned char)s_;
+  if (cnt) {
+    ProfScope ps(c, PK_INNER_C, st);
+    launch_inner_c(c, B, cnt, a, st);
   }
-  return ks16_assemble(c, lt, io, B, nlimbs, acc, tq, st, fused_fp ? 0 : -1);
+  launch_inner8(a, false, true, true);
+  HIP_TRY(hipGetLastError());
+  return CKKS_OK;
 }
 
 // Shared front of the hoisted rotations: inverse transform, ModUp and forward transform of c1 of ct_in
@@ -2240,14 +2242,10 @@ int ckks_hmult_relin(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_a, const 
     io.prod_b = (const u64*)ct_b;
     return keyswitch_impl(c, io, B, nlimbs, (const u64*)evk, (char*)ws, st);
   }
-  // Two-pass rings, double-precision main primes: the products are formed where they are read (first inverse pass, own
-  // digits, assembly), which takes 6 passes over a limb vector where a product kernel of its own and the reads of its
-  // results took 11: 32 products of 24 limbs at 2^16 3328 -> 3099 us, 3 of 11 limbs 230 -> 216, 8 of 13 limbs at 2^15
-  // 308 -> 293. Integer-class primes keep it: their inner product takes neither the inputs of a product nor the assembly. One
-  // such prime among the main limbs keeps it for all of them.
-  bool all_fp = two_pass(c) && c->tune[3] != 1;
-  for (u32 i = 0; i < nlimbs; i++) all_fp = all_fp && host_class(c, c->mod[i]) == 0;
-  if (all_fp) {
+  // Two-pass rings: the products are formed where they are read (first inverse pass, own digits, assembly), which takes 6 passes
+  // over a limb vector where a product kernel of its own and the reads of its results took 11: 32 products of 24 limbs at
+  // 2^16 3328 -> 3099 us, 3 of 11 limbs 230 -> 216, 8 of 13 limbs at 2^15 308 -> 293.
+  if (two_pass(c) && c->tune[3] != 1) {
     KsIo io{nullptr, 0, 0, (u64*)ct_out, {4, 4}, nullptr, 0};
     io.prod_a = (const u64*)ct_a;
     io.prod_b = (const u64*)ct_b;

@@ -207,6 +207,12 @@ __device__ __forceinline__ u64 mont_mul63(u64 x, u64 e, u64 m, u64 minv) {
   return (u64)x1 * e1 + ((u64)u1 * m1 + (mid >> 32)) + (((u64)u1 * m0 + (u32)mid) >> 32);
 }
 
+// x * e mod m, canonical, for x < 2^63 and e < m: two Montgomery products, r2 = 2^128 mod m (mont_r2).
+__device__ __forceinline__ u64 mont_r2(const ModInfo& mi) { return mulmod(mi.c64, mi.c64, mi); }
+__device__ __forceinline__ u64 mont_plain(u64 x, u64 e, u64 r2, u64 m, u64 minv) {
+  return csub(mont_mul63(mont_mul63(x, e, m, minv), r2, m, minv), m);
+}
+
 // Eval-domain Galois map: out[k] = in[k'], 2*brev(k')+1 = (2*brev(k)+1)*g mod 2N. It maps every aligned 16-element
 // segment onto an aligned 16-element segment, so 16 adjacent lanes still read one 128-byte line. Computed on values
 // scaled by 2^(31 - logN), where the reduction modulo 2N is the 32-bit wrap-around.

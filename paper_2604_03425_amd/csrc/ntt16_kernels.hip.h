@@ -7,6 +7,8 @@
 #include "ntt16.hip.h"
 #include "ntt16fp.hip.h"
 
+#include <type_traits>
+
 // ---- standalone passes: grid = (polynomials, N / 4096 tiles, limb slots) ----
 // A batched rotation may give every ciphertext its own Galois element and key: the kernels then take both from
 // small per-ciphertext tables carried in the kernel arguments (at most this many ciphertexts per launch sequence).
@@ -25,8 +27,8 @@ struct Ntt16Args {
   u32 raw_out;                           // forward last pass, double-precision class only: != 0 leaves reduced doubles
   u32 split_out = 0;                     // inverse second pass only: != 0 writes (y + (q-1)/2) mod q as two 30-bit halves
                                          // (bits 0..29, 32..62), the source form of ntt16_bconv_rows_kernel
-  const u64* src_b = nullptr;            // inverse first pass, double-precision class only: != null transforms the products of
-                                         // src and src_b (same layout) instead of src
+  const u64* src_b = nullptr;            // inverse first pass only: != null transforms the products of src and src_b (same
+                                         // layout) instead of src
   u32 galois;                            // inverse first pass only: != 0 reads src through the eval-domain Galois map
   u32 multi = 0;                         // != 0: polynomial p is read through galois_pc[p] instead (p < KS_MULTI_MAX)
   u32 galois_pc[KS_MULTI_MAX];
@@ -116,7 +118,17 @@ __global__ void __launch_bounds__(NTT16_THREADS) ntt16_inv_blocks_kernel(Ntt16Ar
     ntt16_inv_blocks_fp(xd, twfp, mi.qd, mi.qinv, tile, R, (double*)sm);
 #pragma unroll
     for (int i = 0; i < 16; i++) x[i] = (u64)__double_as_longlong(xd[i]);
-  } else if (cls == 2) {
+#pragma unroll
+    for (int i = 0; i < 16; i++) dst[(size_t)h * 256 + i * 16 + j0] = x[i];
+    return;
+  }
+  if (a.src_b) {
+    const u64* sb = a.src_b + (size_t)poly * a.src_poly_stride + ((size_t)slot << logN);
+    const u64 r2 = mont_r2(mi);
+#pragma unroll
+    for (int i = 0; i < 16; i++) x[i] = mont_plain(x[i], sb[(size_t)h * 256 + i * 16 + j0], r2, mi.m, mi.minv);
+  }
+  if (cls == 2) {
     ntt16_inv_blocks<true>(x, tw, mi.m, mi.mu64, tile, R, sm);
   } else {
     ntt16_inv_blocks<false>(x, tw, mi.m, mi.mu64, tile, R, sm);
@@ -383,16 +395,16 @@ struct FwdInnerArgs {
   // acc + r * acc_rot_stride, and galois_pc[r] holds the INVERSE of its Galois element modulo 2N
   u32 nrot = 0;
   u64 acc_rot_stride = 0;
-  // ntt16_fwd_blocks_inner_c_kernel on main-prime slots only: fin_tq != null finishes the key switch in the same
+  // fused kernels on main-prime slots only: fin_tq != null (FIN of the integer ones) finishes the key switch in the same
   // kernel instead of storing the accumulator: out = (sum - NTT(tq)) / P (+ addends), with the arguments of
-  // FwdFinalArgs (tq after the row pass, [B*2][nlimbs][N]; pinv [nlimbs] as (1/P, (1/P)/q); addend modes per component)
+  // FwdFinalArgs (tq after the row pass, [B*2][nlimbs][N]; pinv [nlimbs]; addend modes per component)
   const u64* fin_tq = nullptr;
   u64* fin_out = nullptr;
   const u64* fin_add2 = nullptr;
   const u64* fin_add_src = nullptr;
   const ulonglong2* fin_pinv = nullptr;
   u32 fin_mode0 = 0, fin_mode1 = 0, fin_galois = 0, fin_add2_three = 0;
-  // the same kernel: != null switches the product of the second components of two ciphertexts ([B][2][nlimbs][N] each; d is
+  // the same kernels: != null switches the product of the second components of two ciphertexts ([B][2][nlimbs][N] each; d is
   // not read) and adds the other two terms of the product to the result (fin_mode0 == fin_mode1 == 4)
   const u64 *prod_a = nullptr, *prod_b = nullptr;
 };
@@ -618,7 +630,20 @@ ntt16_fwd_blocks_inner_c_kernel(FwdInnerArgs a) {
 // (ntt256_fwd_blocks_int8), which keeps the kernel at 3 waves per SIMD. After the transform a lane holds 8 consecutive
 // coefficients, so key words and accumulators move as 16-byte accesses. Products go through a Montgomery reduction:
 // acc carries the factor 2^-64, which the later stages absorb into their constants.
-template <int CLS>
+// FIN: main limbs, the rest of the key switch too, for both components as ntt16_fwd_blocks_inner_c_kernel does it for one: the
+// accumulators never reach memory, the correction's tiles come through the same LDS image. As an assembly kernel of its own (4
+// more passes over a limb vector, and the products of two ciphertexts in a third kernel, 3 more) 4 products of 12 + 4 60-bit limbs
+// took 286 us, 242 this way.
+typedef u64 inner8_pair __attribute__((ext_vector_type(2), aligned(8)));   // callers' words need the alignment of one word only
+__device__ __forceinline__ void inner8_load(u64 (&v)[8], const u64* p) {
+#pragma unroll
+  for (int k = 0; k < 4; k++) {
+    const inner8_pair w = *(const inner8_pair*)(p + 2 * k);
+    v[2 * k] = w.x;
+    v[2 * k + 1] = w.y;
+  }
+}
+template <int CLS, bool FIN>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
 ntt16_fwd_blocks_inner8_kernel(FwdInnerArgs a) {
   constexpr bool BIG = CLS == 2;
@@ -692,11 +717,21 @@ ntt16_fwd_blocks_inner8_kernel(FwdInnerArgs a) {
   const u32 jo = t < a.nlimbs ? t / a.alpha : 0xFFFFFFFFu;   // the digit that holds limb t itself (none for special slots)
   auto ext_limb = [&](u32 j) { return a.ext + (((size_t)b * beta + j) * a.next + t) * N; };
   u32 jn = jo == 0 ? 1u : 0u;   // next converted digit
+  auto tq_limb = [&](u32 c) { return a.fin_tq + (((size_t)b * 2 + c) * a.nlimbs + t) * N; };
+  auto prod_limb = [&](const u64* p, u32 c) { return p + (((size_t)b * 2 + c) * a.nlimbs + t) * N + posC; };
+  const u64 r2 = FIN && a.prod_a ? mont_r2(mi) : 0;
   if (jn < beta) request(ext_limb(jn));
+  else if (FIN) request(tq_limb(0));
   if (jo != 0xFFFFFFFFu) {   // the own digit first: its loads are in flight together with the first prefetch
     const u64* src = a.d + (size_t)b * a.d_poly_stride + (size_t)t * N;
     request_key(jo);
-    if (g) {
+    if (FIN && a.prod_a) {
+      u64 v[8];
+      inner8_load(x, prod_limb(a.prod_a, 1));
+      inner8_load(v, prod_limb(a.prod_b, 1));
+#pragma unroll
+      for (int c = 0; c < 8; c++) x[c] = mont_plain(x[c], v[c], r2, q, mi.minv);
+    } else if (g) {
 #pragma unroll
       for (int c = 0; c < 8; c++) x[c] = src[galois_src_index(posC + c, g, a.logN)];
     } else {
@@ -719,10 +754,62 @@ ntt16_fwd_blocks_inner8_kernel(FwdInnerArgs a) {
     __builtin_amdgcn_sched_barrier(0);
     // younger than every load the products wait for, so it stays in flight across them (the current tile again when
     // nothing follows: the same static wait counts on every path)
-    request(ext_limb(jnext < beta ? jnext : jcur));
+    request(jnext < beta ? ext_limb(jnext) : FIN ? tq_limb(0) : ext_limb(jcur));
     __builtin_amdgcn_sched_barrier(0);
     multiply();
     jn = jnext;
+  }
+  if (FIN) {
+    const ulonglong2 pv = a.fin_pinv[t];
+    const u32 gf = a.multi ? g : a.fin_galois;
+    const u64 above = BIG ? 8 * q : 128 * q;   // a multiple of q above what the transform leaves
+    auto finish = [&](auto component, const u64 (&acc)[8]) {
+      constexpr u32 c = decltype(component)::value;
+      const u32 mode = c ? a.fin_mode1 : a.fin_mode0;
+      const u64* as = a.fin_add_src + (((size_t)b * 2 + c) * a.nlimbs + t) * N;
+      u64 ev[8];
+      take();
+      ntt256_fwd_blocks_int8<BIG>(x, tw, q, h, 1u << (a.logN - 8), l, smb, [&] {
+        if (mode & 1) inner8_load(ev, a.fin_add2 + ((a.fin_add2_three ? (size_t)b * 3 + c : (size_t)b * 2 + c) * a.nlimbs + t) * N + posC);
+        else if (mode == 4) inner8_load(ev, prod_limb(a.prod_a, 0));
+        else if (mode == 2) {
+#pragma unroll
+          for (int k = 0; k < 8; k++) ev[k] = as[galois_src_index(posC + k, gf, a.logN)];
+        }
+      });
+      __builtin_amdgcn_sched_barrier(0);
+      if (c == 0) request(tq_limb(1));
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int k = 0; k < 8; k++) {
+        if (BIG) x[k] = csub_neg(x[k], 8 * q);
+        x[k] = shoup(acc[k] + above - x[k], pv.x, pv.y, q);
+      }
+      if (mode == 4) {   // d0 = a0 b0, d1 = a0 b1 + a1 b0; ev holds a0
+        u64 f[8];
+        inner8_load(f, prod_limb(a.prod_b, c));
+#pragma unroll
+        for (int k = 0; k < 8; k++) x[k] = addmod(x[k], mont_plain(ev[k], f[k], r2, q, mi.minv), q);
+        if (c) {
+          inner8_load(ev, prod_limb(a.prod_a, 1));
+          inner8_load(f, prod_limb(a.prod_b, 0));
+#pragma unroll
+          for (int k = 0; k < 8; k++) x[k] = addmod(x[k], mont_plain(ev[k], f[k], r2, q, mi.minv), q);
+        }
+      } else if (mode) {
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+          x[k] = addmod(x[k], ev[k], q);
+          if (mode == 3) x[k] = addmod(x[k], as[galois_src_index(posC + k, gf, a.logN)], q);
+        }
+      }
+      u64* o = a.fin_out + (((size_t)b * 2 + c) * a.nlimbs + t) * N + posC;
+#pragma unroll
+      for (int k = 0; k < 4; k++) *(inner8_pair*)(o + 2 * k) = inner8_pair{x[2 * k], x[2 * k + 1]};
+    };
+    finish(std::integral_constant<u32, 0>{}, acc0);
+    finish(std::integral_constant<u32, 1>{}, acc1);
+    return;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no copy into LDS may outlive the workgroup
   if (a.twi && t >= a.nlimbs) {   // uniform
