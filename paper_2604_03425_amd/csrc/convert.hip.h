@@ -65,13 +65,8 @@ struct ConvArgs {
 // a value that is the same in all lanes, said so: what is derived from it then stays in scalar registers
 __device__ __forceinline__ u32 conv_uniform(u32 v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// Tables read at wave-uniform places go through the constant address space: between the barriers and stores of the target
-// loop the compiler would otherwise not use scalar loads for them.
-typedef const __attribute__((address_space(4))) u64* const_u64_ptr;
-__device__ __forceinline__ const_u64_ptr conv_const(const void* p) { return (const_u64_ptr)p; }
-__device__ __forceinline__ double conv_const_double(const_u64_ptr p) { return __longlong_as_double((long long)*p); }
 __device__ __forceinline__ ModInfo conv_mod(const ModInfo* mods, u32 id) {
-  const_u64_ptr p = conv_const(mods + id);
+  const_u64_ptr p = scalar_words(mods + id);
   ModInfo m = {};
 #define CONV_WORD(FIELD) p[offsetof(ModInfo, FIELD) / 8]
   m.m = CONV_WORD(m);
@@ -80,11 +75,6 @@ __device__ __forceinline__ ModInfo conv_mod(const ModInfo* mods, u32 id) {
   m.qinv = __longlong_as_double((long long)CONV_WORD(qinv));
 #undef CONV_WORD
   return m;
-}
-__device__ __forceinline__ void conv_fetch(double& w, const double* tw, u32 i) { w = conv_const_double(conv_const(tw) + i); }
-__device__ __forceinline__ void conv_fetch(ulonglong2& w, const ulonglong2* tw, u32 i) {
-  const_u64_ptr p = conv_const(tw) + 2 * (size_t)i;
-  w = ulonglong2{p[0], p[1]};
 }
 
 // ---- layouts ----
@@ -119,9 +109,9 @@ __device__ __forceinline__ void conv_twiddles(TW (&w)[3], const TW* __restrict__
   u32 blk = threadIdx.x >> s;
   if (s >= 6) {
     blk = conv_uniform(blk);
-    conv_fetch(w[0], tw, (1u << (2 * K)) + blk);
-    conv_fetch(w[1], tw, (2u << (2 * K)) + 2 * blk);
-    conv_fetch(w[2], tw, (2u << (2 * K)) + 2 * blk + 1);
+    scalar_fetch(w[0], tw, (1u << (2 * K)) + blk);
+    scalar_fetch(w[1], tw, (2u << (2 * K)) + 2 * blk);
+    scalar_fetch(w[2], tw, (2u << (2 * K)) + 2 * blk + 1);
     return;
   }
   w[0] = tw[(1u << (2 * K)) + blk];
@@ -134,8 +124,8 @@ __device__ __forceinline__ void conv_twiddles_last(TW (&w)[2], const TW* __restr
   u32 blk = threadIdx.x >> (11 - LOGR);
   if (11 - LOGR >= 6) {
     blk = conv_uniform(blk);
-    conv_fetch(w[0], tw, (1u << (LOGR - 1)) + 2 * blk);
-    conv_fetch(w[1], tw, (1u << (LOGR - 1)) + 2 * blk + 1);
+    scalar_fetch(w[0], tw, (1u << (LOGR - 1)) + 2 * blk);
+    scalar_fetch(w[1], tw, (1u << (LOGR - 1)) + 2 * blk + 1);
     return;
   }
   w[0] = tw[(1u << (LOGR - 1)) + 2 * blk];
@@ -316,7 +306,7 @@ struct ConvTarget {
     id = id_;
     const ModInfo mi = conv_mod(mods, id);
     m = mi.m, qd = mi.qd, qinv = mi.qinv;
-    const u64 r = conv_const(red)[id];
+    const u64 r = scalar_words(red)[id];
     sh = (u32)r;
     mu = (int)(r >> 32);
   }
@@ -487,7 +477,7 @@ __global__ void __launch_bounds__(CONV_THREADS) __attribute__((amdgpu_waves_per_
     const u32 id = a.src_id0 + lo + k;
     const ModInfo mi = conv_mod(a.mods, id);
     ulonglong2 sc;
-    if (!READY) conv_fetch(sc, a.scale, lo + k);
+    if (!READY) scalar_fetch(sc, a.scale, lo + k);
     const u64* s = src + ((size_t)min((u32)k + 1, len - 1) << LOGN) + from;
     u64 now[4];
 #pragma unroll

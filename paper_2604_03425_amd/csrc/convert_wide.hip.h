@@ -85,10 +85,10 @@ __global__ void __launch_bounds__(WIDE_THREADS) conv_wide_kernel(WideArgs a) {
 #pragma unroll
   for (int k = 0; k < 4 * G; k++) {
     const u32 i = min((u32)k, len - 1);   // uniform
-    const u64 m = conv_const(a.mods + a.src_id0 + lo + i)[offsetof(ModInfo, m) / 8], h = m >> 1;
+    const u64 m = scalar_words(a.mods + a.src_id0 + lo + i)[offsetof(ModInfo, m) / 8], h = m >> 1;
     u64 v = y[k];
     if (a.inv) {
-      const const_u64_ptr w = conv_const(a.inv + (size_t)j * a.alpha + i);
+      const const_u64_ptr w = scalar_words(a.inv + (size_t)j * a.alpha + i);
       v = shoup(v, w[0], w[1], m);
     }
     y[k] = (u32)k < len ? conv_cut(csub(v + h, m), 0x8080808080808080ull - h) : 0;

@@ -213,6 +213,17 @@ __device__ __forceinline__ u64 mont_plain(u64 x, u64 e, u64 r2, u64 m, u64 minv)
   return csub(mont_mul63(mont_mul63(x, e, m, minv), r2, m, minv), m);
 }
 
+// Tables read at wave-uniform places go through the constant address space: behind barriers and stores the compiler would
+// otherwise not use scalar loads for them.
+typedef const __attribute__((address_space(4))) u64* const_u64_ptr;
+__device__ __forceinline__ const_u64_ptr scalar_words(const void* p) { return (const_u64_ptr)p; }
+__device__ __forceinline__ double scalar_double(const_u64_ptr p) { return __longlong_as_double((long long)*p); }
+__device__ __forceinline__ void scalar_fetch(double& w, const double* tw, u32 i) { w = scalar_double(scalar_words(tw) + i); }
+__device__ __forceinline__ void scalar_fetch(ulonglong2& w, const ulonglong2* tw, u32 i) {
+  const const_u64_ptr p = scalar_words(tw) + 2 * (size_t)i;
+  w = ulonglong2{p[0], p[1]};
+}
+
 // Eval-domain Galois map: out[k] = in[k'], 2*brev(k')+1 = (2*brev(k)+1)*g mod 2N. It maps every aligned 16-element
 // segment onto an aligned 16-element segment, so 16 adjacent lanes still read one 128-byte line. Computed on values
 // scaled by 2^(31 - logN), where the reduction modulo 2N is the 32-bit wrap-around.

@@ -90,7 +90,13 @@ __device__ __forceinline__ void wl_exchange(T (&x)[4], T* sm) {
 template <class TW>
 __device__ __forceinline__ void wl_twiddles(TW (&w)[3], const TW* __restrict__ tw, int K) {
   u32 blk = threadIdx.x >> (10 - 2 * K);
-  if (K <= 2) blk = __builtin_amdgcn_readfirstlane(blk);
+  if (K <= 2) {
+    blk = __builtin_amdgcn_readfirstlane(blk);
+    scalar_fetch(w[0], tw, (1u << (2 * K)) + blk);
+    scalar_fetch(w[1], tw, (2u << (2 * K)) + 2 * blk);
+    scalar_fetch(w[2], tw, (2u << (2 * K)) + 2 * blk + 1);
+    return;
+  }
   w[0] = tw[(1u << (2 * K)) + blk];
   w[1] = tw[(2u << (2 * K)) + 2 * blk];
   w[2] = tw[(2u << (2 * K)) + 2 * blk + 1];
