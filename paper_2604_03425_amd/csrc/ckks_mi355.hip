@@ -1612,6 +1612,7 @@ int keyswitch_whole12(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
   a.alpha = c->alpha;
   a.beta = lt->beta;
   a.next = lt->next;
+  a.fp_on = c->tune[1] == 0 ? 1u : 0u;
   for (u32& w : a.fp_mask) w = 0;
   for (u32 i = 0; i < c->nm; i++)
     if (host_class(c, c->mod[i]) == 0) a.fp_mask[i >> 5] |= 1u << (i & 31);

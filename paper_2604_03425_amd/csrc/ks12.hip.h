@@ -30,7 +30,7 @@ struct Ks12Args {
   const ulonglong2 *up_scale, *dn_scale, *pinv;
   const u64 *up_mat, *up_off, *dn_mat, *dn_off;
   u32 up_pitch, dn_pitch;
-  u32 nlimbs, nq, nm, alpha, beta, next;
+  u32 nlimbs, nq, nm, alpha, beta, next, fp_on;
   u32 fp_mask[4];          // bit id: modulus id is of double-precision class
   u32 mode0, mode1, add2_three;
   u32 d_galois, add_galois;
@@ -189,7 +189,7 @@ __device__ __forceinline__ void ks12_digits(const Ks12Args& a, u64* sm) {
   const u32 lo = j * a.alpha, hi = min(lo + a.alpha, a.nlimbs);
   if (t >= lo && t < hi) return;   // the digit's own limbs stay as they are
   const u32 id = t < a.nlimbs ? t : t - a.nlimbs + a.nq;
-  const Ks12Mod<FP> md(ks12_mod(a.mods, id));
+  const Ks12Mod<FP> md(a.mods[id]);
   typename Ks12Tables<FP>::W w;
   w.load(Ks12Tables<FP>::fwd(a, id));
   const size_t row = (size_t)j * a.next + t;
@@ -291,18 +291,21 @@ __device__ __forceinline__ void ks12_final(const Ks12Args& a, u64* sm) {
 
 // Both arithmetic kinds share a launch (the kind is uniform per workgroup): a second launch would cost more than the
 // registers that the double-precision workgroups do not need. The kind comes with the arguments, not from the modulus: a trip to
-// memory less before everything else can be requested (8 rotations of 4 limbs with their own keys 36.9 -> 35.2 us).
-#define KS12_KERNEL(NAME, ID, FP_BODY, INT_BODY)                              \
+// memory less before everything else can be requested (8 rotations of 4 limbs with their own keys 36.9 -> 35.2 us); but for the
+// digits, whose integer workgroups start with the scalar loads of a conversion anyway (159 us that way, 167 this way in 19
+// rotations of one 55-bit limb).
+#define KS12_KERNEL(NAME, IS_FP, FP_BODY, INT_BODY)                           \
   __global__ void __launch_bounds__(WL_THREADS) NAME(Ks12Args a) {            \
     __shared__ u64 sm[WL_LDS_WORDS];                                          \
-    const u32 id = ID;                                                        \
-    if ((a.fp_mask[id >> 5] >> (id & 31)) & 1) FP_BODY(a, sm);                \
+    if (IS_FP) FP_BODY(a, sm);                                                \
     else INT_BODY(a, sm);                                                     \
   }
-KS12_KERNEL(ks12_front_kernel, blockIdx.y, ks12_front<true>, ks12_front<false>)
+__device__ __forceinline__ bool ks12_fp(const Ks12Args& a, u32 id) { return (a.fp_mask[id >> 5] >> (id & 31)) & 1; }
+KS12_KERNEL(ks12_front_kernel, ks12_fp(a, blockIdx.y), ks12_front<true>, ks12_front<false>)
 template <bool NARROW>
-KS12_KERNEL(ks12_digits_kernel, (blockIdx.y < a.nlimbs ? blockIdx.y : blockIdx.y - a.nlimbs + a.nq),
+KS12_KERNEL(ks12_digits_kernel,
+            mod_class(a.mods[blockIdx.y < a.nlimbs ? blockIdx.y : blockIdx.y - a.nlimbs + a.nq].m, a.fp_on) == 0,
             (ks12_digits<true, NARROW>), (ks12_digits<false, NARROW>))
-KS12_KERNEL(ks12_special_kernel, a.nq + blockIdx.y, ks12_special<true>, ks12_special<false>)
+KS12_KERNEL(ks12_special_kernel, ks12_fp(a, a.nq + blockIdx.y), ks12_special<true>, ks12_special<false>)
 template <bool NARROW>
-KS12_KERNEL(ks12_final_kernel, blockIdx.y, (ks12_final<true, NARROW>), (ks12_final<false, NARROW>))
+KS12_KERNEL(ks12_final_kernel, ks12_fp(a, blockIdx.y), (ks12_final<true, NARROW>), (ks12_final<false, NARROW>))
