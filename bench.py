@@ -35,9 +35,13 @@ OPS_BUTTERFLY, OPS_MAC, OPS_REDUCE, OPS_SHOUP, OPS_ADD = 24, 8, 16, 14, 4
 # butterfly = 6 (exact product, quotient, remainder) + 2 (add, sub) + 1.5 (range reduction every 4 stages);
 # variable x variable product reduced = 7; constant multiply = 6.
 OPS_BUTTERFLY_FP, OPS_MULRED_FP, OPS_SHOUP_FP = 9.5, 7, 6
-# Base-conversion dot product on 30-bit operand halves: 4 multiply-adds per term, and per output a base-2^30
-# Montgomery reduction of the three sums (22) plus the final correction (5).
-OPS_DOT30, OPS_REDUCE90, OPS_REDUCE60, OPS_PAIR_FP = 4, 27, 12, 4 + 6 / 5
+# Base conversions on the matrix cores: per output 8 byte sums put together (8), the exchange between half-waves (1.5) and the
+# reduction (7); per source its cut into balanced bytes (5) and their exchange (2). The products themselves are matrix work and
+# not in these counts: 64 byte products per term, one v_mfma_i32_32x32x32_i8 per 64 outputs and 4 sources.
+OPS_CONV_OUT, OPS_CONV_SRC = 16.5, 7
+# The separate conversion kernels of up to 8 sources (30-bit operand halves): 4 multiply-adds per term, and per output a
+# base-2^30 Montgomery reduction of the three sums (22) plus the final correction (5).
+OPS_DOT30, OPS_REDUCE90, OPS_PAIR_FP = 4, 27, 4 + 6 / 5
 
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "keyswitch_micro_traffic.json")
@@ -63,7 +67,8 @@ def keyswitch_model(p, B, nl, hrot, hmult, fp_inner=2, bconv=0):
     """Algorithmic bytes and lane-ops per kernel kind for ONE key-switch call on a batch of B (N = 2^16 path:
     double-precision bodies on primes < 2^50, with their inner product as a separate streaming kernel)."""
     N, K, alpha = p.N, len(p.p), p.alpha
-    if bconv == 0 and max(alpha, K) > 8:
+    wide = max(alpha, K) > 8
+    if bconv == 0 and wide:
         bconv = 2    # more sources than the fused conversion takes (parameter sets with alpha = K on both sides of it)
     nxt, beta = nl + K, p.beta(nl)
     ext_mod = list(p.q[:nl]) + list(p.p)
@@ -87,9 +92,10 @@ def keyswitch_model(p, B, nl, hrot, hmult, fp_inner=2, bconv=0):
         if nbytes or nops:
             m["%s<%d>" % (name, cls) if cls is not None else name] = dict(bytes=nbytes, ops=nops)
     # class 0 = double-precision bodies; the 60-bit special primes are class 2 (Harvey integer bodies)
-    put("ntt16_inv_blocks_kernel", 0, (inv_fp * 2 + (B * own_fp if hmult and own_int == 0 and fp_inner != 1 else 0)) * limb,
-        inv_fp * bf_pass_fp)
-    put("ntt16_inv_blocks_kernel", 2, inv_int * 2 * limb, inv_int * bf_pass)
+    # products of a multiplication are formed where they are read; integer special limbs leave the inner product through this pass
+    fused_product = hmult and fp_inner != 1
+    put("ntt16_inv_blocks_kernel", 0, (inv_fp * 2 + (B * own_fp if fused_product else 0)) * limb, inv_fp * bf_pass_fp)
+    put("ntt16_inv_blocks_kernel", 2, B * own_int * (3 if fused_product else 2) * limb, B * own_int * bf_pass)
     inv_rows_ops = inv_fp * (bf_pass_fp + N * OPS_SHOUP_FP) + inv_int * (bf_pass + N * OPS_SHOUP)
     if bconv:
         put("ntt16_inv_rows_kernel", 0, inv_fp * 2 * limb, inv_fp * (bf_pass_fp + N * OPS_SHOUP_FP))
@@ -98,20 +104,17 @@ def keyswitch_model(p, B, nl, hrot, hmult, fp_inner=2, bconv=0):
     fp_t, int_t = [t for t in range(nxt) if fp[t]], [t for t in range(nxt) if not fp[t]]
     dn_fp, dn_int = 2 * own_fp, 2 * own_int     # ModDown targets per ciphertext
     if bconv == 0:
-        # inverse row pass of the sources, conversion (4 FP64 instructions per term and 6 per output between
-        # double-precision limbs, else 4 multiply-adds per term and 12, or 19 to a double-precision target), row pass of the
-        # targets; sources read and targets written once
-        from_int = lambda t: OPS_REDUCE60 + (7 if fp[t] else 0)
-        new_ops = sum(sum(len(dg) * OPS_DOT30 + (6 if fp[t] and all(fp[i] for i in dg) else from_int(t))
-                          for t in range(nxt) if t not in dg) for dg in digits)
+        # inverse row pass of the sources, conversion, row pass of the targets; sources read and targets written once
         put("conv_rows_kernel", None, (B * (nl + new_limbs) + 2 * B * (K + nl)) * limb,
-            inv_rows_ops + B * N * (new_ops + 2 * sum(K * OPS_DOT30 + from_int(t) for t in range(nl))) +
+            inv_rows_ops + B * N * ((new_limbs + 2 * nl) * OPS_CONV_OUT + (nl + 2 * K) * OPS_CONV_SRC) +
             B * ((new_fp + dn_fp) * bf_pass_fp + (new_int + dn_int) * bf_pass))
     elif bconv == 2:
-        # base conversion, as executed: 4 multiply-adds per term on 30-bit halves + a 27-instruction reduction per output
-        put("modup_kernel", None, B * (nl + new_limbs) * limb,
-            B * N * sum((nxt - len(dg)) * ((len(dg) + 1) * OPS_DOT30 + OPS_REDUCE90) for dg in digits))
-        put("moddown_kernel", None, 2 * B * (K + nl) * limb, 2 * B * N * nl * ((K + 1) * OPS_DOT30 + OPS_REDUCE90))
+        # base conversion, as executed: on the matrix cores for more than 8 sources, else 4 multiply-adds per term on 30-bit
+        # halves + a 27-instruction reduction per output (the kinds' names are those of the latter for both)
+        out = lambda n: OPS_CONV_OUT if wide else (n + 1) * OPS_DOT30 + OPS_REDUCE90
+        src = OPS_CONV_SRC if wide else 0
+        put("modup_kernel", None, B * (nl + new_limbs) * limb, B * N * (sum((nxt - len(dg)) * out(len(dg)) for dg in digits) + nl * src))
+        put("moddown_kernel", None, 2 * B * (K + nl) * limb, 2 * B * N * (nl * out(K) + K * src))
         rows_fp, rows_int = B * (new_fp + dn_fp), B * (new_int + dn_int)
         put("ntt16_fwd_rows_kernel", 0, rows_fp * 2 * limb, rows_fp * bf_pass_fp)
         put("ntt16_fwd_rows_kernel", 2, rows_int * 2 * limb, rows_int * bf_pass)
@@ -125,11 +128,9 @@ def keyswitch_model(p, B, nl, hrot, hmult, fp_inner=2, bconv=0):
             B * (N * (up_ops(fp_t) + dn_fp * dn_term) + (new_fp + dn_fp) * bf_pass_fp))
         put("ntt16_bconv_rows_kernel", 2, B * ((nl if new_int else 0) + new_int + (2 * K if dn_int else 0) + dn_int) * limb,
             B * (N * (up_ops(int_t) + dn_int * dn_term) + (new_int + dn_int) * bf_pass))
-    # double-precision main primes: the products of a multiplication are formed where they are read
-    fused_product = hmult and own_int == 0 and fp_inner != 1
     addend = 1 if hrot else 2 if hmult else 0
     if fp_inner != 1:
-        # default on double-precision main limbs: block pass of the digits fused with one key component per workgroup
+        # default: block pass of the digits fused with one key component per workgroup
         # (every converted tile is transformed by both workgroups of its ciphertext: twice in ops, once in bytes, the
         # second read being served by L2), then the block pass of the ModDown correction, the division by P and the
         # addends in the same kernel. Special limbs below 2^50 (none in the benchmark) keep the store of the sums.
@@ -144,10 +145,16 @@ def keyswitch_model(p, B, nl, hrot, hmult, fp_inner=2, bconv=0):
             B * N * n_fp * beta * 2 * OPS_MULRED_FP)
         put("ntt16_fwd_blocks_final_kernel", 0, B * own_fp * (6 + addend) * limb,
             2 * B * own_fp * (bf_pass_fp + N * (OPS_SHOUP_FP + 2)))
-    put("ntt16_fwd_blocks_inner8_kernel", 2, (B * (new_int + own_int + 2 * n_int) + 2 * beta * n_int) * limb,
-        B * (new_int * bf_pass + N * n_int * beta * 2 * mul_redc))
-    put("ntt16_fwd_blocks_final_kernel", 2, B * own_int * (6 + addend) * limb,
-        2 * B * own_int * (bf_pass + N * (OPS_SHOUP + 2 * OPS_ADD)))
+    # integer-class slots: the special ones with their inverse block pass, the main ones with the rest of the key switch
+    inner8_ops = B * (new_int * bf_pass + N * n_int * beta * 2 * mul_redc + 2 * (K - kfp) * bf_pass)
+    if fp_inner != 1:
+        put("ntt16_fwd_blocks_inner8_kernel", 2,
+            (B * (new_int + own_int + 2 * (K - kfp) + (2 + addend + 2) * own_int) + 2 * beta * n_int) * limb,
+            inner8_ops + 2 * B * own_int * (bf_pass + N * (OPS_SHOUP + 2 * OPS_ADD)))
+    else:
+        put("ntt16_fwd_blocks_inner8_kernel", 2, (B * (new_int + own_int + 2 * n_int) + 2 * beta * n_int) * limb, inner8_ops)
+        put("ntt16_fwd_blocks_final_kernel", 2, B * own_int * (6 + addend) * limb,
+            2 * B * own_int * (bf_pass + N * (OPS_SHOUP + 2 * OPS_ADD)))
     if hmult and not fused_product:
         put("tensor_kernel", None, B * nl * 7 * limb, B * nl * N * 4 * mul_redc)
     return m
@@ -815,7 +822,7 @@ def main():
                    hrot_per_s_one_by_one_4_streams=round(B / t_rot_streams, 1),
                    hmult_relin_per_s=round(B / 2 / t_mul, 1),
                  rescale_per_s=round(B / t_rs, 1),
-                 rescale_hbm_frac=round(B * 2 * (4 + 3 * (nl - 1) + 4 * (nl - 1)) * 8 * N / t_rs / 1e9 / PEAK_HBM_GBS, 4),
+                 rescale_hbm_frac=round(B * 2 * (3 + 4 * (nl - 1)) * 8 * N / t_rs / 1e9 / PEAK_HBM_GBS, 4),
                  automorph_eval_GBps=round(B * 2 * nl * 2 * 8 * N / t_au / 1e9, 1),
                  automorph_coeff_GBps=round(B * 2 * nl * 2 * 8 * N / t_auc / 1e9, 1),
                  pmult_hbm_frac=round(B * 2 * nl * 2 * 8 * N / t_pm / 1e9 / PEAK_HBM_GBS, 4),

@@ -1028,11 +1028,8 @@ void conv_plan(const ckks_ctx* c, ConvJob& job, TargetId target_id) {
   const u64 groups = (u64)job.npoly * (c->N / CONV_TILE);
   // From 6 sources on, and where one share would take over a tenth longer than several (a quarter with double-precision sources,
   // whose inverse pass is cheaper), the sources' inverse row pass runs by itself before the shares instead of in each of them
-  // (else its launch costs more than the repeats: 3 products of 11 limbs, 8 special primes 219 us, 205 without). us, the inverse
-  // pass in every share and the best number of them | this: one rotation of 24 limbs, 3 digits, 8 special primes 159 | 151, of
-  // 16 + 8 60-bit limbs 147 | 132, 3 products of 8 of these limbs 209 | 189; four rotations on four streams 542 | 471, 402 | 361,
-  // of 12 + 4 60-bit limbs 307 | 278, of 20 + 5 limbs 410 | 385; with kernels of their own for every step these four took 525,
-  // 352, 302 and 411.
+  // (else its launch costs more than the repeats). us, the inverse pass in every share and the best number of them | this: one
+  // rotation of 24 limbs, 3 digits, 8 special primes 138.7 | 133.4, four 364.4 | 358.2, one of 16 + 8 60-bit limbs 120.5 | 107.7.
   const u32 wsrc = len * (job.fp ? 4 : 6);
   u32 n = conv_shares(groups, wsrc, wtargets, targets);
   const u64 one = conv_cost(groups, wsrc, wtargets, 1), several = conv_cost(groups, wsrc, wtargets, n);
