@@ -1223,7 +1223,8 @@ void launch_inner_c(const ckks_ctx* c, u32 B, u32 nslots, const FwdInnerArgs& a,
 //      integer-class main limbs take the assembly kernel on the accumulators of step 3.
 // With knob 3 = 1 the double-precision slots take a plain block pass, a streaming product and the assembly kernel
 // instead of step 5's fusion. With knob 4 = 0 the double-precision row pass of step 2, where it is a kernel of its own, runs on
-// the context's second stream beside steps 3 and 4, which do not depend on it, and is joined before step 5.
+// the context's second stream beside the integer-class kernels of step 3 and step 4, which do not depend on it, and is joined
+// before the first kernel that reads what it leaves: step 5's, or with knob 3 = 1 the block pass of step 3.
 // acc_add != null (knob 3 at its default only): the sequence stops before ModDown and ADDS the two accumulators, plus
 // P * sigma(io.add_src component 0) on the main primes of the first, to acc_add ([B][2][next][N]).
 int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B, u32 nlimbs, const u64* evk, char* ws,
@@ -1395,12 +1396,13 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
     return CKKS_OK;
   };
   if (special_fp || acc_add || !fused_fp) {
+    if (fork) HIP_TRY(hipStreamWaitEvent(st, c->ev_join, 0));   // (only with knob 3 = 1: no fork with the other two)
     if ((rc = launch_inner_fp(true, acc_add || !fused_fp, st))) return rc;
   }
   if (acc_add) return CKKS_OK;
   // 4.
   if ((rc = ks16_moddown_rows(c, lt, B, nlimbs, acc, tq, st, true))) return rc;
-  if (fork) HIP_TRY(hipStreamWaitEvent(st, c->ev_join, 0));
+  if (fork && fused_fp) HIP_TRY(hipStreamWaitEvent(st, c->ev_join, 0));
   // 5.
   if (!fused_fp) return ks16_assemble(c, lt, io, B, nlimbs, acc, tq, st);
   FwdInnerArgs a = ia;
