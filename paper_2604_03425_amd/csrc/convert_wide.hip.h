@@ -6,10 +6,11 @@
 // eight sums of targets h and 2 + h at the 32 positions of one half-wave; two products, one per half of the positions, and a
 // swap of half-waves give every lane all four targets at its own position.
 //
-// What bounds it: memory (sources read once, targets written once), 4.1 TB/s at 12 sources and 3.0 at 25, where two workgroups fill a
-// compute unit's registers. On the vector units a term took 4 multiply-adds. N = 2^16, both conversions of a key switch: 8
-// rotations of 24 + 12 limbs in 2 digits 216 -> 147 us, 15 of 23 + 25 limbs in one digit 901 -> 384; 12 products of 18 + 9 limbs at
-// 2^15 127 -> 89.
+// What bounds it: memory (sources read once, targets written once), 4.1 TB/s at 12 sources and 3.3 at 25, where the matrix products
+// are 0.4 of the time by their count and the sources leave registers for two workgroups. From 25 sources on some scalar registers of
+// the prologue spill (the rows' addresses). On the vector units a term took 4 multiply-adds. N = 2^16, both conversions of a key
+// switch: 8 rotations of 24 + 12 limbs in 2 digits 216 -> 147 us, 15 of 23 + 25 limbs in one digit 901 -> 344, 2 of 30 + 30 limbs
+// 86 (107 with matrices that waited for a private array in LDS, see below); 12 products of 18 + 9 limbs at 2^15 127 -> 89.
 #pragma once
 #include "convert.hip.h"
 
@@ -57,18 +58,29 @@ __global__ void __launch_bounds__(WIDE_THREADS) conv_wide_kernel(WideArgs a) {
   const u32 lo = j * a.alpha, len = min(a.alpha, a.src_nlimbs - lo);
   const u64* src = a.src + (size_t)blockIdx.z * a.src_poly_stride + (size_t)(a.src_slot0 + lo) * N + n;
   u64* dst = a.dst + ((size_t)blockIdx.z * a.beta + j) * a.dst_poly_stride + n;
-  // the matrices of a group of four targets, 16 bytes a lane and request
-  constexpr int REQUESTS = (G * 64 + WIDE_THREADS - 1) / WIDE_THREADS;
-  const u32 quads = (a.ntarget + 3) / 4;
-  auto request = [&](uint4 (&r)[REQUESTS], u32 quad) {
-    const uint4* p = a.pieces + ((size_t)j * quads + quad) * (G * 64);
+  // The matrices of a group of four targets: through a register where a request a lane is enough, beyond that straight into LDS, 1 KB
+  // a wave and request. (Two requests a lane were an array that the compiler kept in 16 KB of LDS: every word waited for at once and
+  // copied twice; two rotations of 30 + 30 limbs in one digit 324 -> 306 us. With one, straight into LDS is no faster: 8 rotations of
+  // 24 + 12 limbs 727 -> 737, 12 products of 18 + 9 at 2^15 468 -> 475.)
+  constexpr bool DIRECT = G * 64 > WIDE_THREADS;
+  const u32 quads = (a.ntarget + 3) / 4, wave = conv_uniform(t >> 6);
+  const __amdgpu_buffer_rsrc_t pieces = __builtin_amdgcn_make_buffer_rsrc((void*)a.pieces, 0, (int)(a.beta * quads * G * 1024), 0x00020000);
+  uint4 ahead;
+  auto request = [&](u32 quad, u32 buffer) {
+    const u32 first = (j * quads + quad) * G;
+    if (DIRECT) {
 #pragma unroll
-    for (int k = 0; k < REQUESTS; k++) r[k] = p[min(t + k * WIDE_THREADS, G * 64u - 1)];
+      for (u32 g0 = 0; g0 < G; g0 += WIDE_THREADS / 64)
+        if (g0 + wave < G)   // uniform
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(pieces, (lds_void_ptr)&image[buffer][(g0 + wave) * 64], 16, (int)((t & 63) * 16),
+                                                   (int)((first + g0 + wave) * 1024), 0, 0);
+    } else {
+      ahead = a.pieces[(size_t)first * 64 + min(t, G * 64u - 1)];
+    }
   };
-  auto put = [&](const uint4 (&r)[REQUESTS], u32 buffer) {
-#pragma unroll
-    for (int k = 0; k < REQUESTS; k++)
-      if (t + k * WIDE_THREADS < G * 64) image[buffer][t + k * WIDE_THREADS] = r[k];
+  auto arrived = [&](u32 buffer) {
+    if (DIRECT) conv_wait_vector_memory();
+    else if (t < G * 64) image[buffer][t] = ahead;
   };
   // the next group with a target that is not one of the digit's own limbs
   auto skip = [&](u32 quad) {
@@ -77,11 +89,11 @@ __global__ void __launch_bounds__(WIDE_THREADS) conv_wide_kernel(WideArgs a) {
     return quad;
   };
   u32 quad = skip(0);
-  uint4 ahead[REQUESTS];
-  request(ahead, min(quad, quads - 1));
+  request(min(quad, quads - 1), 0);
   u64 y[4 * G];
 #pragma unroll
   for (int k = 0; k < 4 * G; k++) y[k] = src[(size_t)min((u32)k, len - 1) * N];
+  asm volatile("" ::: "memory");   // all of them requested here, not each where it is used
 #pragma unroll
   for (int k = 0; k < 4 * G; k++) {
     const u32 i = min((u32)k, len - 1);   // uniform
@@ -106,11 +118,11 @@ __global__ void __launch_bounds__(WIDE_THREADS) conv_wide_kernel(WideArgs a) {
 #pragma unroll
     for (int f = 0; f < 2; f++) b[f][g] = conv_i32x4{(int)p[f][0], (int)p[f][1], (int)p[f][2], (int)p[f][3]};
   }
-  put(ahead, 0);
+  arrived(0);
   lds_barrier();
   for (u32 buffer = 0; quad < quads; buffer ^= 1) {
     const u32 next = skip(quad + 1);
-    request(ahead, min(next, quads - 1));
+    request(min(next, quads - 1), buffer ^ 1);   // read last before the barrier that ended the turn before
     conv_i32x16 d[2] = {};
 #pragma unroll
     for (int g = 0; g < G; g++) {
@@ -118,6 +130,8 @@ __global__ void __launch_bounds__(WIDE_THREADS) conv_wide_kernel(WideArgs a) {
 #pragma unroll
       for (int f = 0; f < 2; f++) d[f] = __builtin_amdgcn_mfma_i32_32x32x32_i8(rows, b[f][g], d[f], 0, 0, 0);
     }
+    auto wanted = [&](u32 slot) { return slot < a.ntarget && !(a.skip_own && slot >= lo && slot < lo + len); };   // uniform
+    u64 r[4];
 #pragma unroll
     for (int p = 0; p < 2; p++) {
       u32 w[2][3];
@@ -131,14 +145,21 @@ __global__ void __launch_bounds__(WIDE_THREADS) conv_wide_kernel(WideArgs a) {
       for (int k = 0; k < 3; k++) conv_swap32(w[0][k], w[1][k]);
 #pragma unroll
       for (int c = 0; c < 2; c++) {
-        const u32 slot = 4 * quad + 2 * p + c;   // uniform
-        if (slot >= a.ntarget || (a.skip_own && slot >= lo && slot < lo + len)) continue;
+        const u32 slot = 4 * quad + 2 * p + c;
+        if (!wanted(slot)) continue;
         ConvTarget tg;
         tg.fetch(a.mods, a.red, slot, slot < a.main ? slot : slot - a.main + a.special);
-        dst[(size_t)slot * N] = wide_settle(w[c][0], w[c][1], w[c][2], tg);
+        r[2 * p + c] = wide_settle(w[c][0], w[c][1], w[c][2], tg);
+        if (!DIRECT) dst[(size_t)slot * N] = r[2 * p + c];
       }
     }
-    put(ahead, buffer ^ 1);
+    if (DIRECT) __builtin_amdgcn_sched_barrier(0);
+    arrived(buffer ^ 1);
+    if (DIRECT) {   // only now: waiting for the request would be waiting for this turn's stores too
+#pragma unroll
+      for (int c = 0; c < 4; c++)
+        if (wanted(4 * quad + c)) dst[(size_t)(4 * quad + c) * N] = r[c];
+    }
     lds_barrier();
     quad = next;
   }
