@@ -143,9 +143,12 @@ __device__ __forceinline__ void ks12_load_d(typename Ks12Mod<FP>::V (&x)[4], con
 #pragma unroll
   for (int k = 0; k < 4; k++) x[k] = md.load(src[g ? galois_src_index(wl_elem(2, k), g, 12) : wl_elem(2, k)]);
 }
-// Base conversion of `len` split limbs to modulus mi in the round-0 layout, canonical.
+// Base conversion of `len` split limbs to modulus mi in the round-0 layout, canonical. The constants come by scalar loads, said so:
+// of a kernel's two bodies only the first would get them, since the compiler takes its stores for writes that the second may read
+// (integer bodies second, with vector loads: 19 rotations of one 55-bit limb 696 -> 692 us, 2 of 4 60-bit limbs 46.3 -> 46.0, 8
+// products of 5 55-bit limbs 56.9 -> 56.4).
 template <bool NARROW>
-__device__ __forceinline__ void ks12_convert(u64 (&x)[4], const u64* __restrict__ src, u32 len, const u64* __restrict__ crow,
+__device__ __forceinline__ void ks12_convert(u64 (&x)[4], const u64* __restrict__ src, u32 len, const_u64_ptr crow,
                                              u64 offc, const ModInfo& mi) {
   BconvAcc<4, NARROW> acc;
   acc.init(offc);
@@ -176,7 +179,9 @@ __device__ __forceinline__ void ks12_front(const Ks12Args& a, u64* sm) {
   typename Ks12Mod<FP>::V x[4];
   ks12_load_d<FP>(x, a, b, i, md);
   u64 y[4];
-  md.inverse(y, x, w, a.up_scale[i], sm);
+  ulonglong2 sc;
+  scalar_fetch(sc, a.up_scale, i);
+  md.inverse(y, x, w, sc, sm);
   u64* dst = a.dcoef + ((size_t)b * a.nlimbs + i) * 4096;
 #pragma unroll
   for (int k = 0; k < 4; k++) dst[wl_elem(0, k)] = ks12_split(y[k], md.mi.m);
@@ -194,8 +199,8 @@ __device__ __forceinline__ void ks12_digits(const Ks12Args& a, u64* sm) {
   w.load(Ks12Tables<FP>::fwd(a, id));
   const size_t row = (size_t)j * a.next + t;
   u64 y[4];
-  ks12_convert<NARROW>(y, a.dcoef + ((size_t)b * a.nlimbs + lo) * 4096, hi - lo, a.up_mat + row * a.up_pitch, a.up_off[row],
-                       md.mi);
+  ks12_convert<NARROW>(y, a.dcoef + ((size_t)b * a.nlimbs + lo) * 4096, hi - lo, scalar_words(a.up_mat + row * a.up_pitch),
+                       *scalar_words(a.up_off + row), md.mi);
   typename Ks12Mod<FP>::V x[4];
 #pragma unroll
   for (int k = 0; k < 4; k++) x[k] = md.load(y[k]);
@@ -239,7 +244,9 @@ __device__ __forceinline__ void ks12_special(const Ks12Args& a, u64* sm) {
   typename Ks12Mod<FP>::V s[4];
   ks12_inner<FP>(s, a, bc >> 1, bc & 1, t, id, md);
   u64 y[4];
-  md.inverse(y, s, w, a.dn_scale[t - a.nlimbs], sm);
+  ulonglong2 sc;
+  scalar_fetch(sc, a.dn_scale, t - a.nlimbs);
+  md.inverse(y, s, w, sc, sm);
   u64* o = a.acc + ((size_t)bc * a.next + t) * 4096;
 #pragma unroll
   for (int k = 0; k < 4; k++) o[wl_elem(0, k)] = ks12_split(y[k], md.mi.m);
@@ -265,14 +272,16 @@ __device__ __forceinline__ void ks12_final(const Ks12Args& a, u64* sm) {
     if (mode & 2) ew[k] = as[galois_src_index(n, g, 12)];
   }
   u64 y[4];
-  ks12_convert<NARROW>(y, a.acc + ((size_t)bc * a.next + a.nlimbs) * 4096, a.next - a.nlimbs, a.dn_mat + (size_t)i * a.dn_pitch, a.dn_off[i], md.mi);
+  ks12_convert<NARROW>(y, a.acc + ((size_t)bc * a.next + a.nlimbs) * 4096, a.next - a.nlimbs,
+                       scalar_words(a.dn_mat + (size_t)i * a.dn_pitch), *scalar_words(a.dn_off + i), md.mi);
   typename Ks12Mod<FP>::V x[4];
 #pragma unroll
   for (int k = 0; k < 4; k++) x[k] = md.load(y[k]);
   md.forward(x, w, sm);
   typename Ks12Mod<FP>::V s[4];
   ks12_inner<FP>(s, a, b, c, i, i, md);
-  const ulonglong2 pv = a.pinv[i];
+  ulonglong2 pv;
+  scalar_fetch(pv, a.pinv, i);
   const size_t o0 = (size_t)b * 2 * pl + lo, o1 = o0 + pl;
   u64* o = a.out + (size_t)bc * pl + lo;
 #pragma unroll
@@ -292,8 +301,8 @@ __device__ __forceinline__ void ks12_final(const Ks12Args& a, u64* sm) {
 // Both arithmetic kinds share a launch (the kind is uniform per workgroup): a second launch would cost more than the
 // registers that the double-precision workgroups do not need. The kind comes with the arguments, not from the modulus: a trip to
 // memory less before everything else can be requested (8 rotations of 4 limbs with their own keys 36.9 -> 35.2 us); but for the
-// digits, whose integer workgroups start with the scalar loads of a conversion anyway (159 us that way, 167 this way in 19
-// rotations of one 55-bit limb).
+// digits, whose integer workgroups start with the scalar loads of a conversion anyway (687 us that way, 693 this way in 19
+// rotations of one 55-bit limb; nothing between them in the others).
 #define KS12_KERNEL(NAME, IS_FP, FP_BODY, INT_BODY)                           \
   __global__ void __launch_bounds__(WL_THREADS) NAME(Ks12Args a) {            \
     __shared__ u64 sm[WL_LDS_WORDS];                                          \
