@@ -98,10 +98,6 @@ inline u32 h_brev(u32 x, u32 bits) {
   return r;
 }
 
-struct Pass {
-  u32 s0, k, logC, tile_log;
-};
-
 // Rows of constants per target in up_mat / dn_mat (the smallest of these that covers n): what the kernels that read them are
 // instantiated for (4, 8) or walk over.
 inline u32 bconv_rows(u32 n) { return n <= 4 ? 4 : n <= 8 ? 8 : n <= 15 ? 15 : n <= 24 ? 24 : n <= 36 ? 36 : 45; }
@@ -184,7 +180,6 @@ struct ckks_ctx {
   double* d_twfp_inv = nullptr;
   hipStream_t side = nullptr;       // second stream for the fork/join inside a key switch (default priority)
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-  std::vector<Pass> passes;  // forward order
   // Base-conversion constants of every limb count 1..nq, built when the context is created (and again when knob 1
   // or 5 changes): levels[nlimbs] points into one device allocation, d_levels.
   std::vector<LevelTables> levels;
@@ -535,8 +530,6 @@ LimbMap ext_map(const ckks_ctx* c, u32 nlimbs) {
   return m;
 }
 
-// Enqueue a transform of npoly polynomials x slots [slot0, slot0+nslots): reads src, writes dst (src == dst for an
-// in-place transform; out of place is supported at N = 2^12 .. 2^16). Rows are *_stride elements apart.
 // Modulus class (must match mod_class() on the device).
 inline int host_class(const ckks_ctx* c, u64 m) {
   if (c->tune[1] == 0 && (m >> 50) == 0) return 0;
@@ -680,6 +673,8 @@ int launch_limbs(const ckks_ctx* c, bool inverse, const u64* src, u64 src_stride
   HIP_TRY(hipGetLastError());
   return CKKS_OK;
 }
+// Enqueue a transform of npoly polynomials x slots [slot0, slot0+nslots): reads src, writes dst (src == dst for an
+// in-place transform). Rows are *_stride elements apart.
 int launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, u64 src_stride, u64* dst, u64 dst_stride, u32 npoly,
                u32 slot0, u32 nslots, const LimbMap& ids_from_slot0, u32 skip_beta, u32 skip_nq, hipStream_t st,
                const NttOpts& opt = NttOpts()) {
@@ -738,9 +733,11 @@ int launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, u64 src_stride, 
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
   }
+  // 2^17: stages 0 .. 8 and 9 .. 16 on tiles of 4096 elements
+  if (!opt.plain()) return fail(CKKS_EINVAL, "internal: a part of a transform on a ring that has only whole ones");
   if (src != dst) {
     ProfScope ps(c, PK_COPY, st);
-    // generic path is in place: copy the slots first (rows may be strided)
+    // in place: copy the slots first (rows may be strided)
     HIP_TRY(hipMemcpy2DAsync(dst + (size_t)slot0 * c->N, dst_stride * 8, src + (size_t)slot0 * c->N, src_stride * 8,
                              (size_t)nslots * c->N * 8, npoly, hipMemcpyDeviceToDevice, st));
   }
@@ -754,15 +751,14 @@ int launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, u64 src_stride, 
   a.skip_alpha = c->alpha;
   a.skip_nq = skip_nq;
   a.ids = ids_from_slot0;
-  const size_t np = c->passes.size();
-  for (size_t i = 0; i < np; i++) {
-    const Pass& p = c->passes[inverse ? np - 1 - i : i];
-    a.s0 = p.s0;
-    a.k = p.k;
-    a.logC = p.logC;
-    a.tile_log = p.tile_log;
-    dim3 grid(npoly, c->N >> p.tile_log, nslots);
-    size_t lds = sizeof(u64) << p.tile_log;
+  a.tile_log = 12;
+  for (int pass = 0; pass < 2; pass++) {
+    const bool first = inverse ? pass == 1 : pass == 0;
+    a.s0 = first ? 0 : 9;
+    a.k = first ? 9 : 8;
+    a.logC = first ? 3 : 0;
+    dim3 grid(npoly, c->N >> a.tile_log, nslots);
+    size_t lds = sizeof(u64) << a.tile_log;
     ProfScope ps(c, kind, st);
     if (inverse)
       hipLaunchKernelGGL(ntt_pass_kernel<true>, grid, dim3(NTT_THREADS), lds, st, a);
@@ -1871,14 +1867,6 @@ int ckks_ctx_create(ckks_ctx** out, uint32_t logN, const uint64_t* q, uint32_t n
       return fail(CKKS_EINVAL, "modulus " + std::to_string(i) +
                                    " must be a distinct prime < 2^60, = 1 mod 2N, with psi^N = -1");
     }
-  }
-  // pass plan
-  if (logN <= 12) {
-    c->passes.push_back(Pass{0, logN, 0, logN});
-  } else {
-    u32 k1 = logN - 8;
-    c->passes.push_back(Pass{0, k1, 12 - k1, 12});
-    c->passes.push_back(Pass{k1, 8, 0, 12});
   }
   // tables
   std::vector<ModInfo> mods(c->nm);

@@ -9,7 +9,7 @@ struct LimbMap {
   unsigned char id[CKKS_MAX_SLOTS];
 };
 
-// One pass of a multi-pass transform: stages [s0, s0+k) of the logN-stage butterfly network,
+// One pass of the transform of 2^17: stages [s0, s0+k) of the logN-stage butterfly network,
 // on tiles of 2^tile_log elements = (hi blocks) x (2^k "mid" values) x (2^logC consecutive "lo" values).
 struct NttArgs {
   u64* data;
