@@ -310,7 +310,8 @@ int ckks_prof_copy(ckks_ctx* ctx, void* dst, const void* src, size_t bytes, void
 /* Tuning knobs for experiments (defaults in brackets):
  * knob 0 [-1] workgroup-to-tile mapping of the kernels for N = 2^13 .. 2^16: 0..4 forces one mapping, -1 chooses per kernel (no
  *             effect on the conversions of knob 2 = 0 and on hoisted sums of several double-precision rotations);
- * knob 1 [0]  != 0 turns the double-precision bodies for primes < 2^50 off (integer bodies everywhere);
+ * knob 1 [0]  != 0 turns the double-precision bodies for primes < 2^50 off (integer bodies in every transform, product and sum;
+ *             conversions of more than 8 sources go on ending in doubles on targets < 2^50);
  * knob 2 [0]  base conversions of ModUp, ModDown and Rescale: 0 = with the row passes on both sides of them in one kernel, where
  *             a conversion has at most 8 sources of one arithmetic kind and every prime with integer bodies is above 36 bits
  *             (2 otherwise); 1 = inside the following row pass only (Rescale: as 2); 2 = kernels of their own (1 and 2
@@ -319,10 +320,11 @@ int ckks_prof_copy(ckks_ctx* ctx, void* dst, const void* src, size_t bytes, void
  *             correction and final assembly in one kernel, products of two ciphertexts formed where they are read; 1 =
  *             separate kernels;
  * knob 4 [1]  0 lets a key switch run the double-precision row pass of the converted digits on a second stream
- *             owned by the context, beside the special-prime chain, joined before the result is assembled (only where
+ *             owned by the context, beside the special-prime chain, joined before those digits are read (only where
  *             that pass is a kernel of its own, see knob 2);
- * knob 5 [0]  != 0 makes the conversions that are kernels of their own (at most 8 sources) use the general four-sum
- *             accumulation with a 128-bit Montgomery reduction, also where the bit sizes of the bases allow the three-sum form;
+ * knob 5 [0]  != 0 makes the conversions that are kernels of their own (at most 8 sources), those of knob 2 = 1 and those of
+ *             N = 2^12 use the general four-sum accumulation with a 128-bit Montgomery reduction, also where the bit sizes of
+ *             the bases allow the three-sum form;
  * knob 6 [0]  != 0 computes the inner sums of ckks_pcmm_bsgs with the integer kernel on every limb;
  * knob 7 [0]  > 0 caps the number of giant steps whose inner sums one pass over the baby-step ciphertexts
  *             computes (default and maximum 24).

@@ -162,7 +162,7 @@ struct ckks_ctx {
   // Tuning knobs (ckks_tune_set; meanings in the public header). 0: workgroup mapping of the two-pass kernels (-1: per
   // kernel); 1: integer bodies everywhere; 2: base conversions with the row passes on both sides of them (0, where they fit),
   // inside the following one (1) or kernels of their own (2); 3: 2 = inner product fused with the final assembly on
-  // double-precision main limbs, 1 = separate kernels; 4: 0 = fork a row pass that is a kernel of its own onto the second
+  // main limbs, 1 = separate kernels; 4: 0 = fork a row pass that is a kernel of its own onto the second
   // stream; 5: general base-conversion reduction; 6: integer PCMM inner sums; 7: cap on giant steps per pass.
   int tune[8] = {-1, 0, 0, 2, 1, 0, 0, 0};
   bool prof_on = false;
@@ -547,9 +547,8 @@ inline u32 map_mode_inner(const ckks_ctx* c, bool shared_key) {
 // The two-pass transforms and the kernels fused with them serve N = 2^13 .. 2^16. Below 2^13 a row pass would have fewer
 // rows than one radix-16 round; 2^17 needs 512 rows, more than a 4096-element tile with whole 128-byte lines holds. What
 // they replaced on 2^13 .. 2^15 was the stage-by-stage ntt_pass_kernel with one kernel per step of a key switch (a
-// butterfly's operands through LDS every stage, integer arithmetic throughout): 37 transforms of 4 limbs in both
-// directions at 2^13 104 -> 52 us, 12 rotations at 2^14 (5 limbs) 287 -> 117 us, 8 products at 2^15 (13 limbs)
-// 833 -> 348 us.
+// butterfly's operands through LDS every stage, integer arithmetic throughout): 12 rotations at 2^14 (5 limbs) 287 -> 117 us,
+// 8 products at 2^15 (13 limbs) 833 -> 348 us. Whole transforms of 2^13 and 2^14 hold a limb per workgroup instead (launch_limbs).
 inline bool two_pass(const ckks_ctx* c) { return c->logN >= 13 && c->logN <= 16; }
 // Ring 2^12: a key switch in four kernels that hold a whole limb per workgroup (ks12.hip.h). 8 rotations with their own
 // keys (4 limbs, 2 digits), which took ten launches each: 322 -> 37 us; 8 rotations of one key (5 limbs, 3 digits) 60 -> 46 us.
@@ -903,8 +902,8 @@ struct KsIo {
   const u64* const* evk_pc = nullptr;
   const u64* add2 = nullptr;   // [B][2][nlimbs][N] plain addend of mode bit 0 (two-pass path); null = out, in place
   bool add2_three = false;     // add2 is [B][3][nlimbs][N]; its first two components are the addends
-  // ring 2^12, and two-pass rings where every main prime is double precision (mode {4, 4}): d is the product of the second
-  // components of two ciphertexts [B][2][nlimbs][N], whose other two product terms are the addends
+  // ring 2^12, and two-pass rings with knob 3 at its default (mode {4, 4}): d is the product of the second components of two
+  // ciphertexts [B][2][nlimbs][N], whose other two product terms are the addends
   const u64 *prod_a = nullptr, *prod_b = nullptr;
   bool steps = false;          // ring 2^12: one kernel per step (whole_limb said no)
 };
@@ -1216,11 +1215,12 @@ void launch_inner_c(const ckks_ctx* c, u32 B, u32 nslots, const FwdInnerArgs& a,
 //      keys 5623 -> 5383 us, one rotation 147 -> 139); ModDown conversion and row pass (as step 2)
 //   5. double-precision main limbs: [block pass of the digits + evk inner product + block pass of the ModDown
 //      correction + (sum - correction) / P + addends] in one kernel, so their accumulators never reach memory;
-//      integer-class main limbs take the assembly kernel on the accumulators of step 3.
-// With knob 3 = 1 the double-precision slots take a plain block pass, a streaming product and the assembly kernel
-// instead of step 5's fusion. With knob 4 = 0 the double-precision row pass of step 2, where it is a kernel of its own, runs on
-// the context's second stream beside the integer-class kernels of step 3 and step 4, which do not depend on it, and is joined
-// before the first kernel that reads what it leaves: step 5's, or with knob 3 = 1 the block pass of step 3.
+//      integer-class main limbs the same in theirs (the kernel of step 3, carried to the end).
+// With knob 3 = 1 the main limbs' accumulators are stored (integer-class ones by step 3, double-precision ones by a plain block
+// pass and a streaming product) and the assembly kernel replaces step 5. With knob 4 = 0 the double-precision row pass of step 2,
+// where it is a kernel of its own, runs on the context's second stream beside the integer-class kernels of step 3 and step 4, which
+// do not depend on it, and is joined before the first kernel that reads what it leaves: step 5's, or with knob 3 = 1 the block
+// pass of step 3.
 // acc_add != null (knob 3 at its default only): the sequence stops before ModDown and ADDS the two accumulators, plus
 // P * sigma(io.add_src component 0) on the main primes of the first, to acc_add ([B][2][next][N]).
 int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B, u32 nlimbs, const u64* evk, char* ws,

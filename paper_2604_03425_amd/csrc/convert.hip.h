@@ -20,8 +20,8 @@
 // What bounds it: instruction issue, at a clock rate that falls with the power the instructions take (1.65 - 1.75 GHz here).
 // Vector instructions per target and position: 17 for the conversion (20 to an integer target), 38 and 74 for the row pass, LDS
 // addresses included; on the vector units alone the conversion of 8 sources took 38 (double precision on both sides), 56 (integer
-// sources) and 50 (integer targets). N = 2^16, 64 ciphertexts of 24 limbs, 3 digits of 8, 8 special primes: ModUp 1394 -> 1303 us,
-// ModDown 1034 -> 893; one such ciphertext 35.5 -> 31.6 and 24.1 -> 22.2 (inverse pass apart). The conversion, row passes and
+// sources) and 50 (integer targets). N = 2^16, 64 ciphertexts of 24 limbs, 3 digits of 8, 8 special primes: ModUp 1325 -> 1230 us,
+// ModDown 989 -> 846; one such ciphertext 34.6 -> 30.9 and 23.6 -> 21.7 (inverse pass apart). The conversion, row passes and
 // inverse pass as kernels of their own took 2030 and 1440 us.
 #pragma once
 #include "radix4.hip.h"
@@ -263,8 +263,8 @@ __device__ __forceinline__ void conv_inv_rows(u64 (&x)[4], const ulonglong2* __r
 // v_mfma_i32_32x32x32_i8 takes four sources: lane (h, n) = (lane / 32, lane % 32) supplies 16 bytes, sources 2h and 2h + 1 of
 // position n in the second operand, of row n in the first, and receives rows 8b + 4h + r of column n. Rows are dealt so that lane
 // half h gets the 8 sums (b, r) = (p / 4, p % 4) of target h of a pair; the upper 16 rows of the product are not used (a full
-// one would serve four targets, whose results do not fit the registers; the matrix cores are idle nine tenths of the time). A lane's four
-// positions of all sources become the operands of 2 x 4 products by swaps of half-waves, in place.
+// one would serve four targets, whose results do not fit the registers; the matrix cores are busy an eighth of the time, by their
+// counter). A lane's four positions of all sources become the operands of 2 x 4 products by swaps of half-waves, in place.
 typedef int conv_i32x4 __attribute__((ext_vector_type(4)));
 typedef const __attribute__((address_space(3))) u32* lds_const_ptr;
 typedef int conv_i32x16 __attribute__((ext_vector_type(16)));

@@ -145,8 +145,8 @@ __device__ __forceinline__ void ks12_load_d(typename Ks12Mod<FP>::V (&x)[4], con
 }
 // Base conversion of `len` split limbs to modulus mi in the round-0 layout, canonical. The constants come by scalar loads, said so:
 // of a kernel's two bodies only the first would get them, since the compiler takes its stores for writes that the second may read
-// (integer bodies second, with vector loads: 19 rotations of one 55-bit limb 696 -> 692 us, 2 of 4 60-bit limbs 46.3 -> 46.0, 8
-// products of 5 55-bit limbs 56.9 -> 56.4).
+// (integer bodies second, with vector loads: a matrix product with 18 rotations of one 55-bit limb 696 -> 692 us, 2 rotations of 4
+// 60-bit limbs 46.3 -> 46.0, 8 products of 5 55-bit limbs 56.9 -> 56.4).
 template <bool NARROW>
 __device__ __forceinline__ void ks12_convert(u64 (&x)[4], const u64* __restrict__ src, u32 len, const_u64_ptr crow,
                                              u64 offc, const ModInfo& mi) {
@@ -301,8 +301,8 @@ __device__ __forceinline__ void ks12_final(const Ks12Args& a, u64* sm) {
 // Both arithmetic kinds share a launch (the kind is uniform per workgroup): a second launch would cost more than the
 // registers that the double-precision workgroups do not need. The kind comes with the arguments, not from the modulus: a trip to
 // memory less before everything else can be requested (8 rotations of 4 limbs with their own keys 36.9 -> 35.2 us); but for the
-// digits, whose integer workgroups start with the scalar loads of a conversion anyway (687 us that way, 693 this way in 19
-// rotations of one 55-bit limb; nothing between them in the others).
+// digits, whose integer workgroups start with the scalar loads of a conversion anyway (687 us that way, 693 this way in a
+// matrix product with 18 rotations of one 55-bit limb; nothing between them in the others).
 #define KS12_KERNEL(NAME, IS_FP, FP_BODY, INT_BODY)                           \
   __global__ void __launch_bounds__(WL_THREADS) NAME(Ks12Args a) {            \
     __shared__ u64 sm[WL_LDS_WORDS];                                          \
