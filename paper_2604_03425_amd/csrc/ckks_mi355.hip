@@ -1152,8 +1152,9 @@ int ks16_moddown_rows(ckks_ctx* c, const LevelTables* lt, u32 B, u32 nlimbs, u64
 }
 
 // Last kernel of a key switch on the two-pass path: block pass of tq fused with (acc - tq) / P and the addends.
+// int_only leaves the double-precision limbs to another kernel.
 int ks16_assemble(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B, u32 nlimbs, const u64* acc, const u64* tq,
-                  hipStream_t st) {
+                  hipStream_t st, bool int_only = false) {
   FwdFinalArgs a;
   a.tq = tq;
   a.acc = acc;
@@ -1176,7 +1177,10 @@ int ks16_assemble(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B, u32
     for (u32 i = 0; i < B; i++) a.galois_pc[i] = io.galois_pc[i];
   }
   a.map_mode = map_mode_pass(c);
-  auto cls_of = [&](u32 s) { return host_class(c, c->mod[s]); };
+  auto cls_of = [&](u32 s) {
+    const int k = host_class(c, c->mod[s]);
+    return int_only && k == 0 ? -1 : k;
+  };
   launch_by_class(c, PK_FWD_FINAL, a, B * 2, nlimbs, cls_of, st,
                   [&](int cls, dim3 grid) { LAUNCH_CLASS_KERNEL(ntt16_fwd_blocks_final_kernel, cls, grid, st, a); });
   HIP_TRY(hipGetLastError());
@@ -1205,6 +1209,24 @@ void launch_inner_c(const ckks_ctx* c, u32 B, u32 nslots, const FwdInnerArgs& a,
   }
 }
 
+// Whether the integer-class main limbs store their sums beside the special limbs' (step 3) and are assembled from there, instead of
+// taking all digits and both corrections in line at the end of the call (step 5). The former costs a write and a read of the sums;
+// it is faster where the workgroups of both are one round and the digits are many, so that a lone limb's chain is what the call
+// ends with. us, in line | stored: 4 rotations at 2^13, one 60-bit limb and four smaller in 5 digits 114.0 | 107.3; one at 2^15, 1 + 12
+// limbs in 5 digits 137.2 | 131.1, at 2^16, 1 + 23 in 4 digits 208.8 | 204.8; 4 at 2^14, 6 60-bit limbs in 6 digits 85.7 | 74.6. With
+// two digits (4 of 1 + 3 limbs at 2^13) 85.4 | 88.0, with four and no double-precision limb (16 of 4 limbs at 2^13) 73.9 | 74.7, beyond
+// a round (one of 14 60-bit limbs in 5 digits at 2^16, 544 workgroups) 129.0 | 130.4; at 512 (16 of 1 + 3 limbs at 2^15) 187.7 | 188.0.
+// A product also needs the kernel that forms its three terms then, which reads and writes whole limbs: up to 2^20 words of a batch's
+// polynomial (one of 2 + 12 limbs at 2^16, 2^19.8 words, 163.6 | 159.6; 2 of 1 + 14, 2^20.9, 251 | 256).
+bool int_sums_stored(const ckks_ctx* c, u32 B, u32 nlimbs, bool product) {
+  u32 mains = 0, specials = 0;
+  for (u32 i = 0; i < nlimbs; i++) mains += host_class(c, c->mod[i]) != 0;
+  for (u32 k = 0; k < c->np; k++) specials += host_class(c, c->mod[c->nq + k]) != 0;
+  const u32 beta = (nlimbs + c->alpha - 1) / c->alpha;
+  return mains && beta >= (mains < nlimbs ? 4 : 5) && (u64)B * (c->N / 2048) * (mains + specials) <= 512 &&
+         (!product || (u64)B * nlimbs * c->N <= 1u << 20);
+}
+
 // Two-pass path: transforms fused with their neighbours.
 //   1. INTT(d) with (Q_j/q_i)^-1 / N folded in
 //   2. ModUp conversion and row pass of every slot a digit does not own
@@ -1215,7 +1237,8 @@ void launch_inner_c(const ckks_ctx* c, u32 B, u32 nslots, const FwdInnerArgs& a,
 //      keys 5623 -> 5383 us, one rotation 147 -> 139); ModDown conversion and row pass (as step 2)
 //   5. double-precision main limbs: [block pass of the digits + evk inner product + block pass of the ModDown
 //      correction + (sum - correction) / P + addends] in one kernel, so their accumulators never reach memory;
-//      integer-class main limbs the same in theirs (the kernel of step 3, carried to the end).
+//      integer-class main limbs the same in theirs (the kernel of step 3, carried to the end), or by the assembly kernel from sums
+//      that step 3 stored (int_sums_stored).
 // With knob 3 = 1 the main limbs' accumulators are stored (integer-class ones by step 3, double-precision ones by a plain block
 // pass and a streaming product) and the assembly kernel replaces step 5. With knob 4 = 0 the double-precision row pass of step 2,
 // where it is a kernel of its own, runs on the context's second stream beside the integer-class kernels of step 3 and step 4, which
@@ -1364,7 +1387,8 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
       else hipLaunchKernelGGL((ntt16_fwd_blocks_inner8_kernel<2, false>), grid, block, 0, st, a);
     }
   };
-  launch_inner8(ia, true, acc_add || !fused_fp, false);
+  const bool stored = fused_fp && !acc_add && !io.prod_a && int_sums_stored(c, B, nlimbs, false);
+  launch_inner8(ia, true, acc_add || !fused_fp || stored, false);
   HIP_TRY(hipGetLastError());
   // double-precision slots whose accumulators are needed in memory: the special ones always (ModDown reads them),
   // the main ones when the result is accumulated or when the fusion of step 5 is switched off
@@ -1420,6 +1444,7 @@ int keyswitch_fused16(ckks_ctx* c, const LevelTables* lt, const KsIo& io, u32 B,
     ProfScope ps(c, PK_INNER_C, st);
     launch_inner_c(c, B, cnt, a, st);
   }
+  if (stored) return ks16_assemble(c, lt, io, B, nlimbs, acc, tq, st, true);
   launch_inner8(a, false, true, true);
   HIP_TRY(hipGetLastError());
   return CKKS_OK;
@@ -2243,7 +2268,7 @@ int ckks_hmult_relin(ckks_ctx* c, uint64_t* ct_out, const uint64_t* ct_a, const 
   // Two-pass rings: the products are formed where they are read (first inverse pass, own digits, assembly), which takes 6 passes
   // over a limb vector where a product kernel of its own and the reads of its results took 11: 32 products of 24 limbs at
   // 2^16 3328 -> 3099 us, 3 of 11 limbs 230 -> 216, 8 of 13 limbs at 2^15 308 -> 293.
-  if (two_pass(c) && c->tune[3] != 1) {
+  if (two_pass(c) && c->tune[3] != 1 && !int_sums_stored(c, B, nlimbs, true)) {
     KsIo io{nullptr, 0, 0, (u64*)ct_out, {4, 4}, nullptr, 0};
     io.prod_a = (const u64*)ct_a;
     io.prod_b = (const u64*)ct_b;
