@@ -548,7 +548,7 @@ inline u32 map_mode_inner(const ckks_ctx* c, bool shared_key) {
 // rows than one radix-16 round; 2^17 needs 512 rows, more than a 4096-element tile with whole 128-byte lines holds. What
 // they replaced on 2^13 .. 2^15 was the stage-by-stage ntt_pass_kernel with one kernel per step of a key switch (a
 // butterfly's operands through LDS every stage, integer arithmetic throughout): 12 rotations at 2^14 (5 limbs) 287 -> 117 us,
-// 8 products at 2^15 (13 limbs) 833 -> 348 us. Whole transforms of 2^13 and 2^14 hold a limb per workgroup instead (launch_limbs).
+// 8 products at 2^15 (13 limbs) 833 -> 348 us. Whole transforms of 2^13 and most of 2^14 hold a limb per workgroup instead (limb_whole).
 inline bool two_pass(const ckks_ctx* c) { return c->logN >= 13 && c->logN <= 16; }
 // Ring 2^12: a key switch in four kernels that hold a whole limb per workgroup (ks12.hip.h). 8 rotations with their own
 // keys (4 limbs, 2 digits), which took ten launches each: 322 -> 37 us; 8 rotations of one key (5 limbs, 3 digits) 60 -> 46 us.
@@ -632,8 +632,23 @@ struct NttOpts {
            exclude_class < 0;
   }
 };
-// Whole transforms of rings up to this one hold a limb per workgroup (ntt_limb.hip.h).
+// Whether a whole transform holds a limb per workgroup (ntt_limb.hip.h): always up to 2^13. A limb of 2^14 takes a compute unit's
+// LDS, so a round is 256 limbs, and one that is not half full leaves units idle that the two-pass kernels, four workgroups a limb,
+// would use. us for n limbs of one arithmetic kind, both forms in turn (two-pass | whole), forward: 50-bit primes n = 32 11.4 | 16.0, 128
+// 17.7 | 17.7, 144 19.8 | 17.3, 288 29.0 | 33.3, 400 41.0 | 35.1, 544 49.8 | 52.7, 656 57.8 | 54.7; 60-bit ones 32 13.5 | 21.2, 144
+// 25.1 | 22.9, 656 70.8 | 68.8. Their inverses gain later: 60-bit ones 144 26.9 | 25.7, 656 76.6 | 78.5, 720 82.8 | 80.2. From eight
+// rounds on memory decides (2080 limbs 183 | 155, 60-bit inverses 236 | 235). Limbs of two kinds are two launches a pass for the
+// two-pass kernels: 4 limbs 22.5 | 20.1 us, 256 36.0 | 24.0, 1280 119 | 103.
 #define LIMB_MAX_LOGN 14
+bool limb_whole(const ckks_ctx* c, u32 npoly, u32 nslots, const LimbMap& ids) {
+  if (c->logN < LIMB_MAX_LOGN) return true;
+  if (c->logN > LIMB_MAX_LOGN) return false;
+  const int cls = host_class(c, c->mod[ids.id[0]]);
+  for (u32 s = 1; s < nslots; s++)
+    if (host_class(c, c->mod[ids.id[s]]) != cls) return true;
+  const u64 limbs = (u64)npoly * nslots, full = (limbs - 1) / 256, last = limbs - full * 256;
+  return full >= 8 || last > (cls == 0 || full < 2 ? 128 : 192);
+}
 template <int LOGN>
 void launch_limb_kernel(bool inverse, dim3 grid, hipStream_t st, const LimbArgs& a) {
   if (inverse) hipLaunchKernelGGL((ntt_limb_kernel<LOGN, true>), grid, dim3(Limb<LOGN>::THREADS), 0, st, a);
@@ -679,7 +694,8 @@ int launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, u64 src_stride, 
                const NttOpts& opt = NttOpts()) {
   if (npoly == 0 || nslots == 0) return CKKS_OK;
   const int kind = inverse ? PK_NTT_INV : PK_NTT_FWD;
-  if (c->logN <= LIMB_MAX_LOGN && opt.plain()) return launch_limbs(c, inverse, src, src_stride, dst, dst_stride, npoly, slot0, nslots, ids_from_slot0, skip_beta, skip_nq, st);
+  if (opt.plain() && limb_whole(c, npoly, nslots, ids_from_slot0))
+    return launch_limbs(c, inverse, src, src_stride, dst, dst_stride, npoly, slot0, nslots, ids_from_slot0, skip_beta, skip_nq, st);
   if (two_pass(c)) {
     Ntt16Args a;
     a.logN = c->logN;

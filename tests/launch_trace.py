@@ -55,7 +55,7 @@ int hipStreamSynchronize(void*) { return 0; }
 CALLS = r"""
 import ctypes as C, json, sys
 from ckks_inputs.params import CkksParams, find_ntt_primes, find_psi
-logN, q_bits, p_bits, dnum, knobs, nl, B = json.loads(sys.argv[2])
+logN, q_bits, p_bits, dnum, knobs, nl, B, calls = json.loads(sys.argv[2])
 primes = []
 for bits in q_bits + p_bits:
     primes += find_ntt_primes(bits, 1, logN, exclude=set(primes))
@@ -74,8 +74,12 @@ for k, v in knobs:
 a, b, out, key, ws, st = (C.c_void_p(n << 40) for n in (1, 2, 3, 4, 5, 6))
 nl = nl or nq
 n = C.c_size_t(lib.ckks_workspace_bytes(ctx, 3, B, nl, 0))
-check(lib.ckks_hrot(ctx, out, a, B, nl, 5, key, ws, n, st))
-check(lib.ckks_hmult_relin(ctx, out, a, b, B, nl, key, ws, n, st))
+ids = (C.c_uint32 * nl)(*range(nl))
+for call in calls:
+    if call == "hrot": check(lib.ckks_hrot(ctx, out, a, B, nl, 5, key, ws, n, st))
+    if call == "hmult": check(lib.ckks_hmult_relin(ctx, out, a, b, B, nl, key, ws, n, st))
+    if call == "ntt": check(lib.ckks_ntt(ctx, a, B, ids, nl, st))
+    if call == "intt": check(lib.ckks_intt(ctx, a, B, ids, nl, st))
 """
 
 _folder = None
@@ -94,13 +98,13 @@ def _runtime():
     return _folder.name
 
 
-def trace(shape, knobs, nl=0, B=2):
-    """("launch", stream, kernel), ("record" or "wait", stream, event) of one rotation and one product of B ciphertexts
+def trace(shape, knobs, nl=0, B=2, calls=("hrot", "hmult")):
+    """("launch", stream, kernel), ("record" or "wait", stream, event) of `calls` on B ciphertexts (transforms: polynomials)
     of nl limbs (0: all). shape: logN, sizes of the main primes, of the special primes, digits."""
     import paper_2604_03425_amd as pkg
     env = dict(os.environ, LD_LIBRARY_PATH=_runtime(), PYTHONPATH=ROOT)
     res = subprocess.run([sys.executable, "-c", CALLS, pkg.library_path(),
-                          json.dumps(list(shape) + [sorted(knobs.items()), nl, B])], env=env,
+                          json.dumps(list(shape) + [sorted(knobs.items()), nl, B, calls])], env=env,
                          stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)
     assert res.returncode == 0, res.stderr
     return [line.split() for line in res.stdout.splitlines()]
