@@ -140,13 +140,26 @@ __device__ __forceinline__ void limb_fwd(const u64* __restrict__ src, u64* __res
 #pragma unroll
   for (int r = 0; r < 16; r++) x[r] = u2d(src[L::elem(0, r)]);
   limb_twiddles<LOGN>(wa, tw, 1);
-  if (L::F == 3) limb_twiddles<LOGN>(wb, tw, 2);
   radix16_fwd_fp(x, q, qinv, [&](int s, int g) { return tw[(1 << s) + g]; });
   limb_exchange<LOGN, 0, 1>(x, sm);
   radix16_fwd_fp(x, q, qinv, [&](int s, int g) { return wa[NTT16_TW_INDEX(s, g)]; });
   if (L::F == 3) {
+    // Only now: lanes read them 64 bytes apart, the most lines of any request here, and where two workgroups share a compute unit they
+    // would be in the way of its data (2^12, forward, with the ending below: 300 limbs 9.57 -> 9.19 us, 600 12.8 -> 12.2).
+    __builtin_amdgcn_sched_barrier(0);
+    limb_twiddles<LOGN>(wb, tw, 2);
+    __builtin_amdgcn_sched_barrier(0);
     limb_exchange<LOGN, 1, L::F - 1>(x, sm);
     radix16_fwd_fp(x, q, qinv, [&](int s, int g) { return wb[NTT16_TW_INDEX(s, g)]; });
+  }
+  if (L::LAST == 0) {   // the residues leave as they are read back
+    const u32 from = L::word(L::base(L::F - 1)), to = L::word(L::base(L::F));
+#pragma unroll
+    for (int r = 0; r < 16; r++) sm[from + L::word(L::step(L::F - 1, r))] = x[r];
+    wave_lds_sync();
+#pragma unroll
+    for (int r = 0; r < 16; r++) dst[L::elem(L::F, r)] = d2u_canon(sm[to + L::word(L::step(L::F, r))], q);
+    return;
   }
   limb_exchange<LOGN, L::F - 1, L::F>(x, sm);
   limb_last<LOGN, false>(tw, [&](int X, int Y, double w, int, int, int) {
@@ -292,10 +305,11 @@ struct LimbArgs {
   unsigned char id[128];                // slot -> modulus id
 };
 
-// Both arithmetic kinds share a launch (the kind is uniform per workgroup). 4 waves per SIMD: what the LDS leaves at 2^13 and what
-// 1024 lanes need at 2^14.
+// Both arithmetic kinds share a launch (the kind is uniform per workgroup). 4 waves per SIMD: what the LDS leaves at 2^13, what
+// 1024 lanes need at 2^14, and without which the inverses of 2^10 and 2^11 take 132 registers (2000 limbs of 2^11 16.3 -> 18.8 us).
+// Left to itself 2^12 takes 123 and is faster (300 limbs: 50-bit inverses 10.05 -> 9.52 us, 60-bit forward 13.0 -> 12.6).
 template <int LOGN, bool INV>
-__global__ void __launch_bounds__(Limb<LOGN>::THREADS) __attribute__((amdgpu_waves_per_eu(4))) ntt_limb_kernel(LimbArgs a) {
+__global__ void __launch_bounds__(Limb<LOGN>::THREADS) __attribute__((amdgpu_waves_per_eu(LOGN == 12 ? 1 : 4))) ntt_limb_kernel(LimbArgs a) {
   __shared__ __attribute__((aligned(16))) u64 sm[Limb<LOGN>::WORDS];
   const u32 poly = blockIdx.x, slot = blockIdx.y;
   if (a.skip_beta) {
