@@ -617,7 +617,7 @@ void launch_rows(u32 logN, bool inverse, int cls, dim3 grid, hipStream_t st, con
 
 struct NttOpts {
   u32 galois = 0;                     // two-pass inverse only: read src through the eval-domain Galois map
-  const u64* src_b = nullptr;         // two-pass inverse only: transform the products of src and src_b (double precision)
+  const u64* src_b = nullptr;         // two-pass inverse only: transform the products of src and src_b
   const u32* galois_pc = nullptr;     // same, one element per polynomial (host array, npoly <= KS_MULTI_MAX entries)
   const ulonglong2* scale = nullptr;  // two-pass inverse only: per-slot constants (from slot0) replacing N^-1
   bool split_out = false;             // N = 2^16 inverse only: write the shifted, split form the fused base conversion reads
@@ -742,7 +742,11 @@ int launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, u64 src_stride, 
     } else {
       if (!opt.rows_only)
         launch_by_class(c, PK_INV_BLOCKS, a, npoly, nslots, cls_of, st,
-                        [&](int cls, dim3 grid) { LAUNCH_CLASS_KERNEL(ntt16_inv_blocks_kernel, cls, grid, st, a); });
+                        [&](int cls, dim3 grid) {
+                          if (cls == 1 && a.src_b) hipLaunchKernelGGL((ntt16_inv_blocks_kernel<1, true>), grid, dim3(NTT16_THREADS), 0, st, a);
+                          else if (cls == 2 && a.src_b) hipLaunchKernelGGL((ntt16_inv_blocks_kernel<2, true>), grid, dim3(NTT16_THREADS), 0, st, a);
+                          else LAUNCH_CLASS_KERNEL(ntt16_inv_blocks_kernel, cls, grid, st, a);
+                        });
       if (!opt.blocks_only) rows(b, PK_INV_ROWS);
     }
     HIP_TRY(hipGetLastError());

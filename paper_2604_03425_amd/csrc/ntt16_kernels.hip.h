@@ -92,7 +92,9 @@ __global__ void __launch_bounds__(NTT16_THREADS) ntt16_fwd_blocks_kernel(Ntt16Ar
 #pragma unroll
   for (int i = 0; i < 16; i++) dst[(size_t)h * 256 + i * 16 + j0] = x[i];
 }
-template <int CLS>
+// PRODUCT: integer classes only, a.src_b is given. (As a branch on a.src_b every inverse transform of 51-bit limbs took 2 to 2.7 % longer, of
+// 60-bit ones up to 1 %: 100 limbs of 2^16 56.5 -> 58.0 us, 57.9 -> 58.0. In double precision it costs nothing.)
+template <int CLS, bool PRODUCT = false>
 __global__ void __launch_bounds__(NTT16_THREADS) ntt16_inv_blocks_kernel(Ntt16Args a) {
   NTT16_PROLOGUE(a.logN, NTT16_LDS_BYTES / 8)
   const u32 t = threadIdx.x, j0 = t & 15, h = tile * 16 + (t >> 4);
@@ -118,20 +120,15 @@ __global__ void __launch_bounds__(NTT16_THREADS) ntt16_inv_blocks_kernel(Ntt16Ar
     ntt16_inv_blocks_fp(xd, twfp, mi.qd, mi.qinv, tile, R, (double*)sm);
 #pragma unroll
     for (int i = 0; i < 16; i++) x[i] = (u64)__double_as_longlong(xd[i]);
-#pragma unroll
-    for (int i = 0; i < 16; i++) dst[(size_t)h * 256 + i * 16 + j0] = x[i];
-    return;
-  }
-  if (a.src_b) {
-    const u64* sb = a.src_b + (size_t)poly * a.src_poly_stride + ((size_t)slot << logN);
-    const u64 r2 = mont_r2(mi);
-#pragma unroll
-    for (int i = 0; i < 16; i++) x[i] = mont_plain(x[i], sb[(size_t)h * 256 + i * 16 + j0], r2, mi.m, mi.minv);
-  }
-  if (cls == 2) {
-    ntt16_inv_blocks<true>(x, tw, mi.m, mi.mu64, tile, R, sm);
   } else {
-    ntt16_inv_blocks<false>(x, tw, mi.m, mi.mu64, tile, R, sm);
+    if (PRODUCT) {
+      const u64* sb = a.src_b + (size_t)poly * a.src_poly_stride + ((size_t)slot << logN);
+      const u64 r2 = mont_r2(mi);
+#pragma unroll
+      for (int i = 0; i < 16; i++) x[i] = mont_plain(x[i], sb[(size_t)h * 256 + i * 16 + j0], r2, mi.m, mi.minv);
+    }
+    if (cls == 2) ntt16_inv_blocks<true>(x, tw, mi.m, mi.mu64, tile, R, sm);
+    else ntt16_inv_blocks<false>(x, tw, mi.m, mi.mu64, tile, R, sm);
   }
 #pragma unroll
   for (int i = 0; i < 16; i++) dst[(size_t)h * 256 + i * 16 + j0] = x[i];
