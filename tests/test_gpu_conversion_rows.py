@@ -1,5 +1,5 @@
 """GPU parity of the base conversion fused with the row passes around it, where its instantiations differ: source counts
-around 4 and 8, the separate kernels beyond, each arithmetic kind on either side, short digits, shares of the targets."""
+around 4, 6 and 8, the separate kernels beyond, each arithmetic kind on either side, short digits, shares of the targets."""
 import pytest
 
 import test_gpu_two_pass_rings as calls
@@ -13,10 +13,10 @@ SHAPES = [
     ((14, 8, 45, 8, 60, 1), 7, 2),     # a digit one limb short
     ((15, 7, 50, 6, 60, 1), 7, 1),
     ((13, 9, 50, 9, 60, 1), 9, 1),     # one source more than the fused kernel takes
-    ((13, 8, 60, 8, 60, 1), 8, 1),     # 60-bit primes on both sides
+    ((13, 8, 60, 8, 60, 1), 8, 1),     # 60-bit primes on both sides: the general reduction
     ((14, 4, 51, 4, 60, 1), 4, 2),     # 51-bit sources
     ((13, 6, 50, 3, 50, 2), 6, 2),     # double precision on both sides, special primes too
-    ((13, 3, 30, 2, 50, 2), 3, 40),    # 30-bit targets
+    ((13, 3, 30, 2, 50, 2), 3, 40),    # 30-bit targets: the general reduction, which keeps the separate kernels
 ]
 
 
@@ -66,6 +66,45 @@ def test_shares_of_the_targets(shape, B, alone):
     gpu.ckks_hmult_relin(gc, out, d_ct, d_ct2, B, nl, d_evk, ws)
     assert_same(to_host(out)[some], rc.hmult_relin(ct[some], ct2[some], evk), "hmult_relin")
     gc.close()
+
+
+def test_double_precision_conversion_is_exact_at_its_bounds():
+    """The recurrence of the conversion of double-precision sources, in correctly rounded double arithmetic: the running sum
+    stays in its binade, both parts are exact, and what one quotient of their sum leaves is congruent and at most 1.3 moduli."""
+    import random
+    from fractions import Fraction
+
+    def rnd(x):   # one rounding to double, ties to even, as the hardware's fma and add do
+        return float(x)
+    M, rng = 1.5 * 2.0 ** 102, random.Random(3)
+    top = (1 << 50) - 27     # the largest sources and targets (primality plays no part in the bounds)
+    for trial in range(300):
+        n = rng.choice([1, 4, 8])
+        q = rng.choice([top, top, (1 << 40) - 87, (1 << 20) + 7])
+        sign = rng.choice([1, -1])
+        if trial % 3:
+            ys = [rng.randint(-(top // 2), top // 2) for _ in range(n)]
+            cs = [rng.randint(-(q // 2), q // 2) for _ in range(n)]
+        else:                # every product at the largest magnitude, all of one sign
+            ys, cs = [sign * (top // 2)] * n, [q // 2] * n
+        H, L = M, 0.0
+        for y, c in zip(ys, cs):
+            Hn = rnd(Fraction(y) * c + Fraction(H))
+            assert 2.0 ** 102 <= Hn < 2.0 ** 103
+            h = Hn - H
+            assert Fraction(h) == Fraction(Hn) - Fraction(H)
+            rest = Fraction(y) * c - Fraction(h)
+            assert abs(rest) <= 2 ** 49 and Fraction(rnd(rest)) == rest
+            assert Fraction(L) + rest == Fraction(L + float(rest))
+            H, L = Hn, L + float(rest)
+        total, h, qinv = sum(y * c for y, c in zip(ys, cs)), H - M, 1.0 / q
+        assert Fraction(h) + Fraction(L) == total
+        t = round(rnd(Fraction(L) * Fraction(qinv) + Fraction(h * qinv)))
+        r = Fraction(h) - Fraction(t) * q
+        assert Fraction(rnd(r)) == r
+        out = rnd(r) + L
+        assert Fraction(out) == r + Fraction(L)
+        assert (Fraction(out) - total) % q == 0 and abs(out) <= 1.3 * q
 
 
 @gpu_only

@@ -116,13 +116,11 @@ def test_keyswitch(gpu, shape, nlimbs, B):
 
 @pytest.mark.parametrize("shape,nlimbs,B", [((12, 6, 50, 3, 60, 2), 6, 2), ((16, 4, 50, 2, 60, 2), 4, 2)])
 def test_keyswitch_general_reduction(gpu, shape, nlimbs, B):
-    """Base conversions forced onto the general four-sum / 128-bit reduction where the three-sum form would do (at 2^16 as kernels
-    of their own: knob 5 means nothing to the fused conversion)."""
+    """Base conversions forced onto the general four-sum / 128-bit reduction where the three-sum form would do."""
     import torch
     from gpu_util import to_dev, to_host, assert_same
     p = shape_params(shape)
     rc, gc = ref.RefContext(p), gpu.Context(p)
-    gpu.ckks_tune_set(gc, 2, 2)
     gpu.ckks_tune_set(gc, 5, 1)
     d = uniform_residues(13, p.q[:nlimbs], (B,), p.N)
     evk = uniform_residues(14, p.moduli, (p.dnum, 2), p.N)

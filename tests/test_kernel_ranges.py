@@ -213,6 +213,28 @@ def test_centred_representative_by_rounding():
                 assert (r - v) % q == 0 and abs(r) <= h
 
 
+def test_conversion_of_eight_double_precision_sources():
+    """H + L of eight products of 2^98, reduced with one rounded quotient: exact, at most 1.3 q."""
+    rng = random.Random(13)
+    for bits in (50, 40):
+        q, M = _fp_prime(bits), 3 << 101
+        for _ in range(200):
+            H, L, want = M, 0, 0
+            for _ in range(8):
+                y = rng.choice((-1, 1)) * ((1 << 49) - 1 - rng.choice((0, rng.randrange(1 << 48))))
+                c = rng.choice((1, 1, -1)) * (q // 2 - rng.choice((0, rng.randrange(q // 2))))
+                want += y * c
+                Hn = int(float(H + y * c))
+                L += y * c - (Hn - H)
+                H = Hn
+                assert abs(L) <= 1 << 53
+            h = H - M
+            t = round(float(L * (1.0 / q) + float(h) * (1.0 / q)))
+            assert abs(h - t * q) <= 1 << 53
+            x = h - t * q + L
+            assert (x - want) % q == 0 and abs(x) <= 1.3 * q
+
+
 def test_inverse_ranges_with_products_left_alone():
     """60-bit primes: sums corrected by 8m stay below 8m; the sum of two products (below 4m) needs no correction."""
     rng = random.Random(14)
@@ -280,6 +302,63 @@ def _odd_below(bits):
     return (1 << bits) - 59
 
 
+def _redc60(sums, m):
+    """Two words of the base-2^30 Montgomery reduction of a + b 2^30 + c 2^60; no word may pass 2^64."""
+    M30 = (1 << 30) - 1
+    a, b, c = sums
+    q0, q1, qi = m & M30, m >> 30, -pow(m, -1, 1 << 30) & M30
+    u = (a & M30) * qi & M30
+    a += u * q0
+    assert a <= M64 and a & M30 == 0
+    b += (a >> 30) + u * q1
+    assert b <= M64
+    u = (b & M30) * qi & M30
+    b += u * q0
+    assert b <= M64 and b & M30 == 0
+    c += (b >> 30) + u * q1
+    assert c <= M64
+    return c
+
+
+def test_conversion_of_split_sources():
+    """At most 8 sources: V / 2^60 modulo m below V / 2^60 + m <= 9m. To a double-precision target the result goes through
+    an offset, 2^62 - 4m in the top sum: what is left of it after subtracting 2^62 is exact in doubles and below 2^53."""
+    rng = random.Random(16)
+    M30, tried = (1 << 30) - 1, 0
+    for bs in (60, 55, 51, 50, 36, 30):
+        for bt in (60, 52, 50, 45, 36):
+            for n in range(1, 9):
+                if not _narrow_ok(n, bs, bt, bt):
+                    continue
+                tried += 1
+                m = _odd_below(bt)
+                for trial in range(20):
+                    worst = trial % 2 == 0
+                    ys = [(1 << bs) - 1 if worst else rng.getrandbits(bs) for _ in range(n)]
+                    cs = [m - 1 if worst else rng.randrange(m) for _ in range(n)]
+                    off = m - 1 if worst else rng.randrange(m)
+                    V = off + sum(y * c for y, c in zip(ys, cs))
+                    a, b, c = off & M30, off >> 30, 0
+                    for y, k in zip(ys, cs):
+                        a += (y & M30) * (k & M30)
+                        b += (y & M30) * (k >> 30) + (y >> 30) * (k & M30)
+                        c += (y >> 30) * (k >> 30)
+                    assert max(a, b, c) <= M64
+                    r = _redc60((a, b, c), m)
+                    assert (r * (1 << 60) - V) % m == 0 and r <= V // (1 << 60) + m and r < 9 * m
+                    if bt <= 50:
+                        v = _redc60((a, b, c + (1 << 62) - 4 * m), m)
+                        assert v == r + (1 << 62) - 4 * m and -4 * m <= v - (1 << 62) < 5 * m <= 1 << 53
+                        hi, lo = 2.0 ** 84 + 2.0 ** 32 * (v >> 32), 2.0 ** 52 + (v & 0xFFFFFFFF)
+                        assert int(hi) == (1 << 84) + (v >> 32 << 32)
+                        big = 2.0 ** 84 + 2.0 ** 62 + 2.0 ** 52
+                        assert int(big) == (1 << 84) + (1 << 62) + (1 << 52)
+                        x = (hi - big) + lo
+                        assert int(x) == v - (1 << 62)
+                        assert abs(_fp_reduce(int(x), m)) <= m // 2
+    assert tried > 150
+
+
 def _redc90(sums, m):
     """Three words of the base-2^30 Montgomery reduction of a + b 2^30 + c 2^60; no word may pass 2^64."""
     M30 = (1 << 30) - 1
@@ -301,7 +380,7 @@ def _redc90(sums, m):
     return (c >> 30) + u * q1
 
 
-def test_conversion_of_split_sources():
+def test_endings_of_the_separate_conversions():
     """At most 8 sources, and the sources above half their modulus times one constant: in three sums V / 2^90 modulo m below
     m + 2^34, in four sums V / 2^64 below 2m, so that one subtraction ends both."""
     rng = random.Random(16)
