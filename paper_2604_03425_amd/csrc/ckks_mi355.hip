@@ -636,18 +636,24 @@ struct NttOpts {
 // LDS, so a round is 256 limbs, and one that is not half full leaves units idle that the two-pass kernels, four workgroups a limb,
 // would use. us for n limbs of one arithmetic kind, both forms in turn (two-pass | whole), forward: 50-bit primes n = 32 11.4 | 16.0, 128
 // 17.7 | 17.7, 144 19.8 | 17.3, 288 29.0 | 33.3, 400 41.0 | 35.1, 544 49.8 | 52.7, 656 57.8 | 54.7; 60-bit ones 32 13.5 | 21.2, 144
-// 25.1 | 22.9, 656 70.8 | 68.8. Their inverses gain later: 60-bit ones 144 26.9 | 25.7, 656 76.6 | 78.5, 720 82.8 | 80.2. From eight
-// rounds on memory decides (2080 limbs 183 | 155, 60-bit inverses 236 | 235). Limbs of two kinds are two launches a pass for the
-// two-pass kernels: 4 limbs 22.5 | 20.1 us, 256 36.0 | 24.0, 1280 119 | 103.
+// 25.1 | 22.9, 656 70.8 | 68.8, 900 93.3 | 91.7 (51-bit ones 88.8 | 91.2). Their inverses gain later: 60-bit ones 144 26.9 | 25.7, 656 76.6 | 78.5, 720 82.8 | 80.2.
+// With the rounds the gain shrinks, since loads and stores of a unit's only workgroup do not overlap with its stages, and where those
+// take longer (inverses, and the spills of integer ones) it turns: 50-bit inverses 1024 87.9 | 85.1, 1450 117 | 120; 51-bit primes
+// forward 1024 97.2 | 94.7, 1450 133 | 137, inverse 512 60.1 | 55.9, 700 78.8 | 80.7, 1200 120 | 134; 60-bit inverses 768 85.2 | 83.3, 1024
+// 108 | 109, 1200 124 | 134. From eight rounds on (256 MB, what the last-level cache holds) a pass over memory less decides: 2100
+// limbs forward 188 | 158, 60-bit ones 228 | 197, inverse 190 | 177; integer inverses 2100 231 | 234, 2304 261 | 251. Limbs of two kinds are
+// two launches a pass for the two-pass kernels: 4 limbs 22.5 | 20.1 us, 256 36.0 | 24.0, 1280 119 | 103.
 #define LIMB_MAX_LOGN 14
-bool limb_whole(const ckks_ctx* c, u32 npoly, u32 nslots, const LimbMap& ids) {
+bool limb_whole(const ckks_ctx* c, bool inverse, u32 npoly, u32 nslots, const LimbMap& ids) {
   if (c->logN < LIMB_MAX_LOGN) return true;
   if (c->logN > LIMB_MAX_LOGN) return false;
   const int cls = host_class(c, c->mod[ids.id[0]]);
   for (u32 s = 1; s < nslots; s++)
     if (host_class(c, c->mod[ids.id[s]]) != cls) return true;
   const u64 limbs = (u64)npoly * nslots, full = (limbs - 1) / 256, last = limbs - full * 256;
-  return full >= 8 || last > (cls == 0 || full < 2 ? 128 : 192);
+  if (full >= 8) return !inverse || cls == 0 || full > 8 || last > 128;
+  static const u32 rounds[2][3] = {{8, 4, 8}, {4, 2, 3}};   // [inverse][class] that the whole form is ahead for
+  return full < rounds[inverse][cls] && last > (full < 2 || cls == 0 || (cls == 2 && !inverse) ? 128 : 192);
 }
 template <int LOGN>
 void launch_limb_kernel(bool inverse, dim3 grid, hipStream_t st, const LimbArgs& a) {
@@ -694,7 +700,7 @@ int launch_ntt(const ckks_ctx* c, bool inverse, const u64* src, u64 src_stride, 
                const NttOpts& opt = NttOpts()) {
   if (npoly == 0 || nslots == 0) return CKKS_OK;
   const int kind = inverse ? PK_NTT_INV : PK_NTT_FWD;
-  if (opt.plain() && limb_whole(c, npoly, nslots, ids_from_slot0))
+  if (opt.plain() && limb_whole(c, inverse, npoly, nslots, ids_from_slot0))
     return launch_limbs(c, inverse, src, src_stride, dst, dst_stride, npoly, slot0, nslots, ids_from_slot0, skip_beta, skip_nq, st);
   if (two_pass(c)) {
     Ntt16Args a;
