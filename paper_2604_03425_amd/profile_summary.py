@@ -35,7 +35,8 @@ def kind(name):
     base = n.split("<")[0]
     if base in ("modup_kernel", "moddown_kernel", "conv_rows_kernel", "ntt16_fwd_blocks_inner_c_kernel"):
         return base
-    if base in ("ntt16_bconv_rows_kernel", "ntt16_fwd_rows_kernel", "ntt16_inv_rows_kernel", "ntt16_fwd_blocks_inner8_kernel"):
+    if base in ("ntt16_bconv_rows_kernel", "ntt16_fwd_rows_kernel", "ntt16_inv_rows_kernel", "ntt16_inv_blocks_kernel",
+                "ntt16_fwd_blocks_inner8_kernel"):
         return base + "<" + n.split("<")[1].split(",")[0].strip(" >") + ">"
     return n
 

@@ -37,3 +37,13 @@ def test_wide_conversions_keep_their_arrays_in_registers(groups):
     assert k[".group_segment_fixed_size"] == 2 * groups * 1024   # two images of the matrices, nothing else
     assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0
     assert k[".vgpr_count"] <= (128 if groups <= 9 else 168)     # two workgroups of 8 waves to a compute unit, or one
+
+
+def test_profiles_name_the_two_pass_kernels_as_the_library_does():
+    """The per-kernel tables join a trace's names with the library's kinds: every kind of a two-pass kernel is found under its name."""
+    import subprocess
+    from paper_2604_03425_amd import binding, profile_summary
+    names = subprocess.run(["c++filt"], input="\n".join(_kernels()), stdout=subprocess.PIPE, text=True, check=True).stdout.splitlines()
+    lib = binding._lib
+    kinds = {lib.ckks_prof_kind_name(k).decode() for k in range(lib.ckks_prof_num_kinds())}
+    assert {k for k in kinds if k.startswith("ntt16_")} <= {profile_summary.kind(n) for n in names}
