@@ -118,6 +118,7 @@ struct LevelTables {
   // matrices of bytes of (Q_j/q_i) mod m_t ([beta][next]) and (P/p_k) mod q_i ([nlimbs]; on two-pass rings with 2^-64 on
   // integer-class targets), for conv_rows_kernel (at most 8 sources) or conv_wide_kernel
   uint4 *up_pieces = nullptr, *dn_pieces = nullptr;
+  double *up_direct = nullptr, *dn_direct = nullptr;   // ConvArgs::direct: two-pass rings with every prime below 2^50
   u64* up_off = nullptr;           // [beta][next] -sum_i ((q_i-1)/2) (Q_j/q_i) mod m_t, scaled like up_mat
   u64* dn_off = nullptr;           // [nlimbs]     -sum_k ((p_k-1)/2) (P/p_k) mod q_i, scaled like dn_mat_plain
   u32 up_pitch = 0, dn_pitch = 0;  // constants per target in up_mat / dn_mat_plain
@@ -313,6 +314,11 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
   };
   std::vector<unsigned char> up_pieces(pieces_bytes(t.beta, next, up_groups, up_wide), 0);
   std::vector<unsigned char> dn_pieces(pieces_bytes(1, nlimbs, dn_groups, dn_wide), 0);
+  const bool all_fp = c->logN >= 13 && c->logN <= 16 && std::all_of(c->mod.begin(), c->mod.begin() + c->nm, is_fp);
+  const bool up_vec = all_fp && alpha <= CONV_DIRECT_SRC, dn_vec = all_fp && K <= CONV_DIRECT_SRC;
+  std::vector<double> up_direct(up_vec ? (size_t)t.beta * next * CONV_MAX_SRC : 0, 0.0);
+  std::vector<double> dn_direct(dn_vec ? (size_t)nlimbs * CONV_MAX_SRC : 0, 0.0);
+  auto centred = [](u64 v, u64 m) { return v > m / 2 ? -(double)(m - v) : (double)v; };
   std::vector<u64> up_plain((size_t)next * alpha), dn_plain((size_t)nlimbs * K);   // (Q_j/q_i) mod m_t of one digit, (P/p_k) mod q_i
   t.up_pitch = R + 1;
   t.dn_pitch = RK + 1;
@@ -329,6 +335,7 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
         for (u32 k = lo; k < hi; k++)
           if (k != i) v = h_mul(v, c->mod[k] % m, m);
         up_plain[(size_t)s * alpha + (i - lo)] = v;
+        if (up_vec) up_direct[((size_t)j * next + s) * CONV_MAX_SRC + (i - lo)] = centred(v, m);
         up_mat[((size_t)j * next + s) * (R + 1) + (i - lo)] = mont_up(v, m);
       }
     }
@@ -361,6 +368,7 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
       for (u32 r = 0; r < K; r++)
         if (r != k) v = h_mul(v, c->mod[c->nq + r] % m, m);
       dn_plain[(size_t)i * K + k] = v;
+      if (dn_vec) dn_direct[(size_t)i * CONV_MAX_SRC + k] = centred(v, m);
       dn_mat[(size_t)i * (RK + 1) + k] = mont_dn(v, m);
     }
   }
@@ -453,6 +461,8 @@ LevelTables build_level(const ckks_ctx* c, u32 nlimbs, LevelArena& arena) {
   t.dn_mat_plain = arena.add(dn_mat_plain);
   t.up_pieces = (uint4*)arena.add(up_pieces);
   t.dn_pieces = (uint4*)arena.add(dn_pieces);
+  if (up_vec) t.up_direct = arena.add(up_direct);
+  if (dn_vec) t.dn_direct = arena.add(dn_direct);
   t.up_off = arena.add(up_off);
   t.dn_off = arena.add(dn_off);
   t.pinv2 = arena.add(pinv2);
@@ -497,6 +507,8 @@ int build_levels(ckks_ctx* c) {
     rebase(t.up_inv); rebase(t.up_mat); rebase(t.dn_inv); rebase(t.dn_mat); rebase(t.pinv);
     rebase(t.up_scale); rebase(t.dn_scale); rebase(t.dn_mat_plain); rebase(t.pinv2);
     rebase(t.up_pieces); rebase(t.dn_pieces); rebase(t.up_off); rebase(t.dn_off);
+    if (t.up_direct) rebase(t.up_direct);
+    if (t.dn_direct) rebase(t.dn_direct);
     rebase(t.rs_pieces); rebase(t.rs_scale); rebase(t.rs_one); rebase(t.rs_mat); rebase(t.rs_qinv); rebase(t.rs_qinv16);
   }
   if (c->d_levels) {
@@ -984,6 +996,13 @@ struct ConvJob {
   u32 npoly;
   bool fp, ready;
 };
+template <int LOGR>
+void launch_conv_direct(const ConvJob& j, dim3 grid, hipStream_t st) {
+  const dim3 block(CONV_THREADS);
+  if (j.a.alpha <= 4) hipLaunchKernelGGL((conv_rows_kernel<LOGR, 4, true, false, true>), grid, block, 0, st, j.a);
+  else if (j.ready) hipLaunchKernelGGL((conv_rows_kernel<LOGR, CONV_DIRECT_SRC, true, true, true>), grid, block, 0, st, j.a);
+  else hipLaunchKernelGGL((conv_rows_kernel<LOGR, CONV_DIRECT_SRC, true, false, true>), grid, block, 0, st, j.a);
+}
 template <int LOGR, int MAXLEN, bool READY>
 void launch_conv_len(const ConvJob& j, dim3 grid, hipStream_t st) {
   const dim3 block(CONV_THREADS);
@@ -993,7 +1012,8 @@ void launch_conv_len(const ConvJob& j, dim3 grid, hipStream_t st) {
 #define CONV_READY_MIN_SRC 6
 template <int LOGR>
 void launch_conv_of(const ConvJob& j, dim3 grid, hipStream_t st) {
-  if (j.a.alpha <= 4) launch_conv_len<LOGR, 4, false>(j, grid, st);
+  if (j.a.direct) launch_conv_direct<LOGR>(j, grid, st);
+  else if (j.a.alpha <= 4) launch_conv_len<LOGR, 4, false>(j, grid, st);
   else if (j.ready) launch_conv_len<LOGR, 8, true>(j, grid, st);
   else launch_conv_len<LOGR, 8, false>(j, grid, st);
 }
@@ -1088,6 +1108,7 @@ ConvJob conv_up_job(const ckks_ctx* c, const LevelTables* lt, const u64* dcoef, 
   a.skip_own = 1;
   a.ntarget = lt->next;
   a.pieces = lt->up_pieces;
+  a.direct = lt->up_direct;
   a.scale = lt->up_scale;
   job.npoly = B * lt->beta;
   conv_plan(c, job, [&](u32 s) { return s < nlimbs ? s : s - nlimbs + c->nq; });
@@ -1108,6 +1129,7 @@ ConvJob conv_down_job(const ckks_ctx* c, const LevelTables* lt, const u64* acc, 
   a.skip_own = 0;
   a.ntarget = nlimbs;
   a.pieces = lt->dn_pieces;
+  a.direct = lt->dn_direct;
   a.scale = lt->dn_scale;
   job.npoly = B * 2;
   conv_plan(c, job, [](u32 s) { return s; });

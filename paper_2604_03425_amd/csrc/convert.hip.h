@@ -54,6 +54,9 @@ struct ConvArgs {
   u32 nfp, nint;             // targets by arithmetic kind: tslot[0 .. nfp), tslot[nfp .. nfp + nint)
   u32 nsplit;                // workgroups that share the targets of a (polynomial, tile)
   const uint4* pieces;       // [beta][ntarget] matrices of bytes of the constants (layout: conv_request_rows)
+  // != null, double precision on both sides and at most CONV_DIRECT_SRC sources: [beta][ntarget][CONV_MAX_SRC] centred constants
+  // (C/c_k) mod m_t for the conversion on the vector units
+  const double* direct = nullptr;
   const ConvReduction* red;     // [nm] per modulus id, read on integer targets
   const ulonglong2* scale;   // [src_nlimbs] per source (Q_j/q_i)^-1 / N, in the form of its class
   const ulonglong2 *tw, *twi;
@@ -379,6 +382,86 @@ __device__ __forceinline__ u64 conv_settle(u32 lo, long long hi, const ConvTarge
   const u64 v = (u64)conv_mad(s, m0, (long long)((u64)(u32)hi << 32 | lo));
   return (u64)((u32)(v >> 32) + (u32)s * m1) << 32 | (u32)v;
 }
+// ---- double precision on both sides, few sources: on the vector units ----
+// The matrix products of a pair of targets cost what four or eight sources cost, whatever their number, and a lone workgroup's start
+// waits for its matrices; up to 6 sources the sums below are fewer instructions. 460 calls with 1 to 8 sources, every prime below
+// 2^50, all two-pass rings: 2 to 4 % faster this way up to 6 sources, even at 8 (not built for 7). us, matrix cores | here: one
+// rotation of 5 + 5 limbs in one digit at 2^13 45.3 | 42.5, 24 of them 75.9 | 70.6; 24 of 2 + 2 limbs at 2^16 155 | 150; 24 of 3 + 1 limbs
+// in 3 digits at 2^15 131.6 | 126.2.
+#define CONV_DIRECT_SRC 6
+template <int MAXLEN>
+struct ConvFpTarget {
+  u32 slot, id;
+  double q, qinv, c[MAXLEN];
+  __device__ __forceinline__ void fetch(const ConvArgs& a, u32 target, u32 j) {
+    slot = target & 255;
+    id = target >> 8;
+    const ModInfo mi = conv_mod(a.mods, id);
+    q = mi.qd, qinv = mi.qinv;
+    const const_u64_ptr p = scalar_words(a.direct + ((size_t)j * a.ntarget + slot) * CONV_MAX_SRC);
+#pragma unroll
+    for (int k = 0; k < MAXLEN; k++) c[k] = scalar_double(p + k);
+  }
+};
+// Sources y (centred integers, |y| < 2^49, doubles kept as words) times constants |c| < 2^49, summed exactly as H + L. H starts at
+// 1.5 * 2^102, in whose binade adding a product rounds it to a multiple of 2^50; what that adds to H is exact (both lie in the binade:
+// at most 8 products of 2^98), and so is the rest of the product, an integer of magnitude at most 2^49, which goes to L (at most
+// 2^52). Then H - 1.5 * 2^102 + L = t q + x with the quotient off by at most 1.25, so that H - 1.5 * 2^102 - t q stays below 2^53.
+// 4 instructions a term and 6 at the end. Out: |x| <= 1.3 q.
+template <int MAXLEN>
+__device__ __forceinline__ void convert_fp(double (&x)[4], const u64 (&y)[CONV_DIRECT_SRC][4], const ConvFpTarget<MAXLEN>& tg) {
+  static_assert(MAXLEN <= CONV_DIRECT_SRC && CONV_DIRECT_SRC <= 8, "more products leave the binade of H");
+  constexpr double M = 1.5 * 5070602400912917605986812821504.0;   // 1.5 * 2^102
+  double H[4], L[4];
+#pragma unroll
+  for (int i = 0; i < 4; i++) H[i] = M, L[i] = 0.0;
+#pragma unroll
+  for (int k = 0; k < MAXLEN; k++)
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const double yk = __longlong_as_double((long long)y[k][i]), Hn = __builtin_fma(yk, tg.c[k], H[i]), h = Hn - H[i];
+      L[i] += __builtin_fma(yk, tg.c[k], -h);
+      H[i] = Hn;
+    }
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    const double h = H[i] - M;
+    x[i] = __builtin_fma(-__builtin_rint(__builtin_fma(L[i], tg.qinv, h * tg.qinv)), tg.q, h) + L[i];
+  }
+}
+// Targets share, share + nsplit, .. less the digit's own limbs, which stand together in the list. What is uniform about one is fetched
+// one target ahead, its place in the list two ahead.
+template <int LOGR, int MAXLEN>
+__device__ __forceinline__ void conv_direct_targets(const ConvArgs& a, const u64 (&y)[CONV_DIRECT_SRC][4], u32 j, u32 lo, u32 len, u32 share,
+                                                    u32 pos, u64* dst, u64* sm) {
+  constexpr int LOGN = LOGR + 8;
+  const u32 skip = a.skip_own ? len : 0, count = a.nfp - skip;
+  if (share >= count) return;   // uniform
+  auto at = [&](u32 i) {
+    i = min(i, count - 1);
+    return a.target[i + (i >= lo ? skip : 0)];
+  };
+  ConvFpTarget<MAXLEN> tg, next;
+  next.fetch(a, at(share), j);
+  u32 info = at(share + a.nsplit);
+  lds_barrier();   // the last inverse exchange has been read everywhere
+#pragma nounroll
+  for (u32 n = share; n < count; n += a.nsplit) {
+    tg = next;
+    next.fetch(a, info, j);
+    info = at(n + 2 * a.nsplit);
+    const double* tw = a.twfp + ((size_t)tg.id << LOGN);
+    ConvTwiddles<double> w;
+    w.load(tw);
+    __builtin_amdgcn_sched_barrier(0);
+    double x[4];
+    convert_fp<MAXLEN>(x, y, tg);
+    conv_fwd_rows<LOGR>(x, w, tw, tg.q, tg.qinv, (double*)sm, [] {});
+    double* d = (double*)dst + ((size_t)tg.slot << LOGN) + pos;
+#pragma unroll
+    for (int i = 0; i < 4; i++) d[i * 256] = x[i];
+  }
+}
 // All sources at the lane's four positions as operands: y[i][f][g], columns = positions i of lane half f, sources 4g .. 4g + 3.
 template <int MAXLEN>
 struct ConvSources {
@@ -446,7 +529,8 @@ __device__ __forceinline__ void conv_each(F f) {
 // One workgroup per (polynomial, tile, share of the targets), tiles fastest. The 64-byte row pieces of two adjacent tiles
 // (N = 2^16) make one line: the XCD-contiguous order keeps them on one L2.
 // READY: src holds what the inverse row pass makes of the sources (canonical residues, scaled).
-template <int LOGR, int MAXLEN, bool SRC_FP, bool READY>
+// DIRECT: double precision on both sides, on the vector units (a.direct).
+template <int LOGR, int MAXLEN, bool SRC_FP, bool READY, bool DIRECT = false>
 __global__ void __launch_bounds__(CONV_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4))) conv_rows_kernel(ConvArgs a) {
   __shared__ u64 sm[2 * CONV_TILE_WORDS];
   __shared__ u64 second[MAXLEN == 4 ? 1 : CONV_TILE];
@@ -463,7 +547,7 @@ __global__ void __launch_bounds__(CONV_THREADS) __attribute__((amdgpu_waves_per_
   // the sources' positions: READY in the first round's layout, in which the targets start
   const u32 from = READY ? (threadIdx.x >> L) * 256 + (tile << L) + (threadIdx.x & ((1u << L) - 1)) : pos;
   constexpr u32 step = READY ? (CONV_THREADS >> L) * 256 : 256;
-  u64 y[MAXLEN][4];
+  u64 y[DIRECT ? CONV_DIRECT_SRC : MAXLEN][4];   // (with four rows of DIRECT the compiler makes one register tuple of it, and copies of that)
   u64 ahead[4];   // the next source's words are requested before the current one is transformed
 #pragma unroll
   for (int i = 0; i < 4; i++) ahead[i] = src[from + i * step];
@@ -499,7 +583,10 @@ __global__ void __launch_bounds__(CONV_THREADS) __attribute__((amdgpu_waves_per_
       }
       // |x| <= q, and (q + 1) / 2 is 2^-51 or more away from q/2 in units of q: no rounding of x / q can pass one half
 #pragma unroll
-      for (int i = 0; i < 4; i++) y[k][i] = conv_cut(fp_reduce(x[i], mi.qinv, mi.qd));
+      for (int i = 0; i < 4; i++) {
+        const double v = fp_reduce(x[i], mi.qinv, mi.qd);
+        y[k][i] = DIRECT ? (u64)__double_as_longlong(v) : conv_cut(v);
+      }
     } else {
       u64 x[4];
 #pragma unroll
@@ -514,6 +601,7 @@ __global__ void __launch_bounds__(CONV_THREADS) __attribute__((amdgpu_waves_per_
       for (int i = 0; i < 4; i++) y[k][i] = conv_cut(csub(x[i] + h, mi.m), off8);
     }
   });
+  if constexpr (DIRECT) return conv_direct_targets<LOGR, MAXLEN>(a, y, j, lo, len, share, pos, dst, sm);
   ConvSources<MAXLEN> ys;
 #pragma unroll
   for (int i = 0; i < 4; i++)
